@@ -38,6 +38,7 @@
 #include "lccrf_chain_smem.h"
 #include "lccrf_device.h"
 #include "lccrf_launch.h"
+#include "lccrf_linear.h"
 
 namespace lccrf {
 
@@ -340,31 +341,23 @@ constexpr bool half_turns() {
 template <typename G>
 constexpr int turn_floats() { return 2 * G::TCAP * (G::TCAP + 4); }
 
+// Steps over positions first .. first + n - 1 from the vector published in sm.rvec[buf] (O: its offset less its normaliser);
+// on return the vector behind them is there, and those in front of every position are stored.
 template <typename G, typename TIN, int PF, bool ALIGNED>
 __device__ __forceinline__ void forward_half_turned(ChainSmem<G>& sm, float* __restrict__ tiles, const ChainArgs& a,
-                                                    const Span& sp, int tid) {
+                                                    int b, int first, int n, int tid, int& buf, double& O) {
     static_assert(G::ITEMS == 4 && PF == 4 && G::LPR * 4 == G::TCAP && G::WAVES * (256 / G::LPR) == G::TCAP,
                   "a wave owns 256 / LPR whole columns, a lane four rows LPR apart");
     constexpr int LPR = G::LPR, ROWS = G::TCAP, STRIDE = G::TCAP + 4;
     const int lane = tid & 63, wave = tid >> 6;
-    const int b = sp.b, N = a.N, T = a.T;
-    const int p0 = sp.p0, h = forward_end(a, sp.p0, sp.e);
+    const int N = a.N, T = a.T;
     const int c4 = 4 * (tid % LPR), r0 = tid / LPR;
     const size_t TT = (size_t)T * T, vb = (size_t)b * N;
     const TIN* phib = static_cast<const TIN*>(a.phi) + (size_t)b * N * TT;
     const bool exact_only = a.exact_only != 0;
     const int rowl = lane % LPR, colw = (256 / LPR) * wave + 4 * (lane / LPR);
     const int kk = 2 * (lane & 1) + ((lane >> 1) & 1);  // the column reduce4_over_lanes leaves in this lane
-
-    double O = 0.0;
-    {
-        float v0 = LCCRF_NEG_INF;
-        if (tid < T) v0 = sp.first ? Elem<TIN>::get(phib + tid) * kLog2e : a.Fv[((size_t)b * a.C + sp.c - 1) * T + tid];
-        if (!sp.first) O = a.OF[(size_t)b * a.C + sp.c - 1];
-        publish_columns<G>(sm, 0, tid, v0);
-    }
-    const int first = p0 + 1, n = h - p0;  // positions first .. h
-    int buf = 0, nstep = 0;
+    int nstep = 0;
     if (n > 0) {
         float ring[PF][4][4];
         auto load = [&](int i, int slot) { load_tile<G, TIN, ALIGNED>(phib + (size_t)i * TT, T, c4, r0, ring[slot], b != a.B - 1 || i != N - 1); };
@@ -463,10 +456,6 @@ __device__ __forceinline__ void forward_half_turned(ChainSmem<G>& sm, float* __r
     } else {
         __syncthreads();
     }
-    const float d = read_shift<G>(sm, buf);
-    O += (double)d;
-    if (tid < T) a.ua[(vb + h) * T + tid] = sm.rvec[buf][tid] - d;
-    if (tid == 0) a.Oa[vb + h] = O;
 }
 
 // The forward chain of the second pass in the same turned form (four-wave geometry, 32 < T <= 64):
@@ -666,7 +655,16 @@ __global__ __launch_bounds__(G::W) void chain_half_kernel(ChainArgs a) {
     if constexpr (half_turns<G, ALIGNED, PF>() && !STRUCT) {  // (structured tiles are formed in registers: nothing to turn)
         if (dir == 0) {
             extern __shared__ __attribute__((aligned(16))) float turn_tiles[];
-            forward_half_turned<G, TIN, PF, ALIGNED>(sm, turn_tiles, a, sp, tid);
+            float v0 = LCCRF_NEG_INF;
+            if (tid < T) v0 = sp.first ? Elem<TIN>::get(phib + tid) * kLog2e : a.Fv[((size_t)b * a.C + sp.c - 1) * T + tid];
+            double Of = sp.first ? 0.0 : a.OF[(size_t)b * a.C + sp.c - 1];
+            publish_columns<G>(sm, 0, tid, v0);
+            int bf = 0;
+            forward_half_turned<G, TIN, PF, ALIGNED>(sm, turn_tiles, a, b, p0 + 1, h - p0, tid, bf, Of);
+            const float d = read_shift<G>(sm, bf);
+            Of += (double)d;
+            if (tid < T) a.ua[(vb + h) * T + tid] = sm.rvec[bf][tid] - d;
+            if (tid == 0) a.Oa[vb + h] = Of;
             return;
         }
     }
@@ -749,6 +747,108 @@ __global__ __launch_bounds__(G::W) void chain_half_kernel(ChainArgs a) {
         if (tid < T) a.ub[(vb + h) * T + tid] = sm.rvec[buf][tid] - d;
         if (tid == 0) a.Ob[vb + h] = O;
     }
+}
+
+// ---------------------------------------------------------------------------------------
+// Pass 1 over whole sequences of dense potentials: steps in scaled probabilities (linear_run) as long as they are accepted,
+// and from one that is not, a block of positions in the log domain (the loops of chain_half_kernel).
+// The log-domain steps are out of line: their registers are no concern of the quick way's.  (Arguments of a call travel in
+// vector registers; an argument struct would go through scratch memory.)
+extern __shared__ __attribute__((aligned(16))) float half_smem[];  // the quick way's shared state, or the turned tiles
+template <typename G, typename TIN, bool ALIGNED>
+__device__ __attribute__((noinline)) LogStepsResult chain_log_steps(const void* phi, float* ua, float* ub, double* Oa, double* Ob, int B,
+                                                                    int N, int T, int exact_only, int b, int dir, int first, int n,
+                                                                    float v0, double O) {
+    __shared__ ChainSmem<G> sm;
+    const int tid = threadIdx.x;
+    ChainArgs a{};
+    a.phi = uniform(phi);
+    a.B = uniform(B); a.N = uniform(N); a.T = uniform(T);
+    a.ua = uniform(ua); a.ub = uniform(ub);
+    a.Oa = uniform(Oa); a.Ob = uniform(Ob);
+    a.exact_only = uniform(exact_only);
+    b = uniform(b); first = uniform(first); n = uniform(n);
+    smem_init<G>(sm, tid);
+    __syncthreads();
+    publish_columns<G>(sm, 0, tid, v0);
+    __syncthreads();
+    int buf = 0;
+    if (uniform(dir) == 0) {
+        forward_half_turned<G, TIN, 4, ALIGNED>(sm, half_smem, a, b, first, n, tid, buf, O);
+    } else {
+        constexpr int PF = 4, ITEMS = G::ITEMS;
+        const int c4 = 4 * (tid % G::LPR), r0 = tid / G::LPR;
+        const size_t TT = (size_t)a.T * a.T, vb = (size_t)b * a.N;
+        const TIN* phib = static_cast<const TIN*>(a.phi) + vb * TT;
+        float ring[PF][ITEMS][4], none[ITEMS];
+#pragma unroll
+        for (int k = 0; k < ITEMS; ++k) none[k] = 0.f;
+        int nstep = 0;
+        auto load = [&](int i, int slot) {
+            load_tile<G, TIN, ALIGNED>(phib + (size_t)i * TT, a.T, c4, r0, ring[slot], b != a.B - 1 || i != a.N - 1);
+        };
+        walk<PF>(first, first - n + 1, -1, load, [&](int i, int slot) {
+            settle_tile<G, ALIGNED>(ring[slot], a.T, c4);
+            const float d = read_shift<G>(sm, buf);
+            O += (double)d;
+            const float4 q = *reinterpret_cast<const float4*>(&sm.rvec[buf][c4]);
+            const float ub4[4] = {q.x - d, q.y - d, q.z - d, q.w - d};
+            if (tid < a.T) a.ub[(vb + i) * a.T + tid] = sm.rvec[buf][tid] - d;
+            if (tid == 0) a.Ob[vb + i] = O;
+            bwd_advance<G, false, ALIGNED>(sm, buf, nstep, a.exact_only != 0, tid, c4, r0, a.T, ring[slot], ub4, d, none, nullptr);
+        });
+    }
+    const LogStepsResult r{tid < a.T ? sm.rvec[buf][tid] : LCCRF_NEG_INF, O};
+    __syncthreads();
+    return r;
+}
+
+// ITEMS: rows a thread holds of a matrix, at least linear_items(G::W, T).
+template <typename G, typename TIN, bool ALIGNED, int ITEMS>
+__global__ __launch_bounds__(G::W, 4) void linear_half_kernel(ChainArgs a) {  // (four waves a SIMD: large batches of 33 .. 64 tags)
+    using LG = LinGeo<G::WAVES, G::TCAP, ITEMS>;
+    LinSmem<LG>& lin = *reinterpret_cast<LinSmem<LG>*>(half_smem);
+    const int tid = threadIdx.x;
+    const int dir = blockIdx.x & 1, b = blockIdx.x >> 1;
+    const int N = a.N, T = a.T;
+    const int L = clamp_length(a.lengths, b, N);
+    if (L == 0 || (a.full_forward && dir == 1)) return;
+    const int e = L - 1;
+    const int mid = meeting_point(0, e);
+    const size_t vb = (size_t)b * N;
+    const TIN* phib = static_cast<const TIN*>(a.phi) + vb * T * T;
+    float* uout = (dir == 0 ? a.ua : a.ub) + vb * T;
+    double* Oout = (dir == 0 ? a.Oa : a.Ob) + vb;
+    // the vector the chain starts from, and the positions it walks
+    const int start = a.extend ? mid : dir == 0 ? 0 : e;
+    const int end = a.extend ? (dir == 0 ? e : 0) : dir == 0 ? forward_end(a, 0, e) : mid;
+    const int first = dir == 0 ? start + 1 : start, n = dir == 0 ? end - start : start - end;
+    float v = LCCRF_NEG_INF;
+    double O = 0.0;
+    if (a.extend) {
+        if (tid < T) v = uout[(size_t)start * T + tid];
+        O = Oout[start];
+    } else if (tid < T) {
+        v = dir == 0 ? Elem<TIN>::get(phib + tid) * kLog2e : 0.f;
+    }
+    int steps = 0;
+    LogBlocks blocks;
+    for (;;) {
+        const int before = steps;
+        if (!a.exact_only) {
+            if (dir == 0) steps = linear_run<LG, TIN, ALIGNED, false>(lin, {phib, T, first, n, uout, Oout}, v, steps, O);
+            else steps = linear_run<LG, TIN, ALIGNED, true>(lin, {phib, T, first, n, uout, Oout}, v, steps, O);
+        }
+        if (steps >= n) break;
+        const int m = a.exact_only ? n : blocks.next(steps - before, n - steps);
+        const LogStepsResult r = chain_log_steps<G, TIN, ALIGNED>(a.phi, a.ua, a.ub, a.Oa, a.Ob, a.B, N, T, a.exact_only, b, dir,
+                                                                  dir == 0 ? first + steps : first - steps, m, v, O);
+        v = r.v;
+        O = r.O;
+        steps += m;
+    }
+    if (tid < T) uout[(size_t)end * T + tid] = v;
+    if (tid == 0) Oout[end] = O;
 }
 
 // ---------------------------------------------------------------------------------------
@@ -939,20 +1039,57 @@ struct PairPlan {
     int* failed;
     int dtype;
     int poll_limit;
+    int cus;
 };
 
-template <typename G, typename TIN, bool ALIGNED, int PF1, int PF2>
-static hipError_t launch_geo(int op, ChainArgs a, hipStream_t st, hipEvent_t between, const PairPlan& pair) {
-    hipError_t e = hipSuccess;
+// The first pass in the log domain (whole sequences, the chunks of the scan) ...
+template <typename G, typename TIN, bool ALIGNED, int PF1>
+static hipError_t launch_chain_half(const ChainArgs& a, hipStream_t st) {
     size_t turn_bytes = 0;
     if constexpr (half_turns<G, ALIGNED, PF1>()) {
         turn_bytes = turn_floats<G>() * sizeof(float);
-        e = hipFuncSetAttribute(reinterpret_cast<const void*>(&chain_half_kernel<G, TIN, ALIGNED, PF1>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)turn_bytes);
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&chain_half_kernel<G, TIN, ALIGNED, PF1>),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)turn_bytes);
         if (e != hipSuccess) return e;
     }
     hipLaunchKernelGGL((chain_half_kernel<G, TIN, ALIGNED, PF1>), dim3(2 * a.B * a.C), dim3(G::W), turn_bytes, st, a);
-    e = hipGetLastError();
+    return hipGetLastError();
+}
+// ... and in scaled probabilities (whole sequences).
+template <typename G, typename TIN, bool ALIGNED, int ITEMS>
+static hipError_t launch_linear_items(const ChainArgs& a, hipStream_t st) {
+    const size_t lin = sizeof(LinSmem<LinGeo<G::WAVES, G::TCAP, ITEMS>>), turn = turn_floats<G>() * sizeof(float);
+    const size_t bytes = lin > turn ? lin : turn;
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&linear_half_kernel<G, TIN, ALIGNED, ITEMS>),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((linear_half_kernel<G, TIN, ALIGNED, ITEMS>), dim3(2 * a.B), dim3(G::W), bytes, st, a);
+    return hipGetLastError();
+}
+template <typename G, typename TIN, bool ALIGNED>
+static hipError_t launch_linear_half(const ChainArgs& a, hipStream_t st) {
+    const int items = linear_items(G::W, a.T);  // 2 (33 or 65 tags) .. 4
+    if (items <= 2) return launch_linear_items<G, TIN, ALIGNED, 2>(a, st);
+    if (items == 3) return launch_linear_items<G, TIN, ALIGNED, 3>(a, st);
+    if (items == 4) return launch_linear_items<G, TIN, ALIGNED, 4>(a, st);
+    return hipErrorInvalidValue;
+}
+
+template <typename G, typename TIN, bool ALIGNED, int PF1, int PF2>
+static hipError_t launch_geo(int op, ChainArgs a, hipStream_t st, hipEvent_t between, const PairPlan& pair) {
+    // Few chains of 65 .. 127 tags: marginals as launch_stream makes them (us, so / second pass with the chains, N=128:
+    // 72 tags, single precision B=64 204 / 279, B=128 315 / 313, bfloat16 B=128 240 / 301; 100 tags, single precision
+    // B=64 294 / 331, B=128 501 / 421, bfloat16 B=64 251 / 311, B=128 403 / 354; 128 tags have
+    // the paired second pass).  The line lies below where they cross: where hard constraints send the chains to the log-domain
+    // steps, two launches of them must not cost more than what is saved (80 tags, B=64, two tags forbidden everywhere 478 / 451).
+    const bool spread = op == 1 && a.chunk <= 0 && a.T > 64 && a.T < 128 && pair.cus > 0 &&
+                        (long long)a.B * a.T <= (long long)pair.cus * (pair.dtype == 0 ? 16 : 24);
+    // Otherwise the first pass runs in scaled probabilities for bfloat16 rows off the 8-byte grid, which linear_run widens
+    // where they are used and not where they are loaded (B=64 N=256 T=99 log-partition 292 -> 169 us, B=1024 N=64 T=45 160 -> 92);
+    // elsewhere the turned steps are as quick or quicker at these sizes (single precision B=64 N=256 T=100 185 / 178,
+    // B=64 N=512 T=128 422 / 469, B=64 N=256 T=64 104 / 108).
+    const bool linear = a.chunk <= 0 && !a.exact_only && (spread || (!ALIGNED && sizeof(TIN) == 2));
+    hipError_t e = linear ? launch_linear_half<G, TIN, ALIGNED>(a, st) : launch_chain_half<G, TIN, ALIGNED, PF1>(a, st);
     if (e != hipSuccess) return e;
     if (between) {
         e = hipEventRecord(between, st);
@@ -962,6 +1099,12 @@ static hipError_t launch_geo(int op, ChainArgs a, hipStream_t st, hipEvent_t bet
     if (op == 0) {
         hipLaunchKernelGGL(logz_combine_kernel, dim3(a.B), dim3(64), 0, st, a);
         return hipGetLastError();
+    }
+    if (spread) {
+        ChainArgs rest = a;
+        rest.extend = 1;
+        e = launch_linear_half<G, TIN, ALIGNED>(rest, st);
+        return e != hipSuccess ? e : launch_edge_marginals(pair.dtype, a, st);
     }
     if (pair.mail) {
         // two workgroups per chain, speculative steps only; whatever they flag as failed is redone below
@@ -1029,8 +1172,8 @@ static hipError_t launch_wave(int op, int dtype, const ChainArgs& a, hipStream_t
     return launch_wave_pass(true, dtype, a, st);
 }
 
-// Both passes in row batches (128 < T <= 256).
-static hipError_t launch_stream(int op, int dtype, const ChainArgs& a, hipStream_t st, hipEvent_t between) {
+// Both passes in row batches (128 < T <= 256).  cus: compute units of the device (0: unknown).
+static hipError_t launch_stream(int op, int dtype, const ChainArgs& a, hipStream_t st, hipEvent_t between, int cus = 0) {
     hipError_t e = launch_stream_pass(false, dtype, a, st);
     if (e != hipSuccess) return e;
     if (between) {
@@ -1041,6 +1184,17 @@ static hipError_t launch_stream(int op, int dtype, const ChainArgs& a, hipStream
     if (op == 0) {
         hipLaunchKernelGGL(logz_combine_kernel, dim3(a.B), dim3(64), 0, st, a);
         return hipGetLastError();
+    }
+    // Few chains: their second halves take their steps without writing, and one more kernel writes the marginals with the
+    // whole chip.  It moves a third more bytes, so it pays while two workgroups a sequence leave enough of the chip idle (us,
+    // so / second pass with the chains: 136 tags, N=128, single precision B=64 545 / 593, B=96 712 / 655, bfloat16 B=96
+    // 538 / 590, B=128 653 / 626; 201 tags, N=64, B=48 470 / 535, B=64 575 / 581, B=96 794 / 658, bfloat16 B=64 468 / 562;
+    // 256 tags, N=48, B=32 462 / 472, B=48 568 / 510, bfloat16 B=32 339 / 386, B=48 431 / 426).
+    if (cus > 0 && (long long)a.B * a.T <= (long long)cus * (dtype == 0 ? 40 : 48)) {
+        ChainArgs rest = a;
+        rest.extend = 1;
+        e = launch_stream_pass(false, dtype, rest, st);
+        return e != hipSuccess ? e : launch_edge_marginals(dtype, a, st);
     }
     return launch_stream_pass(true, dtype, a, st);
 }
@@ -1055,7 +1209,7 @@ hipError_t launch_full_forward(int dtype, const void* phi, const int32_t* length
     a.full_forward = 1;
     if (wave_supported(T)) return launch_wave(2, dtype, a, st, nullptr);
     if (stream_supported(T)) return launch_stream(2, dtype, a, st, nullptr);
-    const PairPlan pair{nullptr, nullptr, dtype, 0};
+    const PairPlan pair{nullptr, nullptr, dtype, 0, 0};
     const bool aligned = (T % 4) == 0;
     if (dtype == 0)
         return aligned ? launch_T<float, true>(2, a, st, nullptr, pair) : launch_T<float, false>(2, a, st, nullptr, pair);
@@ -1114,10 +1268,10 @@ hipError_t launch_sequential_sum(int op, int dtype, const void* phi, const int32
     }
     if (wave_supported(T)) return launch_wave(op, dtype, a, st, between);
     if (emit) return (T % 4) == 0 ? launch_structured_sum<true>(op, a, st, between) : launch_structured_sum<false>(op, a, st, between);
-    if (stream_supported(T)) return launch_stream(op, dtype, a, st, between);
+    if (stream_supported(T)) return launch_stream(op, dtype, a, st, between, exact_only ? 0 : cus);
     // Pairs pay off when one workgroup per chain would leave at least half of the chip idle.
     const bool use_pairs = op == 1 && !exact_only && mail && failed && pair_supported(T) && 4 * B <= cus;
-    const PairPlan pair{use_pairs ? mail : nullptr, failed, dtype, pair_poll_limit};
+    const PairPlan pair{use_pairs ? mail : nullptr, failed, dtype, pair_poll_limit, exact_only ? 0 : cus};
     if (use_pairs) {
         a.pair_mail = mail;
         a.pair_failed = failed;
@@ -1158,7 +1312,7 @@ hipError_t launch_chunked_marginals(int dtype, const void* phi, const int32_t* l
         return launch_wave_chunks(dtype, a, st);
     }
     if (wave_supported(T)) return launch_wave(1, dtype, a, st, between);
-    const PairPlan pair{nullptr, nullptr, dtype, 0};
+    const PairPlan pair{nullptr, nullptr, dtype, 0, 0};
     const bool aligned = (T % 4) == 0;
     if (dtype == 0)
         return aligned ? launch_T<float, true>(1, a, st, between, pair) : launch_T<float, false>(1, a, st, between, pair);

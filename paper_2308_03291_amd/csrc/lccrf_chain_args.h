@@ -53,6 +53,9 @@ struct ChainArgs {
     // 1: the forward chain runs over the whole span and stores every alpha; no backward chain
     // (first pass of sampling, whose backward sweep needs alpha everywhere).
     int full_forward;
+    // 1: a first pass over the other halves (row-batch kernels, whole sequences): the chains start from the vectors that
+    // an ordinary first pass has stored for the meeting position and run on to the far ends, vectors stored.
+    int extend;
 };
 
 // The stretch of positions one pair of workgroups handles: all of a sequence, or one chunk.
@@ -105,6 +108,8 @@ bool wave_chunks_fused(int chunk);
 // marginals exactly as launch_wave_pass.
 bool stream_supported(int T);
 hipError_t launch_stream_pass(bool second_pass, int dtype, const ChainArgs& a, hipStream_t st);
+// Marginals and logZ of whole sequences from the vectors of every position (lccrf_stream.hip).
+hipError_t launch_edge_marginals(int dtype, const ChainArgs& a, hipStream_t st);
 // The first pass in an expectation mode at those tag counts (0: entropy, a.ha / a.hb; 1: cross-entropy,
 // 2: KL divergence, with a.psi and a.hoff), leaving what entropy_half_kernel leaves (lccrf_extras.hip).
 hipError_t launch_stream_expect(int mode, int dtype, const ChainArgs& a, hipStream_t st);

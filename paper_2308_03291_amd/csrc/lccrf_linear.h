@@ -1,0 +1,356 @@
+// A stretch of a sum-product chain in scaled probabilities, by a whole workgroup: the quick way through the first
+// pass at 33 .. 256 tags (lccrf_chain.hip, lccrf_stream.hip).
+//
+// A step of the log-domain kernels exponentiates the matrix once its own input vector is known, so the exponentials
+// sit on the chain of dependent work, and while the partial sums are merged nothing else runs.  Here a step is a
+// plain vector-matrix product,
+//     S_n(u) = 2^-k_{n-1} sum_v S_{n-1}(v) E_n(v, u),      E_n = 2^(phi_n log2 e - c_n),
+// (k_{n-1} the exponent of the largest entry of S_{n-1}, c_n an integer) whose matrix is exponentiated one step AHEAD,
+// between the two barriers of the step before: the dependent part of a step is one fused multiply-add a potential,
+// one exchange through LDS and no exponential or logarithm.  All scales are powers of two, so they round nothing.
+//
+// c_n has to be chosen before S_{n-1} is known: it is the growth of the step before the last one (the exponent the
+// largest entry gained there), the first two matrices taking what the first step will grow by, less kLinearHead: the entries of
+// a vector reach further below its largest than the growth strays from one step to the next.  A step is accepted if every
+// sum lies in [2^-60, 2^60] and the largest entry of the vector it started from was at least 2^-30: whatever
+// underflowed in it (an E below 2^-126, a product below 2^-126) is then at most 256 * 2^-66 + 256 * 2^-36 < 2^-27 of the sum
+// it belongs to, for every entry separately.  At a step that is not accepted the stretch ends, with the vector in front
+// of that step; the caller's log-domain steps take over from there.
+//
+// Layout.  Q4 = ceil(T / 4) threads cover a row, four columns each (whatever lanes and waves they fall into: nothing here
+// reduces across lanes of a row), so the G = W / Q4 row groups of a workgroup fit the tag count, not the next power of two.
+// Thread (g, cl) holds rows g, g + G, ... : the threads of a wave read one contiguous stretch of the matrix.  The last piece of a
+// row is moved back to end with it (T >= 4) and rows past the matrix are its last row again: every load lies inside the
+// matrix whatever the tag count.  What is then held twice meets an exact zero in the sums over it, or is never looked at.
+// Forward, the groups' partial sums of a column meet in LDS; backward, the Q4 threads' partial sums of a row: Q threads
+// share a column or row there.
+#pragma once
+
+#include "lccrf_device.h"
+
+
+namespace lccrf {
+
+constexpr int kLinearHead = 24;
+
+template <int WAVES_, int TCAP_, int ITEMS_>
+struct LinGeo {
+    static constexpr int WAVES = WAVES_, TCAP = TCAP_, ITEMS = ITEMS_, W = 64 * WAVES_;
+    static constexpr int Q = W / TCAP;     // threads that merge a column or a row
+    static constexpr int most_groups() {   // of the tag counts that take this ITEMS (or fewer rows than that)
+        int most = 0;
+        for (int t = TCAP / 2 + 1; t <= TCAP; ++t) {
+            const int groups = W / ((t + 3) / 4);
+            const int need = (t + groups - 1) / groups;
+            if (need <= ITEMS && need > ITEMS - (ITEMS > 12 ? 2 : 1) && groups > most) most = groups;
+        }
+        return most;
+    }
+    static constexpr int PARTS = (most_groups() + Q - 1) / Q;  // partial sums of a column a merging thread adds up
+    static constexpr int GMAX = PARTS * Q + 1;     // groups there is room for (the last: threads that are left over)
+    static constexpr int STRIDE = TCAP + 64 / Q;   // floats between the groups' partial sums: no bank conflicts either way
+    static constexpr int ROW4 = TCAP / 4 / Q;      // floats of a row's partial sums a merging thread adds up ...
+    static constexpr int RSTRIDE = TCAP / 4 + 4;   // ... and between rows
+    static constexpr int IPAD = (ITEMS + 3) / 4 * 4;  // entries of the vector a group reads (forward)
+    static constexpr int VEC = GMAX * IPAD > TCAP + 16 ? GMAX * IPAD : TCAP + 16;
+    static constexpr int FORWARD = GMAX * STRIDE, BACKWARD = ITEMS * GMAX * RSTRIDE;
+    static constexpr int SCRATCH = FORWARD > BACKWARD ? FORWARD : BACKWARD;
+    static_assert((Q == 4 || Q == 8) && ROW4 % 4 == 0 && PARTS >= 1, "a column or row is merged inside eight lanes");
+};
+// Rows a thread holds for a tag count.
+constexpr int linear_items(int W, int T) {
+    const int groups = W / ((T + 3) / 4);
+    return (T + groups - 1) / groups;
+}
+
+template <typename LG>
+struct LinSmem {
+    alignas(16) float part[LG::SCRATCH];  // partial sums: [group][STRIDE] forward, [row = (item, group)][RSTRIDE] backward
+    // S_n.  Forward: entry v = g + G k at g IPAD + k, as the groups read it; zeros in between.  Backward: in order, zeros
+    // from TCAP on, and from TCAP + 8 on the entries of a row's last piece, zero where its neighbour holds them already.
+    alignas(16) float vec[2][LG::VEC];
+    alignas(16) float wmax[2][16];        // per-wave largest entries of S_n; +inf: the step was not accepted
+};
+
+// Four consecutive potentials as they lie in memory (bfloat16 is widened where the piece is used: widening at the load
+// would wait for it there).  ALIGNED: the tag count is a multiple of four; otherwise a row starts wherever an element may.
+// (Odd counts of bfloat16 tags: 8-byte loads from odd half words take the memory pipeline longer, 3.5 us a step at 201 tags
+// where 202 tags take 2.8; the words around the piece with a shift, 12 bytes or 8 + 2 a piece, take 4.4 and more.  Plain loads:
+// the non-temporal hint gains nothing on tensors that exceed the memory-side cache, 3.65 against 3.79 us a step at 200 tags,
+// and costs a fifth on those that it holds.)
+typedef __attribute__((address_space(1))) char GlobalBytes;
+#define LCCRF_GLOBAL(T) const __attribute__((address_space(1))) T*
+template <typename TIN> struct RawPiece;
+template <> struct RawPiece<float> {
+    static constexpr int WORDS = 4;
+    typedef vec4f type;
+    template <bool ALIGNED>
+    static __device__ __forceinline__ type load(const GlobalBytes* p) {
+        if constexpr (ALIGNED) return *(LCCRF_GLOBAL(vec4f))p;
+        else return *(LCCRF_GLOBAL(vec4f_anywhere))p;
+    }
+    static __device__ __forceinline__ float get(const type& r, int j) { return r[j]; }
+};
+template <> struct RawPiece<uint16_t> {
+    static constexpr int WORDS = 2;
+    typedef vec2u type;
+    template <bool ALIGNED>
+    static __device__ __forceinline__ type load(const GlobalBytes* p) {
+        if constexpr (ALIGNED) return *(LCCRF_GLOBAL(vec2u))p;
+        else return *(LCCRF_GLOBAL(vec2u_anywhere))p;
+    }
+    static __device__ __forceinline__ float get(const type& r, int j) {
+        return __uint_as_float((j & 1) ? r[j >> 1] & 0xffff0000u : r[j >> 1] << 16);
+    }
+};
+
+__device__ __forceinline__ float max16(const float* w) {  // of sixteen floats in LDS
+    const float4 q0 = *reinterpret_cast<const float4*>(w), q1 = *reinterpret_cast<const float4*>(w + 4);
+    const float4 q2 = *reinterpret_cast<const float4*>(w + 8), q3 = *reinterpret_cast<const float4*>(w + 12);
+    const float a = max3_raw(max3_raw(q0.x, q0.y, q0.z), q0.w, q1.x), b = max3_raw(max3_raw(q1.y, q1.z, q1.w), q2.x, q2.y);
+    const float c = max3_raw(max3_raw(q2.z, q2.w, q3.x), q3.y, q3.z);
+    return max3_raw(max3_raw(a, b, c), q3.w, q3.w);
+}
+// A value that is the same in every lane, said so: it and what follows from it stay in scalar registers.
+__device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
+template <typename P>
+__device__ __forceinline__ P* uniform(P* p) {
+    const unsigned long long v = (unsigned long long)p;
+    const unsigned lo = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)v), hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(v >> 32));
+    return (P*)(((unsigned long long)hi << 32) | lo);
+}
+__device__ __forceinline__ double uniform(double x) {
+    const long long v = __double_as_longlong(x);
+    const unsigned lo = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)v), hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(v >> 32));
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+__device__ __forceinline__ float uniform_f(float x) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x))); }
+
+// What a stretch of log-domain steps returns, out of line: this thread's entry of the vector behind it and its offset.
+struct LogStepsResult {
+    float v;
+    double O;
+};
+
+// How many log-domain steps follow a run that came to a step it cannot take: few if it got far (an odd position), sixteen if
+// not, and the whole rest once two runs have got less than eight steps far (hard constraints at every position, potentials
+// hundreds of bits apart).
+struct LogBlocks {
+    int poor = 0;
+    __device__ __forceinline__ int next(int progress, int rest) {
+        poor += progress < 8 ? 1 : 0;
+        return poor >= 2 ? rest : min(progress >= 16 ? 2 : 16, rest);
+    }
+};
+
+// What a run works on (uniform over the workgroup).  Step s (0 .. n - 1) of the chain takes the matrix of position
+// first + s (forward) or first - s (backward).
+template <typename TIN, bool BACKWARD>
+struct LinJob {
+    const TIN* phib;  // potentials of the sequence
+    int T, first, n;
+    float* uout;   // where the normalised vectors go, [N][T] of the sequence (base-2 logarithms) ...
+    double* Oout;  // ... and their offsets, [N]
+    __device__ __forceinline__ int matrix(int s) const { return BACKWARD ? first - s : first + s; }
+    __device__ __forceinline__ int position(int s) const { return BACKWARD ? first - s : first - 1 + s; }  // of the vector behind s steps
+};
+
+// Takes steps from `from` on while they are accepted; returns the steps done in all.  v: thread tid's entry of the
+// vector in front of step `from` (base-2 logarithms; -inf from tid = T on), O its offset; on return those of the
+// vector behind the last step taken.  The vectors in front of every step taken are stored to uout / Oout; that of the
+// last one is not (the caller stores it or goes on from it).  Called by the whole workgroup.
+template <typename LG, typename TIN, bool ALIGNED, bool BACKWARD>
+__device__ __forceinline__ int linear_run(LinSmem<LG>& ls, const LinJob<TIN, BACKWARD>& job, float& v0, int from, double& O) {
+    constexpr int ITEMS = LG::ITEMS, Q = LG::Q, TCAP = LG::TCAP;
+    using Raw = RawPiece<TIN>;
+    // Pieces in flight: as many whole tiles as fit the registers beside E (PH of them, three at most), half or a quarter
+    // of a tile of single precision where not even one does.
+    constexpr int kRawRegs = Raw::WORDS * ITEMS, kFree = (sizeof(TIN) == 2 ? 86 : 88) - 4 * ITEMS;
+    constexpr bool HALF = kRawRegs > kFree;
+    constexpr int PH = HALF ? 1 : kFree / kRawRegs > 3 ? 3 : kFree / kRawRegs;
+    constexpr int R = HALF ? (kRawRegs / 2 + 4 * ITEMS > 92 ? ITEMS / 4 : ITEMS / 2) : PH * ITEMS;
+    static_assert(!HALF || ITEMS % R == 0, "a whole fraction of a tile");
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int T = job.T;
+    const int n = job.n;
+    if (from >= n) return from;
+    // The largest entry, and whether every entry is an exact zero or within 2^-120 of it: held without loss, whatever its
+    // products lose is below 2^-126.
+    const float top = xor_max<1, 64>(v0);
+    if (lane == 0) ls.wmax[0][wave] = top;
+    if (tid >= LG::WAVES && tid < 16) ls.wmax[0][tid] = LCCRF_NEG_INF;
+    __syncthreads();
+    const float d = uniform_f(finite_or_zero(max16(ls.wmax[0])));
+    const bool fine = v0 == LCCRF_NEG_INF || v0 - d >= -120.f;
+    if (lane == 0) ls.wmax[1][wave] = __all(fine) ? 0.f : 1.f;
+    if (tid >= LG::WAVES && tid < 16) ls.wmax[1][tid] = 0.f;
+    __syncthreads();
+    if (uniform_f(max16(ls.wmax[1])) != 0.f) return from;
+
+    const size_t TT = (size_t)T * T;
+    const int Q4 = (T + 3) >> 2, G = LG::W / Q4;  // threads a row, row groups
+    const int g = tid / Q4, cl = tid - g * Q4;    // (g = G: left over, holds zeros of the vector)
+    const int c4 = min(4 * cl, T - 4);
+    const unsigned voff = (unsigned)(g * T + c4) * (unsigned)sizeof(TIN);
+    const unsigned voff_last = (unsigned)(min(g + G * (ITEMS - 1), T - 1) * T + c4) * (unsigned)sizeof(TIN);
+    const size_t row_step = (size_t)(uniform(G) * T);
+
+    typename Raw::type raw[R];
+    float e[ITEMS][4];
+    // row k of this thread's part of the matrix of step s (past the end: the last one again, never used)
+    auto fetch = [&](int s, int k) {
+        auto row = (const GlobalBytes*)(job.phib + (size_t)job.matrix(s < n ? s : n - 1) * TT + (k < ITEMS - 1 ? row_step * k : 0));
+        asm("" : "+s"(row));  // uniform, in scalar registers (not an address of its own per row, hoisted out of the loop)
+        return Raw::template load<ALIGNED>(row + (k < ITEMS - 1 ? voff : voff_last));
+    };
+    // E of step s from the ring, shift c; every piece that is used up is requested again for what follows
+    auto prepare = [&](int s, int slot, int shift) __attribute__((always_inline)) {
+        const float c = (float)shift;
+#pragma unroll
+        for (int k = 0; k < ITEMS; ++k) {
+            const int r = HALF ? k % R : slot * ITEMS + k;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) e[k][j] = ex2(__builtin_fmaf(Raw::get(raw[r], j), kLog2e, -c));
+            if constexpr (HALF) raw[r] = k + R < ITEMS ? fetch(s, k + R) : fetch(s + 1, k + R - ITEMS);
+            else raw[r] = fetch(s + PH, k);
+            if (k % 2 == 1) __builtin_amdgcn_sched_barrier(0);  // (keeps the new loads from being hoisted over the old values' use)
+        }
+    };
+#pragma unroll
+    for (int r = 0; r < R; ++r) raw[r] = HALF ? fetch(from, r) : fetch(from + r / ITEMS, r % ITEMS);
+
+    // where the entries of the vector lie, for the thread that publishes (`mine`) or stores (tid) one
+    const auto slot_of = [&](int v) { return BACKWARD ? v : v % G * LG::IPAD + v / G; };
+    const int mine = min(tid / Q, T - 1), vmine = slot_of(mine);
+    const int vcopy = BACKWARD && mine >= 4 * (Q4 - 1) ? TCAP + 8 + mine - (T - 4) : vmine;  // (or the same place again)
+    for (int k = tid; k < 2 * LG::VEC; k += LG::W) (&ls.vec[0][0])[k] = 0.f;
+    for (int k = tid; k < LG::SCRATCH; k += LG::W) ls.part[k] = 0.f;
+    __syncthreads();
+    if (tid < T) {
+        const float x = ex2(v0 - d);
+        ls.vec[0][slot_of(tid)] = x;
+        if (BACKWARD && tid >= 4 * (Q4 - 1)) ls.vec[0][TCAP + 8 + tid - (T - 4)] = x;
+    }
+    if (tid < 16) ls.wmax[1][tid] = LCCRF_NEG_INF;
+    __syncthreads();
+    // where this thread finds the entries of its rows (forward) or columns (backward), and leaves its partial sums
+    const int vfrom = !BACKWARD ? g * LG::IPAD : g == G ? TCAP : cl == Q4 - 1 ? TCAP + 8 : 4 * cl;
+    const int pslot = BACKWARD ? g * LG::RSTRIDE + cl : g * LG::STRIDE + 4 * cl;
+    // merging: this thread adds up part tid % Q of column or row `mine` (forward, the columns of the piece that was moved
+    // back are counted from its start)
+    const int mslot = BACKWARD ? (mine / G * LG::GMAX + mine % G) * LG::RSTRIDE + (tid % Q) * LG::ROW4
+                               : (tid % Q) * LG::STRIDE + (mine < 4 * (Q4 - 1) ? mine : 4 * (Q4 - 1) + mine - (T - 4));
+    // The first matrix's shift: the largest of its entries plus that of the vector it meets, among the pieces at hand, which
+    // is what the first step grows by (up to the logarithm of the tag count).
+    float big = LCCRF_NEG_INF;
+#pragma unroll
+    for (int k = 0; k < (R < ITEMS ? R : ITEMS); ++k)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            big = fmaxf(big, __builtin_fmaf(Raw::get(raw[k], j), kLog2e, lg2(ls.vec[0][vfrom + (BACKWARD ? j : k)])));
+    big = xor_max<1, 64>(big);
+    if (lane == 0) ls.wmax[1][wave] = big;
+    __syncthreads();
+    // (shifts and exponents are integers in scalar registers; far inside the range of an int)
+    big = max16(ls.wmax[1]);
+    int c_cur = uniform((int)fminf(fmaxf(ceilf(finite_or_zero(big)), -0x1p20f), 0x1p20f)) - kLinearHead, c_last = c_cur + kLinearHead - 1;
+    __syncthreads();
+    if (tid < 32) ls.wmax[tid >> 4][tid & 15] = tid == 0 ? 1.f : 0.f;
+    prepare(from, 0, c_cur);
+    __syncthreads();
+
+    int done = from, buf = 0;
+    const double O0 = uniform(O + (double)d);
+    long long Oi = 0, Oi_last = 0;  // offset of the vector in vec[buf] and of the one before it, less O0
+    bool rejected = false;
+    const auto step = [&](int slot_next) __attribute__((always_inline)) -> bool {  // false: the run is over
+        const float M = uniform_f(max16(ls.wmax[buf]));
+        if (!(M <= 0x1p60f)) {
+            rejected = true;
+            return false;
+        }
+        if (done == n || !(M >= 0x1p-30f)) return false;
+        const int k = uniform(__builtin_amdgcn_frexp_expf(M));
+        // (c_last + k: what the last step grew by.  In front of the first step c_last stands for what the first one will
+        // grow by, less the exponent 1 of its vector.)
+        const int c_next = max(min(c_last + k, 1 << 20), -(1 << 20)) - kLinearHead;
+        const float* vin = &ls.vec[buf][vfrom];
+        if constexpr (!BACKWARD) {
+            float acc[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int r4 = 0; r4 < ITEMS; r4 += 4) {
+                const float4 v4 = *reinterpret_cast<const float4*>(vin + r4);
+                const float v[4] = {v4.x, v4.y, v4.z, v4.w};
+#pragma unroll
+                for (int r = r4; r < (r4 + 4 < ITEMS ? r4 + 4 : ITEMS); ++r)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) acc[j] = __builtin_fmaf(e[r][j], v[r - r4], acc[j]);
+            }
+            *reinterpret_cast<float4*>(&ls.part[pslot]) = make_float4(acc[0], acc[1], acc[2], acc[3]);
+        } else {
+            const float4 v = *reinterpret_cast<const float4*>(vin);
+#pragma unroll
+            for (int r = 0; r < ITEMS; ++r)
+                ls.part[pslot + r * LG::GMAX * LG::RSTRIDE] = __builtin_fmaf(e[r][0], v.x, e[r][1] * v.y) + __builtin_fmaf(e[r][2], v.z, e[r][3] * v.w);
+        }
+        // the vector in front of this step is final: store it (off the dependent path), its largest entry brought below 1:
+        // the closer the logarithms are to zero, the less their rounding takes
+        {
+            auto out = (__attribute__((address_space(1))) char*)(job.uout + (size_t)job.position(done) * T);
+            asm("" : "+s"(out));  // (as above)
+            *(__attribute__((address_space(1))) float*)(out + 4u * (unsigned)min(tid / Q, T - 1)) = lg2(__builtin_amdgcn_ldexpf(ls.vec[buf][vmine], -k));  // (Q threads, the same value)
+        }
+        if (tid == 0) job.Oout[job.position(done)] = O0 + (double)(Oi + k);
+        __syncthreads();
+        const float* part = &ls.part[mslot];
+        float s;
+        if constexpr (!BACKWARD) {
+            s = part[0];
+#pragma unroll
+            for (int p = 1; p < LG::PARTS; ++p) s += part[p * Q * LG::STRIDE];
+        } else {
+            float4 x = *reinterpret_cast<const float4*>(part);
+#pragma unroll
+            for (int p = 4; p < LG::ROW4; p += 4) {
+                const float4 y = *reinterpret_cast<const float4*>(part + p);
+                x.x += y.x; x.y += y.y; x.z += y.z; x.w += y.w;
+            }
+            s = (x.x + x.y) + (x.z + x.w);
+        }
+        s = __builtin_amdgcn_ldexpf(xor_sum<1, Q>(s), -k);
+        ls.vec[buf ^ 1][vmine] = s;
+        if constexpr (BACKWARD) ls.vec[buf ^ 1][vcopy] = s;
+        const float m = __all(sum_in_range(s)) ? xor_max<1, 64>(s) : __builtin_huge_valf();
+        if (lane == 0) ls.wmax[buf ^ 1][wave] = m;
+        Oi_last = Oi;
+        Oi += k + c_cur;
+        c_last = c_cur;
+        c_cur = c_next;
+        prepare(done + 1, slot_next, c_next);
+        buf ^= 1;
+        ++done;
+        __syncthreads();
+        return true;
+    };
+    if constexpr (PH == 1) {
+        while (step(0)) {}
+    } else if constexpr (PH == 2) {
+        while (step(1) && step(0)) {}
+    } else {
+        while (step(1) && step(2) && step(0)) {}
+    }
+    if (rejected) {  // the vector in front of the rejected step is still in the other buffer
+        buf ^= 1;
+        --done;
+        Oi = Oi_last;
+    }
+    if (done == from) return from;
+    const int k = uniform(__builtin_amdgcn_frexp_expf(uniform_f(max16(ls.wmax[buf]))));
+    if (tid < T) v0 = lg2(__builtin_amdgcn_ldexpf(ls.vec[buf][slot_of(tid)], -k));
+    O = O0 + (double)(Oi + k);
+    __syncthreads();  // (the shared state may be used for something else now)
+    return done;
+}
+
+}  // namespace lccrf

@@ -1,21 +1,23 @@
 // Sum-product chains for tag sets of 129 .. 256: the matrix of a position streams through registers in
 // row batches.
 //
-// Same two passes, same two chains per sequence and same workspace as lccrf_chain.hip (section
-// "Sequence Tagging" of the paper for the forward recursion, "Computing Marginals" Eq. 3-4 for what the
-// second pass writes).  A matrix of up to 256 x 256 potentials is 64 numbers a thread of a 1024-thread
-// workgroup; held as one tile it spills (a tile, its exponentials and the marginals' factors do not fit
-// 128 registers), and nothing in a step needs it whole: the speculative step (one shift for the whole
-// matrix, see lccrf_chain.hip) only adds up exponentials.  So a matrix is taken as four batches of 64 rows,
-// four rows a thread, through a ring of four batch slots that is refilled across position boundaries: the
-// loads of the next position are in flight while this position's sums are merged.
+// Same two chains per sequence and same workspace as lccrf_chain.hip (section "Sequence Tagging" of the paper for the
+// forward recursion, "Computing Marginals" Eq. 3-4 for what the second pass writes).  A matrix of up to 256 x 256
+// potentials is 64 numbers a thread of a 1024-thread workgroup; held as one tile with its exponentials and the marginals'
+// factors it does not fit 128 registers.
 //
+// First pass (stream_half_kernel): the scaled probabilities of lccrf_linear.h, whose exponentials replace the potentials they come
+// from in the registers; steps those do not accept are taken by stream_log_steps.
+// Second pass, few chains: the first pass's kernel runs on to the far ends (extend), then edge_marginal_kernel writes the
+// marginals of every edge, the whole chip at once.
+// Second pass, many chains (stream_marginal_kernel), and the log-domain steps: a matrix is taken as four batches of 64 rows,
+// four rows a thread, through a ring of batch slots that is refilled across position boundaries.  Nothing in a speculative step
+// (one shift for the whole matrix, see lccrf_chain.hip) needs the matrix whole: it only adds up exponentials.
 //   lane l of wave w holds, of batch q, rows 64 q + 4 w + k (k < 4), columns 4 l .. 4 l + 3:
 //   a wave reads four whole rows (16-byte loads, 1 KB contiguous each).
 //   forward (sum over rows): per-thread column sums over all batches, then across the 16 waves through LDS;
 //   backward (sum over columns): a row is complete inside its wave and batch: four rows at a time by the
 //   packed lane reduction, results straight into the next vector.
-//
 // A rejected speculative step is replayed exactly by streaming the same matrix again from memory (it is in
 // the cache: it was read microseconds ago): thread-local maxima in a first sweep, exponentials against
 // them in a second (forward), or row maximum and row sum batch by batch (backward).
@@ -23,6 +25,7 @@
 #include "lccrf_chain_smem.h"
 #include "lccrf_device.h"
 #include "lccrf_launch.h"
+#include "lccrf_linear.h"
 
 namespace lccrf {
 
@@ -86,16 +89,15 @@ __device__ __forceinline__ void load_vec4(const float* __restrict__ vec, int T, 
 
 }  // namespace
 
-// WITH_MU false: pass 1 (both half chains, vectors stored); true: pass 2 (both chains continue past the
-// meeting point and write the marginals).
+// n positions of a chain in the log domain, from position `first` on: the speculative step, and its exact replay.  The
+// vector in front of them is in sm.rvec[buf] (published, a barrier behind it), O its offset less its normaliser; on
+// return the last vector is there.  WITH_MU: the marginals of every position are written as well (second pass);
+// otherwise the vector in front of every position is stored (first pass).
 template <typename TIN, bool ALIGNED, bool WITH_MU>
-__global__ __launch_bounds__(1024) void stream_chain_kernel(ChainArgs a) {
-    __shared__ ChainSmem<SG> sm;
+__device__ __forceinline__ void stream_walk(ChainSmem<SG>& sm, const ChainArgs& a, int b, int dir, int first, int n,
+                                            double lz2, bool feasible, int& buf, double& O) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int dir = blockIdx.x & 1;
-    const int b = blockIdx.x >> 1;
     const int N = a.N, T = a.T;
-    const int L = clamp_length(a.lengths, b, N);
     const size_t TT = (size_t)T * T;
     const size_t vb = (size_t)b * N;
     const TIN* phib = static_cast<const TIN*>(a.phi) + (size_t)b * N * TT;
@@ -103,64 +105,7 @@ __global__ __launch_bounds__(1024) void stream_chain_kernel(ChainArgs a) {
     const bool exact_only = a.exact_only != 0;
     const int NBq = (T + kBatchRows - 1) / kBatchRows;  // batches a matrix: 3 or 4
     const int c4 = 4 * lane;
-
-    if (WITH_MU && dir == 0) {  // positions past the end carry no edge: their marginals are zero
-        const size_t z0 = (size_t)L * TT, z1 = (size_t)N * TT;
-        if (ALIGNED) {
-            float4* p = reinterpret_cast<float4*>(mub);
-            for (size_t k = z0 / 4 + tid; k < z1 / 4; k += 1024) p[k] = make_float4(0.f, 0.f, 0.f, 0.f);
-        } else {
-            for (size_t k = z0 + tid; k < z1; k += 1024) mub[k] = 0.f;
-        }
-    }
-    if (L == 0) {
-        if (WITH_MU && dir == 0 && tid == 0 && a.logZ) a.logZ[b] = 0.f;
-        return;
-    }
-    const int e = L - 1;
-    const int h = WITH_MU ? meeting_point(0, e) : forward_end(a, 0, e);
-    if (!WITH_MU && a.full_forward && dir == 1) return;
-
-    smem_init<SG>(sm, tid);
-    double lz2 = 0.0;
-    bool feasible = true;
-    if constexpr (WITH_MU) {
-        lz2 = midpoint_log2z<SG>(sm, a, vb, h, T, tid);
-        feasible = lz2 > -1.0e300;  // false: no path has a finite score, marginals are 0
-        if (dir == 0 && tid == 0 && a.logZ) a.logZ[b] = (float)(lz2 * kLn2);
-    } else {
-        __syncthreads();
-    }
-
-    // the vector the chain starts from, and the positions it walks
-    double O = 0.0;
-    int first, n;
-    {
-        float v0 = LCCRF_NEG_INF;
-        if (!WITH_MU) {
-            if (dir == 0) {
-                if (tid < T) v0 = Elem<TIN>::get(phib + tid) * kLog2e;
-                first = 1; n = h;
-            } else {
-                if (tid < T) v0 = 0.f;
-                first = e; n = e - h;
-            }
-        } else {
-            if (dir == 0) {
-                if (tid < T) v0 = a.ua[(vb + h) * T + tid];
-                O = a.Oa[vb + h];
-                first = h + 1; n = e - h;
-            } else {
-                if (tid < T) v0 = a.ub[(vb + h) * T + tid];
-                O = a.Ob[vb + h];
-                first = h; n = h;
-            }
-        }
-        publish_columns<SG>(sm, 0, tid, v0);
-        __syncthreads();
-    }
-
-    int buf = 0, nstep = 0;
+    int nstep = 0;
     float kappa = 0.f;  // running correction that keeps each position's marginals summing to one
     // state of the position in progress
     float d = 0.f, K = 0.f, tot = 0.f, wm = LCCRF_NEG_INF;
@@ -372,12 +317,6 @@ __global__ __launch_bounds__(1024) void stream_chain_kernel(ChainArgs a) {
                 ++nstep;
             }
         });
-        if constexpr (!WITH_MU) {
-            const float dl = read_shift<SG>(sm, buf);
-            O += (double)dl;
-            if (tid < T) a.ua[(vb + h) * T + tid] = sm.rvec[buf][tid] - dl;
-            if (tid == 0) a.Oa[vb + h] = O;
-        }
     } else {
         // ---------------- backward chain ----------------
         walk<kStreamRing<WITH_MU>>(0, n * NBq - 1, +1, load_backward, [&](int u, int slot) {
@@ -438,24 +377,214 @@ __global__ __launch_bounds__(1024) void stream_chain_kernel(ChainArgs a) {
                 ++nstep;
             }
         });
-        if constexpr (!WITH_MU) {
-            const float dl = read_shift<SG>(sm, buf);
-            O += (double)dl;
-            if (tid < T) a.ub[(vb + h) * T + tid] = sm.rvec[buf][tid] - dl;
-            if (tid == 0) a.Ob[vb + h] = O;
+    }
+}
+
+// Pass 2: both chains continue past the meeting point and write the marginals.
+template <typename TIN, bool ALIGNED>
+__global__ __launch_bounds__(1024) void stream_marginal_kernel(ChainArgs a) {
+    __shared__ ChainSmem<SG> sm;
+    const int tid = threadIdx.x;
+    const int dir = blockIdx.x & 1;
+    const int b = blockIdx.x >> 1;
+    const int N = a.N, T = a.T;
+    const int L = clamp_length(a.lengths, b, N);
+    const size_t TT = (size_t)T * T;
+    const size_t vb = (size_t)b * N;
+    float* mub = a.mu + (size_t)b * N * TT;
+
+    if (dir == 0) {  // positions past the end carry no edge: their marginals are zero
+        const size_t z0 = (size_t)L * TT, z1 = (size_t)N * TT;
+        if (ALIGNED) {
+            float4* p = reinterpret_cast<float4*>(mub);
+            for (size_t k = z0 / 4 + tid; k < z1 / 4; k += 1024) p[k] = make_float4(0.f, 0.f, 0.f, 0.f);
         } else {
-            // position 0: p(y_0 = t) = softmax_t(alpha_0(t) + beta_0(t)) in row 0, zeros elsewhere
-            for (int k = T + tid; k < (int)TT; k += 1024) mub[k] = 0.f;
-            if (tid < 64) {
-                float m = LCCRF_NEG_INF;
-                for (int t = tid; t < T; t += 64) m = fmaxf(m, a.ua[vb * T + t] + sm.rvec[buf][t]);
-                m = xor_max<1, 64>(m);
-                float S = 0.f;
-                for (int t = tid; t < T; t += 64) S += ex2(a.ua[vb * T + t] + sm.rvec[buf][t] - finite_or_zero(m));
-                S = xor_sum<1, 64>(S);
-                const float c = (feasible && S > 0.f) ? 1.0f / S : 0.f;
-                for (int t = tid; t < T; t += 64) mub[t] = c * ex2(a.ua[vb * T + t] + sm.rvec[buf][t] - finite_or_zero(m));
-            }
+            for (size_t k = z0 + tid; k < z1; k += 1024) mub[k] = 0.f;
+        }
+    }
+    if (L == 0) {
+        if (dir == 0 && tid == 0 && a.logZ) a.logZ[b] = 0.f;
+        return;
+    }
+    const int e = L - 1;
+    const int h = meeting_point(0, e);
+
+    smem_init<SG>(sm, tid);
+    const double lz2 = midpoint_log2z<SG>(sm, a, vb, h, T, tid);
+    const bool feasible = lz2 > -1.0e300;  // false: no path has a finite score, marginals are 0
+    if (dir == 0 && tid == 0 && a.logZ) a.logZ[b] = (float)(lz2 * kLn2);
+
+    // the vectors the chains start from, and the positions they walk
+    double O = (dir == 0 ? a.Oa : a.Ob)[vb + h];
+    publish_columns<SG>(sm, 0, tid, tid < T ? (dir == 0 ? a.ua : a.ub)[(vb + h) * T + tid] : LCCRF_NEG_INF);
+    __syncthreads();
+    int buf = 0;
+    stream_walk<TIN, ALIGNED, true>(sm, a, b, dir, dir == 0 ? h + 1 : h, dir == 0 ? e - h : h, lz2, feasible, buf, O);
+    if (dir == 1) {
+        // position 0: p(y_0 = t) = softmax_t(alpha_0(t) + beta_0(t)) in row 0, zeros elsewhere
+        for (int k = T + tid; k < (int)TT; k += 1024) mub[k] = 0.f;
+        if (tid < 64) {
+            float m = LCCRF_NEG_INF;
+            for (int t = tid; t < T; t += 64) m = fmaxf(m, a.ua[vb * T + t] + sm.rvec[buf][t]);
+            m = xor_max<1, 64>(m);
+            float S = 0.f;
+            for (int t = tid; t < T; t += 64) S += ex2(a.ua[vb * T + t] + sm.rvec[buf][t] - finite_or_zero(m));
+            S = xor_sum<1, 64>(S);
+            const float c = (feasible && S > 0.f) ? 1.0f / S : 0.f;
+            for (int t = tid; t < T; t += 64) mub[t] = c * ex2(a.ua[vb * T + t] + sm.rvec[buf][t] - finite_or_zero(m));
+        }
+    }
+}
+
+// The log-domain steps of a first pass, out of line: their registers are no concern of the quick way's.  v0: this
+// thread's entry of the vector in front of position `first` (-inf from T on), O its offset; returns the entry of the
+// vector behind the last position and its offset.  (Arguments of a call travel in vector registers; an argument struct
+// would go through scratch memory.)
+template <typename TIN, bool ALIGNED>
+__device__ __attribute__((noinline)) LogStepsResult stream_log_steps(const void* phi, float* ua, float* ub, double* Oa, double* Ob, int B,
+                                                                     int N, int T, int exact_only, int b, int dir, int first, int n,
+                                                                     float v0, double O) {
+    __shared__ ChainSmem<SG> sm;
+    const int tid = threadIdx.x;
+    ChainArgs a{};
+    a.phi = uniform(phi);
+    a.B = uniform(B); a.N = uniform(N); a.T = uniform(T);
+    a.ua = uniform(ua); a.ub = uniform(ub);
+    a.Oa = uniform(Oa); a.Ob = uniform(Ob);
+    a.exact_only = uniform(exact_only);
+    smem_init<SG>(sm, tid);
+    __syncthreads();
+    publish_columns<SG>(sm, 0, tid, v0);
+    __syncthreads();
+    int buf = 0;
+    stream_walk<TIN, ALIGNED, false>(sm, a, uniform(b), uniform(dir), uniform(first), uniform(n), 0.0, true, buf, O);
+    const LogStepsResult r{tid < a.T ? sm.rvec[buf][tid] : LCCRF_NEG_INF, O};
+    __syncthreads();
+    return r;
+}
+
+// Pass 1: both half chains, vectors stored.  The steps are taken in scaled probabilities (linear_run) as long as they are
+// accepted, and from one that is not, a block of positions in the log domain (LogBlocks).
+// ITEMS: rows a thread holds of a matrix there, at least linear_items(1024, T).
+template <typename TIN, bool ALIGNED, int ITEMS>
+__global__ __launch_bounds__(1024) void stream_half_kernel(ChainArgs a) {
+    using LG = LinGeo<16, 256, ITEMS>;
+    __shared__ LinSmem<LG> lin;
+    const int tid = threadIdx.x;
+    const int dir = blockIdx.x & 1, b = blockIdx.x >> 1;
+    const int N = a.N, T = a.T;
+    const int L = clamp_length(a.lengths, b, N);
+    if (L == 0 || (a.full_forward && dir == 1)) return;
+    const int e = L - 1;
+    const int mid = meeting_point(0, e);
+    const size_t vb = (size_t)b * N;
+    const TIN* phib = static_cast<const TIN*>(a.phi) + vb * T * T;
+    float* uout = (dir == 0 ? a.ua : a.ub) + vb * T;
+    double* Oout = (dir == 0 ? a.Oa : a.Ob) + vb;
+    // the vector the chain starts from, and the positions it walks
+    const int start = a.extend ? mid : dir == 0 ? 0 : e;
+    const int end = a.extend ? (dir == 0 ? e : 0) : dir == 0 ? forward_end(a, 0, e) : mid;
+    const int first = dir == 0 ? start + 1 : start, n = dir == 0 ? end - start : start - end;
+    float v = LCCRF_NEG_INF;
+    double O = 0.0;
+    if (a.extend) {
+        if (tid < T) v = uout[(size_t)start * T + tid];
+        O = Oout[start];
+    } else if (tid < T) {
+        v = dir == 0 ? Elem<TIN>::get(phib + tid) * kLog2e : 0.f;
+    }
+    int steps = 0;
+    LogBlocks blocks;
+    for (;;) {
+        const int before = steps;
+        if (!a.exact_only) {
+            if (dir == 0) steps = linear_run<LG, TIN, ALIGNED, false>(lin, {phib, T, first, n, uout, Oout}, v, steps, O);
+            else steps = linear_run<LG, TIN, ALIGNED, true>(lin, {phib, T, first, n, uout, Oout}, v, steps, O);
+        }
+        if (steps >= n) break;
+        const int m = a.exact_only ? n : blocks.next(steps - before, n - steps);
+        const LogStepsResult r = stream_log_steps<TIN, ALIGNED>(a.phi, a.ua, a.ub, a.Oa, a.Ob, a.B, N, T, a.exact_only, b, dir,
+                                                                dir == 0 ? first + steps : first - steps, m, v, O);
+        v = r.v;
+        O = r.O;
+        steps += m;
+    }
+    if (tid < T) uout[(size_t)end * T + tid] = v;
+    if (tid == 0) Oout[end] = O;
+}
+
+// ---------------------------------------------------------------------------------------
+// Marginals of every position at once from the vectors of all positions (alpha and beta everywhere: two first passes, the
+// second with `extend`):
+//     mu_i(s, t) = 2^(ua_{i-1}(s) + phi2_i(s, t) + ub_i(t) + K_i),   K_i = Oa_{i-1} - Oa_i - log2 sum_t 2^(ua_i(t) + ub_i(t)),
+// one workgroup a position.  K_i comes from the position's own vectors (the sum over its edges is sum_t alpha_i(t) beta_i(t)),
+// so rounding drift between the chains' offsets does not reach the result.  Nothing here depends on another position:
+// where two workgroups a sequence leave most of the chip idle, the chains take their steps without writing and this kernel
+// moves the bytes with the whole chip.
+constexpr int kEdgeThreads = 256;
+template <typename TIN, bool ALIGNED>
+__global__ __launch_bounds__(kEdgeThreads) void edge_marginal_kernel(ChainArgs a) {
+    using Raw = RawPiece<TIN>;
+    __shared__ float av[256], bv[256], red[2][4];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int N = a.N, T = a.T, TT = T * T;
+    const int b = blockIdx.x / N, i = blockIdx.x % N;
+    const int L = clamp_length(a.lengths, b, N);
+    const size_t vb = (size_t)b * N;
+    float* mu = a.mu + (vb + i) * TT;
+    const auto clear = [&](int from) {  // entries from .. TT - 1
+        if (ALIGNED) {
+            for (int k = from / 4 + tid; k < TT / 4; k += kEdgeThreads) stream_store4(mu + 4 * k, 0.f, 0.f, 0.f, 0.f);
+        } else {
+            for (int k = from + tid; k < TT; k += kEdgeThreads) mu[k] = 0.f;
+        }
+    };
+    if (i >= L) {
+        if (i == 0 && tid == 0 && a.logZ) a.logZ[b] = 0.f;
+        clear(0);
+        return;
+    }
+    // log2 sum_t 2^(ua_i(t) + ub_i(t))
+    const float* ua_i = a.ua + (vb + i) * T;
+    const float* ub_i = a.ub + (vb + i) * T;
+    const float beta = tid < T ? ub_i[tid] : LCCRF_NEG_INF;
+    const float z = tid < T ? ua_i[tid] + beta : LCCRF_NEG_INF;
+    const float wm = xor_max<1, 64>(z);
+    if (lane == 0) red[0][wave] = wm;
+    av[tid] = i > 0 && tid < T ? a.ua[(vb + i - 1) * T + tid] : 0.f;
+    bv[tid] = beta;
+    __syncthreads();
+    const float M = fmaxf(fmaxf(red[0][0], red[0][1]), fmaxf(red[0][2], red[0][3]));
+    const float ws = xor_sum<1, 64>(ex2(z - finite_or_zero(M)));
+    if (lane == 0) red[1][wave] = ws;
+    __syncthreads();
+    const float lz = M + lg2((red[1][0] + red[1][1]) + (red[1][2] + red[1][3]));
+    if (a.logZ && tid == 0 && i == meeting_point(0, L - 1)) a.logZ[b] = (float)(((double)lz + a.Oa[vb + i] + a.Ob[vb + i]) * kLn2);
+    if (i == 0) {  // p(y_0 = t) in row 0
+        if (tid < T) mu[tid] = M == LCCRF_NEG_INF ? 0.f : ex2(z - lz);
+        clear(T);
+        return;
+    }
+    if (M == LCCRF_NEG_INF) {  // no path has a finite score
+        clear(0);
+        return;
+    }
+    const float K = (float)(a.Oa[vb + i - 1] - a.Oa[vb + i]) - lz;
+    // A wave takes whole rows; the last piece of a row is moved back to end with it (what it holds twice is written
+    // twice, the same values).
+    const TIN* mat = static_cast<const TIN*>(a.phi) + (vb + i) * TT;
+    if (4 * lane < T) {
+        const int c4 = min(4 * lane, T - 4);
+        const float b0 = bv[c4] + K, b1 = bv[c4 + 1] + K, b2 = bv[c4 + 2] + K, b3 = bv[c4 + 3] + K;
+#pragma unroll 8
+        for (int s = wave; s < T; s += kEdgeThreads / 64) {
+            const typename Raw::type r = Raw::template load<ALIGNED>((const GlobalBytes*)(mat + (size_t)s * T + c4));
+            const float as = av[s];
+            const float m0 = ex2(__builtin_fmaf(Raw::get(r, 0), kLog2e, as) + b0), m1 = ex2(__builtin_fmaf(Raw::get(r, 1), kLog2e, as) + b1);
+            const float m2 = ex2(__builtin_fmaf(Raw::get(r, 2), kLog2e, as) + b2), m3 = ex2(__builtin_fmaf(Raw::get(r, 3), kLog2e, as) + b3);
+            float* out = mu + (size_t)s * T + c4;
+            if (ALIGNED) stream_store4(out, m0, m1, m2, m3);
+            else store4_anywhere(out, m0, m1, m2, m3);
         }
     }
 }
@@ -826,21 +955,48 @@ hipError_t launch_stream_expect(int mode, int dtype, const ChainArgs& a, hipStre
 }
 
 template <typename TIN, bool ALIGNED>
-static hipError_t launch_stream_t(bool second_pass, const ChainArgs& a, hipStream_t st) {
-    if (second_pass)
-        hipLaunchKernelGGL((stream_chain_kernel<TIN, ALIGNED, true>), dim3(2 * a.B), dim3(1024), 0, st, a);
-    else
-        hipLaunchKernelGGL((stream_chain_kernel<TIN, ALIGNED, false>), dim3(2 * a.B), dim3(1024), 0, st, a);
+static hipError_t launch_stream_half(const ChainArgs& a, hipStream_t st) {
+    const dim3 grid(2 * a.B), block(1024);
+    const int items = linear_items(1024, a.T);  // 5 (129 tags) .. 16 (256 tags)
+#define LCCRF_STREAM_HALF(I) else if (items <= I) hipLaunchKernelGGL((stream_half_kernel<TIN, ALIGNED, I>), grid, block, 0, st, a)
+    if (items < 1) return hipErrorInvalidValue;
+    LCCRF_STREAM_HALF(5); LCCRF_STREAM_HALF(6); LCCRF_STREAM_HALF(7); LCCRF_STREAM_HALF(8); LCCRF_STREAM_HALF(9); LCCRF_STREAM_HALF(10);
+    LCCRF_STREAM_HALF(11); LCCRF_STREAM_HALF(12); LCCRF_STREAM_HALF(14); LCCRF_STREAM_HALF(16);
+    else return hipErrorInvalidValue;
+#undef LCCRF_STREAM_HALF
+    return hipGetLastError();
+}
+template <typename TIN, bool ALIGNED>
+static hipError_t launch_stream_marginal(const ChainArgs& a, hipStream_t st) {
+    hipLaunchKernelGGL((stream_marginal_kernel<TIN, ALIGNED>), dim3(2 * a.B), dim3(1024), 0, st, a);
     return hipGetLastError();
 }
 
 bool stream_supported(int T) { return T > 128 && T <= 256; }
 
+hipError_t launch_edge_marginals(int dtype, const ChainArgs& a, hipStream_t st) {
+    if (a.T < 4 || a.T > 256 || a.chunk > 0 || a.emit) return hipErrorInvalidValue;
+    const bool aligned = (a.T % 4) == 0;
+    const dim3 grid((unsigned)a.B * a.N), block(kEdgeThreads);
+    if (dtype == 0) {
+        if (aligned) hipLaunchKernelGGL((edge_marginal_kernel<float, true>), grid, block, 0, st, a);
+        else hipLaunchKernelGGL((edge_marginal_kernel<float, false>), grid, block, 0, st, a);
+    } else {
+        if (aligned) hipLaunchKernelGGL((edge_marginal_kernel<uint16_t, true>), grid, block, 0, st, a);
+        else hipLaunchKernelGGL((edge_marginal_kernel<uint16_t, false>), grid, block, 0, st, a);
+    }
+    return hipGetLastError();
+}
+
 hipError_t launch_stream_pass(bool second_pass, int dtype, const ChainArgs& a, hipStream_t st) {
     if (!stream_supported(a.T) || a.chunk > 0 || a.emit) return hipErrorInvalidValue;
     const bool aligned = (a.T % 4) == 0;
-    if (dtype == 0) return aligned ? launch_stream_t<float, true>(second_pass, a, st) : launch_stream_t<float, false>(second_pass, a, st);
-    return aligned ? launch_stream_t<uint16_t, true>(second_pass, a, st) : launch_stream_t<uint16_t, false>(second_pass, a, st);
+    if (second_pass) {
+        if (dtype == 0) return aligned ? launch_stream_marginal<float, true>(a, st) : launch_stream_marginal<float, false>(a, st);
+        return aligned ? launch_stream_marginal<uint16_t, true>(a, st) : launch_stream_marginal<uint16_t, false>(a, st);
+    }
+    if (dtype == 0) return aligned ? launch_stream_half<float, true>(a, st) : launch_stream_half<float, false>(a, st);
+    return aligned ? launch_stream_half<uint16_t, true>(a, st) : launch_stream_half<uint16_t, false>(a, st);
 }
 
 }  // namespace lccrf

@@ -1,0 +1,43 @@
+"""First passes in scaled probabilities (33 .. 256 tags) and marginals written by a kernel of their own, against the
+oracle: the tag counts at the edges of every instantiation (rows a thread holds, pieces off the 16-byte grid), steps that
+are not accepted (forbidden tags, jumps of the scale, vectors hundreds of bits apart) in the middle of accepted ones, and
+every short length.  Tolerances as everywhere for these queries (fp32 sums of a few hundred terms: 1e-5)."""
+import pytest
+import torch
+
+from paper_2308_03291_amd import workloads
+from test_gpu_parity import check_case, crf  # noqa: F401  (crf: the module-scoped binding fixture)
+
+pytestmark = pytest.mark.gpu
+
+TAGS = [65, 66, 88, 89, 101, 126, 129, 132, 141, 144, 157, 161, 176, 177, 189, 200, 201, 204, 205, 212, 225, 240, 241, 255, 256]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("T", TAGS)
+def test_linear_first_pass_and_edge_marginals(crf, oracle_mod, T, dtype):
+    N = 30
+    phi, _ = workloads.random_case(7100 + T, 7, N, T, scale=2.0, dtype=dtype)
+    phi[1, 11, :, 5] = float("-inf")      # a forbidden tag: a step that is not accepted, among others that are
+    phi[2, 7] += 250.0                    # jumps of the scale in either half
+    phi[2, 23] -= 250.0
+    phi[3, :, :, T - 1] = float("-inf")   # a tag forbidden everywhere: log-domain steps throughout
+    lens = torch.tensor([N, N - 1, N, N, 2, 1, 0], dtype=torch.int32)
+    check_case(crf, oracle_mod, phi, lens, what=f"linear T={T} {dtype}", queries=("logz", "mu"))
+
+
+@pytest.mark.parametrize("T", [45, 63, 99, 201])
+def test_bfloat16_rows_off_the_grid(crf, oracle_mod, T):
+    """The first pass of larger batches (no edge marginals) at odd tag counts, the tensor's last matrix included."""
+    phi, _ = workloads.random_case(7300 + T, 130, 9, T, scale=1.5, dtype="bf16")
+    check_case(crf, oracle_mod, phi, None, what=f"odd rows T={T}", queries=("logz", "mu"), algo=crf.ALGO_SEQUENTIAL)
+
+
+def test_nothing_is_read_past_the_tensor(crf, oracle_mod):
+    """NaN right behind the potentials (T odd: rows end anywhere)."""
+    for T, dtype in ((129, "f32"), (201, "bf16"), (67, "f32"), (99, "bf16")):
+        phi, _ = workloads.random_case(7400 + T, 2, 9, T, dtype=dtype)
+        flat = torch.full((phi.numel() + 64,), float("nan"), dtype=phi.dtype, device="cuda")
+        flat[:phi.numel()] = phi.reshape(-1).cuda()
+        check_case(crf, oracle_mod, phi, None, poison=False, what=f"tensor end T={T}", queries=("logz", "mu"),
+                   device_phi=flat[:phi.numel()].view(phi.shape))
