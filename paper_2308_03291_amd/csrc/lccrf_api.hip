@@ -593,8 +593,10 @@ static int cross_query(bool kl, const void* phi_p, const void* phi_q, lccrf_dtyp
     const SumWorkspace w = sum_workspace(B, N, T);
     char* base = static_cast<char*>(workspace);
     hipStream_t st = static_cast<hipStream_t>(stream);
-    // log Z_q first: the chains of p then reuse the vectors' storage, the double-precision result stays
-    hipError_t e = launch_log_partition64(phi_q, dt, lengths, B, N, T, w, base, st);
+    // log Z_q first: the chains of p then reuse the vectors' storage, the double-precision result stays (unless both run in
+    // one launch)
+    const bool together = !scan_pays_entropy(B, N, T) && lccrf::cross_runs_both(N, T);
+    hipError_t e = together ? hipSuccess : launch_log_partition64(phi_q, dt, lengths, B, N, T, w, base, st);
     if (scan_pays_entropy(B, N, T)) {
         // Long chains over few tags: the chains of p under the chunked scan, as for the entropy; the second
         // pass adds up the expectation of phi_q (of phi_q - phi_p) edge by edge from the marginals of p it
@@ -626,7 +628,7 @@ static int cross_query(bool kl, const void* phi_p, const void* phi_q, lccrf_dtyp
                                 reinterpret_cast<float*>(base + w.ub), reinterpret_cast<double*>(base + w.Oa),
                                 reinterpret_cast<double*>(base + w.Ob), reinterpret_cast<float*>(base + w.ha),
                                 reinterpret_cast<float*>(base + w.hb), reinterpret_cast<double*>(base + w.hoff),
-                                reinterpret_cast<const double*>(base + w.lz64), out, st);
+                                together ? nullptr : reinterpret_cast<const double*>(base + w.lz64), out, st);
     return e == hipSuccess ? LCCRF_OK : LCCRF_ELAUNCH;
 }
 

@@ -154,11 +154,12 @@ __device__ __forceinline__ void load_row4(const TIN* __restrict__ mat, int T, in
 
 __device__ __forceinline__ float expectation_of(float U, float S) { return S > 0.f ? U / S : 0.f; }
 
-template <typename G, typename TIN, bool ALIGNED, int MODE>
-__global__ __launch_bounds__(G::W) void entropy_half_kernel(ChainArgs a) {
-    __shared__ EntropySmem<G> sm;
+// PLAIN: the chain alone, no expectation (the chains of the second sequence potentials, see entropy_half_kernel); `row` says
+// in which row of ua / ub / Oa / Ob its vector of the meeting position goes.
+template <typename G, typename TIN, bool ALIGNED, int MODE, bool PLAIN>
+__device__ __forceinline__ void expect_half(EntropySmem<G>& sm, const ChainArgs& a, int v, const void* phi, const void* psi, int row) {
     constexpr int ITEMS = G::ITEMS, PF = 2;
-    constexpr bool CROSS = MODE != 0;
+    constexpr bool CROSS = MODE != 0 && !PLAIN;
     // the second tile travels through a ring of its own where registers allow (QRING); the
     // sixteen-wave geometries have 128 registers a thread: there its rows are fetched where they
     // are used
@@ -167,15 +168,15 @@ __global__ __launch_bounds__(G::W) void entropy_half_kernel(ChainArgs a) {
     constexpr int QITEMS = QRING ? ITEMS : 1, QPF = QRING ? PF : 1;
     constexpr bool SPEC = (ITEMS == 4 || ITEMS == 8) && G::LPR >= 16;  // speculative step first
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int b = blockIdx.x >> 1, dir = blockIdx.x & 1;
+    const int b = v >> 1, dir = v & 1;
     const int N = a.N, T = a.T;
     const int L = clamp_length(a.lengths, b, N);
     if (L == 0) return;
     const int e = L - 1, h = meeting_point(0, e);
     const int c4 = 4 * (tid % G::LPR), r0 = tid / G::LPR;
     const size_t TT = (size_t)T * T, vb = (size_t)b * N;
-    const TIN* phib = static_cast<const TIN*>(a.phi) + (size_t)b * N * TT;
-    const TIN* psib = CROSS ? static_cast<const TIN*>(a.psi) + (size_t)b * N * TT : phib;
+    const TIN* phib = static_cast<const TIN*>(phi) + (size_t)b * N * TT;
+    const TIN* psib = CROSS ? static_cast<const TIN*>(psi) + (size_t)b * N * TT : phib;
 
     for (int k = tid; k < 2 * G::TCAP; k += G::W) {
         (&sm.rvec[0][0])[k] = LCCRF_NEG_INF;
@@ -264,17 +265,17 @@ __global__ __launch_bounds__(G::W) void entropy_half_kernel(ChainArgs a) {
                         const float ex = ex2(arg);
                         ls[j] += ex;
                         if (CROSS) lu[j] += ex > 0.f ? ex * (hin[k] + f[j]) : 0.f;
-                        else lu[j] = __builtin_fmaf(ex, hin[k] - log2_term(arg), lu[j]);
+                        else if (!PLAIN) lu[j] = __builtin_fmaf(ex, hin[k] - log2_term(arg), lu[j]);
                     }
                 }
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     ls[j] = xor_sum<G::LPR, 64>(ls[j]);
-                    lu[j] = xor_sum<G::LPR, 64>(lu[j]);
+                    if (!PLAIN) lu[j] = xor_sum<G::LPR, 64>(lu[j]);
                 }
                 if (lane < G::LPR) {
                     *reinterpret_cast<float4*>(&sm.psum[wave][c4]) = make_float4(ls[0], ls[1], ls[2], ls[3]);
-                    *reinterpret_cast<float4*>(&sm.pU[wave][c4]) = make_float4(lu[0], lu[1], lu[2], lu[3]);
+                    if (!PLAIN) *reinterpret_cast<float4*>(&sm.pU[wave][c4]) = make_float4(lu[0], lu[1], lu[2], lu[3]);
                 }
                 __syncthreads();
                 if (wave < G::COLWAVES) {
@@ -284,11 +285,11 @@ __global__ __launch_bounds__(G::W) void entropy_half_kernel(ChainArgs a) {
 #pragma unroll
                         for (int w = 0; w < G::WAVES; ++w) {
                             S += sm.psum[w][tid];
-                            U += sm.pU[w][tid];
+                            if (!PLAIN) U += sm.pU[w][tid];
                         }
                         good = sum_in_range(S);
                         sm.rvec[buf ^ 1][tid] = d + lg2(S);
-                        sm.hvec[buf ^ 1][tid] = CROSS ? expectation_of(U, S) : entropy_of(U, S);
+                        if (!PLAIN) sm.hvec[buf ^ 1][tid] = CROSS ? expectation_of(U, S) : entropy_of(U, S);
                     }
                     if (!__all(good) && lane == 0) sm.bad[flag] = 1;
                 }
@@ -331,17 +332,17 @@ __global__ __launch_bounds__(G::W) void entropy_half_kernel(ChainArgs a) {
                     const float ex = ex2(arg);
                     ls[j] += ex;
                     if (CROSS) lu[j] += ex > 0.f ? ex * (hin[k] + f[j]) : 0.f;
-                    else lu[j] = __builtin_fmaf(ex, hin[k] - log2_term(arg), lu[j]);
+                    else if (!PLAIN) lu[j] = __builtin_fmaf(ex, hin[k] - log2_term(arg), lu[j]);
                 }
             }
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 ls[j] = xor_sum<G::LPR, 64>(ls[j]);
-                lu[j] = xor_sum<G::LPR, 64>(lu[j]);
+                if (!PLAIN) lu[j] = xor_sum<G::LPR, 64>(lu[j]);
             }
             if (lane < G::LPR) {
                 *reinterpret_cast<float4*>(&sm.psum[wave][c4]) = make_float4(ls[0], ls[1], ls[2], ls[3]);
-                *reinterpret_cast<float4*>(&sm.pU[wave][c4]) = make_float4(lu[0], lu[1], lu[2], lu[3]);
+                if (!PLAIN) *reinterpret_cast<float4*>(&sm.pU[wave][c4]) = make_float4(lu[0], lu[1], lu[2], lu[3]);
             }
             __syncthreads();
             if (tid < T) {
@@ -349,11 +350,11 @@ __global__ __launch_bounds__(G::W) void entropy_half_kernel(ChainArgs a) {
 #pragma unroll
                 for (int w = 0; w < G::WAVES; ++w) {
                     S += sm.psum[w][tid];
-                    U += sm.pU[w][tid];
+                    if (!PLAIN) U += sm.pU[w][tid];
                     Mt = fmaxf(Mt, sm.pmax[w][tid]);
                 }
                 sm.rvec[buf ^ 1][tid] = Mt + lg2(S);  // Mt = -inf gives S = 0: -inf
-                sm.hvec[buf ^ 1][tid] = CROSS ? expectation_of(U, S) : entropy_of(U, S);
+                if (!PLAIN) sm.hvec[buf ^ 1][tid] = CROSS ? expectation_of(U, S) : entropy_of(U, S);
             }
             __syncthreads();
             buf ^= 1;
@@ -392,7 +393,7 @@ __global__ __launch_bounds__(G::W) void entropy_half_kernel(ChainArgs a) {
                         const float ex = ex2(arg);
                         Sl[k] += ex;
                         if (CROSS) Ul[k] += ex > 0.f ? ex * (hin[j] + f[j]) : 0.f;
-                        else Ul[k] = __builtin_fmaf(ex, hin[j] - log2_term(arg), Ul[k]);
+                        else if (!PLAIN) Ul[k] = __builtin_fmaf(ex, hin[j] - log2_term(arg), Ul[k]);
                     }
                 }
                 // four rows at a time: each lane ends up with the complete sums of one of them
@@ -401,11 +402,11 @@ __global__ __launch_bounds__(G::W) void entropy_half_kernel(ChainArgs a) {
 #pragma unroll
                 for (int k0 = 0; k0 < ITEMS; k0 += 4) {
                     const float S = reduce4_over_lanes<G::LPR>(Sl[k0], Sl[k0 + 1], Sl[k0 + 2], Sl[k0 + 3], lane);
-                    const float U = reduce4_over_lanes<G::LPR>(Ul[k0], Ul[k0 + 1], Ul[k0 + 2], Ul[k0 + 3], lane);
+                    const float U = PLAIN ? 0.f : reduce4_over_lanes<G::LPR>(Ul[k0], Ul[k0 + 1], Ul[k0 + 2], Ul[k0 + 3], lane);
                     const int s = r0 + (k0 + kk) * G::RPP;
                     if ((tid % G::LPR) < 4 && s < T) {
                         sm.rvec[buf ^ 1][s] = d + lg2(S);
-                        sm.hvec[buf ^ 1][s] = CROSS ? expectation_of(U, S) : entropy_of(U, S);
+                        if (!PLAIN) sm.hvec[buf ^ 1][s] = CROSS ? expectation_of(U, S) : entropy_of(U, S);
                     }
                     good = good && (s >= T || sum_in_range(S));
                 }
@@ -433,13 +434,13 @@ __global__ __launch_bounds__(G::W) void entropy_half_kernel(ChainArgs a) {
                     const float ex = ex2(arg);
                     Sl += ex;
                     if (CROSS) Ul += ex > 0.f ? ex * (hin[j] + f[j]) : 0.f;
-                    else Ul = __builtin_fmaf(ex, hin[j] - log2_term(arg), Ul);
+                    else if (!PLAIN) Ul = __builtin_fmaf(ex, hin[j] - log2_term(arg), Ul);
                 }
-                const float S = xor_sum<1, G::LPR>(Sl), U = xor_sum<1, G::LPR>(Ul);
+                const float S = xor_sum<1, G::LPR>(Sl), U = PLAIN ? 0.f : xor_sum<1, G::LPR>(Ul);
                 const int s = r0 + k * G::RPP;
                 if (c4 == 0 && s < T) {
                     sm.rvec[buf ^ 1][s] = m + lg2(S);
-                    sm.hvec[buf ^ 1][s] = CROSS ? expectation_of(U, S) : entropy_of(U, S);
+                    if (!PLAIN) sm.hvec[buf ^ 1][s] = CROSS ? expectation_of(U, S) : entropy_of(U, S);
                 }
             }
             __syncthreads();
@@ -450,16 +451,37 @@ __global__ __launch_bounds__(G::W) void entropy_half_kernel(ChainArgs a) {
     const float d = shift();
     O += (double)d;
     if (tid < T) {
-        (dir == 0 ? a.ua : a.ub)[(vb + h) * T + tid] = sm.rvec[buf][tid] - d;
-        (dir == 0 ? a.ha : a.hb)[(size_t)b * T + tid] = sm.hvec[buf][tid];
+        (dir == 0 ? a.ua : a.ub)[(vb + row) * T + tid] = sm.rvec[buf][tid] - d;
+        if (!PLAIN) (dir == 0 ? a.ha : a.hb)[(size_t)b * T + tid] = sm.hvec[buf][tid];
     }
-    if (tid == 0) (dir == 0 ? a.Oa : a.Ob)[vb + h] = O;
+    if (tid == 0) (dir == 0 ? a.Oa : a.Ob)[vb + row] = O;
     if (CROSS && tid == 0) a.hoff[2 * b + dir] = Hoff;
 }
 
+// The row of ua / ub / Oa / Ob that the chains of psi leave their vectors of the meeting position h in (N >= 2): not h, which
+// holds those of phi.
+__device__ __forceinline__ int psi_row(int h) { return h > 0 ? h - 1 : 1; }
+
+// Workgroups 0 .. 2 B - 1: the half chains of phi with their expectations.  With a.psi_chains (cross-entropy and divergence),
+// workgroups 2 B .. 4 B - 1 run the plain half chains of psi beside them, for its log-partition: as launches one after the
+// other either leaves half of the chip idle (B=64, N=256, 64 tags: 96 + 172 us, together 176).
+template <typename G, typename TIN, bool ALIGNED, int MODE>
+__global__ __launch_bounds__(G::W) void entropy_half_kernel(ChainArgs a) {
+    __shared__ EntropySmem<G> sm;
+    const int v = blockIdx.x;
+    if (MODE == 0 || v < 2 * a.B) {
+        const int L = clamp_length(a.lengths, v >> 1, a.N);
+        expect_half<G, TIN, ALIGNED, MODE, false>(sm, a, v, a.phi, a.psi, meeting_point(0, L - 1));
+    } else if constexpr (MODE != 0) {
+        const int L = clamp_length(a.lengths, (v - 2 * a.B) >> 1, a.N);
+        expect_half<G, TIN, ALIGNED, MODE, true>(sm, a, v - 2 * a.B, a.psi, nullptr, psi_row(meeting_point(0, L - 1)));
+    }
+}
+
+
 template <typename TIN, bool ALIGNED, int MODE>
 static hipError_t launch_entropy_T(const ChainArgs& a, hipStream_t st) {
-    const dim3 grid(2 * a.B);
+    const dim3 grid((a.psi_chains ? 4 : 2) * a.B);
     if (a.T <= 16)
         hipLaunchKernelGGL((entropy_half_kernel<Geo<4, 1, 1>, TIN, ALIGNED, MODE>), grid, dim3(64), 0, st, a);
     else if (a.T <= 32)
@@ -586,12 +608,27 @@ __global__ __launch_bounds__(64) void cross_combine_kernel(ChainArgs a, const do
         if (p > 0.f) acc += p * (a.ha[(size_t)b * T + t] + a.hb[(size_t)b * T + t]);
     }
     acc = xor_sum<1, 64>(acc);
+    double lzq;
+    if (a.psi_chains) {  // from the vectors the chains of psi have left
+        const size_t r = vb + psi_row(h);
+        float mq = LCCRF_NEG_INF;
+        for (int t = lane; t < T; t += 64) mq = fmaxf(mq, a.ua[r * T + t] + a.ub[r * T + t]);
+        mq = xor_max<1, 64>(mq);
+        float Sq = 0.f;
+        for (int t = lane; t < T; t += 64) Sq += ex2(a.ua[r * T + t] + a.ub[r * T + t] - finite_or_zero(mq));
+        Sq = xor_sum<1, 64>(Sq);
+        lzq = ((double)(mq + lg2(Sq)) + a.Oa[r] + a.Ob[r]) * kLn2;
+    } else {
+        lzq = logZq[b];
+    }
     if (lane == 0) {
         const double E = (double)acc + a.hoff[2 * b] + a.hoff[2 * b + 1];
         const double lzp = (a.Oa[vb + h] + a.Ob[vb + h] + (double)m + (double)lg2(S)) * kLn2;
-        out[b] = (float)(kl ? E - lzp + logZq[b] : logZq[b] - E);
+        out[b] = (float)(kl ? E - lzp + lzq : lzq - E);
     }
 }
+
+bool cross_runs_both(int N, int T) { return N >= 2 && !stream_supported(T); }
 
 hipError_t launch_cross(bool kl, int dtype, const void* phi_p, const void* phi_q, const int32_t* lengths, int B, int N,
                         int T, float* ua, float* ub, double* Oa, double* Ob, float* ha, float* hb, double* hoff,
@@ -601,6 +638,7 @@ hipError_t launch_cross(bool kl, int dtype, const void* phi_p, const void* phi_q
     a.hb = hb;
     a.hoff = hoff;
     a.psi = phi_q;
+    a.psi_chains = logZq ? 0 : 1;
     const hipError_t e = kl ? launch_entropy_mode<2>(dtype, a, st) : launch_entropy_mode<1>(dtype, a, st);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(cross_combine_kernel, dim3(B), dim3(64), 0, st, a, logZq, out, kl ? 1 : 0);
