@@ -404,7 +404,10 @@ int lccrf_auto_algo(lccrf_op op, int B, int N, int T) {
             if (lanes_pay_sum(op == LCCRF_OP_LOGZ ? 0 : 1, B, N, T)) return LCCRF_ALGO_SEQUENTIAL_LANES;
             scan = scan_pays_sum(B, N, T);
             break;
-        case LCCRF_OP_LOG_PROB: scan = scan_pays_sum(B, N, T); break;
+        case LCCRF_OP_LOG_PROB:
+            if (lanes_pay_sum(0, B, N, T)) return LCCRF_ALGO_SEQUENTIAL_LANES;
+            scan = scan_pays_sum(B, N, T);
+            break;
         case LCCRF_OP_SAMPLE: scan = scan_pays_sample(B, N, T); break;
         case LCCRF_OP_ARGMAX:
             scan = scan_taken_max(B, N, T);
@@ -509,7 +512,8 @@ int lccrf_argmax(const void* phi, lccrf_dtype dt, const int32_t* lengths, int B,
 static hipError_t launch_log_partition64(const void* phi, int dt, const int32_t* lengths, int B, int N, int T,
                                          const SumWorkspace& w, char* base, hipStream_t st) {
     double* lz64 = reinterpret_cast<double*>(base + w.lz64);
-    if (scan_pays_sum(B, N, T))
+    const bool lanes = lanes_pay_sum(0, B, N, T);
+    if (!lanes && scan_pays_sum(B, N, T))
         return lccrf::launch_scan_boundaries(
             dt, phi, lengths, B, N, T, scan_chunk(B, N, T), reinterpret_cast<float*>(base + w.Pl),
             reinterpret_cast<float*>(base + w.rel), reinterpret_cast<double*>(base + w.base),
@@ -519,7 +523,8 @@ static hipError_t launch_log_partition64(const void* phi, int dt, const int32_t*
     return lccrf::launch_sequential_sum(0, dt, phi, lengths, B, N, T, reinterpret_cast<float*>(base + w.ua),
                                         reinterpret_cast<float*>(base + w.ub), reinterpret_cast<double*>(base + w.Oa),
                                         reinterpret_cast<double*>(base + w.Ob), nullptr, nullptr, st, nullptr, false,
-                                        nullptr, nullptr, lz64);
+                                        nullptr, nullptr, lz64, nullptr, nullptr, 0, 0, lanes,
+                                        g_lane_poll_limit.load(std::memory_order_relaxed));
 }
 
 int lccrf_log_prob(const void* phi, lccrf_dtype dt, const int32_t* lengths, const int32_t* tags, int B, int N, int T,
@@ -533,9 +538,20 @@ int lccrf_log_prob(const void* phi, lccrf_dtype dt, const int32_t* lengths, cons
     const SumWorkspace w = sum_workspace(B, N, T);
     char* base = static_cast<char*>(workspace);
     hipStream_t st = static_cast<hipStream_t>(stream);
-    double* lz64 = reinterpret_cast<double*>(base + w.lz64);
-    hipError_t e = launch_log_partition64(phi, dt, lengths, B, N, T, w, base, st);
-    if (e == hipSuccess) e = lccrf::launch_path_log_prob(dt, phi, lengths, tags, B, N, T, lz64, log_prob, st);
+    // The log-partition by the schedule lccrf_log_partition takes.  Where that leaves two vectors at the meeting position, the
+    // kernel that gathers the path's score forms log Z from them itself.
+    const bool lanes = lanes_pay_sum(0, B, N, T);
+    float *ua = reinterpret_cast<float*>(base + w.ua), *ub = reinterpret_cast<float*>(base + w.ub);
+    double *Oa = reinterpret_cast<double*>(base + w.Oa), *Ob = reinterpret_cast<double*>(base + w.Ob);
+    const double* lz64 = nullptr;
+    hipError_t e;
+    if (lanes || (T > 32 && !scan_pays_sum(B, N, T))) {
+        e = lccrf::launch_meeting_vectors(dt, phi, lengths, B, N, T, ua, ub, Oa, Ob, lanes, g_lane_poll_limit.load(std::memory_order_relaxed), st);
+    } else {
+        e = launch_log_partition64(phi, dt, lengths, B, N, T, w, base, st);
+        lz64 = reinterpret_cast<const double*>(base + w.lz64);
+    }
+    if (e == hipSuccess) e = lccrf::launch_path_log_prob(dt, phi, lengths, tags, B, N, T, lz64, {ua, ub, Oa, Ob}, log_prob, st);
     return e == hipSuccess ? LCCRF_OK : LCCRF_ELAUNCH;
 }
 

@@ -1216,6 +1216,19 @@ hipError_t launch_full_forward(int dtype, const void* phi, const int32_t* length
     return aligned ? launch_T<uint16_t, true>(2, a, st, nullptr, pair) : launch_T<uint16_t, false>(2, a, st, nullptr, pair);
 }
 
+hipError_t launch_meeting_vectors(int dtype, const void* phi, const int32_t* lengths, int B, int N, int T, float* ua, float* ub,
+                                  double* Oa, double* Ob, bool lanes, int lane_poll_limit, hipStream_t st) {
+    ChainArgs a{phi, lengths, B, N, T, ua, ub, Oa, Ob, nullptr, nullptr, 0, nullptr, 0, 1, nullptr, nullptr, nullptr, nullptr};
+    if (lanes) return launch_lane_pass(false, dtype, a, true, lane_poll_limit, st);
+    if (stream_supported(T)) return launch_stream(2, dtype, a, st, nullptr);
+    if (wave_supported(T)) return hipErrorInvalidValue;  // (their log-partition is one launch already)
+    const PairPlan pair{nullptr, nullptr, dtype, 0, 0};
+    const bool aligned = (T % 4) == 0;
+    if (dtype == 0)
+        return aligned ? launch_T<float, true>(2, a, st, nullptr, pair) : launch_T<float, false>(2, a, st, nullptr, pair);
+    return aligned ? launch_T<uint16_t, true>(2, a, st, nullptr, pair) : launch_T<uint16_t, false>(2, a, st, nullptr, pair);
+}
+
 hipError_t launch_chunked_full_forward(int dtype, const void* phi, const int32_t* lengths, int B, int N, int T,
                                        float* ua, float* ub, double* Oa, double* Ob, int chunk, const float* Fv,
                                        const double* OF, hipStream_t st) {

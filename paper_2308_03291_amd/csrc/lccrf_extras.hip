@@ -12,11 +12,13 @@ namespace lccrf {
 // score is summed in double precision (it and logZ are both of the size of the chain's total,
 // their difference is not).  A tag outside [0, T) makes the result NaN.
 constexpr int kPathThreads = 512;
+// logZ64 null: log Z is formed here, by one of the waves while the others gather, from the vectors a first pass has left at the
+// meeting position (a launch less: the paper's shape 5 us).
 template <typename TIN>
 __global__ __launch_bounds__(kPathThreads) void path_log_prob_kernel(const TIN* __restrict__ phi, const int32_t* __restrict__ lengths,
                                                           const int32_t* __restrict__ tags, int N, int T,
-                                                          const double* __restrict__ logZ64, float* __restrict__ out) {
-    __shared__ double part[kPathThreads / 64];
+                                                          const double* __restrict__ logZ64, MeetingVectors mv, float* __restrict__ out) {
+    __shared__ double part[kPathThreads / 64], lz;
     __shared__ int part_bad[kPathThreads / 64];
     const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int L = clamp_length(lengths, b, N);
@@ -24,6 +26,17 @@ __global__ __launch_bounds__(kPathThreads) void path_log_prob_kernel(const TIN* 
     const TIN* phib = phi + (size_t)b * N * T * T;
     double acc = 0.0;
     bool bad = false;
+    if (!logZ64 && wave == kPathThreads / 64 - 1 && L > 0) {
+        const size_t at = (size_t)b * N + meeting_point(0, L - 1);
+        const float *ua = mv.ua + at * T, *ub = mv.ub + at * T;
+        float m = LCCRF_NEG_INF;
+        for (int t = lane; t < T; t += 64) m = fmaxf(m, ua[t] + ub[t]);
+        m = xor_max<1, 64>(m);
+        float S = 0.f;
+        for (int t = lane; t < T; t += 64) S += ex2(ua[t] + ub[t] - finite_or_zero(m));
+        S = xor_sum<1, 64>(S);
+        if (lane == 0) lz = ((double)(m + lg2(S)) + mv.Oa[at] + mv.Ob[at]) * kLn2;
+    }
     for (int i = tid; i < L; i += kPathThreads) {
         const int t = y[i], s = i > 0 ? y[i - 1] : 0;
         if (t < 0 || t >= T || s < 0 || s >= T) { bad = true; continue; }
@@ -48,18 +61,18 @@ __global__ __launch_bounds__(kPathThreads) void path_log_prob_kernel(const TIN* 
             total += part[w];
             any_bad |= part_bad[w];
         }
-        out[b] = any_bad ? __builtin_nanf("") : (float)(total - logZ64[b]);
+        out[b] = any_bad ? __builtin_nanf("") : (float)(total - (logZ64 ? logZ64[b] : L > 0 ? lz : 0.0));
     }
 }
 
 hipError_t launch_path_log_prob(int dtype, const void* phi, const int32_t* lengths, const int32_t* tags, int B, int N,
-                                int T, const double* logZ64, float* out, hipStream_t st) {
+                                int T, const double* logZ64, const MeetingVectors& mv, float* out, hipStream_t st) {
     if (dtype == 0)
         hipLaunchKernelGGL(path_log_prob_kernel<float>, dim3(B), dim3(kPathThreads), 0, st, static_cast<const float*>(phi), lengths,
-                           tags, N, T, logZ64, out);
+                           tags, N, T, logZ64, mv, out);
     else
         hipLaunchKernelGGL(path_log_prob_kernel<uint16_t>, dim3(B), dim3(kPathThreads), 0, st, static_cast<const uint16_t*>(phi),
-                           lengths, tags, N, T, logZ64, out);
+                           lengths, tags, N, T, logZ64, mv, out);
     return hipGetLastError();
 }
 

@@ -77,9 +77,16 @@ hipError_t launch_scan_boundaries(int dtype, const void* phi, const int32_t* len
 // emit non-null: structured potentials trans + emit (dtype 0; phi is not read), here and in the launchers below.
 
 // log p(y) = score(y) - logZ for one tag path per sequence (lccrf_extras.hip); logZ64: [B] doubles
-// already computed on the same stream.
+// already computed on the same stream, or null: from the vectors launch_meeting_vectors has left there.
+struct MeetingVectors {
+    const float *ua, *ub;
+    const double *Oa, *Ob;
+};
 hipError_t launch_path_log_prob(int dtype, const void* phi, const int32_t* lengths, const int32_t* tags, int B, int N,
-                                int T, const double* logZ64, float* out, hipStream_t st);
+                                int T, const double* logZ64, const MeetingVectors& mv, float* out, hipStream_t st);
+// A first pass alone, for what is made of the vectors of the meeting position (lanes or more than 32 tags).
+hipError_t launch_meeting_vectors(int dtype, const void* phi, const int32_t* lengths, int B, int N, int T, float* ua, float* ub,
+                                  double* Oa, double* Ob, bool lanes, int lane_poll_limit, hipStream_t st);
 // Two-pass forward-backward inside every chunk from those boundary vectors (lccrf_chain.hip); chunk >= 4.
 hipError_t launch_chunked_marginals(int dtype, const void* phi, const int32_t* lengths, int B, int N, int T,
                                     float* ua, float* ub, double* Oa, double* Ob, float* mu, int chunk,
