@@ -15,6 +15,7 @@
 // LDS, and the new vector replaces the oldest one.
 #include "lccrf_device.h"
 #include "lccrf_launch.h"
+#include "lccrf_linear.h"
 
 namespace lccrf {
 
@@ -35,16 +36,18 @@ static size_t semi_lds_bytes(int K, int T, int lpr, int waves) {
     return (size_t)((K + 1) / 2 * 2) * sizeof(double) + ring * sizeof(float) + (size_t)2 * waves * 4 * lpr * sizeof(float) + 16;
 }
 
+// Positions `from` .. L - 1 of sequence b in the log domain, from the shared state described above (ring, base: the K last
+// vectors and their offsets, `cur` the slot of position from - 1, the newest vector's maximum in *dlast; a barrier lies
+// behind it), then logZ.
 template <int LPR, int WAVES, typename TIN, bool ALIGNED>
-__global__ __launch_bounds__(64 * WAVES) void semi_forward_kernel(SemiArgs a) {
+__device__ __forceinline__ void semi_log_steps(const SemiArgs& a, int b, int L, int from, int cur, double R, unsigned char* semi_smem) {
     constexpr int W = 64 * WAVES, RPP = W / LPR, CAP = 4 * LPR, ITEMS = kSemiItems, PF = kSemiPF;
     // One pass of the workgroup covers RPP rows (thread: row r0, columns c4 .. c4+3): a part of one
     // T x T matrix, PPT passes covering it (RPP <= CAP), or TPP whole matrices of consecutive segment
     // lengths (RPP > CAP).  A batch is ITEMS passes.  Which row of its matrix a thread holds in
     // pass p, and which segment length that matrix belongs to, follow from p alone.
     constexpr int PPT = CAP / RPP > 0 ? CAP / RPP : 1, TPP = RPP / CAP > 0 ? RPP / CAP : 1;
-    static_assert((PPT * RPP == CAP || TPP * CAP == RPP) && (PPT == 1 || PPT == 4 || PPT == 16) && ITEMS == 4, "geometry");
-    extern __shared__ __attribute__((aligned(16))) unsigned char semi_smem[];
+    static_assert((PPT * RPP == CAP || TPP * CAP == RPP) && (PPT <= 2 || PPT == 4 || PPT == 16) && ITEMS == 4, "geometry");
     const int K = a.K, T = a.T, N = a.N;
     const int KT = K * T;
     double* base = reinterpret_cast<double*>(semi_smem);
@@ -54,30 +57,14 @@ __global__ __launch_bounds__(64 * WAVES) void semi_forward_kernel(SemiArgs a) {
     float* dlast = psum + WAVES * CAP;  // maximum of the newest vector (T <= 64)
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int b = blockIdx.x;
-    const int L = clamp_length(a.lengths, b, N);
-    if (L == 0) {
-        if (tid == 0) a.logZ[b] = 0.f;
-        return;
-    }
     const int c4 = 4 * (tid % LPR), r0 = (tid / LPR) % CAP, k0 = (tid / LPR) / CAP;  // k0 = 0 unless TPP > 1
     const size_t TT = (size_t)T * T;
     const TIN* phib = static_cast<const TIN*>(a.phi) + (size_t)b * N * K * TT;
     const int nb = ((K + TPP - 1) / TPP * PPT + ITEMS - 1) / ITEMS;  // batches per position
-    const int total = L * nb;
-
-    // The empty prefix sits in the slot "position -1": potential 1 for row 0, nothing else.
-    for (int k = tid; k < KT; k += W) ring[k] = LCCRF_NEG_INF;
-    for (int k = tid; k < K; k += W) base[k] = 0.0;
-    __syncthreads();
-    if (tid == 0) {
-        ring[(K - 1) * T] = 0.f;
-        *dlast = 0.f;
-    }
-    __syncthreads();
+    const int total = (L - from) * nb;
 
     float tile[PF][ITEMS][4];
-    int li = 0, lbt = 0;  // position and batch of the next load
+    int li = from, lbt = 0;  // position and batch of the next load
     auto load = [&](int q, int slot) {
         const TIN* mat = phib + (size_t)li * K * TT;
 #pragma unroll
@@ -100,9 +87,7 @@ __global__ __launch_bounds__(64 * WAVES) void semi_forward_kernel(SemiArgs a) {
         }
     };
 
-    int i = 0, bt = 0;  // position and batch being consumed
-    int cur = K - 1;    // ring slot of position i - 1
-    double R = 0.0;     // offset the new vector is relative to
+    int i = from, bt = 0;  // position and batch being consumed (R: the offset the new vector is relative to)
     float mx[4], sm[4];
     walk<PF>(0, total - 1, +1, load, [&](int, int slot) {
         if (bt == 0) {
@@ -205,6 +190,234 @@ __global__ __launch_bounds__(64 * WAVES) void semi_forward_kernel(SemiArgs a) {
     }
 }
 
+template <int LPR, int WAVES, typename TIN, bool ALIGNED>
+__global__ __launch_bounds__(64 * WAVES) void semi_forward_kernel(SemiArgs a) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char semi_smem[];
+    const int K = a.K, T = a.T, KT = K * T, W = 64 * WAVES;
+    double* base = reinterpret_cast<double*>(semi_smem);
+    float* ring = reinterpret_cast<float*>(base + (K + 1) / 2 * 2);
+    float* dlast = ring + (KT + 3) / 4 * 4 + 2 * WAVES * 4 * LPR;
+    const int tid = threadIdx.x, b = blockIdx.x;
+    const int L = clamp_length(a.lengths, b, a.N);
+    if (L == 0) {
+        if (tid == 0) a.logZ[b] = 0.f;
+        return;
+    }
+    // The empty prefix sits in the slot "position -1": potential 1 for row 0, nothing else.
+    for (int k = tid; k < KT; k += W) ring[k] = LCCRF_NEG_INF;
+    for (int k = tid; k < K; k += W) base[k] = 0.0;
+    __syncthreads();
+    if (tid == 0) {
+        ring[(K - 1) * T] = 0.f;
+        *dlast = 0.f;
+    }
+    __syncthreads();
+    semi_log_steps<LPR, WAVES, TIN, ALIGNED>(a, b, L, 0, K - 1, 0.0, semi_smem);
+}
+
+// ---------------------------------------------------------------------------------------
+// The same recursion in scaled probabilities (see lccrf_linear.h for the linear chain's), 8 .. 64 tags: a step is a product of
+// the K last vectors, laid end to end, with the (K T) x T block exponentiated one step AHEAD, so that no exponential and no
+// logarithm is on the dependent path.  A wave sums its rows' products over its lanes (halving the values a lane carries with
+// every permlane swap), the waves' sums meet in LDS behind the step's one barrier, and every wave adds them up for
+// itself: lane = tag, so the new vector, its scale and the decision whether the step is accepted need no second exchange.
+//
+// Vectors are V_i 2^O_i with an integer O_i; entry (k, s, t) of the block of position i is held as
+//     E = 2^(phi log2 e - c_i - (O_{i-1} - O_{i-1-k})),
+// the vectors' different offsets in the exponents, so that the sums take the vectors as they lie.  V_i is the sum rescaled by the
+// power of two that brings tag 0 into [1/2, 1).  c_i has to be chosen before V_{i-1} is known: it is what tag 0 grew by at the
+// step before the last one (the first two blocks: the largest first potential), less kSemiHead.  A step is accepted if every
+// sum is at least 2^-40 before and within [2^-40, 2^40] after rescaling: what underflowed in it is then at most
+// K T 2^40 2^-126 of a sum of 2^-40, below 2^-30 for K T <= 2^16.  At a step that is not accepted the rest of the sequence goes to
+// the log-domain steps, from the vectors at hand.
+//
+// Layout: row r = k T + s of the block, LPR lanes a row, G = W / LPR row groups; thread (g, cl) holds rows g, g + G, ...; the
+// last piece of a row is moved back to end with it, rows past the block are its last one again, as in lccrf_linear.h.
+// A step of 32 tags, K = 8 costs 0.84 us (log-domain steps 2.0): two LDS round trips and the barrier on the dependent path, then
+// the next block's exponentials, which wait for the newest offset.
+constexpr int kSemiHead = 24;
+constexpr float kSemiLo = 0x1p-40f, kSemiHi = 0x1p40f;
+template <int WAVES, int LPR>
+static size_t semi_linear_bytes(int K) {  // vec[K + 2][4 LPR], partial sums [2][WAVES][4 LPR], offsets [K + 1]
+    return ((size_t)(K + 2) * 4 * LPR + (size_t)2 * WAVES * 4 * LPR + (size_t)K + 1) * sizeof(float);
+}
+
+template <int WAVES, int LPR, int ITEMS, typename TIN, bool ALIGNED>
+__global__ __launch_bounds__(64 * WAVES) void semi_linear_kernel(SemiArgs a) {
+    using Raw = RawPiece<TIN>;
+    constexpr int W = 64 * WAVES, G = W / LPR, VS = 4 * LPR, PH = ITEMS <= 2 ? 3 : WAVES == 16 && sizeof(TIN) == 4 ? 1 : 2;  // (PH positions in flight; sixteen waves have 128 registers)
+    static_assert(LPR == 4 || LPR == 8 || LPR == 16, "16, 32 or 64 tags");
+    extern __shared__ __attribute__((aligned(16))) unsigned char semi_smem[];
+    const int K = a.K, T = a.T, N = a.N, KT = K * T;
+    const int KR = K + 1;  // slots: the K vectors a step takes and the one it makes; slot KR holds zeros
+    float* vec = reinterpret_cast<float*>(semi_smem);
+    float* part = vec + (KR + 1) * VS;
+    int* Oslot = reinterpret_cast<int*>(part + 2 * WAVES * VS);  // (modulo 2^32: only differences of near ones count)
+    const int tid = threadIdx.x, lane = tid & 63, b = blockIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int L = clamp_length(a.lengths, b, N);
+    if (L == 0) {
+        if (tid == 0) a.logZ[b] = 0.f;
+        return;
+    }
+    const size_t block = (size_t)K * T * T;
+    const TIN* phib = static_cast<const TIN*>(a.phi) + (size_t)b * N * block;
+    const int g = tid / LPR, cl = tid % LPR;
+    const int c4 = min(4 * cl, T - 4);
+
+    unsigned voff[ITEMS];
+    int kk[ITEMS], slot[ITEMS], srow[ITEMS];  // segment length less one; ring slot of the vector it meets, and the entry there
+#pragma unroll
+    for (int m = 0; m < ITEMS; ++m) {
+        const int rc = min(g + G * m, KT - 1);
+        kk[m] = rc / T;
+        srow[m] = rc - kk[m] * T;
+        voff[m] = (unsigned)(rc * T + c4) * (unsigned)sizeof(TIN);
+        slot[m] = K - kk[m];  // at position 0 the newest vector (position -1) sits in slot K
+        if (g + G * m >= KT) srow[m] = -1;
+    }
+    typename Raw::type raw[PH][ITEMS];
+    float e[ITEMS][4];
+    auto fetch = [&](int i, int m) {
+        auto base = (const GlobalBytes*)(phib + (size_t)(i < L ? i : L - 1) * block);
+        asm("" : "+s"(base));
+        return Raw::template load<ALIGNED>(base + voff[m]);
+    };
+#pragma unroll
+    for (int p = 0; p < PH; ++p)
+#pragma unroll
+        for (int m = 0; m < ITEMS; ++m) raw[p][m] = fetch(p, m);
+
+    for (int k = tid; k < (KR + 1) * VS; k += W) vec[k] = 0.f;
+    for (int k = tid; k < 2 * WAVES * VS; k += W) part[k] = 0.f;
+    for (int k = tid; k < KR; k += W) Oslot[k] = 0;
+    // position 0 grows by the largest entry of its first row (looked at by every wave for itself)
+    float big = lane < T ? Elem<TIN>::get(phib + lane) * kLog2e : LCCRF_NEG_INF;
+    big = xor_max<1, 64>(big);
+    int c_cur = uniform((int)fminf(fmaxf(ceilf(finite_or_zero(big)), -0x1p20f), 0x1p20f)) - kSemiHead, grew = c_cur + kSemiHead;
+    __syncthreads();
+    // the empty prefix, "position -1": potential 1 for row 0, nothing else
+    if (tid == 0) vec[K * VS] = 1.f;
+    __syncthreads();
+
+    // the block of position i, shift c; O: offset of the vector of position i - 1
+    auto prepare = [&](int i, int p, int shift, int O) __attribute__((always_inline)) {
+#pragma unroll
+        for (int m = 0; m < ITEMS; ++m) {
+            const float c = (float)(shift + (O - Oslot[slot[m]]));
+#pragma unroll
+            for (int j = 0; j < 4; ++j) e[m][j] = ex2(__builtin_fmaf(Raw::get(raw[p][m], j), kLog2e, -c));
+            if (i < K) {  // segments that would start before position 0, rows s > 0 of first segments: never used
+                const bool ok = srow[m] >= 0 && (kk[m] < i || (kk[m] == i && srow[m] == 0));
+#pragma unroll
+                for (int j = 0; j < 4; ++j) e[m][j] = ok ? e[m][j] : 0.f;
+            }
+            raw[p][m] = fetch(i + PH, m);
+        }
+    };
+    prepare(0, 0, c_cur, 0);
+
+    // Which column of the wave's sums a lane ends up with: the swaps leave accumulator 2 (lane >> 5) + ((lane >> 4) & 1) there.
+    const int jcol = 2 * (lane >> 5) + ((lane >> 4) & 1);
+    const int wslot = wave * VS + 4 * cl + jcol;
+    const int last = 4 * ((T + 3) / 4 - 1);  // first column slot of the piece that was moved back
+    const int me = min(lane, T - 1), rslot = me < last ? me : last + me - (T - 4);
+    int i = 0, cur = K;   // position, slot of the vector in front of it
+    long long Oi = 0;     // its offset
+    bool rejected = false;
+    float V = 0.f;        // lane = tag
+    const auto step = [&](int next) __attribute__((always_inline)) -> bool {  // false: the run is over
+        const int c_next = max(min(grew, 1 << 20), -(1 << 20)) - kSemiHead;
+        float acc[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int m = 0; m < ITEMS; ++m) {
+            const float v = vec[srow[m] >= 0 ? slot[m] * VS + srow[m] : KR * VS];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) acc[j] = __builtin_fmaf(e[m][j], v, acc[j]);
+        }
+        // over the wave's row groups: after the swap of a pair the lower half holds the one accumulator, the upper the other
+        const auto pair32 = [](float x, float y) {
+            const auto r = __builtin_amdgcn_permlane32_swap(__float_as_int(x), __float_as_int(y), false, false);
+            return __int_as_float(r[0]) + __int_as_float(r[1]);
+        };
+        const auto pair16 = [](float x, float y) {
+            const auto r = __builtin_amdgcn_permlane16_swap(__float_as_int(x), __float_as_int(y), false, false);
+            return __int_as_float(r[0]) + __int_as_float(r[1]);
+        };
+        float x = pair16(pair32(acc[0], acc[2]), pair32(acc[1], acc[3]));
+        if (LPR <= 8) x += dpp<kDppRowRor8>(x);
+        if (LPR <= 4) x += dpp<kDppRowRor4>(x);
+        float* mine = part + (i & 1) * WAVES * VS;
+        mine[wslot] = x;
+        __syncthreads();
+        float s = mine[rslot];
+#pragma unroll
+        for (int w = 1; w < WAVES; ++w) s += mine[w * VS + rslot];
+        const int k = uniform(__builtin_amdgcn_frexp_expf(s));  // tag 0's
+        const float v = __builtin_amdgcn_ldexpf(s, -k);
+        if (!__all(s >= kSemiLo && v >= kSemiLo && v <= kSemiHi)) {
+            rejected = true;
+            return false;
+        }
+        const int nxt = cur == K ? 0 : cur + 1;
+        vec[nxt * VS + me] = v;  // (every wave, the same values)
+        V = v;
+        grew = c_cur + k;
+        Oi += grew;
+        Oslot[nxt] = (int)Oi;
+        cur = nxt;
+        ++i;
+        if (i == L) return false;
+#pragma unroll
+        for (int m = 0; m < ITEMS; ++m) slot[m] = slot[m] == K ? 0 : slot[m] + 1;
+        c_cur = c_next;
+        prepare(i, next, c_next, (int)Oi);
+        return true;
+    };
+    if constexpr (PH == 1) {
+        while (step(0)) {}
+    } else if constexpr (PH == 2) {
+        while (step(1) && step(0)) {}
+    } else {
+        while (step(1) && step(2) && step(0)) {}
+    }
+    if (!rejected) {  // logZ = logsumexp of the vector of the last position
+        if (wave == 0) {
+            const float S = xor_sum<1, 64>(lane < T ? V : 0.f);
+            if (lane == 0) a.logZ[b] = (float)(((double)Oi + (double)lg2(S)) * kLn2);
+        }
+        return;
+    }
+    // The sums of position i were not accepted: from there on in the log domain, from the K vectors in front of it (those
+    // of positions i - 1, i - 2, ... into slots K - 1, K - 2, ... of the other state; both begin where the other does: through registers).
+    double* base = reinterpret_cast<double*>(semi_smem);
+    float* ring = reinterpret_cast<float*>(base + (K + 1) / 2 * 2);
+    float* dlast = ring + (KT + 3) / 4 * 4 + 2 * WAVES * VS;
+    const auto slot_here = [&](int q) {  // where the vector that goes to slot q lies
+        const int x = cur - (K - 1 - q);
+        return x < 0 ? x + KR : x;
+    };
+    float keep[ITEMS];  // (K T <= ITEMS W / LPR)
+#pragma unroll
+    for (int q = 0; q < ITEMS; ++q) {
+        const int x = tid + q * W;
+        keep[q] = x < KT ? lg2(vec[slot_here(x / T) * VS + x % T]) : 0.f;
+    }
+    const int keepO = tid < K ? (int)Oi - Oslot[slot_here(tid)] : 0;
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < ITEMS; ++q)
+        if (tid + q * W < KT) ring[tid + q * W] = keep[q];
+    if (tid < K) base[tid] = (double)(Oi - keepO);
+    __syncthreads();
+    if (wave == 0) {
+        const float d = xor_max<1, 64>(lane < T ? ring[(K - 1) * T + lane] : LCCRF_NEG_INF);
+        if (lane == 0) *dlast = finite_or_zero(d);
+    }
+    __syncthreads();
+    semi_log_steps<LPR, WAVES, TIN, ALIGNED>(a, b, L, i, K - 1, (double)Oi, semi_smem);
+}
+
 template <int LPR, int WAVES>
 static hipError_t launch_semi_geo(int dtype, const SemiArgs& a, hipStream_t st) {
     const size_t lds = semi_lds_bytes(a.K, a.T, LPR, WAVES);
@@ -218,6 +431,44 @@ static hipError_t launch_semi_geo(int dtype, const SemiArgs& a, hipStream_t st) 
         else hipLaunchKernelGGL((semi_forward_kernel<LPR, WAVES, uint16_t, false>), grid, block, lds, st, a);
     }
     return hipGetLastError();
+}
+
+template <int WAVES, int LPR, int ITEMS>
+static bool launch_semi_items(int dtype, const SemiArgs& a, hipStream_t st, hipError_t& e) {
+    size_t bytes = semi_linear_bytes<WAVES, LPR>(a.K);
+    const size_t log = semi_lds_bytes(a.K, a.T, LPR, WAVES);
+    if (log > bytes) bytes = log;
+    if (bytes > 64 * 1024 || a.K > 64 * WAVES) return false;
+    const bool aligned = (a.T % 4) == 0;
+    const dim3 grid(a.B), block(64 * WAVES);
+    if (dtype == 0) {
+        if (aligned) hipLaunchKernelGGL((semi_linear_kernel<WAVES, LPR, ITEMS, float, true>), grid, block, bytes, st, a);
+        else hipLaunchKernelGGL((semi_linear_kernel<WAVES, LPR, ITEMS, float, false>), grid, block, bytes, st, a);
+    } else {
+        if (aligned) hipLaunchKernelGGL((semi_linear_kernel<WAVES, LPR, ITEMS, uint16_t, true>), grid, block, bytes, st, a);
+        else hipLaunchKernelGGL((semi_linear_kernel<WAVES, LPR, ITEMS, uint16_t, false>), grid, block, bytes, st, a);
+    }
+    e = hipGetLastError();
+    return true;
+}
+// The scaled-probability kernel where it serves the shape: up to eight rows of the (K T) x T block a thread.  false: it does not.
+// Few rows a wave are worth more than few waves (us, N=256 B=1, so / log-domain steps: 32 tags K=8 214 (four waves of eight rows:
+// 289) / 513, K=2 132 / 333; 16 tags K=8 134 / 392; 64 tags K=8 553 / 2044; 8 tags K=2 166 / 321; N=64 B=1024: 32 tags K=8 355 / 383,
+// 20 tags K=3 59 / 162).  A tag that is forbidden everywhere sends a sequence to the log-domain steps at its first position:
+// what was read for the first positions is then read again (32 tags K=8: N=256 B=1 415, N=64 B=1024 408).
+template <int LPR>
+static bool launch_semi_linear(int dtype, const SemiArgs& a, hipStream_t st, hipError_t& e) {
+    const long long rows = (long long)a.K * a.T;
+    constexpr int G = 64 / LPR;  // rows a wave holds at a time
+    if constexpr (LPR == 4) {
+        if (a.K <= 4) return launch_semi_items<1, LPR, 4>(dtype, a, st, e);
+    }
+    if (rows <= 2 * 4 * G) return launch_semi_items<4, LPR, 2>(dtype, a, st, e);
+    if (rows <= 4 * 4 * G) return launch_semi_items<4, LPR, 4>(dtype, a, st, e);
+    if (rows <= 4 * 8 * G) return launch_semi_items<8, LPR, 4>(dtype, a, st, e);
+    if (rows <= 8 * 8 * G) return launch_semi_items<8, LPR, 8>(dtype, a, st, e);
+    if (rows <= 8 * 16 * G) return launch_semi_items<16, LPR, 8>(dtype, a, st, e);
+    return false;
 }
 
 // Geometry by tag count: 4 LPR >= T columns; four waves up to T = 64 (one when T <= 16 and the K
@@ -238,6 +489,11 @@ bool semi_markov_supported(int K, int T) {
 hipError_t launch_semi_markov_forward(int dtype, const void* phi, const int32_t* lengths, int B, int N, int K, int T,
                                       float* logZ, hipStream_t st) {
     const SemiArgs a{phi, lengths, B, N, K, T, logZ};
+    if (T >= 8 && T <= 64) {
+        hipError_t e = hipSuccess;
+        if (T <= 16 ? launch_semi_linear<4>(dtype, a, st, e) : T <= 32 ? launch_semi_linear<8>(dtype, a, st, e) : launch_semi_linear<16>(dtype, a, st, e))
+            return e;
+    }
     if (T <= 16) return K <= 4 ? launch_semi_geo<4, 1>(dtype, a, st) : launch_semi_geo<4, 4>(dtype, a, st);
     if (T <= 32) return launch_semi_geo<8, 4>(dtype, a, st);
     if (T <= 64) return launch_semi_geo<16, 4>(dtype, a, st);

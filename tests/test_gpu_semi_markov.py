@@ -112,3 +112,22 @@ def test_semi_markov_argument_checks(crf):
     out = crf.lccrf_semi_markov_log_partition(torch.zeros(2, 4, 2, 3, 3, device="cuda"),
                                               torch.tensor([0, 1], dtype=torch.int32, device="cuda")).cpu().numpy()
     assert out[0] == 0.0 and out[1] == pytest.approx(math.log(3), rel=1e-6)
+
+
+# 8 .. 64 tags: the kernel in scaled probabilities.  (T, K) on both sides of every line between its instances (rows K T of a
+# position against 2 and 4 of four waves, 4 and 8 of eight, 8 of sixteen, and none), odd tag counts beside them.
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("T,K", [(8, 16), (9, 15), (15, 17), (16, 33), (11, 94), (16, 65), (15, 137), (17, 3), (32, 2), (32, 5), (31, 9),
+                                 (32, 16), (29, 18), (32, 33), (33, 1), (64, 1), (35, 2), (63, 2), (64, 4), (61, 5), (64, 8), (64, 9)])
+def test_semi_markov_steps_that_leave_the_scaled_range(crf, oracle_mod, T, K, dtype):
+    """Sequences whose steps are all ordinary, one that grows by 2^300 at a position, one whose first tag is forbidden from a position
+    on (the scale is taken from it), one whose tags differ by more than single precision's exponents hold, one without any path."""
+    N = 14
+    phi, lens = workloads.semi_markov_case(8300 + 67 * T + K, 6, N, K, T, scale=1.0, ragged=False, min_len=N)
+    lens[5] = 6
+    phi[1, 7:] += 210.0
+    phi[2, 8:, :, :, 0] = float("-inf")
+    phi[3, :, :, :, T // 2] -= 150.0
+    phi[4, 9] = float("-inf")
+    phi[4, 10:, 1:] = float("-inf")
+    _check(crf, oracle_mod, phi.to(dtype), lens, f"T={T} K={K} {dtype}")
