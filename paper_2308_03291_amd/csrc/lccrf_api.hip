@@ -593,7 +593,7 @@ int lccrf_entropy(const void* phi, lccrf_dtype dt, const int32_t* lengths, int B
     const hipError_t e = lccrf::launch_entropy(
         dt, phi, lengths, B, N, T, reinterpret_cast<float*>(base + w.ua), reinterpret_cast<float*>(base + w.ub),
         reinterpret_cast<double*>(base + w.Oa), reinterpret_cast<double*>(base + w.Ob),
-        reinterpret_cast<float*>(base + w.ha), reinterpret_cast<float*>(base + w.hb), entropy,
+        reinterpret_cast<float*>(base + w.ha), reinterpret_cast<float*>(base + w.hb), reinterpret_cast<double*>(base + w.hoff), entropy,
         static_cast<hipStream_t>(stream));
     return e == hipSuccess ? LCCRF_OK : LCCRF_ELAUNCH;
 }

@@ -1,0 +1,265 @@
+// The half chains behind the entropy, the cross-entropy and the divergence in scaled probabilities, 33 .. 64 tags, by a
+// workgroup of four waves (the queries: lccrf_extras.hip; scaled steps: lccrf_linear.h).
+//
+// Beside V(u), the scaled sum over the paths behind tag u, a chain carries X(u) = V(u) h(u), h the expectation of what those
+// paths add up to.  That is linear too,
+//     S(t) = sum_s V(s) E(s,t),   U(t) = sum_s X(s) E(s,t) + V(s) F(s,t),   E = 2^(phi log2 e - c),   F = E f,
+// f(s,t) what the edge adds: the exponent of E for the entropy, which is log alpha(t) less the expected score (base 2, the shifts in
+// the offsets: what the heavy edges add is small, and so are the roundings); psi for the cross-entropy; phi - psi for the
+// divergence.  E and F of the next position are made while the sums of this one are
+// exchanged, so a step has no exponential, logarithm or division on its dependent path, and one barrier: a forward wave sums its
+// rows over its lanes, the waves' sums meet in LDS and every wave adds them up for itself (lane = tag); a backward wave
+// completes its rows and every wave reads them all.  Each wave therefore knows the new vector and decides for itself, all alike,
+// whether the step is accepted.
+//
+// V is S rescaled by the power of two that brings tag 0 into [1/2, 1), its offset an integer; the common part c = U(0) / S(0) of h
+// moves into a double-precision offset at every step, so X stays small.  The shift of a matrix is what tag 0 grew by at
+// the step before, less kExpectHead (the first: its largest entry plus the vector's).  Accepted: every S at least 2^-40 before and
+// within [2^-40, 2^40] after rescaling, every |X| at most 2^60.  What underflowed in S is then at most 64 2^40 2^-126 of 2^-40,
+// less than 2^-40; the same of U, times the size of f.  The first step that is not accepted ends the run.
+//
+// A step costs 0.7 us (64 tags, entropy; the log-domain steps 1.0): two LDS round trips and a barrier on the dependent path, one
+// wave a SIMD.  Entropy B=128 N=128 T=48 50 us (69), divergence B=64 N=256 T=64 131 us (172), there at 4.1 TB/s of p once and q
+// twice.  At B=512 the entropy is bound by memory either way (N=64, 64 tags 101 / 98).
+#pragma once
+
+#include "lccrf_device.h"
+#include "lccrf_linear.h"
+
+namespace lccrf {
+
+constexpr int kExpectHead = 24;
+constexpr int kExpectWaves = 4, kExpectLanes = 16;  // sixteen lanes a row
+constexpr int kExpectPlain = 3;                     // MODE: V alone, no expectation (0, 1, 2: as in lccrf_extras.hip)
+
+struct ExpectSmem {
+    // Forward: [2][wave][64] partial sums (S, U) of the steps in turn, and the vector (V, X), 64 entries and a zero.
+    // Backward: the sums themselves, S and U apart, 64 entries and from 64 on those of a row's last piece (zero where its neighbour
+    // holds them already), then four zeros.
+    alignas(16) float part[2][kExpectWaves][64][2];
+    alignas(16) float vec[68][2];
+    alignas(16) float row[2][2][72];
+};
+
+// The state of a chain, in every wave: lane = tag.  v: base-2 logarithms (-inf past T), h: expectation, natural units (MODE 0: base 2).
+struct ExpectState {
+    float v, h;
+    double O, Hoff;  // offsets of v and h
+};
+
+// Takes steps of the chain while they are accepted (step s: the matrix of position first + s, backward first - s) and returns their
+// number.  Called by the whole workgroup.
+template <typename TIN, bool ALIGNED, bool BACKWARD, int MODE, int ITEMS>
+__device__ __forceinline__ int expect_run(ExpectSmem& sm, const TIN* phib, const TIN* psib, int T, int first, int n, ExpectState& st) {
+    using Raw = RawPiece<TIN>;
+    constexpr int WAVES = kExpectWaves, LPR = kExpectLanes, W = 64 * WAVES, G = W / LPR, PH = 3;
+    constexpr bool CARRY = MODE != kExpectPlain, PSI = MODE == 1 || MODE == 2;
+    constexpr int QN = PSI ? ITEMS : 1;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (n <= 0) return 0;
+    phib = uniform(phib);
+    psib = uniform(psib);
+    first = uniform(first);
+    n = uniform(n);
+    // the vector the run starts from: what it holds without loss, and finite expectations
+    const float top = finite_or_zero(xor_max<1, 64>(st.v));
+    const float d = ceilf(top);
+    const float v0 = ex2(st.v - d), x0 = v0 > 0.f ? v0 * (MODE == 0 ? st.h - d : st.h) : 0.f;
+    if (!__all((st.v == LCCRF_NEG_INF || st.v - d >= -100.f) && fabsf(x0) <= 0x1p60f && fabsf(d) <= 0x1p20f)) return 0;
+
+    const size_t TT = (size_t)T * T;
+    const int Q4 = (T + 3) >> 2;
+    const int g = tid / LPR, cl = tid % LPR, c4 = min(4 * cl, T - 4);
+    unsigned voff[ITEMS];
+#pragma unroll
+    for (int m = 0; m < ITEMS; ++m) voff[m] = (unsigned)(min(g + G * m, T - 1) * T + c4) * (unsigned)sizeof(TIN);
+    typename Raw::type raw[PH][ITEMS], qraw[PH][QN];
+    float e[ITEMS][4], f[CARRY ? ITEMS : 1][4];
+    const auto matrix = [&](const TIN* p, int s) {
+        const int q = uniform(s < n ? s : n - 1);
+        auto base = (const GlobalBytes*)(p + (size_t)(BACKWARD ? first - q : first + q) * TT);
+        asm("" : "+s"(base));
+        return base;
+    };
+    const auto fetch = [&](int s, int p) __attribute__((always_inline)) {
+        const auto base = matrix(phib, s);
+#pragma unroll
+        for (int m = 0; m < ITEMS; ++m) raw[p][m] = Raw::template load<ALIGNED>(base + voff[m]);
+        if constexpr (PSI) {
+            const auto qbase = matrix(psib, s);
+#pragma unroll
+            for (int m = 0; m < ITEMS; ++m) qraw[p][m] = Raw::template load<ALIGNED>(qbase + voff[m]);
+        }
+    };
+#pragma unroll
+    for (int p = 0; p < PH; ++p) fetch(p, p);
+    const auto prepare = [&](int p, int s, int shift) __attribute__((always_inline)) {  // the matrix in slot p, then that of step s into it
+        const float c = (float)shift;
+#pragma unroll
+        for (int m = 0; m < ITEMS; ++m)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const float x = Raw::get(raw[p][m], j);
+                const float arg = __builtin_fmaf(x, kLog2e, -c);
+                e[m][j] = ex2(arg);
+                if constexpr (CARRY) {
+                    // an edge without weight adds nothing, whatever its score
+                    if constexpr (MODE == 0) {
+                        f[m][j] = e[m][j] * fmaxf(arg - (float)kExpectHead, -0x1p100f);
+                    } else {
+                        const float q = Raw::get(qraw[p][m], j);
+                        f[m][j] = e[m][j] > 0.f ? e[m][j] * (MODE == 1 ? q : x - q) : 0.f;
+                    }
+                }
+            }
+        fetch(s, p);
+    };
+
+    // which row or column a lane is left with by the exchanges below, and where the entries lie
+    const int last = 4 * (Q4 - 1), me = min(lane, T - 1);
+    const int zero_from = BACKWARD ? 68 : 64;
+    for (int k = tid; k < (int)(sizeof(ExpectSmem) / sizeof(float)); k += W) reinterpret_cast<float*>(&sm)[k] = 0.f;
+    __syncthreads();
+    if (!BACKWARD && lane < T) {
+        sm.vec[lane][0] = v0;
+        sm.vec[lane][1] = x0;
+    }
+    if (BACKWARD && lane < T) {
+        sm.row[1][0][lane] = v0;
+        sm.row[1][1][lane] = x0;
+        if (lane >= last) {
+            sm.row[1][0][64 + lane - (T - 4)] = v0;
+            sm.row[1][1][64 + lane - (T - 4)] = x0;
+        }
+    }
+    __syncthreads();
+    const int vfrom = !BACKWARD ? 0 : cl < Q4 - 1 ? 4 * cl : cl == Q4 - 1 ? 64 : zero_from;  // backward: this lane's four columns
+    int vrow[ITEMS];                                                                         // forward: its rows
+#pragma unroll
+    for (int m = 0; m < ITEMS; ++m) vrow[m] = g + G * m < T ? g + G * m : zero_from;
+    // forward: the swaps leave accumulator 2 (lane >> 5) + ((lane >> 4) & 1) of the sixteen lanes' four columns in a lane
+    const int wslot = 4 * cl + 2 * (lane >> 5) + ((lane >> 4) & 1), rslot = me < last ? me : last + me - (T - 4);
+    // backward: reduce4_over_lanes leaves row number 2 (lane & 1) + ((lane >> 1) & 1) in a lane
+    const int item = 2 * (lane & 1) + ((lane >> 1) & 1), srow = g + G * item;
+    const bool publishes = cl < 4 && item < ITEMS && srow < T;
+
+    // the first step grows by the largest entry that meets a path
+    float big = LCCRF_NEG_INF;
+#pragma unroll
+    for (int m = 0; m < ITEMS; ++m)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            big = fmaxf(big, __builtin_fmaf(Raw::get(raw[0][m], j), kLog2e, lg2(BACKWARD ? sm.row[1][0][vfrom + j] : sm.vec[vrow[m]][0])));
+    big = xor_max<1, 64>(big);
+    if (lane == 0) sm.part[1][wave][0][0] = big;
+    __syncthreads();
+    big = fmaxf(fmaxf(sm.part[1][0][0][0], sm.part[1][1][0][0]), fmaxf(sm.part[1][2][0][0], sm.part[1][3][0][0]));
+    int grew = uniform((int)fminf(fmaxf(ceilf(finite_or_zero(big)), -0x1p20f), 0x1p20f)), c_cur = grew - kExpectHead;
+    __syncthreads();
+    prepare(0, PH, c_cur);
+
+    int done = 0;
+    long long Oi = 0, Hi = 0;
+    float V = v0, X = x0;       // of the last accepted step, lane = tag
+    double shift = 0.0;         // what has moved out of h so far
+    float hc = 0.f;             // backward: the shift of h and the scale that the sums at hand have yet to be given
+    int k = 0;
+    const auto pair32 = [](float x, float y) {
+        const auto r = __builtin_amdgcn_permlane32_swap(__float_as_int(x), __float_as_int(y), false, false);
+        return __int_as_float(r[0]) + __int_as_float(r[1]);
+    };
+    const auto pair16 = [](float x, float y) {
+        const auto r = __builtin_amdgcn_permlane16_swap(__float_as_int(x), __float_as_int(y), false, false);
+        return __int_as_float(r[0]) + __int_as_float(r[1]);
+    };
+    const auto step = [&](int next) __attribute__((always_inline)) -> bool {  // false: the run is over
+        const int c_next = max(min(grew, 1 << 20), -(1 << 20)) - kExpectHead, par = done & 1;
+        float S = 0.f, U = 0.f;
+        if constexpr (!BACKWARD) {
+            float as[4] = {0.f, 0.f, 0.f, 0.f}, au[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int m = 0; m < ITEMS; ++m) {
+                const float2 q = *reinterpret_cast<const float2*>(sm.vec[vrow[m]]);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    as[j] = __builtin_fmaf(e[m][j], q.x, as[j]);
+                    if constexpr (CARRY) au[j] = __builtin_fmaf(f[m][j], q.x, __builtin_fmaf(e[m][j], q.y, au[j]));
+                }
+            }
+            float2 mine;
+            mine.x = pair16(pair32(as[0], as[2]), pair32(as[1], as[3]));
+            mine.y = CARRY ? pair16(pair32(au[0], au[2]), pair32(au[1], au[3])) : 0.f;
+            *reinterpret_cast<float2*>(sm.part[par][wave][wslot]) = mine;
+            __syncthreads();
+            float2 q[WAVES];
+#pragma unroll
+            for (int w = 0; w < WAVES; ++w) q[w] = *reinterpret_cast<const float2*>(sm.part[par][w][rslot]);
+            prepare(next, done + 1 + PH, c_next);
+            S = (q[0].x + q[1].x) + (q[2].x + q[3].x);
+            if (CARRY) U = (q[0].y + q[1].y) + (q[2].y + q[3].y);
+        } else {
+            // (the rows at hand are the last step's sums as they came out: scaled and shifted here)
+            const float4 r = *reinterpret_cast<const float4*>(&sm.row[par ^ 1][0][vfrom]);
+            float4 u = CARRY ? *reinterpret_cast<const float4*>(&sm.row[par ^ 1][1][vfrom]) : make_float4(0.f, 0.f, 0.f, 0.f);
+            float v[4] = {r.x, r.y, r.z, r.w}, x[4] = {u.x, u.y, u.z, u.w};
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                v[j] = __builtin_amdgcn_ldexpf(v[j], -k);
+                if (CARRY) x[j] = __builtin_fmaf(-hc, v[j], __builtin_amdgcn_ldexpf(x[j], -k));
+            }
+            float ps[4] = {0.f, 0.f, 0.f, 0.f}, pu[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int m = 0; m < ITEMS; ++m) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    ps[m] = __builtin_fmaf(e[m][j], v[j], ps[m]);
+                    if constexpr (CARRY) pu[m] = __builtin_fmaf(f[m][j], v[j], __builtin_fmaf(e[m][j], x[j], pu[m]));
+                }
+            }
+            const float s = reduce4_over_lanes<LPR>(ps[0], ps[1], ps[2], ps[3], lane);
+            const float t = CARRY ? reduce4_over_lanes<LPR>(pu[0], pu[1], pu[2], pu[3], lane) : 0.f;
+            if (publishes) {
+                sm.row[par][0][srow] = s;
+                if (CARRY) sm.row[par][1][srow] = t;
+                if (srow >= last) {
+                    sm.row[par][0][64 + srow - (T - 4)] = s;
+                    if (CARRY) sm.row[par][1][64 + srow - (T - 4)] = t;
+                }
+            }
+            __syncthreads();
+            S = sm.row[par][0][me];
+            if (CARRY) U = sm.row[par][1][me];
+            prepare(next, done + 1 + PH, c_next);
+        }
+        const int k_new = uniform(__builtin_amdgcn_frexp_expf(S));  // tag 0's
+        const float vn = __builtin_amdgcn_ldexpf(S, -k_new);
+        float xn = 0.f, hc_new = 0.f;
+        if constexpr (CARRY) {
+            const float y = __builtin_amdgcn_ldexpf(U, -k_new);
+            hc_new = uniform_f(y * __builtin_amdgcn_rcpf(vn));  // (any number near h of tag 0 will do)
+            xn = __builtin_fmaf(-hc_new, vn, y);
+        }
+        if (!__all(S >= 0x1p-40f && vn >= 0x1p-40f && vn <= 0x1p40f && fabsf(xn) <= 0x1p60f)) return false;
+        V = vn;
+        X = xn;
+        k = k_new;
+        hc = hc_new;
+        if constexpr (!BACKWARD) *reinterpret_cast<float2*>(sm.vec[me]) = make_float2(vn, xn);  // (every wave, the same values)
+        if (CARRY) shift += (double)hc_new;
+        grew = c_cur + k_new;
+        Oi += grew;
+        Hi += c_cur + kExpectHead;
+        c_cur = c_next;
+        return ++done < n;
+    };
+    while (step(1) && step(2) && step(0)) {}
+    __syncthreads();  // (the shared state may be used for something else now)
+    st.v = lane < T ? lg2(V) : LCCRF_NEG_INF;
+    st.h = CARRY && V > 0.f ? X / V : 0.f;
+    st.O += (double)d + (double)Oi;
+    st.Hoff += MODE == 0 ? shift + (double)d + (double)Hi : shift;
+    return done;
+}
+
+}  // namespace lccrf

@@ -4,6 +4,7 @@
 // first pass of the chain kernels; what is here only finishes them.
 #include "lccrf_chain_args.h"
 #include "lccrf_device.h"
+#include "lccrf_expect.h"
 #include "lccrf_launch.h"
 
 namespace lccrf {
@@ -111,7 +112,7 @@ __global__ __launch_bounds__(64) void entropy_combine_kernel(ChainArgs a, float*
         if (p > 0.f) acc += p * (a.ha[(size_t)b * T + t] + a.hb[(size_t)b * T + t] - (z - lS));
     }
     acc = xor_sum<1, 64>(acc);
-    if (lane == 0) H[b] = (float)((double)acc * kLn2);
+    if (lane == 0) H[b] = (float)(((double)acc + (a.hoff ? a.hoff[2 * b] + a.hoff[2 * b + 1] : 0.0)) * kLn2);
 }
 
 static hipError_t launch_entropy_combine(const ChainArgs& a, float* H, hipStream_t st) {
@@ -137,7 +138,7 @@ static hipError_t launch_entropy_combine(const ChainArgs& a, float* H, hipStream
 // weight zero contributes nothing whatever psi holds there.  In modes 1 and 2 a common shift of
 // h (its largest finite entry) moves into a double-precision offset at every step, so the vector
 // stays small however long the chain is.
-// At 33 .. 128 tags every mode first tries every step with one shift for the whole matrix, the normaliser
+// At 33 .. 64 tags the steps of lccrf_expect.h come first, these ones follow where they give up.  At 33 .. 128 tags every mode first tries every step with one shift for the whole matrix, the normaliser
 // of the vector it starts from, as the chain kernels do (lccrf_chain.hip): U / S (+ log2 S) does not depend
 // on the shift as long as no term that matters is flushed, which holds if every sum lies in
 // [2^-60, 2^60]; otherwise the step is replayed exactly on the same registers.  The other geometries take
@@ -169,8 +170,10 @@ __device__ __forceinline__ float expectation_of(float U, float S) { return S > 0
 
 // PLAIN: the chain alone, no expectation (the chains of the second sequence potentials, see entropy_half_kernel); `row` says
 // in which row of ua / ub / Oa / Ob its vector of the meeting position goes.
+// The first `from` steps are taken already: rv, hv are thread tid's entries of the vectors behind them, O and Hoff their offsets.
 template <typename G, typename TIN, bool ALIGNED, int MODE, bool PLAIN>
-__device__ __forceinline__ void expect_half(EntropySmem<G>& sm, const ChainArgs& a, int v, const void* phi, const void* psi, int row) {
+__device__ __forceinline__ void expect_half(EntropySmem<G>& sm, const ChainArgs& a, int v, const void* phi, const void* psi, int row, int from,
+                                            float rv, float hv, double O, double Hoff) {
     constexpr int ITEMS = G::ITEMS, PF = 2;
     constexpr bool CROSS = MODE != 0 && !PLAIN;
     // the second tile travels through a ring of its own where registers allow (QRING); the
@@ -200,12 +203,8 @@ __device__ __forceinline__ void expect_half(EntropySmem<G>& sm, const ChainArgs&
     int nstep = 0;
     __syncthreads();
     if (tid < T) {
-        const float p0 = Elem<TIN>::get(phib + tid);
-        sm.rvec[0][tid] = dir == 0 ? p0 * kLog2e : 0.f;
-        if (CROSS && dir == 0 && p0 != LCCRF_NEG_INF) {  // the score of the first tag belongs to the forward chain
-            const float q0 = Elem<TIN>::get(psib + tid);
-            sm.hvec[0][tid] = MODE == 1 ? q0 : p0 - q0;
-        }
+        sm.rvec[0][tid] = rv;
+        sm.hvec[0][tid] = hv;
     }
     __syncthreads();
 
@@ -227,7 +226,6 @@ __device__ __forceinline__ void expect_half(EntropySmem<G>& sm, const ChainArgs&
 #pragma unroll
         for (int j = 0; j < 4; ++j) f[j] = MODE == 1 ? qv[j] : x[j] - qv[j];
     };
-    double O = 0.0, Hoff = 0.0;
     int buf = 0;
     auto shift = [&]() {  // normaliser of the vector in rvec[buf]: its maximum, by every thread
         float d = LCCRF_NEG_INF;
@@ -244,7 +242,7 @@ __device__ __forceinline__ void expect_half(EntropySmem<G>& sm, const ChainArgs&
     };
 
     if (dir == 0) {
-        walk<PF>(1, h, +1, load, [&](int i, int slot) {
+        walk<PF>(1 + from, h, +1, load, [&](int i, int slot) {
             float (&x)[ITEMS][4] = ring[slot];
             settle_tile<G, ALIGNED>(x, T, c4);
             if constexpr (QRING) settle_tile<G, ALIGNED>(qring[slot], T, c4);
@@ -373,7 +371,7 @@ __device__ __forceinline__ void expect_half(EntropySmem<G>& sm, const ChainArgs&
             buf ^= 1;
         });
     } else {
-        walk<PF>(e, h + 1, -1, load, [&](int i, int slot) {
+        walk<PF>(e - from, h + 1, -1, load, [&](int i, int slot) {
             float (&y)[ITEMS][4] = ring[slot];
             settle_tile<G, ALIGNED>(y, T, c4);
             if constexpr (QRING) settle_tile<G, ALIGNED>(qring[slot], T, c4);
@@ -468,7 +466,7 @@ __device__ __forceinline__ void expect_half(EntropySmem<G>& sm, const ChainArgs&
         if (!PLAIN) (dir == 0 ? a.ha : a.hb)[(size_t)b * T + tid] = sm.hvec[buf][tid];
     }
     if (tid == 0) (dir == 0 ? a.Oa : a.Ob)[vb + row] = O;
-    if (CROSS && tid == 0) a.hoff[2 * b + dir] = Hoff;
+    if (!PLAIN && a.hoff && tid == 0) a.hoff[2 * b + dir] = Hoff;
 }
 
 // The row of ua / ub / Oa / Ob that the chains of psi leave their vectors of the meeting position h in (N >= 2): not h, which
@@ -477,20 +475,95 @@ __device__ __forceinline__ int psi_row(int h) { return h > 0 ? h - 1 : 1; }
 
 // Workgroups 0 .. 2 B - 1: the half chains of phi with their expectations.  With a.psi_chains (cross-entropy and divergence),
 // workgroups 2 B .. 4 B - 1 run the plain half chains of psi beside them, for its log-partition: as launches one after the
-// other either leaves half of the chip idle (B=64, N=256, 64 tags: 96 + 172 us, together 176).
+// other either leaves half of the chip idle (B=64, N=256, 64 tags, log-domain steps: 96 + 172 us, together 176).
+// Where a chain starts: tag t's entry of its vector (base-2 logarithm), and of the expectation of the scores (MODE 0: of phi, base
+// 2), the score of the first tag belonging to the forward chain.
+template <int MODE, bool PLAIN, typename TIN>
+__device__ __forceinline__ void expect_start(const TIN* phib, const TIN* psib, int dir, int t, float& rv, float& hv) {
+    rv = hv = 0.f;
+    if (dir != 0) return;
+    const float p0 = Elem<TIN>::get(phib + t);
+    rv = p0 * kLog2e;
+    if (PLAIN || p0 == LCCRF_NEG_INF) return;
+    if (MODE == 0) {
+        hv = rv;
+        return;
+    }
+    const float q0 = Elem<TIN>::get(psib + t);
+    hv = MODE == 2 ? p0 - q0 : q0;
+}
+
+template <typename G, typename TIN, bool ALIGNED, int MODE, bool PLAIN>
+__device__ __forceinline__ void expect_chain(EntropySmem<G>& sm, const ChainArgs& a, int v, const void* phi, const void* psi, int row) {
+    const size_t at = (size_t)(v >> 1) * a.N * a.T * a.T;
+    float rv = LCCRF_NEG_INF, hv = 0.f;
+    if ((int)threadIdx.x < a.T && a.N > 0)
+        expect_start<MODE, PLAIN>(static_cast<const TIN*>(phi) + at, static_cast<const TIN*>(psi) + at, v & 1, (int)threadIdx.x, rv, hv);
+    if (MODE == 0) hv = 0.f;  // (these steps carry the entropy itself)
+    expect_half<G, TIN, ALIGNED, MODE, PLAIN>(sm, a, v, phi, psi, row, 0, rv, hv, 0.0, 0.0);
+}
 template <typename G, typename TIN, bool ALIGNED, int MODE>
 __global__ __launch_bounds__(G::W) void entropy_half_kernel(ChainArgs a) {
     __shared__ EntropySmem<G> sm;
     const int v = blockIdx.x;
     if (MODE == 0 || v < 2 * a.B) {
         const int L = clamp_length(a.lengths, v >> 1, a.N);
-        expect_half<G, TIN, ALIGNED, MODE, false>(sm, a, v, a.phi, a.psi, meeting_point(0, L - 1));
+        expect_chain<G, TIN, ALIGNED, MODE, false>(sm, a, v, a.phi, a.psi, meeting_point(0, L - 1));
     } else if constexpr (MODE != 0) {
         const int L = clamp_length(a.lengths, (v - 2 * a.B) >> 1, a.N);
-        expect_half<G, TIN, ALIGNED, MODE, true>(sm, a, v - 2 * a.B, a.psi, nullptr, psi_row(meeting_point(0, L - 1)));
+        expect_chain<G, TIN, ALIGNED, MODE, true>(sm, a, v - 2 * a.B, a.psi, nullptr, psi_row(meeting_point(0, L - 1)));
     }
 }
 
+// The same at 33 .. 64 tags: the steps of lccrf_expect.h as long as they are accepted, then those of expect_half.
+template <typename TIN, bool ALIGNED, int MODE, int ITEMS, bool PLAIN>
+__device__ __forceinline__ void expect_linear_chain(EntropySmem<Geo<16, kExpectWaves, 4>>& sm, ExpectSmem& lin, const ChainArgs& a, int v, const void* phi,
+                                                    const void* psi, int row, int h, int e) {
+    constexpr int RUN = PLAIN ? kExpectPlain : MODE;
+    const int lane = threadIdx.x & 63, b = v >> 1, dir = v & 1, T = a.T;
+    const size_t vb = (size_t)b * a.N, at = vb * T * T;
+    const TIN *phib = static_cast<const TIN*>(phi) + at, *psib = RUN == 1 || RUN == 2 ? static_cast<const TIN*>(psi) + at : phib;
+    const int n = dir == 0 ? h : e - h;
+    ExpectState st{LCCRF_NEG_INF, 0.f, 0.0, 0.0};
+    if (lane < T) expect_start<MODE, PLAIN>(phib, psib, dir, lane, st.v, st.h);
+    const int done = dir == 0 ? expect_run<TIN, ALIGNED, false, RUN, ITEMS>(lin, phib, psib, T, 1, n, st)
+                              : expect_run<TIN, ALIGNED, true, RUN, ITEMS>(lin, phib, psib, T, e, n, st);
+    // Entropy of what lies behind a tag: log alpha less the expected score, base 2
+    float hv = st.h;
+    double Hoff = st.Hoff;
+    if (RUN == 0) {
+        hv = st.v > LCCRF_NEG_INF ? st.v - st.h : 0.f;
+        Hoff = st.O - st.Hoff;
+    }
+    if (done < n) {
+        if (RUN == 0) {
+            hv = st.v > LCCRF_NEG_INF ? (float)((double)hv + Hoff) : 0.f;
+            Hoff = 0.0;
+        }
+        expect_half<Geo<16, kExpectWaves, 4>, TIN, ALIGNED, MODE, PLAIN>(sm, a, v, phi, psi, row, done, st.v, hv, st.O, Hoff);
+        return;
+    }
+    if ((int)threadIdx.x < T) {
+        (dir == 0 ? a.ua : a.ub)[(vb + row) * T + lane] = st.v;
+        if (!PLAIN) (dir == 0 ? a.ha : a.hb)[(size_t)b * T + lane] = hv;
+    }
+    if (threadIdx.x == 0) {
+        (dir == 0 ? a.Oa : a.Ob)[vb + row] = st.O;
+        if (!PLAIN) a.hoff[2 * b + dir] = Hoff;
+    }
+}
+template <typename TIN, bool ALIGNED, int MODE, int ITEMS>
+__global__ __launch_bounds__(64 * kExpectWaves) void expect_linear_kernel(ChainArgs a) {
+    __shared__ EntropySmem<Geo<16, kExpectWaves, 4>> sm;
+    __shared__ ExpectSmem lin;
+    const bool plain = MODE != 0 && (int)blockIdx.x >= 2 * a.B;
+    const int v = (int)blockIdx.x - (plain ? 2 * a.B : 0);
+    const int L = clamp_length(a.lengths, v >> 1, a.N);
+    if (L == 0) return;
+    const int e = L - 1, h = meeting_point(0, e);
+    if (MODE == 0 || !plain) expect_linear_chain<TIN, ALIGNED, MODE, ITEMS, false>(sm, lin, a, v, a.phi, a.psi, h, h, e);
+    else if constexpr (MODE != 0) expect_linear_chain<TIN, ALIGNED, MODE, ITEMS, true>(sm, lin, a, v, a.psi, nullptr, psi_row(h), h, e);
+}
 
 template <typename TIN, bool ALIGNED, int MODE>
 static hipError_t launch_entropy_T(const ChainArgs& a, hipStream_t st) {
@@ -499,8 +572,10 @@ static hipError_t launch_entropy_T(const ChainArgs& a, hipStream_t st) {
         hipLaunchKernelGGL((entropy_half_kernel<Geo<4, 1, 1>, TIN, ALIGNED, MODE>), grid, dim3(64), 0, st, a);
     else if (a.T <= 32)
         hipLaunchKernelGGL((entropy_half_kernel<Geo<8, 4, 1>, TIN, ALIGNED, MODE>), grid, dim3(256), 0, st, a);
+    else if (a.T <= 48)
+        hipLaunchKernelGGL((expect_linear_kernel<TIN, ALIGNED, MODE, 3>), grid, dim3(64 * kExpectWaves), 0, st, a);
     else if (a.T <= 64)
-        hipLaunchKernelGGL((entropy_half_kernel<Geo<16, 4, 4>, TIN, ALIGNED, MODE>), grid, dim3(256), 0, st, a);
+        hipLaunchKernelGGL((expect_linear_kernel<TIN, ALIGNED, MODE, 4>), grid, dim3(64 * kExpectWaves), 0, st, a);
     else if (a.T <= 128) {
         if constexpr (MODE == 0)
             hipLaunchKernelGGL((entropy_half_kernel<Geo<32, 16, 4>, TIN, ALIGNED, MODE>), grid, dim3(1024), 0, st, a);
@@ -520,10 +595,11 @@ static hipError_t launch_entropy_mode(int dtype, const ChainArgs& a, hipStream_t
 
 // H(p) [B] for every sequence: first pass in entropy mode, then the combination at the meeting point.
 hipError_t launch_entropy(int dtype, const void* phi, const int32_t* lengths, int B, int N, int T, float* ua, float* ub,
-                          double* Oa, double* Ob, float* ha, float* hb, float* H, hipStream_t st) {
+                          double* Oa, double* Ob, float* ha, float* hb, double* hoff, float* H, hipStream_t st) {
     ChainArgs a{phi, lengths, B, N, T, ua, ub, Oa, Ob, nullptr, nullptr, 0, nullptr, 0, 1, nullptr, nullptr, nullptr, nullptr};
     a.ha = ha;
     a.hb = hb;
+    if (T > 32 && T <= 64) a.hoff = hoff;  // (the other kernels keep the whole of it in ha / hb)
     const hipError_t e = wave_supported(T) ? launch_wave_pass(false, dtype, a, st) : launch_entropy_mode<0>(dtype, a, st);
     if (e != hipSuccess) return e;
     return launch_entropy_combine(a, H, st);

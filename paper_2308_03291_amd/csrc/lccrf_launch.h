@@ -140,7 +140,7 @@ hipError_t launch_chunked_max(int dtype, const void* phi, const int32_t* lengths
 // Entropy H(p) [B] in one read of phi (lccrf_extras.hip, one-wave kernels for T <= 32).  ua / ub / Oa / Ob
 // as for launch_sequential_sum (only the rows of the meeting positions are written); ha, hb: [B][T] floats.
 hipError_t launch_entropy(int dtype, const void* phi, const int32_t* lengths, int B, int N, int T, float* ua, float* ub,
-                          double* Oa, double* Ob, float* ha, float* hb, float* H, hipStream_t st);
+                          double* Oa, double* Ob, float* ha, float* hb, double* hoff, float* H, hipStream_t st);
 
 // Cross-entropy H(p, q) (kl false) or KL(p || q) (kl true) [B]: the half chains of phi_p carry the expected
 // score under phi_q (the expected score difference); logZq [B]: log Z of phi_q (natural logarithm); hoff: [B][2] doubles.
