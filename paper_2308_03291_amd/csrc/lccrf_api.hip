@@ -804,10 +804,11 @@ int lccrf_argmax_structured(const float* emit, const float* trans, const int32_t
                                           emit, trans);
         return e == hipSuccess ? LCCRF_OK : LCCRF_ELAUNCH;
     }
+    // (above 32 tags the kernel for structured potentials is quicker than the chain waves at every batch size)
     const hipError_t e = lccrf::launch_structured_max(emit, trans, lengths, B, N, T,
                                                       reinterpret_cast<uint8_t*>(base + w.bp),
                                                       reinterpret_cast<double*>(base + w.mid), best_score, tags,
-                                                      static_cast<hipStream_t>(stream), lanes_pay_max(B, N, T),
+                                                      static_cast<hipStream_t>(stream), T <= 32 && lanes_pay_max(B, N, T),
                                                       g_lane_poll_limit.load(std::memory_order_relaxed));
     return e == hipSuccess ? LCCRF_OK : LCCRF_ELAUNCH;
 }

@@ -586,7 +586,7 @@ __global__ __launch_bounds__(64 * kMaxWaves, (TP == 32 ? 4 : 1)) void viterbi_la
 }
 
 // ---------------------------------------------------------------------------------------
-// Dense or structured potentials, whole sequences, up to 64 tags.
+// Dense potentials, whole sequences, up to 64 tags; structured ones up to 32.
 bool lane_max_supported(int T) { return T >= 1 && T <= 64; }
 
 template <int TP, int ROWS, typename TIN, bool AL>
@@ -602,8 +602,12 @@ template <typename TIN, bool AL>
 static hipError_t launch_max_T(const VitArgs& a, int poll_limit, hipStream_t st) {
     if (a.T <= 16) return launch_max_kernel<16, 16, TIN, AL>(a, poll_limit, st);
     if (a.T <= 32) return launch_max_kernel<32, 32, TIN, AL>(a, poll_limit, st);
-    if (a.T <= 48) return launch_max_kernel<64, 48, TIN, AL>(a, poll_limit, st);
-    return launch_max_kernel<64, 64, TIN, AL>(a, poll_limit, st);
+    if constexpr (std::is_same<TIN, MaxStructF>::value) {
+        return hipErrorInvalidValue;  // (structured potentials above 32 tags: viterbi_structured_kernel)
+    } else {
+        if (a.T <= 48) return launch_max_kernel<64, 48, TIN, AL>(a, poll_limit, st);
+        return launch_max_kernel<64, 64, TIN, AL>(a, poll_limit, st);
+    }
 }
 template <typename TIN>
 static hipError_t launch_max_src(const VitArgs& a, int poll_limit, hipStream_t st) {

@@ -291,6 +291,103 @@ __global__ __launch_bounds__(G::W) void viterbi_half_kernel(VitArgs a) {
     if (tid < T) mid[tid] = sm.dvec[buf][tid];
 }
 
+// Structured potentials, 33 .. 64 tags, whole sequences.  The transition scores stay in registers and a position brings T emissions,
+// so nothing streams and a step is bound by its arithmetic (an fp32 and an fp64 addition, a conversion, a comparison and three
+// selections an edge) and by what the chain waits for between them.  Lane = the tag the step goes to (forward t, backward s), wave
+// w = the NS tags w NS .. it comes from: a wave takes its sources' scores from its own lanes' registers (v_readlane),
+// keeps the first maximum of each lane in order, and the four waves' candidates meet in LDS behind the step's one barrier,
+// where every wave merges them for itself, so the new scores are in every wave's registers.  The potentials of the next step, which
+// depend on nothing, are formed before the barrier.
+// Whole argmax, us, so / dense tiles formed in registers, four waves, two barriers a step: N=100 B=256 T=45 54 / 91, T=64 63 / 85, B=1024
+// T=64 193 / 215, N=16 B=1024 T=48 34 / 43; against the chain-wave kernels (a ring of matrices in LDS, which these potentials
+// do not need) B=128 T=45 40 / 59, B=1 37 / 54.
+template <int NS, bool BACKWARD>
+__device__ __forceinline__ void structured_chain(const VitArgs& a, int b, int first, int n, double (*pv)[4][64], int (*pi)[4][64], double* mid) {
+    constexpr int PF = 4;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), T = a.T;
+    const bool on = lane < T;
+    const int me = on ? lane : T - 1, s0 = NS * wave;
+    const float* emb = a.emit + (size_t)b * a.N * T;
+    uint8_t* bpb = a.bp + (size_t)b * a.N * T;
+    const double ninf = -__builtin_huge_val();
+    float tr[NS];  // of the edges into (forward) or out of (backward) this lane's tag
+#pragma unroll
+    for (int k = 0; k < NS; ++k) {
+        const int s = s0 + k < T ? s0 + k : T - 1;
+        tr[k] = s0 + k < T ? a.trans[BACKWARD ? me * T + s : s * T + me] : LCCRF_NEG_INF;
+    }
+    double v = !on ? ninf : BACKWARD ? 0.0 : (double)(a.trans[me] + emb[me]);
+    if (n > 0) {
+        const auto position = [&](int q) { return BACKWARD ? first - q : first + q; };
+        float em[PF];
+#pragma unroll
+        for (int p = 0; p < PF; ++p) em[p] = emb[(size_t)position(p < n ? p : n - 1) * T + me];
+        float x[NS];
+        const auto form = [&](float e) __attribute__((always_inline)) {  // the potentials of a step
+#pragma unroll
+            for (int k = 0; k < NS; ++k) {
+                const float ek = BACKWARD ? __int_as_float(__builtin_amdgcn_readlane(__float_as_int(e), s0 + k)) : e;
+                x[k] = tr[k] + ek;
+            }
+        };
+        form(em[0]);
+        int done = 0;
+        bool running = true;
+        while (running) {
+#pragma unroll
+            for (int p = 0; p < PF; ++p) {
+                const int lo = (int)(unsigned)__double_as_longlong(v), hi = __double2hiint(v);
+                double bv[4];
+                int ba[4];
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {  // four runs of consecutive tags: their comparisons overlap
+                    bv[c] = ninf;
+                    ba[c] = kNoArg;
+#pragma unroll
+                    for (int k = c * (NS / 4); k < (c + 1) * (NS / 4); ++k) {
+                        const unsigned dl = (unsigned)__builtin_amdgcn_readlane(lo, s0 + k), dh = (unsigned)__builtin_amdgcn_readlane(hi, s0 + k);
+                        const double val = __longlong_as_double((long long)(((unsigned long long)dh << 32) | dl)) + (double)x[k];
+                        if (val > bv[c]) { bv[c] = val; ba[c] = s0 + k; }
+                    }
+                }
+#pragma unroll
+                for (int c = 1; c < 4; ++c)
+                    if (bv[c] > bv[0]) { bv[0] = bv[c]; ba[0] = ba[c]; }
+                pv[p & 1][wave][lane] = bv[0];
+                pi[p & 1][wave][lane] = ba[0];
+                form(em[(p + 1) % PF]);
+                const int i = position(done);
+                em[p] = emb[(size_t)position(done + PF < n ? done + PF : n - 1) * T + me];
+                __syncthreads();
+                double w = pv[p & 1][0][lane];
+                int arg = pi[p & 1][0][lane];
+#pragma unroll
+                for (int q = 1; q < 4; ++q) {
+                    const double ov = pv[p & 1][q][lane];
+                    const int oa = pi[p & 1][q][lane];
+                    if (ov > w) { w = ov; arg = oa; }
+                }
+                v = on ? w : ninf;
+                if (wave == p && on) bpb[(size_t)i * T + lane] = (uint8_t)(arg == kNoArg ? 0 : arg);
+                if (++done >= n) { running = false; break; }
+            }
+        }
+    }
+    if (wave == 0 && on) mid[lane] = v;
+}
+template <int NS>
+__global__ __launch_bounds__(256) void viterbi_structured_kernel(VitArgs a) {
+    __shared__ double pv[2][4][64];
+    __shared__ int pi[2][4][64];
+    const int dir = blockIdx.x & 1, b = blockIdx.x >> 1;
+    const int L = clamp_length(a.lengths, b, a.N);
+    if (L == 0) return;
+    const int e = L - 1, h = meeting_point(0, e);
+    double* mid = a.mid + ((size_t)b * 2 + dir) * a.T;
+    if (dir == 0) structured_chain<NS, false>(a, b, 1, h, pv, pi, mid);
+    else structured_chain<NS, true>(a, b, e, e - h, pv, pi, mid);
+}
+
 // 129 .. 256 tags: the matrix of a position streams through registers in batches of 64 rows, as in the
 // sum-product kernels for these tag sets (lccrf_stream.hip): lane l of wave w holds, of batch q, rows
 // 64 q + 4 w + k (k < 4), columns 4 l .. 4 l + 3, and a ring of batch slots is refilled across position
@@ -821,7 +918,15 @@ template <bool ALIGNED>
 static hipError_t launch_structured_T(const VitArgs& a, hipStream_t st) {
     if (a.T <= 16) return launch_wave_vit<16, float, ALIGNED, true>(a, st);
     if (a.T <= 32) return launch_wave_vit<32, float, ALIGNED, true>(a, st);
-    if (a.T <= 64) return launch_structured_geo<Geo<16, 4, 4>, ALIGNED>(a, st);
+    if (a.T <= 64) {
+        if (a.chunk > 0) return hipErrorInvalidValue;  // (the max-plus scan ends at 32 tags)
+        if (a.T <= 48) hipLaunchKernelGGL(viterbi_structured_kernel<12>, dim3(2 * a.B), dim3(256), 0, st, a);
+        else hipLaunchKernelGGL(viterbi_structured_kernel<16>, dim3(2 * a.B), dim3(256), 0, st, a);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(viterbi_trace_kernel, dim3(a.B), dim3(kTraceThreads), 0, st, a);
+        return hipGetLastError();
+    }
     return launch_structured_geo<Geo<32, 16, 4>, ALIGNED>(a, st);
 }
 
@@ -829,7 +934,7 @@ static hipError_t launch_structured_T(const VitArgs& a, hipStream_t st) {
 hipError_t launch_structured_max(const float* emit, const float* trans, const int32_t* lengths, int B, int N, int T,
                                  uint8_t* bp, double* mid, float* best_score, int32_t* tags, hipStream_t st, bool lanes,
                                  int lane_poll_limit) {
-    if (T > 128 || (lanes && !lane_max_supported(T))) return hipErrorInvalidValue;
+    if (T > 128 || (lanes && (T > 32 || !lane_max_supported(T)))) return hipErrorInvalidValue;
     const VitArgs a{nullptr, lengths, B, N, T, bp, mid, best_score, tags, 0, 1, nullptr, emit, trans};
     if (lanes) return launch_any(0, a, st, true, lane_poll_limit);
     return (T % 4) == 0 ? launch_structured_T<true>(a, st) : launch_structured_T<false>(a, st);

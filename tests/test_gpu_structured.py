@@ -259,3 +259,24 @@ def test_structured_scan_agrees_with_dense_scan(crf):
     s_a, y_a = crf.lccrf_argmax_structured(emit.cuda(), trans.cuda())
     s_b, y_b = crf.lccrf_argmax(phi)
     assert torch.equal(y_a, y_b) and torch.equal(s_a, s_b)
+
+
+# both numbers of source tags a wave takes, a last wave with all, one or none of its tags
+@pytest.mark.parametrize("T", (33, 36, 37, 45, 48, 49, 52, 61, 64))
+@pytest.mark.parametrize("N", (1, 2, 9, 31))
+def test_structured_argmax_with_the_transitions_in_registers(crf, oracle_mod, T, N):
+    """33 .. 64 tags: tags and scores of the dense call bit for bit, exact ties (integer scores) across the waves' tags, forbidden
+    transitions, a tag and a position without any path included; then against the oracle."""
+    B = 7
+    g = torch.Generator().manual_seed(7310 + 67 * T + N)
+    lens = torch.tensor([N, max(N - 1, 1), 1, 0, min(2, N), N, (N + 1) // 2], dtype=torch.int32)
+    emit = torch.randint(0, 3, (B, N, T), generator=g).to(torch.float32)
+    trans = torch.randint(0, 2, (T, T), generator=g).to(torch.float32)
+    trans[:, T // 2] = trans[T - 1, :] = trans[3, 1] = float("-inf")
+    emit[5, N // 2] = float("-inf")
+    phi = (emit[:, :, None, :] + trans[None, None]).contiguous().cuda()
+    s_a, y_a = crf.lccrf_argmax_structured(emit.cuda(), trans.cuda(), lens.cuda())
+    s_b, y_b = crf.lccrf_argmax(phi, lens.cuda(), algo=crf.ALGO_SEQUENTIAL)
+    assert torch.equal(y_a, y_b) and torch.equal(s_a, s_b)
+    emit, trans = _make(7320 + T, B, N, T)
+    _check(crf, oracle_mod, emit, trans, lens, f"structured argmax T={T} N={N}")
