@@ -298,6 +298,21 @@ inline bool lanes_pay_sum(int op, int B, int N, int T) {
     return op == 0 ? n * (0.18 - 0.0075 * B) < 15.0 : n * (0.41 - 0.0107 * B) < 80.0;
 }
 
+// Whether sampling's forward chain goes to the chain-wave kernels, one workgroup a sequence: always against the one-wave and
+// four-wave kernels (whole draw, us, so / those: B=32 N=256 T=48 124 / 217, B=128 N=256 T=64 254 / 308, B=256 N=128
+// T=32 71 / 120, T=16 54 / 66).  Against the scan (these kernels and the scan): up to 16 tags 12 + 0.245 N and
+// 38 + 0.00085 B N (B=128 N=64 T=16 31 / 36, N=256 80 / 66); 17 .. 32 tags 19 + 0.25 N + 0.0006 B N and 55 + 0.0021 B N, from about
+// 60000 positions on 40 + 0.003 B N (B=128 N=256 T=32 100 / 125, B=32 N=256 88 / 71, B=64 N=1024 330 / 249).  On very peaked
+// potentials these kernels take steps in the log domain (independent normal ones, B=128 N=128 T=32: deviation 12 84 / 96, 20
+// 258 / 100).
+inline bool lanes_pay_sample(int B, int N, int T) {
+    if (!lccrf::lane_chains_supported(T) || B > current_device_cus() || N < 16) return false;
+    if (!scan_pays_sample(B, N, T)) return true;
+    const double n = (double)N;
+    if (T <= 16) return n * (0.245 - 0.00085 * B) <= 16.0;
+    return n * (0.25 - 0.0015 * B) <= 32.0 || n * (0.25 - 0.0024 * B) <= 20.0;
+}
+
 // Whether LCCRF_ALGO_AUTO gives the max-plus chains to the chain-wave kernels (lccrf_lane_max.hip) rather than to
 // the one-wave / four-wave kernels.  They pay while every workgroup (two a sequence, eight waves each) is resident
 // at once: four a compute unit up to 16 tags, two up to 32, one up to 48 (their LDS rings).  Measured, whole
@@ -408,7 +423,10 @@ int lccrf_auto_algo(lccrf_op op, int B, int N, int T) {
             if (lanes_pay_sum(0, B, N, T)) return LCCRF_ALGO_SEQUENTIAL_LANES;
             scan = scan_pays_sum(B, N, T);
             break;
-        case LCCRF_OP_SAMPLE: scan = scan_pays_sample(B, N, T); break;
+        case LCCRF_OP_SAMPLE:
+            if (lanes_pay_sample(B, N, T)) return LCCRF_ALGO_SEQUENTIAL_LANES;
+            scan = scan_pays_sample(B, N, T);
+            break;
         case LCCRF_OP_ARGMAX:
             scan = scan_taken_max(B, N, T);
             if (!scan && lanes_pay_max(B, N, T)) return LCCRF_ALGO_SEQUENTIAL_LANES;
@@ -686,7 +704,8 @@ static int sample_query(const void* phi, lccrf_dtype dt, const int32_t* lengths,
     double* Oa = reinterpret_cast<double*>(base + w.Oa);
     double* Ob = reinterpret_cast<double*>(base + w.Ob);
     hipError_t e;
-    if (scan_pays_sample(B, N, T)) {  // alpha everywhere, chunk by chunk from the scan's boundary vectors
+    const bool lanes = lanes_pay_sample(B, N, T);
+    if (!lanes && scan_pays_sample(B, N, T)) {  // alpha everywhere, chunk by chunk from the scan's boundary vectors
         float* Fv = reinterpret_cast<float*>(base + w.Fv);
         double* OF = reinterpret_cast<double*>(base + w.OF);
         e = lccrf::launch_scan_boundaries(dt, phi, lengths, B, N, T, scan_chunk(B, N, T), reinterpret_cast<float*>(base + w.Pl),
@@ -696,7 +715,8 @@ static int sample_query(const void* phi, lccrf_dtype dt, const int32_t* lengths,
         if (e == hipSuccess)
             e = lccrf::launch_chunked_full_forward(dt, phi, lengths, B, N, T, ua, ub, Oa, Ob, scan_chunk(B, N, T), Fv, OF, st);
     } else {
-        e = lccrf::launch_full_forward(dt, phi, lengths, B, N, T, ua, ub, Oa, Ob, st);
+        e = lccrf::launch_full_forward(dt, phi, lengths, B, N, T, ua, ub, Oa, Ob, lanes,
+                                       g_lane_poll_limit.load(std::memory_order_relaxed), st);
     }
     if (e == hipSuccess)
         e = lccrf::launch_backward_sample(dt, phi, lengths, ua, Oa, seeded ? nullptr : uniforms, seed, B, N, T,

@@ -1204,9 +1204,10 @@ bool lane_chains_supported(int T) { return lane_supported(T); }
 
 // Forward chains over whole sequences, every alpha stored (ua, Oa): the first pass of sampling.
 hipError_t launch_full_forward(int dtype, const void* phi, const int32_t* lengths, int B, int N, int T, float* ua,
-                               float* ub, double* Oa, double* Ob, hipStream_t st) {
+                               float* ub, double* Oa, double* Ob, bool lanes, int lane_poll_limit, hipStream_t st) {
     ChainArgs a{phi, lengths, B, N, T, ua, ub, Oa, Ob, nullptr, nullptr, 0, nullptr, 0, 1, nullptr, nullptr, nullptr, nullptr};
     a.full_forward = 1;
+    if (lanes) return launch_lane_pass(false, dtype, a, false, lane_poll_limit, st);
     if (wave_supported(T)) return launch_wave(2, dtype, a, st, nullptr);
     if (stream_supported(T)) return launch_stream(2, dtype, a, st, nullptr);
     const PairPlan pair{nullptr, nullptr, dtype, 0, 0};

@@ -28,7 +28,7 @@ bool lane_chains_supported(int T);
 // Sampling (lccrf_chain.hip, lccrf_extras.hip): forward chains over whole sequences with every alpha
 // stored, then the backward sweep that draws the tags from the given uniforms [B][N].
 hipError_t launch_full_forward(int dtype, const void* phi, const int32_t* lengths, int B, int N, int T, float* ua,
-                               float* ub, double* Oa, double* Ob, hipStream_t st);
+                               float* ub, double* Oa, double* Ob, bool lanes, int lane_poll_limit, hipStream_t st);
 size_t sample_winmap_bytes(int B, int N, int T);
 // uniforms null: drawn by the counter-based generator under `seed` instead (lccrf_extras.hip, Uniforms).
 hipError_t launch_backward_sample(int dtype, const void* phi, const int32_t* lengths, const float* ua, const double* Oa,

@@ -193,3 +193,15 @@ def test_sample_seeded_matches_the_host_generator(crf, oracle_mod, T, N, seed):
             assert np.array_equal(g[b], want[b]), f"sequence {b} (margin {margin[b]:.2e})"
     lp = oracle_mod.log_prob(phi, g, lens.numpy())
     assert np.isfinite(lp).all()
+
+
+# the forward chain by the chain-wave kernels: every number of tag blocks, full and ragged, N on both sides of their smallest; a
+# position whose step leaves the scaled range (taken in the log domain, its vector stored like the others)
+@pytest.mark.parametrize("N", [15, 16, 33])
+@pytest.mark.parametrize("T", [8, 16, 17, 24, 31, 32, 33, 45, 48, 52, 64])
+def test_sample_forward_chain_by_the_chain_waves(crf, oracle_mod, T, N):
+    phi, lens = workloads.random_case(7600 + 13 * T + N, 6, N, T, scale=1.5, ragged=True, min_len=0)
+    lens[:3] = torch.tensor([N, 1, 2], dtype=lens.dtype)
+    phi[0, N // 2] *= 60.0
+    phi[4, N // 3, :, 0] = float("-inf")
+    _check_every_draw(crf, oracle_mod, phi, lens, 7700 + T + N, f"lanes T={T} N={N}")
