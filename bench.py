@@ -370,7 +370,7 @@ def main():
         alg_bytes = eff_pots * (esz + 4)
         paired = w.T == 128 and 4 * w.B <= torch.cuda.get_device_properties(dev).multi_processor_count
         kernel = "pair_marginal_kernel" if paired else ("wave_marginal_kernel" if w.T <= 32 else
-                                                        "stream_chain_kernel" if w.T > 128 else "chain_marginal_kernel")
+                                                        "stream_marginal_kernel" if w.T > 128 else "chain_marginal_kernel")
     achieved = alg_bytes / (pass2_avg * 1e-3) / 1e9
     roofline = {"bound": "hbm", "kernel": kernel,
                 "achieved": achieved, "peak": HBM_PEAK_GBPS,
