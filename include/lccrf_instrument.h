@@ -41,6 +41,13 @@ int lccrf_marginals_timed(const void* phi, lccrf_dtype dt, const int32_t* length
 int lccrf_stream_probe(const void* in, void* out, size_t bytes, int workgroups, float* sink, void* stream);
 size_t lccrf_stream_probe_bytes(size_t bytes, int workgroups);
 
+/*
+ * The largest row of a T x T matrix that any thread of a first pass in scaled probabilities (33 .. 256 tags) takes, by the
+ * kernels' own arithmetic over every thread and item of the instance the dispatch chooses: at most T - 1, or the pass
+ * reads past the matrix.  Host only; -1 for other tag counts.
+ */
+int lccrf_first_pass_largest_row(int T);
+
 #ifdef __cplusplus
 }
 #endif

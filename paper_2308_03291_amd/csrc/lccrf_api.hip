@@ -833,6 +833,8 @@ int lccrf_argmax_structured(const float* emit, const float* trans, const int32_t
     return e == hipSuccess ? LCCRF_OK : LCCRF_ELAUNCH;
 }
 
+int lccrf_first_pass_largest_row(int T) { return lccrf::first_pass_largest_row(T); }
+
 const char* lccrf_strerror(int code) {
     switch (code) {
         case LCCRF_OK: return "ok";

@@ -803,7 +803,7 @@ __device__ __attribute__((noinline)) LogStepsResult chain_log_steps(const void* 
     return r;
 }
 
-// ITEMS: rows a thread holds of a matrix, at least linear_items(G::W, T).
+// ITEMS: rows a thread holds of a matrix, linear_instance(G::W, T).
 template <typename G, typename TIN, bool ALIGNED, int ITEMS>
 __global__ __launch_bounds__(G::W, 4) void linear_half_kernel(ChainArgs a) {  // (four waves a SIMD: large batches of 33 .. 64 tags)
     using LG = LinGeo<G::WAVES, G::TCAP, ITEMS>;
@@ -1068,10 +1068,11 @@ static hipError_t launch_linear_items(const ChainArgs& a, hipStream_t st) {
 }
 template <typename G, typename TIN, bool ALIGNED>
 static hipError_t launch_linear_half(const ChainArgs& a, hipStream_t st) {
-    const int items = linear_items(G::W, a.T);  // 2 (33 or 65 tags) .. 4
-    if (items <= 2) return launch_linear_items<G, TIN, ALIGNED, 2>(a, st);
-    if (items == 3) return launch_linear_items<G, TIN, ALIGNED, 3>(a, st);
-    if (items == 4) return launch_linear_items<G, TIN, ALIGNED, 4>(a, st);
+    switch (linear_instance(G::W, a.T)) {  // 2 (33 or 65 tags) .. 4
+        case 2: return launch_linear_items<G, TIN, ALIGNED, 2>(a, st);
+        case 3: return launch_linear_items<G, TIN, ALIGNED, 3>(a, st);
+        case 4: return launch_linear_items<G, TIN, ALIGNED, 4>(a, st);
+    }
     return hipErrorInvalidValue;
 }
 

@@ -151,6 +151,9 @@ hipError_t launch_cross(bool kl, int dtype, const void* phi_p, const void* phi_q
 // logZq null: the chains of phi_q run in the same launch (where cross_runs_both says so).
 bool cross_runs_both(int N, int T);
 
+// The largest row of a matrix that a first pass in scaled probabilities takes at 33 .. 256 tags (lccrf_linear.h; -1: none there).
+int first_pass_largest_row(int T);
+
 // Semi-Markov CRF forward (lccrf_semi.hip): logZ [B] from phi [B][N][K][T][T].
 bool semi_markov_supported(int K, int T);
 hipError_t launch_semi_markov_forward(int dtype, const void* phi, const int32_t* lengths, int B, int N, int K, int T,

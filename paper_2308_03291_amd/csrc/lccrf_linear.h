@@ -20,8 +20,8 @@
 // Layout.  Q4 = ceil(T / 4) threads cover a row, four columns each (whatever lanes and waves they fall into: nothing here
 // reduces across lanes of a row), so the G = W / Q4 row groups of a workgroup fit the tag count, not the next power of two.
 // Thread (g, cl) holds rows g, g + G, ... : the threads of a wave read one contiguous stretch of the matrix.  The last piece of a
-// row is moved back to end with it (T >= 4) and rows past the matrix are its last row again: every load lies inside the
-// matrix whatever the tag count.  What is then held twice meets an exact zero in the sums over it, or is never looked at.
+// row is moved back to end with it (T >= 4) and rows past the matrix are its last row again (linear_row): every load lies inside
+// the matrix whatever the tag count.  What is then held twice meets an exact zero in the sums over it, or is never looked at.
 // Forward, the groups' partial sums of a column meet in LDS; backward, the Q4 threads' partial sums of a row: Q threads
 // share a column or row there.
 #pragma once
@@ -57,10 +57,32 @@ struct LinGeo {
     static constexpr int SCRATCH = FORWARD > BACKWARD ? FORWARD : BACKWARD;
     static_assert((Q == 4 || Q == 8) && ROW4 % 4 == 0 && PARTS >= 1, "a column or row is merged inside eight lanes");
 };
-// Rows a thread holds for a tag count.
-constexpr int linear_items(int W, int T) {
-    const int groups = W / ((T + 3) / 4);
-    return (T + groups - 1) / groups;
+// Rows a thread has to hold for a tag count, and the number it is built for (0: none): every count up to twelve, the even ones
+// above (single precision splits the tile of those in halves).
+constexpr int linear_groups(int W, int T) { return W / ((T + 3) / 4); }
+constexpr int linear_items(int W, int T) { return (T + linear_groups(W, T) - 1) / linear_groups(W, T); }
+constexpr int linear_instance(int W, int T) {
+    const int least = W == 1024 && T > 128 ? 5 : 2, need = linear_items(W, T);
+    const int items = need < least ? least : need > 12 ? (need + 1) / 2 * 2 : need;
+    return items <= 16 ? items : 0;
+}
+// The row of the matrix that item k of a thread of row group g takes.  Only the last item's may lie past the matrix, and the
+// item's before it in the instances that serve one row less as well: those take the last row again.
+constexpr int linear_tail(int items) { return items > 12 ? 2 : 1; }
+__host__ __device__ constexpr int linear_row(int items, int T, int groups, int g, int k) {
+    const int row = g + groups * k;
+    return k < items - linear_tail(items) || row < T ? row : T - 1;
+}
+// The largest row that any thread takes (the group of the threads that are left over included), for a check on the host.
+constexpr int linear_largest_row(int W, int T) {
+    const int items = linear_instance(W, T), groups = linear_groups(W, T), pieces = (T + 3) / 4;
+    int most = 0;
+    for (int g = 0; g <= (W - 1) / pieces; ++g)
+        for (int k = 0; k < items; ++k) {
+            const int row = linear_row(items, T, groups, g, k);
+            if (row > most) most = row;
+        }
+    return most;
 }
 
 template <typename LG>
@@ -189,20 +211,23 @@ __device__ __forceinline__ int linear_run(LinSmem<LG>& ls, const LinJob<TIN, BAC
     if (uniform_f(max16(ls.wmax[1])) != 0.f) return from;
 
     const size_t TT = (size_t)T * T;
-    const int Q4 = (T + 3) >> 2, G = LG::W / Q4;  // threads a row, row groups
+    const int Q4 = (T + 3) >> 2, G = linear_groups(LG::W, T);  // threads a row, row groups
     const int g = tid / Q4, cl = tid - g * Q4;    // (g = G: left over, holds zeros of the vector)
     const int c4 = min(4 * cl, T - 4);
     const unsigned voff = (unsigned)(g * T + c4) * (unsigned)sizeof(TIN);
-    const unsigned voff_last = (unsigned)(min(g + G * (ITEMS - 1), T - 1) * T + c4) * (unsigned)sizeof(TIN);
+    constexpr int TAIL = linear_tail(ITEMS), BODY = ITEMS - TAIL;  // (the rows of the first BODY items: linear_row(.., k) = g + G k)
+    unsigned voff_tail[TAIL];
+#pragma unroll
+    for (int k = 0; k < TAIL; ++k) voff_tail[k] = (unsigned)(linear_row(ITEMS, T, G, g, BODY + k) * T + c4) * (unsigned)sizeof(TIN);
     const size_t row_step = (size_t)(uniform(G) * T);
 
     typename Raw::type raw[R];
     float e[ITEMS][4];
     // row k of this thread's part of the matrix of step s (past the end: the last one again, never used)
     auto fetch = [&](int s, int k) {
-        auto row = (const GlobalBytes*)(job.phib + (size_t)job.matrix(s < n ? s : n - 1) * TT + (k < ITEMS - 1 ? row_step * k : 0));
+        auto row = (const GlobalBytes*)(job.phib + (size_t)job.matrix(s < n ? s : n - 1) * TT + (k < BODY ? row_step * k : 0));
         asm("" : "+s"(row));  // uniform, in scalar registers (not an address of its own per row, hoisted out of the loop)
-        return Raw::template load<ALIGNED>(row + (k < ITEMS - 1 ? voff : voff_last));
+        return Raw::template load<ALIGNED>(row + (k < BODY ? voff : voff_tail[k < BODY ? 0 : k - BODY]));
     };
     // E of step s from the ring, shift c; every piece that is used up is requested again for what follows
     auto prepare = [&](int s, int slot, int shift) __attribute__((always_inline)) {

@@ -465,7 +465,7 @@ __device__ __attribute__((noinline)) LogStepsResult stream_log_steps(const void*
 
 // Pass 1: both half chains, vectors stored.  The steps are taken in scaled probabilities (linear_run) as long as they are
 // accepted, and from one that is not, a block of positions in the log domain (LogBlocks).
-// ITEMS: rows a thread holds of a matrix there, at least linear_items(1024, T).
+// ITEMS: rows a thread holds of a matrix there, linear_instance(1024, T).
 template <typename TIN, bool ALIGNED, int ITEMS>
 __global__ __launch_bounds__(1024) void stream_half_kernel(ChainArgs a) {
     using LG = LinGeo<16, 256, ITEMS>;
@@ -957,12 +957,12 @@ hipError_t launch_stream_expect(int mode, int dtype, const ChainArgs& a, hipStre
 template <typename TIN, bool ALIGNED>
 static hipError_t launch_stream_half(const ChainArgs& a, hipStream_t st) {
     const dim3 grid(2 * a.B), block(1024);
-    const int items = linear_items(1024, a.T);  // 5 (129 tags) .. 16 (256 tags)
-#define LCCRF_STREAM_HALF(I) else if (items <= I) hipLaunchKernelGGL((stream_half_kernel<TIN, ALIGNED, I>), grid, block, 0, st, a)
-    if (items < 1) return hipErrorInvalidValue;
-    LCCRF_STREAM_HALF(5); LCCRF_STREAM_HALF(6); LCCRF_STREAM_HALF(7); LCCRF_STREAM_HALF(8); LCCRF_STREAM_HALF(9); LCCRF_STREAM_HALF(10);
-    LCCRF_STREAM_HALF(11); LCCRF_STREAM_HALF(12); LCCRF_STREAM_HALF(14); LCCRF_STREAM_HALF(16);
-    else return hipErrorInvalidValue;
+    switch (linear_instance(1024, a.T)) {  // 5 (129 tags) .. 16 (256 tags)
+#define LCCRF_STREAM_HALF(I) case I: hipLaunchKernelGGL((stream_half_kernel<TIN, ALIGNED, I>), grid, block, 0, st, a); break
+        LCCRF_STREAM_HALF(5); LCCRF_STREAM_HALF(6); LCCRF_STREAM_HALF(7); LCCRF_STREAM_HALF(8); LCCRF_STREAM_HALF(9); LCCRF_STREAM_HALF(10);
+        LCCRF_STREAM_HALF(11); LCCRF_STREAM_HALF(12); LCCRF_STREAM_HALF(14); LCCRF_STREAM_HALF(16);
+        default: return hipErrorInvalidValue;
+    }
 #undef LCCRF_STREAM_HALF
     return hipGetLastError();
 }
@@ -973,6 +973,8 @@ static hipError_t launch_stream_marginal(const ChainArgs& a, hipStream_t st) {
 }
 
 bool stream_supported(int T) { return T > 128 && T <= 256; }
+
+int first_pass_largest_row(int T) { return T > 32 && T <= 256 ? linear_largest_row(T > 64 ? 1024 : 256, T) : -1; }
 
 hipError_t launch_edge_marginals(int dtype, const ChainArgs& a, hipStream_t st) {
     if (a.T < 4 || a.T > 256 || a.chunk > 0 || a.emit) return hipErrorInvalidValue;

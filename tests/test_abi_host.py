@@ -58,6 +58,12 @@ def test_workspace_sizes(lib):
     assert binding.workspace_bytes(9, 1, 8, 8, 0) == 0
 
 
+@pytest.mark.parametrize("T", range(33, 257))
+def test_first_pass_rows_lie_inside_the_matrix(lib, T):
+    """Every tag count, every thread and item of the instance that serves it: the last row, and no row past it."""
+    assert lib.lccrf_first_pass_largest_row(T) == T - 1
+
+
 def test_auto_schedule_is_reported_without_a_gpu(lib):
     """lccrf_auto_algo is host arithmetic: long chains over few tags in small batches take the scan.  (Without a
     device there are no compute units to count and the chain-wave kernels are never chosen; their share of AUTO

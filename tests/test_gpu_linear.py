@@ -33,8 +33,18 @@ def test_bfloat16_rows_off_the_grid(crf, oracle_mod, T):
     check_case(crf, oracle_mod, phi, None, what=f"odd rows T={T}", queries=("logz", "mu"), algo=crf.ALGO_SEQUENTIAL)
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("T", [217, 220, 223, 224, 237, 239, 240])
+def test_last_matrix_of_full_length_sequences(crf, oracle_mod, T, dtype):
+    """Tag counts whose instance holds a row more than they need (217 .. 224, 239, 240), and one that does not; the last
+    sequence ends with the tensor.  (That no row past the matrix is taken is asserted on the host: test_abi_host.py.)"""
+    phi, _ = workloads.random_case(7200 + T, 3, 12, T, scale=2.0, dtype=dtype)
+    check_case(crf, oracle_mod, phi, None, what=f"linear, full length, T={T} {dtype}", queries=("logz", "mu"))
+
+
 def test_nothing_is_read_past_the_tensor(crf, oracle_mod):
-    """NaN right behind the potentials (T odd: rows end anywhere)."""
+    """NaN right behind the potentials (T odd: rows end anywhere).  A value that is read there and meets an exact zero only
+    sends the chain to its log-domain steps: what the kernels may read is asserted on the host (test_abi_host.py)."""
     for T, dtype in ((129, "f32"), (201, "bf16"), (67, "f32"), (99, "bf16")):
         phi, _ = workloads.random_case(7400 + T, 2, 9, T, dtype=dtype)
         flat = torch.full((phi.numel() + 64,), float("nan"), dtype=phi.dtype, device="cuda")
