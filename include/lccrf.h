@@ -214,7 +214,9 @@ int lccrf_log_prob(const void* phi, lccrf_dtype dt, const int32_t* lengths, cons
  * Entropy H(p) = -sum_y p(y) log p(y) of every chain, in nats (paper, section "Entropy and KL
  * Divergence": H(p) = H(p, p) = logZ - sum_e p(e) phi(e)).  Computed in ONE read of phi and without
  * forming the marginals: the two half chains carry the conditional entropy of the path behind
- * them, and the meeting position combines them (the same value up to rounding).
+ * them (or the expected score, from which it follows), and the meeting position combines them.
+ * Accuracy: relative single precision, or some 1e-7 a position in absolute terms where that is more:
+ * the entropy of a nearly deterministic chain is not known to more, and may come out just below zero.
  *   entropy   [B] float32 (device).  Empty chain: 0.  No finite path: NaN.
  * Workspace: lccrf_workspace_bytes(LCCRF_OP_ENTROPY, ...).  Errors as lccrf_log_partition.
  */

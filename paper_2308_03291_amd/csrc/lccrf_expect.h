@@ -12,15 +12,20 @@
 // completes its rows and every wave reads them all.  Each wave therefore knows the new vector and decides for itself, all alike,
 // whether the step is accepted.
 //
-// V is S rescaled by the power of two that brings tag 0 into [1/2, 1), its offset an integer; the common part c = U(0) / S(0) of h
-// moves into a double-precision offset at every step, so X stays small.  The shift of a matrix is what tag 0 grew by at
-// the step before, less kExpectHead (the first: its largest entry plus the vector's).  Accepted: every S at least 2^-40 before and
-// within [2^-40, 2^40] after rescaling, every |X| at most 2^60.  What underflowed in S is then at most 64 2^40 2^-126 of 2^-40,
-// less than 2^-40; the same of U, times the size of f.  The first step that is not accepted ends the run.
+// V is S rescaled by the power of two that gives tag 0 the exponent kExpectHead, its offset an integer.  Only differences of h
+// between the tags matter, so every step takes h of the heaviest tag of the vector it starts from out of all of them, into a
+// double-precision offset (found while the sums of the step are exchanged): X of the tags that carry the weight, and with it
+// the rounding of U, stays as small as what one step adds, also where a single path carries nearly all of it.  (Centred at tag 0,
+// which such a path leaves tens of bits behind, the entropy of a chain of 256 positions was off by 1.3e-4.)
+// The shift of a matrix is what tag 0 grew by at the step before (the first: its largest entry plus the vector's), so that
+// the exponents of the heavy edges are near zero, where they are rounded least.  Accepted: every S at least 2^-40 before and within
+// [2^-28, 2^52] after rescaling (2^40 either side of tag 0), every |X| at most 2^72.  What underflowed in S (an E below 2^-126: its
+// products are held down to 2^-149) is then at most 64 2^52 2^-126 of 2^-40, 2^-28; the same of U, times the size of f.  The
+// first step that is not accepted ends the run.
 //
 // A step costs 0.7 us (64 tags, entropy; the log-domain steps 1.0): two LDS round trips and a barrier on the dependent path, one
-// wave a SIMD.  Entropy B=128 N=128 T=48 50 us (69), divergence B=64 N=256 T=64 131 us (172), there at 4.1 TB/s of p once and q
-// twice.  At B=512 the entropy is bound by memory either way (N=64, 64 tags 101 / 98).
+// wave a SIMD.  Entropy B=128 N=128 T=48 49 us (69), divergence B=64 N=256 T=64 133 us (172), there at 4.0 TB/s of p once and q
+// twice; the heaviest tag costs 0.3 and 3 us of these.  At B=512 the entropy is bound by memory either way (N=64, 64 tags 101 / 98).
 #pragma once
 
 #include "lccrf_device.h"
@@ -28,7 +33,7 @@
 
 namespace lccrf {
 
-constexpr int kExpectHead = 24;
+constexpr int kExpectHead = 12;
 constexpr int kExpectWaves = 4, kExpectLanes = 16;  // sixteen lanes a row
 constexpr int kExpectPlain = 3;                     // MODE: V alone, no expectation (0, 1, 2: as in lccrf_extras.hip)
 
@@ -65,8 +70,8 @@ __device__ __forceinline__ int expect_run(ExpectSmem& sm, const TIN* phib, const
     // the vector the run starts from: what it holds without loss, and finite expectations
     const float top = finite_or_zero(xor_max<1, 64>(st.v));
     const float d = ceilf(top);
-    const float v0 = ex2(st.v - d), x0 = v0 > 0.f ? v0 * (MODE == 0 ? st.h - d : st.h) : 0.f;
-    if (!__all((st.v == LCCRF_NEG_INF || st.v - d >= -100.f) && fabsf(x0) <= 0x1p60f && fabsf(d) <= 0x1p20f)) return 0;
+    const float v0 = ex2(st.v - d + (float)kExpectHead), x0 = v0 > 0.f ? v0 * (MODE == 0 ? st.h - d : st.h) : 0.f;
+    if (!__all((st.v == LCCRF_NEG_INF || st.v - d >= -100.f) && fabsf(x0) <= 0x1p72f && fabsf(d) <= 0x1p20f)) return 0;
 
     const size_t TT = (size_t)T * T;
     const int Q4 = (T + 3) >> 2;
@@ -106,7 +111,7 @@ __device__ __forceinline__ int expect_run(ExpectSmem& sm, const TIN* phib, const
                 if constexpr (CARRY) {
                     // an edge without weight adds nothing, whatever its score
                     if constexpr (MODE == 0) {
-                        f[m][j] = e[m][j] * fmaxf(arg - (float)kExpectHead, -0x1p100f);
+                        f[m][j] = e[m][j] * fmaxf(arg, -0x1p100f);
                     } else {
                         const float q = Raw::get(qraw[p][m], j);
                         f[m][j] = e[m][j] > 0.f ? e[m][j] * (MODE == 1 ? q : x - q) : 0.f;
@@ -155,16 +160,21 @@ __device__ __forceinline__ int expect_run(ExpectSmem& sm, const TIN* phib, const
     if (lane == 0) sm.part[1][wave][0][0] = big;
     __syncthreads();
     big = fmaxf(fmaxf(sm.part[1][0][0][0], sm.part[1][1][0][0]), fmaxf(sm.part[1][2][0][0], sm.part[1][3][0][0]));
-    int grew = uniform((int)fminf(fmaxf(ceilf(finite_or_zero(big)), -0x1p20f), 0x1p20f)), c_cur = grew - kExpectHead;
+    int grew = uniform((int)fminf(fmaxf(ceilf(finite_or_zero(big)), -0x1p20f), 0x1p20f)) - kExpectHead, c_cur = grew;
     __syncthreads();
     prepare(0, PH, c_cur);
 
     int done = 0;
     long long Oi = 0, Hi = 0;
-    float V = v0, X = x0;       // of the last accepted step, lane = tag
+    float V = lane < T ? v0 : 0.f, X = x0;  // of the last accepted step, lane = tag
     double shift = 0.0;         // what has moved out of h so far
     float hc = 0.f;             // backward: the shift of h and the scale that the sums at hand have yet to be given
     int k = 0;
+    const auto heaviest = [&]() __attribute__((always_inline)) {  // h of the heaviest tag of the vector at hand (any number near it will do)
+        const float m = xor_max<1, 64>(V);
+        const int at = __builtin_ctzll(__ballot(V == m) | 1ull << 63);
+        return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(X), at)) * __builtin_amdgcn_rcpf(fmaxf(uniform_f(m), 0x1p-126f));
+    };
     const auto pair32 = [](float x, float y) {
         const auto r = __builtin_amdgcn_permlane32_swap(__float_as_int(x), __float_as_int(y), false, false);
         return __int_as_float(r[0]) + __int_as_float(r[1]);
@@ -174,8 +184,8 @@ __device__ __forceinline__ int expect_run(ExpectSmem& sm, const TIN* phib, const
         return __int_as_float(r[0]) + __int_as_float(r[1]);
     };
     const auto step = [&](int next) __attribute__((always_inline)) -> bool {  // false: the run is over
-        const int c_next = max(min(grew, 1 << 20), -(1 << 20)) - kExpectHead, par = done & 1;
-        float S = 0.f, U = 0.f;
+        const int c_next = max(min(grew, 1 << 20), -(1 << 20)), par = done & 1;
+        float S = 0.f, U = 0.f, centre = 0.f;
         if constexpr (!BACKWARD) {
             float as[4] = {0.f, 0.f, 0.f, 0.f}, au[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -195,6 +205,7 @@ __device__ __forceinline__ int expect_run(ExpectSmem& sm, const TIN* phib, const
             float2 q[WAVES];
 #pragma unroll
             for (int w = 0; w < WAVES; ++w) q[w] = *reinterpret_cast<const float2*>(sm.part[par][w][rslot]);
+            if (CARRY) centre = heaviest();
             prepare(next, done + 1 + PH, c_next);
             S = (q[0].x + q[1].x) + (q[2].x + q[3].x);
             if (CARRY) U = (q[0].y + q[1].y) + (q[2].y + q[3].y);
@@ -230,34 +241,32 @@ __device__ __forceinline__ int expect_run(ExpectSmem& sm, const TIN* phib, const
             __syncthreads();
             S = sm.row[par][0][me];
             if (CARRY) U = sm.row[par][1][me];
+            if (CARRY) centre = heaviest();
             prepare(next, done + 1 + PH, c_next);
         }
-        const int k_new = uniform(__builtin_amdgcn_frexp_expf(S));  // tag 0's
+        const int k_new = uniform(__builtin_amdgcn_frexp_expf(S)) - kExpectHead;  // tag 0's
         const float vn = __builtin_amdgcn_ldexpf(S, -k_new);
-        float xn = 0.f, hc_new = 0.f;
-        if constexpr (CARRY) {
-            const float y = __builtin_amdgcn_ldexpf(U, -k_new);
-            hc_new = uniform_f(y * __builtin_amdgcn_rcpf(vn));  // (any number near h of tag 0 will do)
-            xn = __builtin_fmaf(-hc_new, vn, y);
-        }
-        if (!__all(S >= 0x1p-40f && vn >= 0x1p-40f && vn <= 0x1p40f && fabsf(xn) <= 0x1p60f)) return false;
+        const float xn = CARRY ? __builtin_fmaf(-centre, vn, __builtin_amdgcn_ldexpf(U, -k_new)) : 0.f;
+        if (!__all(S >= 0x1p-40f && vn >= 0x1p-28f && vn <= 0x1p52f && fabsf(xn) <= 0x1p72f)) return false;
         V = vn;
         X = xn;
         k = k_new;
-        hc = hc_new;
+        hc = centre;
         if constexpr (!BACKWARD) *reinterpret_cast<float2*>(sm.vec[me]) = make_float2(vn, xn);  // (every wave, the same values)
-        if (CARRY) shift += (double)hc_new;
+        if (CARRY) shift += (double)centre;
         grew = c_cur + k_new;
         Oi += grew;
-        Hi += c_cur + kExpectHead;
+        Hi += c_cur;
         c_cur = c_next;
         return ++done < n;
     };
     while (step(1) && step(2) && step(0)) {}
     __syncthreads();  // (the shared state may be used for something else now)
-    st.v = lane < T ? lg2(V) : LCCRF_NEG_INF;
+    // (the largest entry brought below 1: the closer the logarithms are to zero, the less their rounding takes)
+    const int kv = uniform(__builtin_amdgcn_frexp_expf(xor_max<1, 64>(V)));
+    st.v = lane < T ? lg2(__builtin_amdgcn_ldexpf(V, -kv)) : LCCRF_NEG_INF;
     st.h = CARRY && V > 0.f ? X / V : 0.f;
-    st.O += (double)d + (double)Oi;
+    st.O += (double)d + (double)(Oi + kv - kExpectHead);
     st.Hoff += MODE == 0 ? shift + (double)d + (double)Hi : shift;
     return done;
 }
