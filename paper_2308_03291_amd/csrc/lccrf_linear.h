@@ -4,18 +4,19 @@
 // A step of the log-domain kernels exponentiates the matrix once its own input vector is known, so the exponentials
 // sit on the chain of dependent work, and while the partial sums are merged nothing else runs.  Here a step is a
 // plain vector-matrix product,
-//     S_n(u) = 2^-k_{n-1} sum_v S_{n-1}(v) E_n(v, u),      E_n = 2^(phi_n log2 e - c_n),
+//     S_n(u) = 2^(kLinearHead - k_{n-1}) sum_v S_{n-1}(v) E_n(v, u),      E_n = 2^(phi_n log2 e - c_n),
 // (k_{n-1} the exponent of the largest entry of S_{n-1}, c_n an integer) whose matrix is exponentiated one step AHEAD,
 // between the two barriers of the step before: the dependent part of a step is one fused multiply-add a potential,
 // one exchange through LDS and no exponential or logarithm.  All scales are powers of two, so they round nothing.
 //
 // c_n has to be chosen before S_{n-1} is known: it is the growth of the step before the last one (the exponent the
-// largest entry gained there), the first two matrices taking what the first step will grow by, less kLinearHead: the entries of
-// a vector reach further below its largest than the growth strays from one step to the next.  A step is accepted if every
-// sum lies in [2^-60, 2^60] and the largest entry of the vector it started from was at least 2^-30: whatever
-// underflowed in it (an E below 2^-126, a product below 2^-126) is then at most 256 * 2^-66 + 256 * 2^-36 < 2^-27 of the sum
-// it belongs to, for every entry separately.  At a step that is not accepted the stretch ends, with the vector in front
-// of that step; the caller's log-domain steps take over from there.
+// largest entry gained there), the first two matrices taking what the first step will grow by.  The exponents of the heavy
+// edges are then near zero, where they are rounded least; the head stands in the vectors, whose largest entry is near
+// 2^kLinearHead: their entries reach further below it than the growth strays from one step to the next.  A step is accepted if every
+// sum lies in [2^-60, 2^60] and the largest entry of the vector it started from was at least 2^-30: an E below 2^-126 is
+// flushed, which takes at most 256 2^k 2^-126 of a sum of 2^(-60 - kLinearHead + k) before scaling, 2^-34, and a product below
+// 2^-126 is still held to 2^-149 (denormals are kept): 256 2^-150 of 2^(-84 - 30), 2^-28, for every entry separately.  At a step that is not accepted
+// the stretch ends, with the vector in front of that step; the caller's log-domain steps take over from there.
 //
 // Layout.  Q4 = ceil(T / 4) threads cover a row, four columns each (whatever lanes and waves they fall into: nothing here
 // reduces across lanes of a row), so the G = W / Q4 row groups of a workgroup fit the tag count, not the next power of two.
@@ -279,7 +280,7 @@ __device__ __forceinline__ int linear_run(LinSmem<LG>& ls, const LinJob<TIN, BAC
     __syncthreads();
     // (shifts and exponents are integers in scalar registers; far inside the range of an int)
     big = max16(ls.wmax[1]);
-    int c_cur = uniform((int)fminf(fmaxf(ceilf(finite_or_zero(big)), -0x1p20f), 0x1p20f)) - kLinearHead, c_last = c_cur + kLinearHead - 1;
+    int c_cur = uniform((int)fminf(fmaxf(ceilf(finite_or_zero(big)), -0x1p20f), 0x1p20f)), c_last = c_cur + kLinearHead - 1;
     __syncthreads();
     if (tid < 32) ls.wmax[tid >> 4][tid & 15] = tid == 0 ? 1.f : 0.f;
     prepare(from, 0, c_cur);
@@ -297,8 +298,8 @@ __device__ __forceinline__ int linear_run(LinSmem<LG>& ls, const LinJob<TIN, BAC
         }
         if (done == n || !(M >= 0x1p-30f)) return false;
         const int k = uniform(__builtin_amdgcn_frexp_expf(M));
-        // (c_last + k: what the last step grew by.  In front of the first step c_last stands for what the first one will
-        // grow by, less the exponent 1 of its vector.)
+        // (c_last + k - kLinearHead: what the last step grew by.  In front of the first step c_last is such that this is what the
+        // first one will grow by, the exponent of its vector being 1.)
         const int c_next = max(min(c_last + k, 1 << 20), -(1 << 20)) - kLinearHead;
         const float* vin = &ls.vec[buf][vfrom];
         if constexpr (!BACKWARD) {
@@ -343,13 +344,13 @@ __device__ __forceinline__ int linear_run(LinSmem<LG>& ls, const LinJob<TIN, BAC
             }
             s = (x.x + x.y) + (x.z + x.w);
         }
-        s = __builtin_amdgcn_ldexpf(xor_sum<1, Q>(s), -k);
+        s = __builtin_amdgcn_ldexpf(xor_sum<1, Q>(s), kLinearHead - k);
         ls.vec[buf ^ 1][vmine] = s;
         if constexpr (BACKWARD) ls.vec[buf ^ 1][vcopy] = s;
         const float m = __all(sum_in_range(s)) ? xor_max<1, 64>(s) : __builtin_huge_valf();
         if (lane == 0) ls.wmax[buf ^ 1][wave] = m;
         Oi_last = Oi;
-        Oi += k + c_cur;
+        Oi += k - kLinearHead + c_cur;
         c_last = c_cur;
         c_cur = c_next;
         prepare(done + 1, slot_next, c_next);

@@ -558,8 +558,11 @@ __global__ __launch_bounds__(kEdgeThreads) void edge_marginal_kernel(ChainArgs a
     const float ws = xor_sum<1, 64>(ex2(z - finite_or_zero(M)));
     if (lane == 0) red[1][wave] = ws;
     __syncthreads();
-    const float lz = M + lg2((red[1][0] + red[1][1]) + (red[1][2] + red[1][3]));
-    if (a.logZ && tid == 0 && i == meeting_point(0, L - 1)) a.logZ[b] = (float)(((double)lz + a.Oa[vb + i] + a.Ob[vb + i]) * kLn2);
+    const float S = (red[1][0] + red[1][1]) + (red[1][2] + red[1][3]);
+    const int Se = __builtin_amdgcn_frexp_expf(S);  // (the logarithm in two parts: the small one rounds next to nothing)
+    const double lzd = (double)M + (double)lg2(__builtin_amdgcn_ldexpf(S, -Se)) + (double)Se;
+    const float lz = (float)lzd;
+    if (a.logZ && tid == 0 && i == meeting_point(0, L - 1)) a.logZ[b] = (float)((lzd + a.Oa[vb + i] + a.Ob[vb + i]) * kLn2);
     if (i == 0) {  // p(y_0 = t) in row 0
         if (tid < T) mu[tid] = M == LCCRF_NEG_INF ? 0.f : ex2(z - lz);
         clear(T);
@@ -569,19 +572,24 @@ __global__ __launch_bounds__(kEdgeThreads) void edge_marginal_kernel(ChainArgs a
         clear(0);
         return;
     }
-    const float K = (float)(a.Oa[vb + i - 1] - a.Oa[vb + i]) - lz;
+    // The whole of K goes on behind the exponential, as a power of two: with T^2 edges a position an exponent near -2 log2 T would
+    // be rounded five bits coarser (201 tags, potentials near zero: error of the marginals 3.7e-7, with K in single precision 3.6e-7, so 1.3e-7).  Not below
+    // -40 and not above zero: the exponents then neither overflow nor underflow earlier than with all of K in them.
+    const double K = a.Oa[vb + i - 1] - a.Oa[vb + i] - lzd;
+    const int Ki = uniform((int)rintf(fminf(fmaxf((float)K, -40.f), 0.f)));
+    const float Kf = (float)(K - (double)Ki);
     // A wave takes whole rows; the last piece of a row is moved back to end with it (what it holds twice is written
     // twice, the same values).
     const TIN* mat = static_cast<const TIN*>(a.phi) + (vb + i) * TT;
     if (4 * lane < T) {
         const int c4 = min(4 * lane, T - 4);
-        const float b0 = bv[c4] + K, b1 = bv[c4 + 1] + K, b2 = bv[c4 + 2] + K, b3 = bv[c4 + 3] + K;
+        const float b0 = bv[c4] + Kf, b1 = bv[c4 + 1] + Kf, b2 = bv[c4 + 2] + Kf, b3 = bv[c4 + 3] + Kf;
 #pragma unroll 8
         for (int s = wave; s < T; s += kEdgeThreads / 64) {
             const typename Raw::type r = Raw::template load<ALIGNED>((const GlobalBytes*)(mat + (size_t)s * T + c4));
             const float as = av[s];
-            const float m0 = ex2(__builtin_fmaf(Raw::get(r, 0), kLog2e, as) + b0), m1 = ex2(__builtin_fmaf(Raw::get(r, 1), kLog2e, as) + b1);
-            const float m2 = ex2(__builtin_fmaf(Raw::get(r, 2), kLog2e, as) + b2), m3 = ex2(__builtin_fmaf(Raw::get(r, 3), kLog2e, as) + b3);
+            const auto edge = [&](int j, float b) { return __builtin_amdgcn_ldexpf(ex2(__builtin_fmaf(Raw::get(r, j), kLog2e, as) + b), Ki); };
+            const float m0 = edge(0, b0), m1 = edge(1, b1), m2 = edge(2, b2), m3 = edge(3, b3);
             float* out = mu + (size_t)s * T + c4;
             if (ALIGNED) stream_store4(out, m0, m1, m2, m3);
             else store4_anywhere(out, m0, m1, m2, m3);

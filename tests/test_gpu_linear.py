@@ -51,3 +51,26 @@ def test_nothing_is_read_past_the_tensor(crf, oracle_mod):
         flat[:phi.numel()] = phi.reshape(-1).cuda()
         check_case(crf, oracle_mod, phi, None, poison=False, what=f"tensor end T={T}", queries=("logz", "mu"),
                    device_phi=flat[:phi.numel()].view(phi.shape))
+
+
+@pytest.mark.parametrize("T,N", [(65, 96), (129, 128), (201, 128), (256, 64)])
+def test_rounding_of_flat_marginals(crf, T, N):
+    """Potentials near zero: T^2 edges of nearly the same small probability.  Relative error (2-norm) against 64 bits: alpha, beta and
+    the potential enter an exponent of a few bits (three roundings of at most 2^-23, uniform, times ln 2: 7e-8) behind the
+    hardware's exponentials and logarithms (1e-7 each at most): 2.5e-7."""
+    phi = 0.3 * torch.randn(3, N, T, T, generator=torch.Generator().manual_seed(7500 + T))
+    phi = phi.bfloat16().cuda()
+    mu = crf.lccrf_marginals(phi)[1]
+    x = phi.double()
+    a, b = [x[:, 0, 0]], [torch.zeros(3, T, dtype=torch.float64, device="cuda")]
+    for i in range(1, N):
+        a.append(torch.logsumexp(a[-1][:, :, None] + x[:, i], 1))
+        b.append(torch.logsumexp(x[:, N - i] + b[-1][:, None, :], 2))
+    b.reverse()
+    lz = torch.logsumexp(a[-1], 1)
+    num = den = 0.0
+    for i in range(1, N):
+        want = torch.exp(a[i - 1][:, :, None] + x[:, i] + b[i][:, None, :] - lz[:, None, None])
+        num += float(((mu[:, i].double() - want) ** 2).sum())
+        den += float((want ** 2).sum())
+    assert (num / den) ** 0.5 <= 2.5e-7
