@@ -295,8 +295,12 @@ __device__ __forceinline__ void lane_chain_wave(const ChainArgs& a, const LaneJo
     const unsigned long long onmask = __builtin_amdgcn_ballot_w64(on);
     unsigned q = 0;
     const unsigned count = (unsigned)jb.count;
-    bool tail = false, carried = false;
-    float lv_carry = LCCRF_NEG_INF;  // the vector in logarithms, where the log-domain steps leave it to the tail
+    bool tail = false;
+    // The vector in logarithms (carried: they are the ones that count), where scaled single precision does not hold it: a vector the
+    // chain starts from with entries further apart than its exponents reach, and what the log-domain steps leave last.
+    // (An entry that has vanished may be the only one that a later position leaves a path through.)
+    bool carried = __builtin_amdgcn_ballot_w64(on && !(lv == LCCRF_NEG_INF || fabsf(lv) <= 120.f)) != 0;
+    float lv_carry = lane < T ? lv : LCCRF_NEG_INF;
     // The matrix of a step: the entries of this lane in the order its rotations consume them, and the shift.
     constexpr int NB = kSplit ? 1 : NBLK;  // blocks of sixteen source tags a lane sums over
     struct Tile {
@@ -334,7 +338,8 @@ __device__ __forceinline__ void lane_chain_wave(const ChainArgs& a, const LaneJo
     // (hard constraints throughout) the chain gives the producers up for good.
     // 0: go on (the matrix of step q is in `nxt`), 2: it did not come, 3: that was the last step, 4: give up.
     const auto slow_steps = [&](Tile& nxt) -> int {
-        float lvs = lane < T ? lg2(V) : LCCRF_NEG_INF;
+        float lvs = carried ? lv_carry : lane < T ? lg2(V) : LCCRF_NEG_INF;
+        carried = false;
         for (int n = 0;; ++n) {
             const int d = lane_log_step<NBLK, TIN, AL, PASS2>(a, jb, (int)q, lvs, O0 + (double)Oi, lz2, meet_only);
             Oi += d;
@@ -348,7 +353,11 @@ __device__ __forceinline__ void lane_chain_wave(const ChainArgs& a, const LaneJo
             sh.V[q % kLaneVecRing][u] = V;
             sh.VOi[q % kLaneVecRing] = (Oi << 1) | 1;
             lds_store_release(&sh.done, (int)q);
-            if (q == count) return 3;
+            if (q == count) {
+                lv_carry = lvs;
+                carried = true;
+                return 3;
+            }
             const bool faithful = !(lane < T) || lvs == LCCRF_NEG_INF || lvs >= -60.f;
             const bool inside = (unsigned)(Oi + (1 << 28)) < (1u << 29);
             if (__builtin_amdgcn_ballot_w64(!faithful) == 0 && inside) break;
@@ -421,7 +430,7 @@ __device__ __forceinline__ void lane_chain_wave(const ChainArgs& a, const LaneJo
     };
     Tile tA, tB;
     if (count > 0) {
-        int why = fetch(0, tA) ? 0 : 2;
+        int why = carried ? 1 : fetch(0, tA) ? 0 : 2;
         for (;;) {
             while (why == 0) {
                 why = step(tA, tB);

@@ -167,3 +167,35 @@ def test_auto_between_the_chain_wave_kernels_and_the_scan_on_long_chains(crf):
     assert A(crf.OP_LOGZ, 16, 1024, 64) == crf.ALGO_SEQUENTIAL_LANES
     assert A(crf.OP_MARGINALS, 16, 1024, 64) == crf.ALGO_SCAN
     assert A(crf.OP_MARGINALS, 32, 1024, 64) == crf.ALGO_SEQUENTIAL
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("T", (8, 16, 20, 32, 45, 48, 64, 100, 160))
+@pytest.mark.parametrize("N", (2, 3, 17, 34))
+def test_penalties_that_a_later_position_takes_back(crf, oracle_mod, T, N, dtype):
+    """Tag 5 costs 100 nats at a position, every other tag there 200 at the next one: the only entry that counts lies 144 bits below
+    the largest of its vector, further than single precision's exponents reach, wherever that vector is: where a chain starts, in
+    its middle, where it ends.  One sequence for every such position; the chain-wave kernels and what AUTO takes.
+    Marginals: exponents of up to 300 bits, each rounded at 2^-16, two of them added and times ln 2, 2.2e-5."""
+    phi, _ = workloads.random_case(9800 + 13 * T + N, N - 1, N, T, dtype=dtype)
+    for b in range(N - 1):
+        phi[b, b, :, 5] -= 100.0
+        other = torch.arange(T) != 5
+        phi[b, b + 1, other, :] -= 200.0
+    dphi = phi.cuda()
+    tags = torch.randint(0, T, (N - 1, N), generator=torch.Generator().manual_seed(T + N), dtype=torch.int32)
+    want, want_mu = oracle_mod.marginals(phi, None)
+    tol = 1e-5 * np.maximum(1.0, np.abs(want))
+    for algo in (crf.ALGO_AUTO, crf.ALGO_SEQUENTIAL_LANES):
+        if algo == crf.ALGO_SEQUENTIAL_LANES and T > 64:
+            continue
+        lz = crf.lccrf_log_partition(dphi, algo=algo).cpu().numpy()
+        assert np.all(np.abs(lz - want) <= tol), f"log Z, algo {algo}: {lz} vs {want}"
+        lz, mu = crf.lccrf_marginals(dphi, algo=algo)
+        assert np.all(np.abs(lz.cpu().numpy() - want) <= tol)
+        assert np.abs(mu.cpu().numpy() - want_mu).max() <= 3e-5, f"marginals, algo {algo}"
+    want_lp = oracle_mod.log_prob(phi, tags.numpy(), None)
+    lp = crf.lccrf_log_prob(dphi, tags.cuda()).cpu().numpy()
+    assert np.all(np.abs(lp - want_lp) <= 1e-5 * np.maximum(1.0, np.maximum(np.abs(want), np.abs(want_lp + want))))
+    got = crf.lccrf_sample_seeded(dphi, 7).cpu().numpy()
+    assert all(got[b, b] == 5 for b in range(N - 1)), "sample"
