@@ -303,8 +303,8 @@ inline bool lanes_pay_sum(int op, int B, int N, int T) {
 // T=32 71 / 120, T=16 54 / 66).  Against the scan (these kernels and the scan): up to 16 tags 12 + 0.245 N and
 // 38 + 0.00085 B N (B=128 N=64 T=16 31 / 36, N=256 80 / 66); 17 .. 32 tags 19 + 0.25 N + 0.0006 B N and 55 + 0.0021 B N, from about
 // 60000 positions on 40 + 0.003 B N (B=128 N=256 T=32 100 / 125, B=32 N=256 88 / 71, B=64 N=1024 330 / 249).  On very peaked
-// potentials these kernels take steps in the log domain (independent normal ones, B=128 N=128 T=32: deviation 12 84 / 96, 20
-// 258 / 100).
+// potentials these kernels take steps in the log domain (independent normal ones, B=128 N=128 T=32: deviation 12 66 / 94, 20
+// 131 / 99; a tag that is forbidden everywhere does not matter, N=256 120 / 163).
 inline bool lanes_pay_sample(int B, int N, int T) {
     if (!lccrf::lane_chains_supported(T) || B > current_device_cus() || N < 16) return false;
     if (!scan_pays_sample(B, N, T)) return true;

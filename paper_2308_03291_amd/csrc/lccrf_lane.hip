@@ -20,20 +20,30 @@
 // stores).  The waves meet only through words in LDS (ready / done / stop), never at a barrier.
 //
 // Vectors are kept as V 2^O with O = O0 + an integer: every matrix is shifted by an integer m, and after every
-// step the vector is rescaled by the power of two that brings tag 0's entry into [1/2, 1) (any accepted entry
+// step the vector is rescaled by the power of two that gives tag 0's entry the exponent kLaneHead (any accepted entry
 // serves as the reference; lane 0's comes without a reduction).  A step is accepted only if every sum lies in
-// [2^-60, 2^60] (kSumLo, kSumHi): then whatever underflowed in it is below 2^-66 of the sum it belongs to, for
-// every entry separately, so the loss does not compound from step to step.  A step that is not accepted (a
-// hard zero from a potential of -inf, entries of one matrix hundreds of bits apart) is taken by the chain wave
+// [2^-60, 2^60] (kSumLo, kSumHi): then whatever underflowed in it (an entry below 2^-126) is below 2^-46 of the sum it belongs to,
+// times what the heaviest tag has over tag 0, for every entry separately, so the loss does not compound from step to step.  First
+// passes over dense potentials also accept sums that are exact zeros (a tag that is forbidden there or everywhere), once one has
+// occurred: the producers say of every matrix whether its entries are all above 2^-80 or exact zeros, so that a zero can be told from
+// an underflow.  A step that is not accepted (entries of one matrix hundreds of bits apart) is taken by the chain wave
 // itself in the log domain, straight from memory, every log-sum-exp shifted by its own maximum, stores and
 // marginals included; the fast path resumes as soon as the vector is one that scaled single precision holds
-// faithfully again.  Eight such steps in a row, or a producer that does not deliver within the poll limit,
-// send the chain wave into the log-domain tail for the rest of its half chain; the producers see `stop` and
-// leave.
+// faithfully again.  Where such steps are frequent (second passes and structured potentials: eight in a row), or if a producer does
+// not deliver within the poll limit, the chain stays in the log domain for the rest of its half.  In a first pass over dense
+// potentials the producers then hand on logarithms (kLaneRaw); otherwise they see `stop` and leave.
+//
+// What that costs (us, so / the scan or one-wave kernels that log-probability and sampling took before these; in parentheses every
+// log-domain step read from memory by the chain wave): log-probability, N=256 B=128 T=32 with a tag forbidden everywhere 51 / 87 (286),
+// N=128 T=48 40 / 97 (196); independent normal potentials, N=128 B=128, T=32 deviation 12 33 / 52 (46), 16 63 / 51 (141), 20 64 / 51 (147),
+// T=48 12 48 / 63 (78), 20 113 / 87 (212), T=64 B=64 12 54 / 66 (81), 20 182 / 87 (286); sampling, T=32 N=256 with a forbidden tag 120 / 163
+// (551), T=32 N=128 12 66 / 94 (82), 20 131 / 99 (256), T=16 N=64 12 34 / 35 (37), 20 66 / 37 (88).  A log-domain step takes
+// 0.5 us (32 tags) from a producer's logarithms, 1.6 from memory; going over costs eight to sixteen of those.
 #include "lccrf_chain_args.h"
 #include "lccrf_device.h"
 #include "lccrf_launch.h"
 #include "lccrf_lds_flags.h"
+#include "lccrf_linear.h"
 
 #include <type_traits>
 
@@ -44,6 +54,8 @@ namespace lccrf {
 // 51.8 -> 47.9 us against seven); above, seven is what the register file holds at two waves a SIMD.
 constexpr int lane_waves(int nblk) { return nblk <= 2 ? 12 : 8; }
 constexpr int kLaneMaxProducers = 11;
+constexpr int kLaneHead = 15;           // what the entries of a vector are held above their value, in powers of two: tag 0's is
+                                        // brought into [1/2, 1), sums far below the largest stay in range (see lane_up)
 constexpr int kLaneVecRing = 16;        // published vectors kept (the chain leads a producer by fewer than that)
 
 template <int NBLK>
@@ -66,8 +78,10 @@ struct LaneShared {
                                     // if the step that produced it was taken in the log domain by the chain wave
     double O0;                      // offset of V_0
     float G[kLaneMaxProducers][64]; // per producer wave: the factors of the stored vector of the other chain
-    unsigned long long ready[S::RING];  // once the matrix of step q sits in slot q % RING: q + 1 in the high word,
-                                        // the matrix's shift (an integer) in the low word: one read brings both
+    unsigned long long ready[S::RING];  // once the matrix of step q sits in slot q % RING: q + 1 in the high word, twice
+                                        // the matrix's shift (an integer) in the low word, plus 1 if no entry but exact
+                                        // zeros lies below 2^-80: one read brings all
+    int raw;                        // from this step on producers hand on the logarithms themselves (INT_MAX: from none)
     int done;                       // steps the chain has accepted
     int stop;                       // first step of the log-domain tail (INT_MAX: none)
 };
@@ -87,9 +101,36 @@ __device__ __forceinline__ void fmac_rotations(float (&acc)[4], float a, const f
 }
 #undef LCCRF_FM
 
+// e[n] += a of the lane n places to the left in its row of sixteen
+__device__ __forceinline__ void add_rotations(float (&e)[16], float a) {
+    e[0] += a;
+#define LCCRF_AR(N) e[N] += dpp<0x120 + N>(a)
+    LCCRF_AR(1); LCCRF_AR(2); LCCRF_AR(3); LCCRF_AR(4); LCCRF_AR(5); LCCRF_AR(6); LCCRF_AR(7); LCCRF_AR(8);
+    LCCRF_AR(9); LCCRF_AR(10); LCCRF_AR(11); LCCRF_AR(12); LCCRF_AR(13); LCCRF_AR(14); LCCRF_AR(15);
+#undef LCCRF_AR
+}
+
 __device__ __forceinline__ float lane_value(float x, int src) {  // src uniform over the wave
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), src));
 }
+
+__device__ __forceinline__ float min3_raw(float a, float b, float c) {
+    float r;
+    asm("v_min3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
+}
+
+constexpr int kLaneRaw = (int)0x80000000;  // in place of a matrix's shift: its entries are base-2 logarithms
+// Whether the producers of this instantiation ever hand on such matrices: in first passes over dense potentials.
+template <typename TIN, bool AL>
+struct LaneSource;
+template <typename TIN, bool AL, bool PASS2>
+constexpr bool lane_takes_raw() { return !PASS2 && !LaneSource<TIN, AL>::kStruct; }
+constexpr bool lane_hands_raw(int nblk) { return nblk <= 3; }  // (above 48 tags the producers have no registers for it)
+
+// Between an entry's logarithm, near zero where it counts, and the entry as it is held.
+__device__ __forceinline__ float lane_up(float l) { return __builtin_amdgcn_ldexpf(ex2(l), kLaneHead); }
+__device__ __forceinline__ float lane_log(float v) { return lg2(__builtin_amdgcn_ldexpf(v, -kLaneHead)); }
 
 // What a chain is working on (uniform over the workgroup).
 struct LaneJob {
@@ -149,15 +190,30 @@ struct LaneSource<StructF, AL> {
     }
 };
 
+// What ends a log-domain step of a first pass: r, the logarithms of the new vector (this lane's tag u; -inf without a tag), less an
+// integer shift, which is returned, into lv, and the stores of its position (by the lanes for which `mine`).
+__device__ __forceinline__ int lane_log_end(const ChainArgs& a, const LaneJob& jb, int i, float r, int u, bool mine, float& lv, double O,
+                                            int meet_only) {
+    const int T = a.T;
+    const float d = fminf(fmaxf(ceilf(finite_or_zero(xor_max<1, 64>(r))), -0x1p30f), 0x1p30f);  // (clamped as in lane_log_step)
+    lv = r - d;
+    const int pos = jb.dir == 0 ? i : i - 1;
+    if (!meet_only || pos == jb.h) {
+        const size_t at = (size_t)jb.b * a.N + pos;
+        if (mine && u < T) (jb.dir == 0 ? a.ua : a.ub)[at * T + u] = lv;
+        if ((threadIdx.x & 63) == 0) (jb.dir == 0 ? a.Oa : a.Ob)[at] = O + (double)d;
+    }
+    return __builtin_amdgcn_readfirstlane((int)d);
+}
+
 // One position in the log domain by the chain wave alone, straight from memory: every log-sum-exp shifted by
 // its own maximum.  lv: the vector that enters step q, base-2 logarithms, lane = tag (-inf from T on), O its
 // offset; on return lv is the result less the integer shift that is returned (its maximum then lies in (-1, 0]).
 // Writes what the step owes to memory: the marginals of its position (second pass), the stored vector (first).
-template <int NBLK, typename TIN, bool AL, bool PASS2>
+template <typename TIN, bool AL, bool PASS2>
 __device__ __forceinline__ int lane_log_step(const ChainArgs& a, const LaneJob& jb, int q, float& lv, double O,
                                              double lz2, int meet_only) {
-    const int lane = threadIdx.x & 63, N = a.N, b = jb.b;
-    int T = a.T;
+    const int lane = threadIdx.x & 63, T = a.T, N = a.N, b = jb.b;
     const size_t TT = (size_t)T * T;
     const LaneSource<TIN, AL> src(a, b);
     const size_t vb = (size_t)b * N;
@@ -173,57 +229,20 @@ __device__ __forceinline__ int lane_log_step(const ChainArgs& a, const LaneJob& 
         K = (float)(O + (jb.dir == 0 ? a.Ob : a.Oa)[vp] - lz2);
         mu_i = a.mu + (vb + i) * TT;
     }
-    float mx = LCCRF_NEG_INF, sum = 0.f;
-    if constexpr (!PASS2 && !LaneSource<TIN, AL>::kStruct) {
-        // All T potentials of a lane are requested before the first is used: one trip to memory a step instead of one for every few
-        // sources (B=128 N=128 T=48, normal potentials of deviation 12, log-probability 198 -> 79 us).  (The second pass and structured potentials have no registers for it.)
-        asm("" : "+s"(T));  // (nothing that follows from it is kept in registers around the steps that are not taken here)
-        constexpr int U = LaneShape<NBLK>::U;
-        float x[U];
-        if constexpr (AL) {
-            if (jb.dir == 0) {
-#pragma unroll
-                for (int v = 0; v < U; ++v) x[v] = src.at(i, v < T ? v : T - 1, me);
-            } else {
-#pragma unroll
-                for (int v = 0; v < U; v += 4) {  // four columns of this lane's row at a time
-                    const int t0 = v < T ? v : T - 4;
-                    float f[4], o[4];
-                    src.fixed_part(me * T + t0, t0, f);
-                    src.piece(i, me * T + t0, t0, f, o);
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) x[v + j] = o[j];
-                }
-            }
-        } else {
-#pragma unroll
-            for (int v = 0; v < U; ++v) {
-                const int w = v < T ? v : T - 1;
-                x[v] = jb.dir == 0 ? src.at(i, w, me) : src.at(i, me, w);
-            }
-        }
-#pragma unroll
-        for (int v = 0; v < U; ++v) {
-            x[v] = v < T ? lane_value(lv, v) + x[v] * kLog2e : LCCRF_NEG_INF;  // (rounded as the second pass rounds it)
-            mx = fmaxf(mx, x[v]);
-        }
-        const float g = finite_or_zero(mx);
-#pragma unroll
-        for (int v = 0; v < U; ++v) sum += ex2(x[v] - g);
-    } else {
-        for (int v = 0; v < T; ++v) {
-            const float x = lane_value(lv, v) + (jb.dir == 0 ? src.at(i, v, me) : src.at(i, me, v)) * kLog2e;
-            mx = fmaxf(mx, x);
-        }
-        const float g = finite_or_zero(mx);
-        for (int v = 0; v < T; ++v) {
-            const float x = lane_value(lv, v) + (jb.dir == 0 ? src.at(i, v, me) : src.at(i, me, v)) * kLog2e;
-            sum += ex2(x - g);
-            if (PASS2 && on) {
-                const float m = ex2(x + other + K);
-                if (jb.dir == 0) mu_i[(size_t)v * T + lane] = m;
-                else mu_i[(size_t)lane * T + v] = m;
-            }
+    float mx = LCCRF_NEG_INF;
+    for (int v = 0; v < T; ++v) {
+        const float x = lane_value(lv, v) + (jb.dir == 0 ? src.at(i, v, me) : src.at(i, me, v)) * kLog2e;
+        mx = fmaxf(mx, x);
+    }
+    const float g = finite_or_zero(mx);
+    float sum = 0.f;
+    for (int v = 0; v < T; ++v) {
+        const float x = lane_value(lv, v) + (jb.dir == 0 ? src.at(i, v, me) : src.at(i, me, v)) * kLog2e;
+        sum += ex2(x - g);
+        if (PASS2 && on) {
+            const float m = ex2(x + other + K);
+            if (jb.dir == 0) mu_i[(size_t)v * T + lane] = m;
+            else mu_i[(size_t)lane * T + v] = m;
         }
     }
     const float r = on ? mx + lg2(sum) : LCCRF_NEG_INF;
@@ -241,10 +260,71 @@ __device__ __forceinline__ int lane_log_step(const ChainArgs& a, const LaneJob& 
 }
 
 // The log-domain tail: steps q0 .. count - 1 of the job.  Returns with lv / O the last vector.
-template <int NBLK, typename TIN, bool AL, bool PASS2>
+template <typename TIN, bool AL, bool PASS2>
 __device__ __forceinline__ void lane_log_tail(const ChainArgs& a, const LaneJob& jb, int q0, float& lv, double& O,
                                               double lz2, int meet_only) {
-    for (int q = q0; q < jb.count; ++q) O += (double)lane_log_step<NBLK, TIN, AL, PASS2>(a, jb, q, lv, O, lz2, meet_only);
+    for (int q = q0; q < jb.count; ++q) O += (double)lane_log_step<TIN, AL, PASS2>(a, jb, q, lv, O, lz2, meet_only);
+}
+
+// The same of a first pass over dense potentials.  Up to 32 tags the lanes hold the vector C times, each copy taking the C-th part of
+// the sources, whose logarithms come through LDS (`buf`, which only this wave uses).  All of a lane's potentials are requested
+// before the first is used, one trip to memory a step.  A lane's P sources are `start` + 4 p + k, or for C = 1 min(4 p, T - 4) + k: the last
+// ones are moved back to end with the matrix, so that no load leaves it, and what is then held twice is left out.
+template <int NBLK, typename TIN, bool AL>
+__device__ __forceinline__ int lane_log_dense(const ChainArgs& a, const LaneJob& jb, float* buf, int q, float& lv, double O, int meet_only) {
+    constexpr int C = NBLK == 1 ? 4 : NBLK == 2 ? 2 : 1, P = LaneShape<NBLK>::U / C, SPAN = 64 / C;
+    const int lane = threadIdx.x & 63, N = a.N;
+    int T = a.T;
+    asm volatile("" : "+s"(T));  // (nothing that follows from it is kept in registers around the steps that are not taken here)
+    const int u = lane % SPAN, c = lane / SPAN;
+    const bool on = u < T;
+    const int me = on ? u : 0;
+    const int start = C == 1 ? 0 : min(c * P, T - P), skip = c * P - start;  // (C > 1: T >= P)
+    const size_t vb = (size_t)jb.b * N;
+    const int i = jb.first + q * jb.sdir;
+    if (lane < SPAN) buf[lane] = lv;
+    __builtin_amdgcn_wave_barrier();
+    auto mat = (const GlobalBytes*)(static_cast<const TIN*>(a.phi) + (vb + i) * T * T);
+    float y[P];
+    if (jb.dir == 0) {
+        const unsigned voff = (unsigned)(start * T + me) * (unsigned)sizeof(TIN);
+#pragma unroll
+        for (int p = 0; p < P / 4; ++p) {
+            auto at = mat + (unsigned)((C == 1 ? min(4 * p, T - 4) : 4 * p) * T) * (unsigned)sizeof(TIN);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                asm volatile("" : "+s"(at));
+                const TIN x = *(LCCRF_GLOBAL(TIN))(at + voff);
+                y[4 * p + k] = Elem<TIN>::get(&x);
+                at += (unsigned)T * (unsigned)sizeof(TIN);
+            }
+        }
+    } else {
+        const unsigned voff = (unsigned)(me * T + start) * (unsigned)sizeof(TIN);
+#pragma unroll
+        for (int p = 0; p < P / 4; ++p) {
+            const auto x = RawPiece<TIN>::template load<AL>(mat + (unsigned)(C == 1 ? min(4 * p, T - 4) : 4 * p) * (unsigned)sizeof(TIN) + voff);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) y[4 * p + k] = RawPiece<TIN>::get(x, k);
+        }
+    }
+    float mx = LCCRF_NEG_INF;
+#pragma unroll
+    for (int p = 0; p < P / 4; ++p)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int s = C == 1 ? min(4 * p, T - 4) : 4 * p;
+            const float x = buf[start + s + k] + y[4 * p + k] * kLog2e;
+            y[4 * p + k] = (C == 1 ? s + k >= 4 * p : s + k >= skip) ? x : LCCRF_NEG_INF;
+            mx = fmaxf(mx, y[4 * p + k]);
+        }
+    mx = xor_max<SPAN, 64>(mx);
+    const float g = finite_or_zero(mx);
+    float part[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int j = 0; j < P; ++j) part[j & 3] += ex2(y[j] - g);
+    const float sum = xor_sum<SPAN, 64>((part[0] + part[1]) + (part[2] + part[3]));
+    return lane_log_end(a, jb, i, on ? mx + lg2(sum) : LCCRF_NEG_INF, u, c == 0, lv, O, meet_only);
 }
 
 // The chain wave.
@@ -284,7 +364,7 @@ __device__ __forceinline__ void lane_chain_wave(const ChainArgs& a, const LaneJo
         lv = on ? (jb.dir == 0 ? a.ua : a.ub)[(vb + jb.h) * T + me] : LCCRF_NEG_INF;
         O = (jb.dir == 0 ? a.Oa : a.Ob)[vb + jb.h];
     }
-    float V = ex2(lv);  // 0 for lanes past T
+    float V = lane_up(lv);  // 0 for lanes past T
     const double O0 = O;
     int Oi = 0;  // O = O0 + Oi: the shifts of the matrices and the rescales so far
     if (copy == 0) sh.V[0][u] = V;
@@ -299,7 +379,7 @@ __device__ __forceinline__ void lane_chain_wave(const ChainArgs& a, const LaneJo
     // The vector in logarithms (carried: they are the ones that count), where scaled single precision does not hold it: a vector the
     // chain starts from with entries further apart than its exponents reach, and what the log-domain steps leave last.
     // (An entry that has vanished may be the only one that a later position leaves a path through.)
-    bool carried = __builtin_amdgcn_ballot_w64(on && !(lv == LCCRF_NEG_INF || fabsf(lv) <= 120.f)) != 0;
+    bool carried = __builtin_amdgcn_ballot_w64(on && !(lv == LCCRF_NEG_INF || fabsf(lv) <= 110.f)) != 0;
     float lv_carry = lane < T ? lv : LCCRF_NEG_INF;
     // The matrix of a step: the entries of this lane in the order its rotations consume them, and the shift.
     constexpr int NB = kSplit ? 1 : NBLK;  // blocks of sixteen source tags a lane sums over
@@ -330,6 +410,22 @@ __device__ __forceinline__ void lane_chain_wave(const ChainArgs& a, const LaneJo
         read_tile(step, t, word);
         return true;
     };
+    // the blocks of sixteen tags of a vector, each in every row of sixteen lanes that meets it
+    const auto blocks_of = [&](float x, float (&Ab)[4]) __attribute__((always_inline)) {
+        if constexpr (NBLK == 1) {
+            Ab[0] = x;
+        } else {
+            const auto p = __builtin_amdgcn_permlane16_swap(__float_as_int(x), __float_as_int(x), false, false);
+            if constexpr (NBLK == 2) {
+                Ab[0] = copy == 0 ? __int_as_float(p[0]) : __int_as_float(p[1]);  // block `copy` in both rows of the copy
+            } else {
+                const auto y = __builtin_amdgcn_permlane32_swap(p[0], p[0], false, false);
+                const auto w = __builtin_amdgcn_permlane32_swap(p[1], p[1], false, false);
+                Ab[0] = __int_as_float(y[0]); Ab[2] = __int_as_float(y[1]);
+                Ab[1] = __int_as_float(w[0]); Ab[3] = __int_as_float(w[1]);
+            }
+        }
+    };
     // Steps that the fast path does not accept (a sum out of range: entries of one matrix hundreds of bits
     // apart, or a hard zero) are taken in the log domain by this wave itself, one position at a time, until the
     // vector is again one that scaled single precision holds faithfully (every entry an exact zero or within
@@ -338,17 +434,17 @@ __device__ __forceinline__ void lane_chain_wave(const ChainArgs& a, const LaneJo
     // (hard constraints throughout) the chain gives the producers up for good.
     // 0: go on (the matrix of step q is in `nxt`), 2: it did not come, 3: that was the last step, 4: give up.
     const auto slow_steps = [&](Tile& nxt) -> int {
-        float lvs = carried ? lv_carry : lane < T ? lg2(V) : LCCRF_NEG_INF;
+        float lvs = carried ? lv_carry : lane < T ? lane_log(V) : LCCRF_NEG_INF;
         carried = false;
         for (int n = 0;; ++n) {
-            const int d = lane_log_step<NBLK, TIN, AL, PASS2>(a, jb, (int)q, lvs, O0 + (double)Oi, lz2, meet_only);
+            const int d = lane_log_step<TIN, AL, PASS2>(a, jb, (int)q, lvs, O0 + (double)Oi, lz2, meet_only);
             Oi += d;
             float lall = lvs;  // every copy of the vector gets its tag's value
             if constexpr (kSplit) {
                 const auto h = __builtin_amdgcn_permlane32_swap(__float_as_int(lvs), __float_as_int(lvs), false, false);
                 lall = __int_as_float(h[0]);
             }
-            V = on ? ex2(lall) : 0.f;
+            V = on ? lane_up(lall) : 0.f;
             ++q;
             sh.V[q % kLaneVecRing][u] = V;
             sh.VOi[q % kLaneVecRing] = (Oi << 1) | 1;
@@ -369,6 +465,95 @@ __device__ __forceinline__ void lane_chain_wave(const ChainArgs& a, const LaneJo
         }
         return fetch(q, nxt) ? 0 : 2;
     };
+    // The same for first passes over dense potentials, which do not give the producers up: where more than a third of the
+    // steps are such for a while (kOften; independent normal potentials of a deviation of fifteen and more), the rest of the chain is taken in the log domain, and the producers are told to hand on the logarithms of the matrices, in the same slots
+    // and the same order: a step adds the rotated vector to them, takes the maximum and adds up the exponentials.  (Matrices that were
+    // exponentiated already are taken from memory by this wave.)  `alone`: no producer is waited for any more.
+    // 0: go on (the matrix of step q is in `nxt`), 2: it did not come, 3: that was the last step, everything is stored.
+    constexpr bool kRaw = lane_takes_raw<TIN, AL, PASS2>();
+    constexpr int kOften = NBLK <= 2 ? 16 : 24;
+    int slow = 0, slow_at = 0;  // two for every log-domain step, less the other steps since, and where the last one led
+    const auto log_steps = [&](Tile& nxt, bool alone) -> int {
+        if constexpr (kRaw) {
+            lv = u < T ? (carried ? lv_carry : lane_log(V)) : LCCRF_NEG_INF;
+            if constexpr (kSplit) {
+                const auto h = __builtin_amdgcn_permlane32_swap(__float_as_int(lv), __float_as_int(lv), false, false);
+                lv = __int_as_float(h[0]);
+            }
+            carried = false;
+            O = O0 + (double)Oi;
+            bool rest = alone;
+            if (alone) lds_store_release(&sh.stop, (int)q);
+            for (;;) {
+                unsigned long long word = 0;
+                if (rest && !alone) {
+                    int spins = 0;
+                    while ((unsigned)__builtin_amdgcn_readfirstlane((int)((word = lds_load_acquire(&sh.ready[q % S::RING])) >> 32)) < q + 1)
+                        if (++spins > poll_limit) {
+                            alone = true;
+                            word = 0;
+                            lds_store_release(&sh.stop, (int)q);
+                            break;
+                        }
+                }
+                int d;
+                if (__builtin_amdgcn_readfirstlane((int)(unsigned)word) == kLaneRaw) {
+                    Tile t;
+                    read_entries(q, t);
+                    float Ab[4];
+                    blocks_of(lv, Ab);
+                    float top[4] = {LCCRF_NEG_INF, LCCRF_NEG_INF, LCCRF_NEG_INF, LCCRF_NEG_INF};
+#pragma unroll
+                    for (int bk = 0; bk < NB; ++bk) add_rotations(t.e[bk], Ab[bk]);
+#pragma unroll
+                    for (int bk = 0; bk < NB; ++bk)
+#pragma unroll
+                        for (int m = 0; m < 16; m += 2) top[(m >> 1) & 3] = max3_raw(top[(m >> 1) & 3], t.e[bk][m], t.e[bk][m + 1]);
+                    float mx = max3_raw(max3_raw(top[0], top[1], top[2]), top[3], top[3]);
+                    if constexpr (kSplit) mx = xor_max<32, 64>(mx);
+                    const float g = finite_or_zero(mx);
+                    float part[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int bk = 0; bk < NB; ++bk)
+#pragma unroll
+                        for (int m = 0; m < 16; ++m) part[m & 3] += ex2(t.e[bk][m] - g);
+                    float sum = (part[0] + part[1]) + (part[2] + part[3]);
+                    if constexpr (kSplit) sum = xor_sum<32, 64>(sum);
+                    d = lane_log_end(a, jb, jb.first + (int)q * jb.sdir, on ? mx + lg2(sum) : LCCRF_NEG_INF, u, copy == 0, lv, O, meet_only);
+                } else {
+                    d = lane_log_dense<NBLK, TIN, AL>(a, jb, sh.G[0], (int)q, lv, O, meet_only);
+                    lv = on ? lv : LCCRF_NEG_INF;
+                }
+                O += (double)d;
+                ++q;
+                if (!rest) {
+                    Oi += d;
+                    V = lane_up(lv);
+                    sh.V[q % kLaneVecRing][u] = V;
+                    sh.VOi[q % kLaneVecRing] = (Oi << 1) | 1;
+                    lds_store_release(&sh.done, (int)q);
+                    if (q == count) return 3;
+                    const bool faithful = lv == LCCRF_NEG_INF || lv >= -110.f;
+                    const bool inside = (unsigned)(Oi + (1 << 28)) < (1u << 29);
+                    slow = max(slow - ((int)q - slow_at - 1), 0) + 2;
+                    slow_at = (int)q;
+                    if (__builtin_amdgcn_ballot_w64(!faithful) == 0 && inside && slow < kOften) return fetch(q, nxt) ? 0 : 2;
+                    if (!inside || slow >= kOften) {
+                        rest = true;
+                        alone = !lane_hands_raw(NBLK);
+                        lds_store_release(alone ? &sh.stop : &sh.raw, (int)q);
+                    }
+                } else {
+                    if (!alone) {
+                        sh.VOi[q % kLaneVecRing] = 1;  // (the stores of this step are done)
+                        lds_store_release(&sh.done, (int)q);
+                    }
+                    if (q == count) return 3;
+                }
+            }
+        }
+        return 3;
+    };
     // One step from the matrix in `cur`; meanwhile the matrix of the next step is read into `nxt`, whether it is
     // there or not, so that it comes back under the products: its flag is looked at before (LDS executes a wave's
     // instructions in order: a flag that was up when it was read means that the reads behind it found the matrix);
@@ -378,24 +563,15 @@ __device__ __forceinline__ void lane_chain_wave(const ChainArgs& a, const LaneJo
     // 3: that was the last step.
     // (Flags and offsets are written by every lane, the same value to the same address: cheaper for a lone
     // wave than masking the write down to one lane.)
-    const auto step = [&](const Tile& cur, Tile& nxt) __attribute__((always_inline)) -> int {
+    // ZEROS: a sum that is zero because every one of its terms is (a tag that is forbidden there or everywhere) is accepted too.  The loop
+    // goes over to that form at the first step that the other one does not accept.
+    const auto step = [&](const Tile& cur, Tile& nxt, auto zeros) __attribute__((always_inline)) -> int {
+        constexpr bool ZEROS = decltype(zeros)::value;
         unsigned long long word_next = lds_load_acquire(&sh.ready[(q + 1) % S::RING]);
         read_entries(q + 1, nxt);
         __builtin_amdgcn_sched_barrier(0);
         float Ab[4];
-        if constexpr (NBLK == 1) {
-            Ab[0] = V;
-        } else {
-            const auto p = __builtin_amdgcn_permlane16_swap(__float_as_int(V), __float_as_int(V), false, false);
-            if constexpr (NBLK == 2) {
-                Ab[0] = copy == 0 ? __int_as_float(p[0]) : __int_as_float(p[1]);  // block `copy` in both rows of the copy
-            } else {
-                const auto x = __builtin_amdgcn_permlane32_swap(p[0], p[0], false, false);
-                const auto w = __builtin_amdgcn_permlane32_swap(p[1], p[1], false, false);
-                Ab[0] = __int_as_float(x[0]); Ab[2] = __int_as_float(x[1]);
-                Ab[1] = __int_as_float(w[0]); Ab[3] = __int_as_float(w[1]);
-            }
-        }
+        blocks_of(V, Ab);
         float acc[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int bk = 0; bk < NB; ++bk) fmac_rotations(acc, Ab[bk], cur.e[bk]);
@@ -406,19 +582,29 @@ __device__ __forceinline__ void lane_chain_wave(const ChainArgs& a, const LaneJo
             const auto h = __builtin_amdgcn_permlane32_swap(__float_as_int(Ssum), __float_as_int(Ssum), false, false);
             Ssum = __int_as_float(h[0]) + __int_as_float(h[1]);
         }
-        const int Onew = Oi + cur.m;
+        const int Onew = Oi + (cur.m >> 1);
         // accepted: every sum in range, and the integer offset far from overflow
         // (S in [kSumLo, kSumHi] as one unsigned comparison of its bits: positive floats order like their bit patterns,
         // negative ones and NaNs fall outside; the comparison leaves the lane mask in scalar registers directly)
         const unsigned long long inr = __builtin_amdgcn_uicmp(__float_as_uint(Ssum) - __float_as_uint(kSumLo),
                                                               __float_as_uint(kSumHi) - __float_as_uint(kSumLo), 37 /* unsigned <= */);
-        if ((inr & onmask) != onmask || (unsigned)(Onew + (1 << 28)) >= (1u << 29)) return 1;
+        unsigned ref = 0;  // the lane whose entry is the reference
+        if ((inr & onmask) != onmask || (unsigned)(Onew + (1 << 28)) >= (1u << 29)) {
+            if constexpr (!ZEROS) return 1;
+            // (no entry of the matrix and none of the vector but exact zeros can have taken part in an underflow)
+            const unsigned long long zero = __builtin_amdgcn_ballot_w64(Ssum == 0.f), some = inr & onmask;
+            if (!(cur.m & 1) || ((inr | zero) & onmask) != onmask || some == 0 || (unsigned)(Onew + (1 << 28)) >= (1u << 29) ||
+                __builtin_amdgcn_ballot_w64(V > 0.f && V < 0x1p-60f) != 0)
+                return 1;
+            ref = (unsigned)__builtin_ctzll(some);
+        }
         // Rescale by the power of two that brings tag 0 into [1/2, 1): any accepted entry serves as the
         // reference (what bounds the vector is the range test above, not where its largest entry lies), and
         // lane 0's comes without a reduction over the lanes.  Lanes without a tag hold an exact zero.
-        const int k = __builtin_amdgcn_readfirstlane(__builtin_amdgcn_frexp_expf(Ssum));
-        V = __builtin_amdgcn_ldexpf(Ssum, -k);
-        Oi = Onew + k;
+        const int kx = __builtin_amdgcn_frexp_expf(Ssum);
+        const int k = ZEROS ? __builtin_amdgcn_readlane(kx, ref) : __builtin_amdgcn_readfirstlane(kx);
+        V = __builtin_amdgcn_ldexpf(Ssum, kLaneHead - k);
+        Oi = Onew + k - kLaneHead;
         ++q;
         sh.V[q % kLaneVecRing][u] = V;
         sh.VOi[q % kLaneVecRing] = Oi << 1;
@@ -431,23 +617,40 @@ __device__ __forceinline__ void lane_chain_wave(const ChainArgs& a, const LaneJo
     Tile tA, tB;
     if (count > 0) {
         int why = carried ? 1 : fetch(0, tA) ? 0 : 2;
+        bool zeros = false;
         for (;;) {
-            while (why == 0) {
-                why = step(tA, tB);
-                if (why != 0) break;
-                why = step(tB, tA);
+            if (!kRaw || !zeros)
+                while (why == 0) {
+                    why = step(tA, tB, std::false_type{});
+                    if (why != 0) break;
+                    why = step(tB, tA, std::false_type{});
+                }
+            if constexpr (kRaw) {
+                if (why == 1 && !zeros && !carried) why = fetch(q, tA) ? 0 : 2;  // (the same matrix, which the slot still holds)
+                zeros = true;
+                while (why == 0) {
+                    why = step(tA, tB, std::true_type{});
+                    if (why != 0) break;
+                    why = step(tB, tA, std::true_type{});
+                }
             }
-            if (why != 1) break;
-            why = slow_steps(tA);  // (outside the loop of the fast path, which stays as tight as it was)
+            if constexpr (kRaw) {
+                if (why == 3) break;
+                why = log_steps(tA, why == 2);
+                if (why == 3) return;
+            } else {
+                if (why != 1) break;
+                why = slow_steps(tA);  // (outside the loop of the fast path, which stays as tight as it was)
+            }
         }
         tail = why != 3;
     }
     O = O0 + (double)Oi;
     on = lane < T;  // from here on lane = tag again (the first copy)
-    lv = !on ? LCCRF_NEG_INF : carried ? lv_carry : lg2(V);
+    lv = !on ? LCCRF_NEG_INF : carried ? lv_carry : lane_log(V);
     if (tail) {
         if (lane == 0) lds_store_release(&sh.stop, (int)q);
-        lane_log_tail<NBLK, TIN, AL, PASS2>(a, jb, (int)q, lv, O, lz2, meet_only);
+        if constexpr (!kRaw) lane_log_tail<TIN, AL, PASS2>(a, jb, (int)q, lv, O, lz2, meet_only);
     } else if (!PASS2 && meet_only && count > 0) {
         // a log-partition call keeps the vectors of the meeting position only: the last of this chain
         if (on) (jb.dir == 0 ? a.ua : a.ub)[(vb + jb.h) * T + lane] = lv;
@@ -466,6 +669,7 @@ __device__ __forceinline__ void lane_producer_wave(const ChainArgs& a, const Lan
                                                    double lz2, int meet_only, int poll_limit) {
     using S = LaneShape<NBLK>;
     constexpr int NG = S::NG, PF = S::PF, W = lane_waves(NBLK) - 1;
+    constexpr bool kRaw = lane_takes_raw<TIN, AL, PASS2>(), kHandsRaw = kRaw && lane_hands_raw(NBLK);
     const int lane = threadIdx.x & 63, T = a.T, N = a.N, b = jb.b;
     const size_t TT = (size_t)T * T;
     const size_t vb = (size_t)b * N;
@@ -530,21 +734,71 @@ __device__ __forceinline__ void lane_producer_wave(const ChainArgs& a, const Lan
         const int q = w + j * W;
         const int i = jb.first + q * jb.sdir;
         const int slot = q % S::RING;
-        // the shift of this matrix: the smallest integer at or above its largest entry (base 2)
-        float mxr = LCCRF_NEG_INF;
+        const auto raw_now = [&]() { return kHandsRaw && __builtin_amdgcn_readfirstlane(lds_load_acquire(&sh.raw)) <= q; };
+        const auto logarithms = [&]() {
 #pragma unroll
-        for (int m = 0; m < NG; ++m) {
-            const float gm = max3_raw(fmaxf(x[p][m][0], x[p][m][1]), x[p][m][2], x[p][m][3]);
-            mxr = fmaxf(mxr, (valid >> m) & 1 ? gm : LCCRF_NEG_INF);
+            for (int m = 0; m < NG; ++m)
+#pragma unroll
+                for (int k = 0; k < 4; ++k) x[p][m][k] *= kLog2e;
+        };
+        const bool raw = raw_now();
+        float sh_m = 0.f;
+        int word = kLaneRaw;
+        if (raw) {
+            logarithms();
+        } else {
+            // the shift of this matrix: the smallest integer at or above its largest entry (base 2)
+            float mxr = LCCRF_NEG_INF;
+#pragma unroll
+            for (int m = 0; m < NG; ++m) {
+                const float gm = max3_raw(fmaxf(x[p][m][0], x[p][m][1]), x[p][m][2], x[p][m][3]);
+                mxr = fmaxf(mxr, (valid >> m) & 1 ? gm : LCCRF_NEG_INF);
+            }
+            // (clamped far inside the range of an int: beyond, the chain's offset check sends the step to the tail)
+            sh_m = fminf(fmaxf(ceilf(finite_or_zero(xor_max<1, 64>(mxr)) * kLog2e), -0x1p29f), 0x1p29f);
+            float least[2] = {0.f, 0.f};
+#pragma unroll
+            for (int m = 0; m < NG; ++m)
+#pragma unroll
+                for (int k = 0; k < 4; ++k) x[p][m][k] = __builtin_fmaf(x[p][m][k], kLog2e, -sh_m);
+            word = (int)sh_m * 2;
+            if constexpr (kRaw) {
+                // whether no entry but exact zeros lies below 2^-80
+#pragma unroll
+                for (int m = 0; m < NG; ++m) {
+                    least[0] = min3_raw(least[0], x[p][m][0], x[p][m][1]);
+                    least[1] = min3_raw(least[1], x[p][m][2], x[p][m][3]);
+                }
+                word |= 1;
+                if (__builtin_amdgcn_ballot_w64(fminf(least[0], least[1]) < -80.f) != 0) {
+                    // (by the bits: read as unsigned numbers less those of -inf, the finite numbers below -80 are the largest)
+                    unsigned low = 0;
+#pragma unroll
+                    for (int m = 0; m < NG; ++m)
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) low = max(low, __float_as_uint(x[p][m][k]) - 0xff800000u);
+                    if (__builtin_amdgcn_ballot_w64(low > 0xc2a00000u - 0xff800000u) != 0) word &= ~1;
+                }
+            }
+#pragma unroll
+            for (int m = 0; m < NG; ++m)
+#pragma unroll
+                for (int k = 0; k < 4; ++k) x[p][m][k] = ex2(x[p][m][k]);
         }
-        // (clamped far inside the range of an int: beyond, the chain's offset check sends the step to the tail)
-        const float sh_m = fminf(fmaxf(ceilf(finite_or_zero(xor_max<1, 64>(mxr)) * kLog2e), -0x1p30f), 0x1p30f);
-#pragma unroll
-        for (int m = 0; m < NG; ++m)
-#pragma unroll
-            for (int k = 0; k < 4; ++k) x[p][m][k] = ex2(__builtin_fmaf(x[p][m][k], kLog2e, -sh_m));
         // the slot is free once the chain has accepted step q - RING
         if (!wait_for(&sh.done, q - S::RING + 1, q)) return false;
+        if constexpr (kHandsRaw) {
+            if (!raw && raw_now()) {  // (once in a chain: the exponentials were in vain)
+                word = kLaneRaw;
+                const int i = jb.first + q * jb.sdir;
+#pragma unroll
+                for (int m = 0; m < NG; ++m) {
+                    src.piece(i, goff[m], gcol[m], fixed[0], x[p][m]);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                logarithms();
+            }
+        }
         float* Es = &sh.E[slot][0][0];
 #pragma unroll
         for (int m = 0; m < NG; ++m)
@@ -553,14 +807,14 @@ __device__ __forceinline__ void lane_producer_wave(const ChainArgs& a, const Lan
                 for (int k = 0; k < 4; ++k) Es[laddr[m][k]] = x[p][m][k];
             }
         if (lane == 0)
-            lds_store_release(&sh.ready[slot], ((unsigned long long)(unsigned)(q + 1) << 32) | (unsigned)(int)sh_m);
+            lds_store_release(&sh.ready[slot], ((unsigned long long)(unsigned)(q + 1) << 32) | (unsigned)word);
         if (PASS2) {
             // the chain has accepted step q: V_q and this matrix make the marginals of position i
             if (!wait_for(&sh.done, q + 1, q)) return false;
             if (sh.VOi[(q + 1) % kLaneVecRing] & 1) return true;  // (the chain wave took this step itself)
             const double Oq = sh.O0 + (double)(sh.VOi[q % kLaneVecRing] >> 1);
             const float c = (float)(Oq + (double)sh_m + oo[p] - lz2);
-            sh.G[w][lane] = lane < T ? ex2(aux[p] + c) : 0.f;
+            sh.G[w][lane] = lane < T ? __builtin_amdgcn_ldexpf(ex2(aux[p] + c), -kLaneHead) : 0.f;
             const float* rowf = jb.dir == 0 ? sh.V[q % kLaneVecRing] : sh.G[w];
             const float* colf = jb.dir == 0 ? sh.G[w] : sh.V[q % kLaneVecRing];
             float* mu_i = a.mu + (vb + i) * TT;
@@ -581,7 +835,7 @@ __device__ __forceinline__ void lane_producer_wave(const ChainArgs& a, const Lan
             const int word = sh.VOi[(q + 1) % kLaneVecRing];
             if (word & 1) return true;  // (the chain wave took this step itself, stores included)
             const float v = sh.V[(q + 1) % kLaneVecRing][lane];
-            if (lane < T) (jb.dir == 0 ? a.ua : a.ub)[(vb + pos) * T + lane] = lg2(v);
+            if (lane < T) (jb.dir == 0 ? a.ua : a.ub)[(vb + pos) * T + lane] = lane_log(v);
             if (lane == 0) (jb.dir == 0 ? a.Oa : a.Ob)[vb + pos] = sh.O0 + (double)(word >> 1);
         }
         return true;
@@ -666,7 +920,7 @@ __global__ __launch_bounds__(64 * lane_waves(NBLK)) void lane_chain_kernel(Chain
     }
     // flags, and zeros where no producer ever writes (source tags past T)
     if (tid < S::RING) sh.ready[tid] = 0ull;
-    if (tid == 0) { sh.done = 0; sh.stop = 0x7fffffff; }
+    if (tid == 0) { sh.done = 0; sh.stop = 0x7fffffff; sh.raw = 0x7fffffff; }
     if (T != S::U) {
         float* Ez = &sh.E[0][0][0];
         for (int k = tid; k < S::RING * (S::U + 1) * S::RS; k += 64 * kLaneWaves) Ez[k] = 0.f;

@@ -199,3 +199,55 @@ def test_penalties_that_a_later_position_takes_back(crf, oracle_mod, T, N, dtype
     assert np.all(np.abs(lp - want_lp) <= 1e-5 * np.maximum(1.0, np.maximum(np.abs(want), np.abs(want_lp + want))))
     got = crf.lccrf_sample_seeded(dphi, 7).cpu().numpy()
     assert all(got[b, b] == 5 for b in range(N - 1)), "sample"
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("T", (8, 9, 13, 16, 17, 19, 20, 30, 32, 33, 45, 48, 52, 64))
+def test_first_pass_exact_zeros_and_log_domain_for_good(crf, oracle_mod, T, dtype):
+    """First passes that accept exact zeros (a tag forbidden everywhere, from a position on, as a predecessor too), that have to tell
+    them from underflows (edges 100 nats below the others beside a forbidden tag), and that go over to the log domain for the rest of a
+    chain (normal potentials of deviation 20 and 12), the producers' logarithms and the matrices taken from memory included.  Log Z by
+    the chain-wave kernels, log-probability and a sample by what AUTO takes."""
+    N, ninf = 75, float("-inf")
+    phi, _ = workloads.random_case(9900 + T, 8, N, T, scale=1.0)
+    phi[0, :, :, T // 2] = ninf
+    phi[1, :, :, 0] = ninf
+    phi[1, 1:, 0, :] = ninf
+    phi[2, N // 3:, :, T - 1] = ninf
+    phi[3, :, :, 1] = ninf
+    phi[3, :, 2, :] -= 100.0
+    phi[3, ::5, :, 3] -= 100.0
+    phi[4] *= 20.0
+    phi[5] *= 12.0
+    phi[6] *= 20.0
+    phi[6, 40:60, 1, :] = ninf
+    phi[7, 20:, :, 1:5] = ninf
+    phi = phi.bfloat16() if dtype == "bf16" else phi
+    lens = torch.tensor([N, N - 1, N, N, N, N, N - 2, N], dtype=torch.int32)
+    check_case(crf, oracle_mod, phi, lens, poison=False, algo=crf.ALGO_SEQUENTIAL_LANES, what=f"zeros T={T} {dtype}", queries=("logz",))
+    tags = crf.lccrf_argmax(phi.cuda(), lens.cuda())[1].clamp_min(0)
+    got = crf.lccrf_log_prob(phi.cuda(), tags, lens.cuda()).cpu().numpy()
+    want = oracle_mod.log_prob(phi, tags.cpu().numpy(), lens.numpy())
+    lz = oracle_mod.log_partition(phi, lens.numpy())
+    assert np.all(np.abs(got - want) <= 1e-5 * np.maximum(1.0, np.maximum(np.abs(lz), np.abs(want + lz)))), f"{got} vs {want}"
+    u = torch.rand(8, N, generator=torch.Generator().manual_seed(T))
+    sample = crf.lccrf_sample(phi.cuda(), u.cuda(), lens.cuda()).cpu().numpy()
+    path, margin = oracle_mod.sample(phi, u.numpy(), lens.numpy())
+    clear = margin > 2e-4
+    assert all(np.array_equal(sample[b], path[b]) for b in range(8) if clear[b])
+    assert np.isfinite(oracle_mod.log_prob(phi, sample, lens.numpy())).all()
+
+
+@pytest.mark.parametrize("T", (16, 32, 48))
+def test_log_domain_for_good_without_the_producers(crf, oracle_mod, T):
+    """The wait made to expire at once: the rest of every chain from memory, entered from accepted and from refused steps.  (First
+    passes: the exponents of the second pass, which is another one, reach 200 bits at deviation 20, rounded at 2^-17.)"""
+    phi, _ = workloads.random_case(9950 + T, 4, 40, T)
+    phi[1] *= 20.0
+    phi[2, :, :, 3] = float("-inf")
+    lens = torch.tensor([40, 40, 39, 2], dtype=torch.int32)
+    crf.set_lane_poll_limit(0)
+    try:
+        check_case(crf, oracle_mod, phi, lens, poison=False, algo=crf.ALGO_SEQUENTIAL_LANES, what=f"no producers T={T}", queries=("logz",))
+    finally:
+        crf.set_lane_poll_limit(-1)
