@@ -42,6 +42,13 @@ int lccrf_stream_probe(const void* in, void* out, size_t bytes, int workgroups, 
 size_t lccrf_stream_probe_bytes(size_t bytes, int workgroups);
 
 /*
+ * 1 where the sequential schedule of lccrf_marginals, in place of a second pass that writes the marginals as the chains go, runs
+ * the chains on to the far ends without writing (a second read of phi) and writes every edge in a kernel of its own (a third).
+ * 0 elsewhere, or without a device.
+ */
+int lccrf_marginals_by_edges(lccrf_dtype dt, int B, int T);
+
+/*
  * The largest row of a T x T matrix that any thread of a first pass in scaled probabilities (33 .. 256 tags) takes, by the
  * kernels' own arithmetic over every thread and item of the instance the dispatch chooses: at most T - 1, or the pass
  * reads past the matrix.  Host only; -1 for other tag counts.

@@ -833,6 +833,9 @@ int lccrf_argmax_structured(const float* emit, const float* trans, const int32_t
     return e == hipSuccess ? LCCRF_OK : LCCRF_ELAUNCH;
 }
 
+int lccrf_marginals_by_edges(lccrf_dtype dt, int B, int T) {
+    return B >= 1 && dtype_ok(dt) && lccrf::marginals_by_edges(dt, B, T, current_device_cus()) ? 1 : 0;
+}
 int lccrf_first_pass_largest_row(int T) { return lccrf::first_pass_largest_row(T); }
 
 const char* lccrf_strerror(int code) {

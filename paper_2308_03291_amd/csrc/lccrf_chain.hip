@@ -833,14 +833,16 @@ __global__ __launch_bounds__(G::W, 4) void linear_half_kernel(ChainArgs a) {  //
     }
     int steps = 0;
     LogBlocks blocks;
+    const float x = tid < T ? (dir == 1 && !a.extend ? Elem<TIN>::get(phib + tid) : v) : 0.f;
+    blocks.hopeless = a.exact_only || (n > 0 && linear_hopeless(phib + (size_t)first * T * T, T, dir == 1, x == LCCRF_NEG_INF, v));
     for (;;) {
         const int before = steps;
-        if (!a.exact_only) {
+        if (!blocks.hopeless) {
             if (dir == 0) steps = linear_run<LG, TIN, ALIGNED, false>(lin, {phib, T, first, n, uout, Oout}, v, steps, O);
             else steps = linear_run<LG, TIN, ALIGNED, true>(lin, {phib, T, first, n, uout, Oout}, v, steps, O);
         }
         if (steps >= n) break;
-        const int m = a.exact_only ? n : blocks.next(steps - before, n - steps);
+        const int m = blocks.next(steps - before, n - steps);
         const LogStepsResult r = chain_log_steps<G, TIN, ALIGNED>(a.phi, a.ua, a.ub, a.Oa, a.Ob, a.B, N, T, a.exact_only, b, dir,
                                                                   dir == 0 ? first + steps : first - steps, m, v, O);
         v = r.v;
@@ -1076,15 +1078,24 @@ static hipError_t launch_linear_half(const ChainArgs& a, hipStream_t st) {
     return hipErrorInvalidValue;
 }
 
+// Whether the second halves of few chains take their steps without writing, and one more kernel writes the marginals with the
+// whole chip.  It moves a third more bytes, so it pays while two workgroups a sequence leave enough of the chip idle.  us, so /
+// second pass with the chains.  136 tags, N=128, single precision B=64 545 / 593, B=96 712 / 655, bfloat16 B=96 538 / 590,
+// B=128 653 / 626; 201 tags, N=64, B=48 470 / 535, B=64 575 / 581, B=96 794 / 658, bfloat16 B=64 468 / 562; 256 tags, N=48, B=32
+// 462 / 472, B=48 568 / 510, bfloat16 B=32 339 / 386, B=48 431 / 426.  N=128: 72 tags, single precision B=64 204 / 279, B=128
+// 315 / 313, bfloat16 B=128 240 / 301; 100 tags, single precision B=64 294 / 331, B=128 501 / 421, bfloat16 B=64 251 / 311, B=128
+// 403 / 354 (128 tags have the paired second pass).  Up to 127 tags the line lies below where they cross: where hard constraints
+// send the chains to the log-domain steps, two launches of them must not cost more than what is saved (N=128 B=64, two tags
+// forbidden everywhere: 80 tags 462 / 466, 100 tags 539 / 541; 136 tags B=32 1218 / 1419).
+bool marginals_by_edges(int dtype, int B, int T, int cus) {
+    if (cus <= 0 || T <= 64 || T == 128 || T > 256) return false;
+    const int limit = T < 128 ? (dtype == 0 ? 16 : 24) : (dtype == 0 ? 40 : 48);
+    return (long long)B * T <= (long long)cus * limit;
+}
+
 template <typename G, typename TIN, bool ALIGNED, int PF1, int PF2>
 static hipError_t launch_geo(int op, ChainArgs a, hipStream_t st, hipEvent_t between, const PairPlan& pair) {
-    // Few chains of 65 .. 127 tags: marginals as launch_stream makes them (us, so / second pass with the chains, N=128:
-    // 72 tags, single precision B=64 204 / 279, B=128 315 / 313, bfloat16 B=128 240 / 301; 100 tags, single precision
-    // B=64 294 / 331, B=128 501 / 421, bfloat16 B=64 251 / 311, B=128 403 / 354; 128 tags have
-    // the paired second pass).  The line lies below where they cross: where hard constraints send the chains to the log-domain
-    // steps, two launches of them must not cost more than what is saved (80 tags, B=64, two tags forbidden everywhere 478 / 451).
-    const bool spread = op == 1 && a.chunk <= 0 && a.T > 64 && a.T < 128 && pair.cus > 0 &&
-                        (long long)a.B * a.T <= (long long)pair.cus * (pair.dtype == 0 ? 16 : 24);
+    const bool spread = op == 1 && a.chunk <= 0 && a.T > 64 && marginals_by_edges(pair.dtype, a.B, a.T, pair.cus);
     // Otherwise the first pass runs in scaled probabilities for bfloat16 rows off the 8-byte grid, which linear_run widens
     // where they are used and not where they are loaded (B=64 N=256 T=99 log-partition 292 -> 169 us, B=1024 N=64 T=45 160 -> 92);
     // elsewhere the turned steps are as quick or quicker at these sizes (single precision B=64 N=256 T=100 185 / 178,
@@ -1174,7 +1185,8 @@ static hipError_t launch_wave(int op, int dtype, const ChainArgs& a, hipStream_t
 }
 
 // Both passes in row batches (128 < T <= 256).  cus: compute units of the device (0: unknown).
-static hipError_t launch_stream(int op, int dtype, const ChainArgs& a, hipStream_t st, hipEvent_t between, int cus = 0) {
+static hipError_t launch_stream(int op, int dtype, ChainArgs a, hipStream_t st, hipEvent_t between, int cus = 0) {
+    a.spread = op == 1 && marginals_by_edges(dtype, a.B, a.T, cus) ? 1 : 0;
     hipError_t e = launch_stream_pass(false, dtype, a, st);
     if (e != hipSuccess) return e;
     if (between) {
@@ -1186,12 +1198,7 @@ static hipError_t launch_stream(int op, int dtype, const ChainArgs& a, hipStream
         hipLaunchKernelGGL(logz_combine_kernel, dim3(a.B), dim3(64), 0, st, a);
         return hipGetLastError();
     }
-    // Few chains: their second halves take their steps without writing, and one more kernel writes the marginals with the
-    // whole chip.  It moves a third more bytes, so it pays while two workgroups a sequence leave enough of the chip idle (us,
-    // so / second pass with the chains: 136 tags, N=128, single precision B=64 545 / 593, B=96 712 / 655, bfloat16 B=96
-    // 538 / 590, B=128 653 / 626; 201 tags, N=64, B=48 470 / 535, B=64 575 / 581, B=96 794 / 658, bfloat16 B=64 468 / 562;
-    // 256 tags, N=48, B=32 462 / 472, B=48 568 / 510, bfloat16 B=32 339 / 386, B=48 431 / 426).
-    if (cus > 0 && (long long)a.B * a.T <= (long long)cus * (dtype == 0 ? 40 : 48)) {
+    if (a.spread) {
         ChainArgs rest = a;
         rest.extend = 1;
         e = launch_stream_pass(false, dtype, rest, st);

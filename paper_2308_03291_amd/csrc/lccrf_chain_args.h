@@ -54,9 +54,10 @@ struct ChainArgs {
     // 1: the forward chain runs over the whole span and stores every alpha; no backward chain
     // (first pass of sampling, whose backward sweep needs alpha everywhere).
     int full_forward;
-    // 1: a first pass over the other halves (row-batch kernels, whole sequences): the chains start from the vectors that
+    // 1: a first pass over the other halves (scaled steps, whole sequences): the chains start from the vectors that
     // an ordinary first pass has stored for the meeting position and run on to the far ends, vectors stored.
     int extend;
+    int spread;  // 1: both of these first passes, with the edge kernel behind them (row-batch kernels: scaled steps whatever the batch)
 };
 
 // The stretch of positions one pair of workgroups handles: all of a sequence, or one chunk.

@@ -151,6 +151,8 @@ hipError_t launch_cross(bool kl, int dtype, const void* phi_p, const void* phi_q
 // logZq null: the chains of phi_q run in the same launch (where cross_runs_both says so).
 bool cross_runs_both(int N, int T);
 
+// Whether the sequential schedule makes marginals from the vectors of every position, edge by edge (lccrf_chain.hip).
+bool marginals_by_edges(int dtype, int B, int T, int cus);
 // The largest row of a matrix that a first pass in scaled probabilities takes at 33 .. 256 tags (lccrf_linear.h; -1: none there).
 int first_pass_largest_row(int T);
 

@@ -465,11 +465,9 @@ __device__ __attribute__((noinline)) LogStepsResult stream_log_steps(const void*
 
 // Pass 1: both half chains, vectors stored.  The steps are taken in scaled probabilities (linear_run) as long as they are
 // accepted, and from one that is not, a block of positions in the log domain (LogBlocks).
-// ITEMS: rows a thread holds of a matrix there, linear_instance(1024, T).
+// ITEMS: rows a thread holds of a matrix there, linear_instance(1024, T); 0: every step in the log domain.
 template <typename TIN, bool ALIGNED, int ITEMS>
 __global__ __launch_bounds__(1024) void stream_half_kernel(ChainArgs a) {
-    using LG = LinGeo<16, 256, ITEMS>;
-    __shared__ LinSmem<LG> lin;
     const int tid = threadIdx.x;
     const int dir = blockIdx.x & 1, b = blockIdx.x >> 1;
     const int N = a.N, T = a.T;
@@ -493,21 +491,38 @@ __global__ __launch_bounds__(1024) void stream_half_kernel(ChainArgs a) {
     } else if (tid < T) {
         v = dir == 0 ? Elem<TIN>::get(phib + tid) * kLog2e : 0.f;
     }
-    int steps = 0;
-    LogBlocks blocks;
-    for (;;) {
-        const int before = steps;
-        if (!a.exact_only) {
-            if (dir == 0) steps = linear_run<LG, TIN, ALIGNED, false>(lin, {phib, T, first, n, uout, Oout}, v, steps, O);
-            else steps = linear_run<LG, TIN, ALIGNED, true>(lin, {phib, T, first, n, uout, Oout}, v, steps, O);
+    if constexpr (ITEMS > 0) {
+        using LG = LinGeo<16, 256, ITEMS>;
+        __shared__ LinSmem<LG> lin;
+        int steps = 0;
+        LogBlocks blocks;
+        const float x = tid < T ? (dir == 1 && !a.extend ? Elem<TIN>::get(phib + tid) : v) : 0.f;
+        blocks.hopeless = n > 0 && linear_hopeless(phib + (size_t)first * T * T, T, dir == 1, x == LCCRF_NEG_INF, v);
+        for (;;) {
+            const int before = steps;
+            if (!blocks.hopeless) {
+                if (dir == 0) steps = linear_run<LG, TIN, ALIGNED, false>(lin, {phib, T, first, n, uout, Oout}, v, steps, O);
+                else steps = linear_run<LG, TIN, ALIGNED, true>(lin, {phib, T, first, n, uout, Oout}, v, steps, O);
+            }
+            if (steps >= n) break;
+            const int m = blocks.next(steps - before, n - steps);
+            const LogStepsResult r = stream_log_steps<TIN, ALIGNED>(a.phi, a.ua, a.ub, a.Oa, a.Ob, a.B, N, T, a.exact_only, b, dir,
+                                                                    dir == 0 ? first + steps : first - steps, m, v, O);
+            v = r.v;
+            O = r.O;
+            steps += m;
         }
-        if (steps >= n) break;
-        const int m = a.exact_only ? n : blocks.next(steps - before, n - steps);
-        const LogStepsResult r = stream_log_steps<TIN, ALIGNED>(a.phi, a.ua, a.ub, a.Oa, a.Ob, a.B, N, T, a.exact_only, b, dir,
-                                                                dir == 0 ? first + steps : first - steps, m, v, O);
-        v = r.v;
-        O = r.O;
-        steps += m;
+    } else {
+        __shared__ ChainSmem<SG> sm;
+        smem_init<SG>(sm, tid);
+        __syncthreads();
+        publish_columns<SG>(sm, 0, tid, v);
+        __syncthreads();
+        int buf = 0;
+        stream_walk<TIN, ALIGNED, false>(sm, a, b, dir, first, n, 0.0, true, buf, O);
+        const float d = read_shift<SG>(sm, buf);
+        O += (double)d;
+        v = tid < T ? sm.rvec[buf][tid] - d : LCCRF_NEG_INF;
     }
     if (tid < T) uout[(size_t)end * T + tid] = v;
     if (tid == 0) Oout[end] = O;
@@ -962,13 +977,28 @@ hipError_t launch_stream_expect(int mode, int dtype, const ChainArgs& a, hipStre
     return aligned ? launch_stream_expect_t<uint16_t, true>(mode, a, st) : launch_stream_expect_t<uint16_t, false>(mode, a, st);
 }
 
+// Whether a first pass takes scaled steps.  Their time a position grows with the rows a thread holds, they draw 5.2 TB/s at most; the
+// log-domain steps take 3.5 us (three batches of rows, up to 192 tags) or 5.2 us and draw 6.3 TB/s.  Log-partition, us, log-domain /
+// scaled, N=64 (N=16 .. 26 in the same order of lines behind the semicolon: tensors that the memory-side cache holds).  Single precision: 136
+// tags B=32 105 / 58, B=96 113 / 106, B=128 120 / 130, B=256 238 / 244; 150 tags B=256 299 / 284; 160 tags B=32 108 / 72, B=64 114 / 120,
+// B=128 133 / 168; 40 / 35 at B=64; 180 tags B=32 117 / 81, B=64 126 / 138; 192 tags B=32 113 / 120, B=64 123 / 151; 200 tags B=64
+// 181 / 161, B=96 194 / 193, B=128 216 / 249; 51 / 38 at B=64; 212 tags B=64 192 / 185, B=96 207 / 218; 220 tags B=32 176 / 180, B=64
+// 196 / 210; 256 tags B=32 189 / 207, B=64 209 / 250; 52 / 44 at B=32.  bfloat16: 180 tags B=128 125 / 126, B=256 249 / 241; 192 tags B=96
+// 125 / 123, B=256 218 / 239; 201 tags B=256 341 / 259; 212 tags B=256 227 / 228; 220 tags B=64 150 / 145, B=128 162 / 193; 232 tags B=64
+// 151 / 150, B=128 163 / 206; 256 tags B=32 148 / 139, B=64 150 / 175.
+static bool scaled_pays(bool single, int B, int T) {
+    if (single) return T <= 152 || B <= (T <= 180 ? 48 : T <= 192 ? 24 : T <= 212 ? 80 : 24);
+    return T <= 212 || B <= (T <= 240 ? 64 : 32);
+}
 template <typename TIN, bool ALIGNED>
 static hipError_t launch_stream_half(const ChainArgs& a, hipStream_t st) {
     const dim3 grid(2 * a.B), block(1024);
-    switch (linear_instance(1024, a.T)) {  // 5 (129 tags) .. 16 (256 tags)
+    const int items = linear_instance(1024, a.T);
+    if (items < 5) return hipErrorInvalidValue;
+    switch (!a.exact_only && (a.spread || scaled_pays(sizeof(TIN) == 4, a.B, a.T)) ? items : 0) {  // 5 (129 tags) .. 16 (256 tags)
 #define LCCRF_STREAM_HALF(I) case I: hipLaunchKernelGGL((stream_half_kernel<TIN, ALIGNED, I>), grid, block, 0, st, a); break
         LCCRF_STREAM_HALF(5); LCCRF_STREAM_HALF(6); LCCRF_STREAM_HALF(7); LCCRF_STREAM_HALF(8); LCCRF_STREAM_HALF(9); LCCRF_STREAM_HALF(10);
-        LCCRF_STREAM_HALF(11); LCCRF_STREAM_HALF(12); LCCRF_STREAM_HALF(14); LCCRF_STREAM_HALF(16);
+        LCCRF_STREAM_HALF(11); LCCRF_STREAM_HALF(12); LCCRF_STREAM_HALF(14); LCCRF_STREAM_HALF(16); LCCRF_STREAM_HALF(0);
         default: return hipErrorInvalidValue;
     }
 #undef LCCRF_STREAM_HALF

@@ -42,6 +42,37 @@ def test_last_matrix_of_full_length_sequences(crf, oracle_mod, T, dtype):
     check_case(crf, oracle_mod, phi, None, what=f"linear, full length, T={T} {dtype}", queries=("logz", "mu"))
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("T", [45, 67, 99, 136, 201])
+def test_tags_that_chains_cannot_start_with(crf, oracle_mod, T, dtype):
+    """A tag forbidden everywhere (as a successor, as a predecessor too), one that is forbidden at the start only, one whose only way in
+    comes from a tag that is itself unreachable, several at once: whether a chain tries scaled steps is decided by such tags."""
+    N, ninf = 17, float("-inf")
+    phi, _ = workloads.random_case(7600 + T, 7, N, T, dtype=dtype)
+    phi[0, :, :, 7] = ninf
+    phi[1, :, :, 7] = ninf
+    phi[1, 1:, 7, :] = ninf
+    phi[2, 0, :, 7:12] = ninf
+    phi[3, 0, :, 3:5] = ninf
+    phi[3, 1, :, 3] = ninf
+    phi[3, 1, 4, 3] = 0.0
+    phi[4, :, :, T - 1] = ninf
+    phi[4, 0, :, 0] = ninf
+    phi[5, :, :, 2:] = ninf
+    lens = torch.tensor([N, N, N, N, N - 1, N, 2], dtype=torch.int32)
+    check_case(crf, oracle_mod, phi, lens, what=f"no start T={T} {dtype}", queries=("logz", "mu"), algo=crf.ALGO_SEQUENTIAL)
+
+
+@pytest.mark.parametrize("T,B,dtype", [(152, 49, "f32"), (153, 48, "f32"), (153, 49, "f32"), (180, 49, "f32"), (181, 24, "f32"), (192, 25, "f32"),
+                                       (193, 80, "f32"), (212, 81, "f32"), (213, 24, "f32"), (256, 25, "f32"), (213, 64, "bf16"),
+                                       (240, 65, "bf16"), (241, 32, "bf16"), (256, 33, "bf16")])
+def test_either_side_of_the_batch_that_scaled_steps_pay_for(crf, oracle_mod, T, B, dtype):
+    phi, _ = workloads.random_case(7700 + T + B, B, 4, T, scale=1.5, dtype=dtype)
+    lens = torch.randint(0, 5, (B,), generator=torch.Generator().manual_seed(T)).to(torch.int32)
+    lens[-1] = 4
+    check_case(crf, oracle_mod, phi, lens, what=f"batch T={T} B={B} {dtype}", queries=("logz",))
+
+
 def test_nothing_is_read_past_the_tensor(crf, oracle_mod):
     """NaN right behind the potentials (T odd: rows end anywhere).  A value that is read there and meets an exact zero only
     sends the chain to its log-domain steps: what the kernels may read is asserted on the host (test_abi_host.py)."""
