@@ -366,11 +366,17 @@ def main():
     else:
         # dominant kernel: second pass = one read of phi + one write of mu over the positions in the chains.
         # With few sequences and T = 128 that pass is the two-workgroups-per-chain kernel (plus two
-        # few-microsecond helpers the event interval also covers: mailbox reset, exact fix-up launch).
+        # few-microsecond helpers the event interval also covers: mailbox reset, exact fix-up launch); with few sequences of
+        # 65 .. 256 tags otherwise the chains run on to the far ends first (one read of phi) and a kernel of its own reads it
+        # again and writes every edge: both in this interval.
         alg_bytes = eff_pots * (esz + 4)
         paired = w.T == 128 and 4 * w.B <= torch.cuda.get_device_properties(dev).multi_processor_count
+        by_edges = bool(crf.load_library().lccrf_marginals_by_edges(crf.LCCRF_F32 if esz == 4 else crf.LCCRF_BF16, w.B, w.T))
         kernel = "pair_marginal_kernel" if paired else ("wave_marginal_kernel" if w.T <= 32 else
                                                         "stream_marginal_kernel" if w.T > 128 else "chain_marginal_kernel")
+        if by_edges and algo in (crf.ALGO_AUTO, crf.ALGO_SEQUENTIAL):
+            kernel = f"{'stream' if w.T > 128 else 'linear'}_half_kernel (second halves) + edge_marginal_kernel"
+            alg_bytes = eff_pots * (2 * esz + 4)
     achieved = alg_bytes / (pass2_avg * 1e-3) / 1e9
     roofline = {"bound": "hbm", "kernel": kernel,
                 "achieved": achieved, "peak": HBM_PEAK_GBPS,
@@ -378,7 +384,8 @@ def main():
                 # counters cannot be read inside the run: this figure comes from the committed rocprofv3 --pmc summary
                 "traffic": committed_traffic(w.key), "traffic_source": f"profiles/marginals_{w.key}_traffic.txt (committed)",
                 "algorithmic_bytes_per_launch": alg_bytes, "avg_launch_ms": pass2_avg,
-                "first_pass": {"kernel": "lane_chain_kernel (first pass)" if lanes_taken else "chain_half_kernel",
+                "first_pass": {"kernel": "lane_chain_kernel (first pass)" if lanes_taken else
+                               "stream_half_kernel" if w.T > 128 else "chain_half_kernel",
                                "algorithmic_bytes": eff_pots * esz,
                                "avg_ms": sum(pass1) / len(pass1),
                                "frac": eff_pots * esz / (sum(pass1) / len(pass1) * 1e-3) / 1e9 / HBM_PEAK_GBPS},
