@@ -236,6 +236,7 @@ __global__ __launch_bounds__(64 * WAVES) void semi_forward_kernel(SemiArgs a) {
 // A step of 32 tags, K = 8 costs 0.84 us (log-domain steps 2.0): two LDS round trips and the barrier on the dependent path, then
 // the next block's exponentials, which wait for the newest offset.
 constexpr int kSemiHead = 24;
+constexpr int kSemiLookFirst = 256;  // batches above the number of compute units
 constexpr float kSemiLo = 0x1p-40f, kSemiHi = 0x1p40f;
 template <int WAVES, int LPR>
 static size_t semi_linear_bytes(int K) {  // vec[K + 2][4 LPR], partial sums [2][WAVES][4 LPR], offsets [K + 1]
@@ -283,16 +284,21 @@ __global__ __launch_bounds__(64 * WAVES) void semi_linear_kernel(SemiArgs a) {
         asm("" : "+s"(base));
         return Raw::template load<ALIGNED>(base + voff[m]);
     };
+    // A tag that the sequence cannot start with is an exact zero in the first vector, which is not accepted.  With many sequences
+    // it is looked for before the first blocks are fetched: others hide the wait, and nothing is read twice.
+    float big = lane < T ? Elem<TIN>::get(phib + lane) * kLog2e : LCCRF_NEG_INF;
+    bool rejected = a.B > kSemiLookFirst && __any(lane < T && big == LCCRF_NEG_INF);
+    if (!rejected) {
 #pragma unroll
-    for (int p = 0; p < PH; ++p)
+        for (int p = 0; p < PH; ++p)
 #pragma unroll
-        for (int m = 0; m < ITEMS; ++m) raw[p][m] = fetch(p, m);
+            for (int m = 0; m < ITEMS; ++m) raw[p][m] = fetch(p, m);
+    }
 
     for (int k = tid; k < (KR + 1) * VS; k += W) vec[k] = 0.f;
     for (int k = tid; k < 2 * WAVES * VS; k += W) part[k] = 0.f;
     for (int k = tid; k < KR; k += W) Oslot[k] = 0;
     // position 0 grows by the largest entry of its first row (looked at by every wave for itself)
-    float big = lane < T ? Elem<TIN>::get(phib + lane) * kLog2e : LCCRF_NEG_INF;
     big = xor_max<1, 64>(big);
     int c_cur = uniform((int)fminf(fmaxf(ceilf(finite_or_zero(big)), -0x1p20f), 0x1p20f)) - kSemiHead, grew = c_cur + kSemiHead;
     __syncthreads();
@@ -315,7 +321,7 @@ __global__ __launch_bounds__(64 * WAVES) void semi_linear_kernel(SemiArgs a) {
             raw[p][m] = fetch(i + PH, m);
         }
     };
-    prepare(0, 0, c_cur, 0);
+    if (!rejected) prepare(0, 0, c_cur, 0);
 
     // Which column of the wave's sums a lane ends up with: the swaps leave accumulator 2 (lane >> 5) + ((lane >> 4) & 1) there.
     const int jcol = 2 * (lane >> 5) + ((lane >> 4) & 1);
@@ -324,7 +330,6 @@ __global__ __launch_bounds__(64 * WAVES) void semi_linear_kernel(SemiArgs a) {
     const int me = min(lane, T - 1), rslot = me < last ? me : last + me - (T - 4);
     int i = 0, cur = K;   // position, slot of the vector in front of it
     long long Oi = 0;     // its offset
-    bool rejected = false;
     float V = 0.f;        // lane = tag
     const auto step = [&](int next) __attribute__((always_inline)) -> bool {  // false: the run is over
         const int c_next = max(min(grew, 1 << 20), -(1 << 20)) - kSemiHead;
@@ -374,7 +379,8 @@ __global__ __launch_bounds__(64 * WAVES) void semi_linear_kernel(SemiArgs a) {
         prepare(i, next, c_next, (int)Oi);
         return true;
     };
-    if constexpr (PH == 1) {
+    if (rejected) {
+    } else if constexpr (PH == 1) {
         while (step(0)) {}
     } else if constexpr (PH == 2) {
         while (step(1) && step(0)) {}
@@ -454,8 +460,9 @@ static bool launch_semi_items(int dtype, const SemiArgs& a, hipStream_t st, hipE
 // The scaled-probability kernel where it serves the shape: up to eight rows of the (K T) x T block a thread.  false: it does not.
 // Few rows a wave are worth more than few waves (us, N=256 B=1, so / log-domain steps: 32 tags K=8 214 (four waves of eight rows:
 // 289) / 513, K=2 132 / 333; 16 tags K=8 134 / 392; 64 tags K=8 553 / 2044; 8 tags K=2 166 / 321; N=64 B=1024: 32 tags K=8 355 / 383,
-// 20 tags K=3 59 / 162).  A tag that is forbidden everywhere sends a sequence to the log-domain steps at its first position:
-// what was read for the first positions is then read again (32 tags K=8: N=256 B=1 415, N=64 B=1024 408).
+// 20 tags K=3 55 / 151).  A tag that is forbidden everywhere sends a sequence to the log-domain steps at its first position; in
+// large batches before anything is fetched (32 tags K=8 N=64, so / log-domain steps alone: B=1024 384 / 391 (blocks fetched first:
+// 393), B=300 167 / 176, B=1 108 / 127; 20 tags K=3 B=1024 152 / 151).
 template <int LPR>
 static bool launch_semi_linear(int dtype, const SemiArgs& a, hipStream_t st, hipError_t& e) {
     const long long rows = (long long)a.K * a.T;

@@ -131,3 +131,18 @@ def test_semi_markov_steps_that_leave_the_scaled_range(crf, oracle_mod, T, K, dt
     phi[4, 9] = float("-inf")
     phi[4, 10:, 1:] = float("-inf")
     _check(crf, oracle_mod, phi.to(dtype), lens, f"T={T} K={K} {dtype}")
+
+
+@pytest.mark.parametrize("T,K", [(9, 3), (8, 16), (20, 3), (32, 8), (64, 8)])
+def test_a_large_batch_looks_for_a_forbidden_first_tag(crf, oracle_mod, T, K):
+    """More sequences than compute units: those that a tag cannot start are handed to the log-domain steps before anything is
+    fetched, beside others that are not, one that ends at once, an empty one and one without any path."""
+    B, N = 259, 5
+    phi, _ = workloads.semi_markov_case(8600 + 67 * T + K, B, N, K, T, scale=1.0)
+    lens = torch.full((B,), N, dtype=torch.int32)
+    phi[0::3, :, :, :, T - 1] = float("-inf")  # a tag that is forbidden everywhere
+    phi[1::6, 0, 0, 0, 0] = float("-inf")      # one that cannot start
+    phi[3, 0, 0, 0] = float("-inf")            # nothing that ends at the first position, so only longer segments start
+    phi[5] = float("-inf")
+    lens[6], lens[7], lens[8] = 1, 1, 0
+    _check(crf, oracle_mod, phi, lens, f"T={T} K={K}")
