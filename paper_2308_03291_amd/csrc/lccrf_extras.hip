@@ -473,9 +473,6 @@ __device__ __forceinline__ void expect_half(EntropySmem<G>& sm, const ChainArgs&
 // holds those of phi.
 __device__ __forceinline__ int psi_row(int h) { return h > 0 ? h - 1 : 1; }
 
-// Workgroups 0 .. 2 B - 1: the half chains of phi with their expectations.  With a.psi_chains (cross-entropy and divergence),
-// workgroups 2 B .. 4 B - 1 run the plain half chains of psi beside them, for its log-partition: as launches one after the
-// other either leaves half of the chip idle (B=64, N=256, 64 tags, log-domain steps: 96 + 172 us, together 176).
 // Where a chain starts: tag t's entry of its vector (base-2 logarithm), and of the expectation of the scores (MODE 0: of phi, base
 // 2), the score of the first tag belonging to the forward chain.
 template <int MODE, bool PLAIN, typename TIN>
@@ -502,6 +499,9 @@ __device__ __forceinline__ void expect_chain(EntropySmem<G>& sm, const ChainArgs
     if (MODE == 0) hv = 0.f;  // (these steps carry the entropy itself)
     expect_half<G, TIN, ALIGNED, MODE, PLAIN>(sm, a, v, phi, psi, row, 0, rv, hv, 0.0, 0.0);
 }
+// Workgroups 0 .. 2 B - 1: the half chains of phi with their expectations.  With a.psi_chains (cross-entropy and divergence),
+// workgroups 2 B .. 4 B - 1 run the plain half chains of psi beside them, for its log-partition: as launches one after the
+// other either leaves half of the chip idle (B=64, N=256, 64 tags, log-domain steps: 96 + 172 us, together 176).
 template <typename G, typename TIN, bool ALIGNED, int MODE>
 __global__ __launch_bounds__(G::W) void entropy_half_kernel(ChainArgs a) {
     __shared__ EntropySmem<G> sm;
