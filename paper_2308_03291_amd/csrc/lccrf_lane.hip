@@ -56,7 +56,8 @@ constexpr int lane_waves(int nblk) { return nblk <= 2 ? 12 : 8; }
 constexpr int kLaneMaxProducers = 11;
 constexpr int kLaneHead = 15;           // what the entries of a vector are held above their value, in powers of two: tag 0's is
                                         // brought into [1/2, 1), sums far below the largest stay in range (see lane_up)
-constexpr int kLaneVecRing = 16;        // published vectors kept (the chain leads a producer by fewer than that)
+constexpr int kLaneVecRing = 16;        // published vectors kept (the chain leads a producer by fewer than that, see `arrived`)
+static_assert(kLaneVecRing > kLaneMaxProducers + 1, "a vector is not replaced while its producer may read it");
 
 template <int NBLK>
 struct LaneShape {
@@ -401,12 +402,19 @@ __device__ __forceinline__ void lane_chain_wave(const ChainArgs& a, const LaneJo
         t.m = __builtin_amdgcn_readfirstlane((int)(unsigned)word);
         read_entries(step, t);
     };
-    // waits for the matrix of `step` (bounded) and reads it; false: it did not come
-    const auto fetch = [&](unsigned step, Tile& t) -> bool {
+    // Waits for the matrix of `step` (bounded); false: it did not come.  No step is taken without, in the log domain neither, unless the
+    // producers are given up: the producer of step q has done with q's vector and offset in their ring once it delivers its
+    // next matrix, so the chain leads it by no more steps than there are producers.
+    const auto arrived = [&](unsigned step, unsigned long long& word) -> bool {
         int spins = 0;
-        unsigned long long word;
         while ((unsigned)__builtin_amdgcn_readfirstlane((int)((word = lds_load_acquire(&sh.ready[step % S::RING])) >> 32)) < step + 1)
             if (++spins > poll_limit) return false;
+        return true;
+    };
+    // ... and reads it
+    const auto fetch = [&](unsigned step, Tile& t) -> bool {
+        unsigned long long word;
+        if (!arrived(step, word)) return false;
         read_tile(step, t, word);
         return true;
     };
@@ -437,6 +445,12 @@ __device__ __forceinline__ void lane_chain_wave(const ChainArgs& a, const LaneJo
         float lvs = carried ? lv_carry : lane < T ? lane_log(V) : LCCRF_NEG_INF;
         carried = false;
         for (int n = 0;; ++n) {
+            unsigned long long word;
+            if (!arrived(q, word)) {
+                lv_carry = lvs;
+                carried = true;
+                return 4;
+            }
             const int d = lane_log_step<TIN, AL, PASS2>(a, jb, (int)q, lvs, O0 + (double)Oi, lz2, meet_only);
             Oi += d;
             float lall = lvs;  // every copy of the vector gets its tag's value
@@ -466,8 +480,9 @@ __device__ __forceinline__ void lane_chain_wave(const ChainArgs& a, const LaneJo
         return fetch(q, nxt) ? 0 : 2;
     };
     // The same for first passes over dense potentials, which do not give the producers up: where more than a third of the
-    // steps are such for a while (kOften; independent normal potentials of a deviation of fifteen and more), the rest of the chain is taken in the log domain, and the producers are told to hand on the logarithms of the matrices, in the same slots
-    // and the same order: a step adds the rotated vector to them, takes the maximum and adds up the exponentials.  (Matrices that were
+    // steps are such for a while (kOften; independent normal potentials of a deviation of fifteen and more), the rest of the chain is
+    // taken in the log domain, and the producers are told to hand on the logarithms of the matrices, in the same slots and the same
+    // order: a step adds the rotated vector to them, takes the maximum and adds up the exponentials.  (Matrices that were
     // exponentiated already are taken from memory by this wave.)  `alone`: no producer is waited for any more.
     // 0: go on (the matrix of step q is in `nxt`), 2: it did not come, 3: that was the last step, everything is stored.
     constexpr bool kRaw = lane_takes_raw<TIN, AL, PASS2>();
@@ -486,15 +501,10 @@ __device__ __forceinline__ void lane_chain_wave(const ChainArgs& a, const LaneJo
             if (alone) lds_store_release(&sh.stop, (int)q);
             for (;;) {
                 unsigned long long word = 0;
-                if (rest && !alone) {
-                    int spins = 0;
-                    while ((unsigned)__builtin_amdgcn_readfirstlane((int)((word = lds_load_acquire(&sh.ready[q % S::RING])) >> 32)) < q + 1)
-                        if (++spins > poll_limit) {
-                            alone = true;
-                            word = 0;
-                            lds_store_release(&sh.stop, (int)q);
-                            break;
-                        }
+                if (!alone && !arrived(q, word)) {
+                    alone = rest = true;
+                    word = 0;
+                    lds_store_release(&sh.stop, (int)q);
                 }
                 int d;
                 if (__builtin_amdgcn_readfirstlane((int)(unsigned)word) == kLaneRaw) {
