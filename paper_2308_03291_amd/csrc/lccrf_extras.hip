@@ -138,8 +138,9 @@ static hipError_t launch_entropy_combine(const ChainArgs& a, float* H, hipStream
 // weight zero contributes nothing whatever psi holds there.  In modes 1 and 2 a common shift of
 // h (its largest finite entry) moves into a double-precision offset at every step, so the vector
 // stays small however long the chain is.
-// At 33 .. 64 tags the steps of lccrf_expect.h come first, these ones follow where they give up.  At 33 .. 128 tags every mode first tries every step with one shift for the whole matrix, the normaliser
-// of the vector it starts from, as the chain kernels do (lccrf_chain.hip): U / S (+ log2 S) does not depend
+// At 33 .. 64 tags the steps of lccrf_expect.h come first, these ones follow where they give up.  At 33 .. 128 tags
+// every mode first tries every step with one shift for the whole matrix, the normaliser of the vector it
+// starts from, as the chain kernels do (lccrf_chain.hip): U / S (+ log2 S) does not depend
 // on the shift as long as no term that matters is flushed, which holds if every sum lies in
 // [2^-60, 2^60]; otherwise the step is replayed exactly on the same registers.  The other geometries take
 // plain exact steps (every sum against its own maximum): the forward step takes the column maxima

@@ -15,8 +15,8 @@
 // 2^kLinearHead: their entries reach further below it than the growth strays from one step to the next.  A step is accepted if every
 // sum lies in [2^-60, 2^60] and the largest entry of the vector it started from was at least 2^-30: an E below 2^-126 is
 // flushed, which takes at most 256 2^k 2^-126 of a sum of 2^(-60 - kLinearHead + k) before scaling, 2^-34, and a product below
-// 2^-126 is still held to 2^-149 (denormals are kept): 256 2^-150 of 2^(-84 - 30), 2^-28, for every entry separately.  At a step that is not accepted
-// the stretch ends, with the vector in front of that step; the caller's log-domain steps take over from there.
+// 2^-126 is still held to 2^-149 (denormals are kept): 256 2^-150 of 2^(-84 - 30), 2^-28, for every entry
+// separately.  At a step that is not accepted the stretch ends, with the vector in front of that step; the caller's log-domain steps take over from there.
 //
 // Layout.  Q4 = ceil(T / 4) threads cover a row, four columns each (whatever lanes and waves they fall into: nothing here
 // reduces across lanes of a row), so the G = W / Q4 row groups of a workgroup fit the tag count, not the next power of two.
