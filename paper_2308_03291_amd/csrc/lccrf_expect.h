@@ -1,5 +1,5 @@
 // The half chains behind the entropy, the cross-entropy and the divergence in scaled probabilities, 33 .. 64 tags, by a
-// workgroup of four waves (the queries: lccrf_extras.hip; scaled steps: lccrf_linear.h).
+// workgroup of four or eight waves (the queries, and which: lccrf_extras.hip; scaled steps: lccrf_linear.h).
 //
 // Beside V(u), the scaled sum over the paths behind tag u, a chain carries X(u) = V(u) h(u), h the expectation of what those
 // paths add up to.  That is linear too,
@@ -23,9 +23,11 @@
 // products are held down to 2^-149) is then at most 64 2^52 2^-126 of 2^-40, 2^-28; the same of U, times the size of f.  The
 // first step that is not accepted ends the run.
 //
-// A step costs 0.7 us (64 tags, entropy; the log-domain steps 1.0): two LDS round trips and a barrier on the dependent path, one
-// wave a SIMD.  Entropy B=128 N=128 T=48 49 us (69), divergence B=64 N=256 T=64 133 us (172), there at 4.0 TB/s of p once and q
-// twice; the heaviest tag costs 0.3 and 3 us of these.  At B=512 the entropy is bound by memory either way (N=64, 64 tags 101 / 98).
+// A step costs 0.6 us (48 tags, entropy; the log-domain steps 1.0): two LDS round trips and a barrier on the dependent path, and
+// the issue of some 250 instructions by the one wave of a SIMD.  The trip of the new vector through LDS is covered by the
+// exponentials of the next matrix, and the matrices are counted as they arrive (see `step`): entropy B=128 N=128 T=48 48.5 -> 45.8 us
+// (log-domain steps 69), divergence B=64 N=256 T=64 130 -> 121, with eight waves 110 (172), there at 4.8 TB/s of p once and q twice.
+// At B=512 the entropy is bound by memory either way (N=64, 64 tags 99 / 98).
 #pragma once
 
 #include "lccrf_device.h"
@@ -34,14 +36,15 @@
 namespace lccrf {
 
 constexpr int kExpectHead = 12;
-constexpr int kExpectWaves = 4, kExpectLanes = 16;  // sixteen lanes a row
+constexpr int kExpectLanes = 16;  // sixteen lanes a row
 constexpr int kExpectPlain = 3;                     // MODE: V alone, no expectation (0, 1, 2: as in lccrf_extras.hip)
 
+template <int WAVES>
 struct ExpectSmem {
     // Forward: [2][wave][64] partial sums (S, U) of the steps in turn, and the vector (V, X), 64 entries and a zero.
     // Backward: the sums themselves, S and U apart, 64 entries and from 64 on those of a row's last piece (zero where its neighbour
     // holds them already), then four zeros.
-    alignas(16) float part[2][kExpectWaves][64][2];
+    alignas(16) float part[2][WAVES][64][2];
     alignas(16) float vec[68][2];
     alignas(16) float row[2][2][72];
 };
@@ -54,10 +57,10 @@ struct ExpectState {
 
 // Takes steps of the chain while they are accepted (step s: the matrix of position first + s, backward first - s) and returns their
 // number.  Called by the whole workgroup.
-template <typename TIN, bool ALIGNED, bool BACKWARD, int MODE, int ITEMS>
-__device__ __forceinline__ int expect_run(ExpectSmem& sm, const TIN* phib, const TIN* psib, int T, int first, int n, ExpectState& st) {
+template <int WAVES, int ITEMS, typename TIN, bool ALIGNED, bool BACKWARD, int MODE>
+__device__ __forceinline__ int expect_run(ExpectSmem<WAVES>& sm, const TIN* phib, const TIN* psib, int T, int first, int n, ExpectState& st) {
     using Raw = RawPiece<TIN>;
-    constexpr int WAVES = kExpectWaves, LPR = kExpectLanes, W = 64 * WAVES, G = W / LPR, PH = 3;
+    constexpr int LPR = kExpectLanes, W = 64 * WAVES, G = W / LPR, PH = 3;
     constexpr bool CARRY = MODE != kExpectPlain, PSI = MODE == 1 || MODE == 2;
     constexpr int QN = PSI ? ITEMS : 1;
     const int tid = threadIdx.x, lane = tid & 63;
@@ -124,7 +127,7 @@ __device__ __forceinline__ int expect_run(ExpectSmem& sm, const TIN* phib, const
     // which row or column a lane is left with by the exchanges below, and where the entries lie
     const int last = 4 * (Q4 - 1), me = min(lane, T - 1);
     const int zero_from = BACKWARD ? 68 : 64;
-    for (int k = tid; k < (int)(sizeof(ExpectSmem) / sizeof(float)); k += W) reinterpret_cast<float*>(&sm)[k] = 0.f;
+    for (int k = tid; k < (int)(sizeof(ExpectSmem<WAVES>) / sizeof(float)); k += W) reinterpret_cast<float*>(&sm)[k] = 0.f;
     __syncthreads();
     if (!BACKWARD && lane < T) {
         sm.vec[lane][0] = v0;
@@ -159,7 +162,8 @@ __device__ __forceinline__ int expect_run(ExpectSmem& sm, const TIN* phib, const
     big = xor_max<1, 64>(big);
     if (lane == 0) sm.part[1][wave][0][0] = big;
     __syncthreads();
-    big = fmaxf(fmaxf(sm.part[1][0][0][0], sm.part[1][1][0][0]), fmaxf(sm.part[1][2][0][0], sm.part[1][3][0][0]));
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) big = fmaxf(big, sm.part[1][w][0][0]);
     int grew = uniform((int)fminf(fmaxf(ceilf(finite_or_zero(big)), -0x1p20f), 0x1p20f)) - kExpectHead, c_cur = grew;
     __syncthreads();
     prepare(0, PH, c_cur);
@@ -183,14 +187,33 @@ __device__ __forceinline__ int expect_run(ExpectSmem& sm, const TIN* phib, const
         const auto r = __builtin_amdgcn_permlane16_swap(__float_as_int(x), __float_as_int(y), false, false);
         return __int_as_float(r[0]) + __int_as_float(r[1]);
     };
-    const auto step = [&](int next) __attribute__((always_inline)) -> bool {  // false: the run is over
-        const int c_next = max(min(grew, 1 << 20), -(1 << 20)), par = done & 1;
+    // The entries of the vector that this thread multiplies by (forward: of its rows; backward: of its columns, as the last
+    // step's sums came out), requested as soon as they are written: the exponentials of the next matrix cover the trip.
+    float2 vq[BACKWARD ? 1 : ITEMS];
+    float4 vr, xr;
+    const auto request = [&](int par) __attribute__((always_inline)) {
+        if constexpr (!BACKWARD) {
+#pragma unroll
+            for (int m = 0; m < ITEMS; ++m) vq[m] = *reinterpret_cast<const float2*>(sm.vec[vrow[m]]);
+        } else {
+            vr = *reinterpret_cast<const float4*>(&sm.row[par][0][vfrom]);
+            xr = CARRY ? *reinterpret_cast<const float4*>(&sm.row[par][1][vfrom]) : make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+    };
+    request(1);
+    // (No branch around a load in here, and none out of the loop over the ring's slots: where paths with and without a step's
+    // loads meet, the compiler takes none of them for granted and waits for the newest before it uses the oldest.  A step that
+    // is not accepted, and those behind it or behind the last one up to the end of the round, change nothing that is returned.)
+    bool going = true;
+    int at = 0;  // steps begun
+    const auto step = [&](int next) __attribute__((always_inline)) {
+        const int c_next = max(min(grew, 1 << 20), -(1 << 20)), par = at & 1;
         float S = 0.f, U = 0.f, centre = 0.f;
         if constexpr (!BACKWARD) {
             float as[4] = {0.f, 0.f, 0.f, 0.f}, au[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int m = 0; m < ITEMS; ++m) {
-                const float2 q = *reinterpret_cast<const float2*>(sm.vec[vrow[m]]);
+                const float2 q = vq[m];
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     as[j] = __builtin_fmaf(e[m][j], q.x, as[j]);
@@ -206,14 +229,14 @@ __device__ __forceinline__ int expect_run(ExpectSmem& sm, const TIN* phib, const
 #pragma unroll
             for (int w = 0; w < WAVES; ++w) q[w] = *reinterpret_cast<const float2*>(sm.part[par][w][rslot]);
             if (CARRY) centre = heaviest();
-            prepare(next, done + 1 + PH, c_next);
-            S = (q[0].x + q[1].x) + (q[2].x + q[3].x);
-            if (CARRY) U = (q[0].y + q[1].y) + (q[2].y + q[3].y);
+#pragma unroll
+            for (int w = 0; w < WAVES; w += 4) {
+                S += (q[w].x + q[w + 1].x) + (q[w + 2].x + q[w + 3].x);
+                if (CARRY) U += (q[w].y + q[w + 1].y) + (q[w + 2].y + q[w + 3].y);
+            }
         } else {
             // (the rows at hand are the last step's sums as they came out: scaled and shifted here)
-            const float4 r = *reinterpret_cast<const float4*>(&sm.row[par ^ 1][0][vfrom]);
-            float4 u = CARRY ? *reinterpret_cast<const float4*>(&sm.row[par ^ 1][1][vfrom]) : make_float4(0.f, 0.f, 0.f, 0.f);
-            float v[4] = {r.x, r.y, r.z, r.w}, x[4] = {u.x, u.y, u.z, u.w};
+            float v[4] = {vr.x, vr.y, vr.z, vr.w}, x[4] = {xr.x, xr.y, xr.z, xr.w};
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 v[j] = __builtin_amdgcn_ldexpf(v[j], -k);
@@ -241,26 +264,36 @@ __device__ __forceinline__ int expect_run(ExpectSmem& sm, const TIN* phib, const
             __syncthreads();
             S = sm.row[par][0][me];
             if (CARRY) U = sm.row[par][1][me];
+            request(par);
             if (CARRY) centre = heaviest();
-            prepare(next, done + 1 + PH, c_next);
         }
         const int k_new = uniform(__builtin_amdgcn_frexp_expf(S)) - kExpectHead;  // tag 0's
         const float vn = __builtin_amdgcn_ldexpf(S, -k_new);
         const float xn = CARRY ? __builtin_fmaf(-centre, vn, __builtin_amdgcn_ldexpf(U, -k_new)) : 0.f;
-        if (!__all(S >= 0x1p-40f && vn >= 0x1p-28f && vn <= 0x1p52f && fabsf(xn) <= 0x1p72f)) return false;
-        V = vn;
-        X = xn;
+        going = going && __all(S >= 0x1p-40f && vn >= 0x1p-28f && vn <= 0x1p52f && fabsf(xn) <= 0x1p72f);
+        V = going ? vn : V;
+        X = going ? xn : X;
         k = k_new;
         hc = centre;
-        if constexpr (!BACKWARD) *reinterpret_cast<float2*>(sm.vec[me]) = make_float2(vn, xn);  // (every wave, the same values)
-        if (CARRY) shift += (double)centre;
+        if constexpr (!BACKWARD) {
+            *reinterpret_cast<float2*>(sm.vec[me]) = make_float2(vn, xn);  // (every wave, the same values)
+            request(0);
+        }
+        if (CARRY) shift += going ? (double)centre : 0.0;
         grew = c_cur + k_new;
-        Oi += grew;
-        Hi += c_cur;
+        Oi += going ? grew : 0;
+        Hi += going ? c_cur : 0;
+        done += going ? 1 : 0;
+        going = going && done < n;
         c_cur = c_next;
-        return ++done < n;
+        ++at;
+        prepare(next, at + PH, c_next);
     };
-    while (step(1) && step(2) && step(0)) {}
+    while (going) {
+        step(1);
+        step(2);
+        step(0);
+    }
     __syncthreads();  // (the shared state may be used for something else now)
     // (the largest entry brought below 1: the closer the logarithms are to zero, the less their rounding takes)
     const int kv = uniform(__builtin_amdgcn_frexp_expf(xor_max<1, 64>(V)));

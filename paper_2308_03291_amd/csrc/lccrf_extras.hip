@@ -183,7 +183,7 @@ __device__ __forceinline__ void expect_half(EntropySmem<G>& sm, const ChainArgs&
     constexpr bool LATE_PSI = CROSS && G::WAVES >= 16;
     constexpr bool QRING = CROSS && !LATE_PSI;
     constexpr int QITEMS = QRING ? ITEMS : 1, QPF = QRING ? PF : 1;
-    constexpr bool SPEC = (ITEMS == 4 || ITEMS == 8) && G::LPR >= 16;  // speculative step first
+    constexpr bool SPEC = (ITEMS == 2 || ITEMS == 4 || ITEMS == 8) && G::LPR >= 16;  // speculative step first
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int b = v >> 1, dir = v & 1;
     const int N = a.N, T = a.T;
@@ -392,11 +392,9 @@ __device__ __forceinline__ void expect_half(EntropySmem<G>& sm, const ChainArgs&
             if constexpr (SPEC) {
                 const int flag = nstep & 3;
                 if (tid == 0) sm.bad[(nstep + 1) & 3] = 0;
-                float Sl[ITEMS], Ul[ITEMS];
+                float Sl[ITEMS < 4 ? 4 : ITEMS] = {}, Ul[ITEMS < 4 ? 4 : ITEMS] = {};
 #pragma unroll
                 for (int k = 0; k < ITEMS; ++k) {
-                    Sl[k] = 0.f;
-                    Ul[k] = 0.f;
                     float f[4] = {0.f, 0.f, 0.f, 0.f};
                     if constexpr (CROSS) edge_term(i, slot, k, y[k], f);
 #pragma unroll
@@ -517,8 +515,10 @@ __global__ __launch_bounds__(G::W) void entropy_half_kernel(ChainArgs a) {
 }
 
 // The same at 33 .. 64 tags: the steps of lccrf_expect.h as long as they are accepted, then those of expect_half.
-template <typename TIN, bool ALIGNED, int MODE, int ITEMS, bool PLAIN>
-__device__ __forceinline__ void expect_linear_chain(EntropySmem<Geo<16, kExpectWaves, 4>>& sm, ExpectSmem& lin, const ChainArgs& a, int v, const void* phi,
+template <int WAVES>
+using ExpectGeo = Geo<16, WAVES, 16 / WAVES>;
+template <int WAVES, int ITEMS, typename TIN, bool ALIGNED, int MODE, bool PLAIN>
+__device__ __forceinline__ void expect_linear_chain(EntropySmem<ExpectGeo<WAVES>>& sm, ExpectSmem<WAVES>& lin, const ChainArgs& a, int v, const void* phi,
                                                     const void* psi, int row, int h, int e) {
     constexpr int RUN = PLAIN ? kExpectPlain : MODE;
     const int lane = threadIdx.x & 63, b = v >> 1, dir = v & 1, T = a.T;
@@ -537,8 +537,8 @@ __device__ __forceinline__ void expect_linear_chain(EntropySmem<Geo<16, kExpectW
         hopeless = __ballot(lane < T && st.v != LCCRF_NEG_INF && Elem<TIN>::get(mat + (dir == 0 ? lane * T + t : t * T + lane)) != LCCRF_NEG_INF) == 0;
     }
     const int done = hopeless ? 0
-                     : dir == 0 ? expect_run<TIN, ALIGNED, false, RUN, ITEMS>(lin, phib, psib, T, 1, n, st)
-                                : expect_run<TIN, ALIGNED, true, RUN, ITEMS>(lin, phib, psib, T, e, n, st);
+                     : dir == 0 ? expect_run<WAVES, ITEMS, TIN, ALIGNED, false, RUN>(lin, phib, psib, T, 1, n, st)
+                                : expect_run<WAVES, ITEMS, TIN, ALIGNED, true, RUN>(lin, phib, psib, T, e, n, st);
     // Entropy of what lies behind a tag: log alpha less the expected score, base 2
     float hv = st.h;
     double Hoff = st.Hoff;
@@ -551,7 +551,7 @@ __device__ __forceinline__ void expect_linear_chain(EntropySmem<Geo<16, kExpectW
             hv = st.v > LCCRF_NEG_INF ? (float)((double)hv + Hoff) : 0.f;
             Hoff = 0.0;
         }
-        expect_half<Geo<16, kExpectWaves, 4>, TIN, ALIGNED, MODE, PLAIN>(sm, a, v, phi, psi, row, done, st.v, hv, st.O, Hoff);
+        expect_half<ExpectGeo<WAVES>, TIN, ALIGNED, MODE, PLAIN>(sm, a, v, phi, psi, row, done, st.v, hv, st.O, Hoff);
         return;
     }
     if ((int)threadIdx.x < T) {
@@ -563,17 +563,17 @@ __device__ __forceinline__ void expect_linear_chain(EntropySmem<Geo<16, kExpectW
         if (!PLAIN) a.hoff[2 * b + dir] = Hoff;
     }
 }
-template <typename TIN, bool ALIGNED, int MODE, int ITEMS>
-__global__ __launch_bounds__(64 * kExpectWaves) void expect_linear_kernel(ChainArgs a) {
-    __shared__ EntropySmem<Geo<16, kExpectWaves, 4>> sm;
-    __shared__ ExpectSmem lin;
+template <int WAVES, int ITEMS, typename TIN, bool ALIGNED, int MODE>
+__global__ __launch_bounds__(64 * WAVES) void expect_linear_kernel(ChainArgs a) {
+    __shared__ EntropySmem<ExpectGeo<WAVES>> sm;
+    __shared__ ExpectSmem<WAVES> lin;
     const bool plain = MODE != 0 && (int)blockIdx.x >= 2 * a.B;
     const int v = (int)blockIdx.x - (plain ? 2 * a.B : 0);
     const int L = clamp_length(a.lengths, v >> 1, a.N);
     if (L == 0) return;
     const int e = L - 1, h = meeting_point(0, e);
-    if (MODE == 0 || !plain) expect_linear_chain<TIN, ALIGNED, MODE, ITEMS, false>(sm, lin, a, v, a.phi, a.psi, h, h, e);
-    else if constexpr (MODE != 0) expect_linear_chain<TIN, ALIGNED, MODE, ITEMS, true>(sm, lin, a, v, a.psi, nullptr, psi_row(h), h, e);
+    if (MODE == 0 || !plain) expect_linear_chain<WAVES, ITEMS, TIN, ALIGNED, MODE, false>(sm, lin, a, v, a.phi, a.psi, h, h, e);
+    else if constexpr (MODE != 0) expect_linear_chain<WAVES, ITEMS, TIN, ALIGNED, MODE, true>(sm, lin, a, v, a.psi, nullptr, psi_row(h), h, e);
 }
 
 template <typename TIN, bool ALIGNED, int MODE>
@@ -584,9 +584,20 @@ static hipError_t launch_entropy_T(const ChainArgs& a, hipStream_t st) {
     else if (a.T <= 32)
         hipLaunchKernelGGL((entropy_half_kernel<Geo<8, 4, 1>, TIN, ALIGNED, MODE>), grid, dim3(256), 0, st, a);
     else if (a.T <= 48)
-        hipLaunchKernelGGL((expect_linear_kernel<TIN, ALIGNED, MODE, 3>), grid, dim3(64 * kExpectWaves), 0, st, a);
-    else if (a.T <= 64)
-        hipLaunchKernelGGL((expect_linear_kernel<TIN, ALIGNED, MODE, 4>), grid, dim3(64 * kExpectWaves), 0, st, a);
+        hipLaunchKernelGGL((expect_linear_kernel<4, 3, TIN, ALIGNED, MODE>), grid, dim3(256), 0, st, a);
+    else if (a.T <= 64) {
+        // Eight waves where every workgroup has a compute unit to itself and an edge takes two potentials: the matrices are then most of
+        // a step (divergence, us, eight waves / four: B=64 N=256 T=64 110 / 121, B=64 N=200 T=57 bfloat16 89 / 106, B=32 N=64 T=64
+        // 34 / 37; B=128 N=64 T=64 60 / 49).  With fewer tags or one potential an edge it is the instructions that every wave
+        // executes alike (divergence B=16 N=100 T=40 47 / 45; entropy B=64 N=128 T=64 55 / 49, B=128 N=128 T=48 56 / 45).
+        if constexpr (MODE != 0) {
+            if (grid.x <= 256) {
+                hipLaunchKernelGGL((expect_linear_kernel<8, 2, TIN, ALIGNED, MODE>), grid, dim3(512), 0, st, a);
+                return hipGetLastError();
+            }
+        }
+        hipLaunchKernelGGL((expect_linear_kernel<4, 4, TIN, ALIGNED, MODE>), grid, dim3(256), 0, st, a);
+    }
     else if (a.T <= 128) {
         if constexpr (MODE == 0)
             hipLaunchKernelGGL((entropy_half_kernel<Geo<32, 16, 4>, TIN, ALIGNED, MODE>), grid, dim3(1024), 0, st, a);

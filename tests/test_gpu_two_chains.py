@@ -181,3 +181,18 @@ def test_two_chains_largest_tag_sets_replays_bf16_and_forbidden_edges(crf, oracl
     p[3, :, torch.arange(T), torch.arange(T)] = 0.0
     q[4, 12, :, :] = ninf            # q has no finite path, p has
     _check(crf, oracle_mod, p, q, None, f"-inf T={T}")
+
+
+@pytest.mark.parametrize("B,T,N,dtype", [(64, 49, 8, "f32"), (65, 49, 8, "f32"), (3, 61, 34, "bf16"), (65, 64, 14, "bf16"), (64, 64, 15, "f32"),
+                                         (2, 52, 2, "f32"), (4, 57, 100, "f32")])
+def test_two_chains_either_side_of_the_wide_workgroups(crf, oracle_mod, B, T, N, dtype):
+    """49 .. 64 tags: workgroups of eight waves up to 64 sequences, of four above; every remainder of the positions a half
+    chain takes over the three in flight; a step that the scaled probabilities do not accept in the middle of a chain, and a tag
+    that is forbidden everywhere (the log-domain steps of either workgroup)."""
+    p, q, lens = _pair(7700 + 13 * T + N, B, N, T, dtype=dtype, ragged=True, min_len=0)
+    _check(crf, oracle_mod, p, q, lens, f"B={B} T={T} N={N}")
+    p[0, N // 3, 2, :] = -200.0
+    p[0, N // 3, :, 1] = 150.0
+    p[1, :, :, 3] = float("-inf")
+    p[1, :, 3, :] = float("-inf")
+    _check(crf, oracle_mod, p, q, None, f"rejected steps B={B} T={T} N={N}")
