@@ -251,3 +251,15 @@ def test_log_domain_for_good_without_the_producers(crf, oracle_mod, T):
         check_case(crf, oracle_mod, phi, lens, poison=False, algo=crf.ALGO_SEQUENTIAL_LANES, what=f"no producers T={T}", queries=("logz",))
     finally:
         crf.set_lane_poll_limit(-1)
+
+
+@pytest.mark.parametrize("T", (12, 30, 45, 60))
+def test_a_step_that_is_not_accepted_at_every_place_of_a_round(crf, oracle_mod, T):
+    """The quick steps go two a round: a step that scaled probabilities do not take (entries two hundred bits apart) at every
+    position of a short chain, once each, so that it falls on either half of a round, the first and the last step included."""
+    N = 12
+    phi, _ = workloads.random_case(9700 + T, N, N, T, scale=1.5)
+    for i in range(1, N):
+        phi[i, i, :, 2] += 90.0
+        phi[i, i, 1, :] -= 90.0
+    check_case(crf, oracle_mod, phi, None, algo=crf.ALGO_SEQUENTIAL_LANES, what=f"refused steps T={T}", queries=("logz", "mu"))
