@@ -16,6 +16,7 @@
 #include "lccrf_device.h"
 #include "lccrf_launch.h"
 #include "lccrf_linear.h"
+#include "lccrf_rotate.h"
 
 namespace lccrf {
 
@@ -424,6 +425,374 @@ __global__ __launch_bounds__(64 * WAVES) void semi_linear_kernel(SemiArgs a) {
     semi_log_steps<LPR, WAVES, TIN, ALIGNED>(a, b, L, i, K - 1, (double)Oi, semi_smem);
 }
 
+// ---------------------------------------------------------------------------------------
+// The same in scaled probabilities with the recursion taken off the streaming work, as in lccrf_lane.hip.  Of the K T rows that the step
+// of position p sums over, only the T of segments of one position meet the vector that the step before has just made; the others
+// meet older ones.  So one wave takes the dependent part alone: a T x T product by lane rotations (lccrf_rotate.h), the sums of
+// the other rows added to it.  The other waves ("helpers") work ahead of it: while it makes V_p they exponentiate the first matrix
+// of position p + 2 into LDS and sum up the rows of longer segments of position p + 1.  The waves meet at one barrier a position.
+//
+// Offsets and tests are those of the kernel above.  With g_p the running average of what tag 0 grows by, up to position p, the first
+// matrix of p is held with the shift c_p = g_{p-3} less kSemiHead and the helpers' sums of p are in units of
+// 2^(O_{p-2} + 2 g_{p-2} - kSemiSumHead): their exponents reach kSemiSumHead - kSemiHead further below the sum they go into, which
+// is what the chain may stray from that forecast; if it strays further (the sums would have to be scaled up), the step is not
+// accepted (independent normal potentials: none of 100 chains of 64 positions up to a deviation of 5, at 8 none that is not refused
+// for the spread of its vector as well).
+//
+// A position of 32 tags costs 0.42 us with K = 1, which is the chain, and 0.08 more for every row of longer segments a helper thread holds:
+// 0.70 with K = 8 where every wave doing the whole step costs 0.84 (B=1 N=64 56.3 -> 49.1 us); 0.40 for 11 tags, K = 3 (0.68).
+constexpr int kSemiSumHead = kSemiHead + 40;
+template <int WAVES, int NBLK>
+struct SemiChainShape {
+    static constexpr int U = 16 * NBLK, RS = U + 4, VS = U, H = WAVES - 1;
+    static constexpr int E0 = (U + 1) * RS;             // floats of an exponentiated matrix, in the chain wave's order (row U: zeros)
+    static constexpr int FIXED = 2 * E0 + 2 * H * 64;   // two of them, and the helpers' sums
+    static size_t bytes(int K) { return (size_t)(FIXED + (K + 1) * VS + (K + 1 + 3) / 4 * 4 + 12) * sizeof(float); }
+};
+
+// MR: rows of longer segments a helper thread holds; M0: rows of the first matrix.
+template <int WAVES, int NBLK, int MR, int M0, typename TIN>
+__global__ __launch_bounds__(64 * WAVES) void semi_chain_kernel(SemiArgs a) {
+    using Raw = RawPiece<TIN>;
+    using S = SemiChainShape<WAVES, NBLK>;
+    constexpr int W = 64 * WAVES, LPR = 4 * NBLK, H = S::H, G = 64 * H / LPR, ITEMS = MR + M0;
+    constexpr int PH = Raw::WORDS * ITEMS * 3 <= (WAVES == 16 ? 64 : 96) ? 3 : 2;  // positions in flight
+    static_assert(G * M0 >= S::U, "the helpers cover a matrix");
+    constexpr bool kSplit = NBLK == 2;
+    constexpr int NB = kSplit ? 1 : NBLK;
+    extern __shared__ __attribute__((aligned(16))) unsigned char semi_smem[];
+    const int K = a.K, T = a.T, N = a.N, KT = K * T, KR = K + 1;
+    float* E0 = reinterpret_cast<float*>(semi_smem);
+    float* part = E0 + 2 * S::E0;      // [2][H][64]
+    float* vec = part + 2 * H * 64;    // [K + 1][VS]: V_q in slot (q + 1) % (K + 1)
+    int* Oslot = reinterpret_cast<int*>(vec + KR * S::VS);
+    int* info = Oslot + (KR + 3) / 4 * 4;  // [2][4]: for the interval of position p, at p & 1: forecast of O_{p+1}, shift of the first matrix of p + 2, whether to go on
+    double* Odouble = reinterpret_cast<double*>(info + 8);
+    const int tid = threadIdx.x, lane = tid & 63, b = blockIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int L = clamp_length(a.lengths, b, N);
+    if (L == 0) {
+        if (tid == 0) a.logZ[b] = 0.f;
+        return;
+    }
+    const size_t block = (size_t)K * T * T;
+    const TIN* phib = static_cast<const TIN*>(a.phi) + (size_t)b * N * block;
+    for (int k = tid; k < S::FIXED + KR * S::VS; k += W) E0[k] = 0.f;
+    for (int k = tid; k < KR; k += W) Oslot[k] = 0;
+    int stop = 0;         // position that is not accepted (L: none)
+    if (wave == 0) {
+        // ---------------- the chain ----------------
+        __builtin_amdgcn_s_setprio(2);
+        const int u = kSplit ? lane & 31 : lane, copy = kSplit ? lane >> 5 : 0;
+        const bool on = u < T;
+        const int urow = on ? u : S::U;
+        const float x0 = on ? Elem<TIN>::get(phib + u) * kLog2e : LCCRF_NEG_INF;
+        const int m0 = uniform((int)fminf(fmaxf(ceilf(finite_or_zero(xor_max<1, 64>(x0))), -0x1p20f), 0x1p20f));
+        const auto accepted = [&](float s, float v) { return __all(!on || (s >= kSemiLo && v >= kSemiLo && v <= kSemiHi)); };
+        float s = on ? ex2(x0 - (float)(m0 - kSemiHead)) : 0.f;
+        int k = uniform(__builtin_amdgcn_frexp_expf(s));
+        float V = __builtin_amdgcn_ldexpf(s, -k);
+        long long O = m0 - kSemiHead + k;
+        // What tag 0 grows by, on average: the last growth alone strays with the potentials (deviation 3: by ten bits and more)
+        int grew4 = 4 * (m0 + 5);
+        const auto average = [&]() { return max(min(grew4 >> 2, 1 << 20), -(1 << 20)); };
+        int grew = average();
+        const bool good0 = accepted(s, V);
+        __syncthreads();  // (everything is cleared)
+        // (the empty prefix, V_{-1}: potential 1 for row 0, nothing else)
+        if (lane == 0) vec[0] = 1.f;
+        if (on && copy == 0) vec[1 % KR * S::VS + u] = V;
+        int bA = (int)O + grew, bB = (int)O + 2 * grew;   // forecasts of O_p and O_{p+1}
+        int cA = grew - kSemiHead, cB = cA, cC = cA;      // shifts of the first matrices of p, p + 1, p + 2
+        if (lane == 0) {
+            Oslot[1 % KR] = (int)O;
+            info[0] = bA; info[1] = cA; info[2] = good0 ? 1 : 0;
+            info[4] = bB; info[5] = cA; info[6] = 1;
+            *Odouble = 0.0;
+        }
+        __syncthreads();
+        stop = good0 ? L : 0;
+        if (good0 && L > 1) {
+            __syncthreads();  // the helpers' interval 0
+            struct Tile {
+                float e[NB][16];
+            } tA, tB;
+            const auto read_tile = [&](int p, Tile& t) __attribute__((always_inline)) {
+                const float* row = E0 + (p & 1) * S::E0 + urow * S::RS + (kSplit ? 16 * copy : 0);
+#pragma unroll
+                for (int bk = 0; bk < NB; ++bk)
+#pragma unroll
+                    for (int g = 0; g < 4; ++g) {
+                        const float4 v = *reinterpret_cast<const float4*>(row + 16 * bk + 4 * g);
+                        t.e[bk][4 * g] = v.x; t.e[bk][4 * g + 1] = v.y; t.e[bk][4 * g + 2] = v.z; t.e[bk][4 * g + 3] = v.w;
+                    }
+            };
+            read_tile(1, tA);
+            __syncthreads();
+            int slot = 2 % KR;  // of V_p
+            const auto step = [&](int p, const Tile& cur, Tile& nxt) __attribute__((always_inline)) -> bool {  // false: the chain ends here
+                float r[H];
+                const float* mine = part + (p & 1) * H * 64 + u;
+#pragma unroll
+                for (int w = 0; w < H; ++w) r[w] = mine[64 * w];
+                read_tile(p + 1, nxt);  // (made an interval ago; past the end whatever is there, never used)
+                __builtin_amdgcn_sched_barrier(0);
+                float Ab[4], acc[4];
+                rotation_blocks<NBLK>(V, copy, Ab);
+                mul_rotations(acc, Ab[0], cur.e[0]);
+#pragma unroll
+                for (int bk = 1; bk < NB; ++bk) fmac_rotations(acc, Ab[bk], cur.e[bk]);
+                float x = (acc[0] + acc[1]) + (acc[2] + acc[3]);
+                if constexpr (kSplit) {
+                    const auto h = __builtin_amdgcn_permlane32_swap(__float_as_int(x), __float_as_int(x), false, false);
+                    x = __int_as_float(h[0]) + __int_as_float(h[1]);
+                }
+#pragma unroll
+                for (int step = 1; step < H; step *= 2)
+#pragma unroll
+                    for (int w = 0; w + step < H; w += 2 * step) r[w] += r[w + step];
+                const float sum = r[0];
+                const int D = bA - kSemiSumHead - (int)O - cA;
+                x += on ? __builtin_amdgcn_ldexpf(sum, D) : 0.f;
+                const int kx = uniform(__builtin_amdgcn_frexp_expf(x));
+                const float v = __builtin_amdgcn_ldexpf(x, -kx);
+                const bool good = accepted(x, v) && D <= 0;
+                if (good) {
+                    V = v;
+                    O += cA + kx;
+                    grew4 += cA + kx - (grew4 >> 2);
+                    grew = average();
+                    bA = bB;
+                    bB = (int)O + 2 * grew;
+                    cA = cB;
+                    cB = cC;
+                    cC = grew - kSemiHead;
+                }
+                if (on) vec[slot * S::VS + u] = V;
+                Oslot[slot] = (int)O;
+                slot = slot + 1 == KR ? 0 : slot + 1;
+                *reinterpret_cast<int4*>(info + 4 * ((p + 1) & 1)) = make_int4(bB, cC, good ? 1 : 0, 0);
+                if (!good) {
+                    stop = p;
+                    *Odouble = (double)O;
+                }
+                __syncthreads();
+                return good && p + 1 < L;
+            };
+            for (int p = 1;; p += 2) {
+                if (!step(p, tA, tB)) break;
+                if (!step(p + 1, tB, tA)) break;
+            }
+        }
+        if (stop == L) {  // logZ = logsumexp of the vector of the last position
+            const float z = xor_sum<1, 64>(on && copy == 0 ? V : 0.f);
+            if (lane == 0) a.logZ[b] = (float)(((double)O + (double)lg2(z)) * kLn2);
+            return;
+        }
+        __builtin_amdgcn_s_setprio(0);
+    } else {
+        // ---------------- the helpers ----------------
+        const int h = tid - 64, g = h / LPR, cl = h % LPR, c4 = min(4 * cl, T - 4);
+        unsigned voff[ITEMS];
+        int kk[MR], srow[MR], slot[MR];  // segment length less one, row (-1: none), where the vector it meets stands
+        const int RT = KT - T;
+#pragma unroll
+        for (int m = 0; m < MR; ++m) {
+            const int rc = max(min(g + G * m, RT - 1), 0);
+            kk[m] = K > 1 ? 1 + rc / T : 0;
+            srow[m] = g + G * m < RT ? rc % T : -1;
+            voff[m] = (unsigned)((kk[m] * T + rc % T) * T + c4) * (unsigned)sizeof(TIN);
+            slot[m] = kk[m] <= 1 ? 0 : 1 - kk[m] + KR;  // of V_{-kk}, for the rows of position 1
+        }
+#pragma unroll
+        for (int m = 0; m < M0; ++m) voff[MR + m] = (unsigned)(min(g + G * m, T - 1) * T + c4) * (unsigned)sizeof(TIN);
+        typename Raw::type raw[PH][ITEMS], first[M0];
+        const auto position = [&](int p) {
+            auto base = (const GlobalBytes*)(phib + (size_t)(p < L ? p : L - 1) * block);
+            asm("" : "+s"(base));
+            return base;
+        };
+        const auto fetch = [&](int p, int at) __attribute__((always_inline)) {  // what the interval of position p takes
+            const auto next = position(p + 1), after = position(p + 2);
+#pragma unroll
+            for (int m = 0; m < MR; ++m) raw[at][m] = Raw::template load<false>(next + voff[m]);
+#pragma unroll
+            for (int m = MR; m < ITEMS; ++m) raw[at][m] = Raw::template load<false>(after + voff[m]);
+        };
+        // (a tag that the sequence cannot start with: with many sequences looked for before anything is fetched, as above)
+        const bool vain = a.B > kSemiLookFirst && __any(lane < T && Elem<TIN>::get(phib + min(lane, T - 1)) == LCCRF_NEG_INF);
+        if (!vain) {
+            const auto next = position(1);
+#pragma unroll
+            for (int m = 0; m < M0; ++m) first[m] = Raw::template load<false>(next + voff[MR + m]);
+#pragma unroll
+            for (int p = 0; p < PH; ++p) {
+                fetch(p, p);
+                asm volatile("" ::: "memory");  // (in this order: the loop's waits count on it)
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        // where the entries of a row of the first matrix go
+        int eaddr[M0][4];
+#pragma unroll
+        for (int m = 0; m < M0; ++m) {
+            const int v = min(g + G * m, T - 1);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) eaddr[m][j] = (c4 + j) * S::RS + 16 * (v >> 4) + ((c4 + j - v) & 15);
+        }
+        // over the wave's row groups: the swaps leave accumulator 2 (lane >> 5) + ((lane >> 4) & 1) in a lane
+        const auto pair32 = [](float x, float y) {
+            const auto r = __builtin_amdgcn_permlane32_swap(__float_as_int(x), __float_as_int(y), false, false);
+            return __int_as_float(r[0]) + __int_as_float(r[1]);
+        };
+        const auto pair16 = [](float x, float y) {
+            const auto r = __builtin_amdgcn_permlane16_swap(__float_as_int(x), __float_as_int(y), false, false);
+            return __int_as_float(r[0]) + __int_as_float(r[1]);
+        };
+        const int jcol = 2 * (lane >> 5) + ((lane >> 4) & 1);
+        const int target = c4 + jcol;  // the tag whose sum this lane ends up with (several lanes the same, with the same sum)
+        __syncthreads();
+        __syncthreads();
+        bool going = L > 1 && !vain;
+        if (going) {   // the first matrix of position 1
+            const float c = (float)uniform(info[1]);
+#pragma unroll
+            for (int m = 0; m < M0; ++m)
+                if (g + G * m < T) {
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) E0[S::E0 + eaddr[m][j]] = ex2(__builtin_fmaf(Raw::get(first[m], j), kLog2e, -c));
+                }
+        }
+        int p = 0;
+        const auto interval = [&](int at) __attribute__((always_inline)) {
+            // (everything from LDS is requested before any of it is waited for)
+            const int4 in = *reinterpret_cast<const int4*>(info + 4 * (p & 1));
+            float xv[MR];
+            int Ov[MR];
+#pragma unroll
+            for (int m = 0; m < MR; ++m) {
+                xv[m] = vec[slot[m] * S::VS + max(srow[m], 0)];
+                Ov[m] = Oslot[slot[m]];
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            going = going && uniform(in.z) != 0 && p < L;
+            const int base = uniform(in.x) - kSemiSumHead, shift = uniform(in.y);
+            float e[MR][4];
+#pragma unroll
+            for (int m = 0; m < MR; ++m) {
+                const float c = (float)(base - Ov[m]);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) e[m][j] = ex2(__builtin_fmaf(Raw::get(raw[at][m], j), kLog2e, -c));
+            }
+            if (p + 1 < K) {  // segments that would start before position 0, rows s > 0 of first segments: never used
+#pragma unroll
+                for (int m = 0; m < MR; ++m) {
+                    const bool ok = kk[m] <= p || (kk[m] == p + 1 && srow[m] == 0);
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) e[m][j] = ok ? e[m][j] : 0.f;
+                }
+            }
+            float acc[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int m = 0; m < MR; ++m) {
+                const float v = srow[m] >= 0 ? xv[m] : 0.f;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) acc[j] = __builtin_fmaf(e[m][j], v, acc[j]);
+            }
+            float x = pair16(pair32(acc[0], acc[2]), pair32(acc[1], acc[3]));
+            if (LPR <= 8) x += dpp<kDppRowRor8>(x);
+            if (LPR <= 4) x += dpp<kDppRowRor4>(x);
+            float e0[M0][4];
+#pragma unroll
+            for (int m = 0; m < M0; ++m)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) e0[m][j] = ex2(__builtin_fmaf(Raw::get(raw[at][MR + m], j), kLog2e, -(float)shift));
+            // All of it made here, in front of the loads that go where the potentials were: left to itself the compiler moves some of it
+            // behind them and then waits for the new ones.
+            asm volatile("" : "+v"(x));
+#pragma unroll
+            for (int m = 0; m < M0; ++m)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) asm volatile("" : "+v"(e0[m][j]));
+            __builtin_amdgcn_sched_barrier(0);
+            if (going) {
+                part[((p + 1) & 1) * H * 64 + (wave - 1) * 64 + target] = x;
+                float* to = E0 + (p & 1) * S::E0;
+#pragma unroll
+                for (int m = 0; m < M0; ++m)
+                    if (g + G * m < T) {
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) to[eaddr[m][j]] = e0[m][j];
+                    }
+            }
+#pragma unroll
+            for (int m = 0; m < MR; ++m) slot[m] = slot[m] + 1 == KR ? 0 : slot[m] + 1;
+            fetch(p + PH, at);
+            ++p;
+            if (going) {
+                __syncthreads();
+                if (p == 1) __syncthreads();  // (the chain has read the matrix of position 1 before that of position 3 takes its place)
+            }
+        };
+        while (going) {
+            interval(0);
+            interval(1);
+            if constexpr (PH > 2) interval(2);
+        }
+        if (L > 1) {
+            // the chain's last word: the interval it ended in
+            const int4 in0 = *reinterpret_cast<const int4*>(info), in1 = *reinterpret_cast<const int4*>(info + 4);
+            if (uniform(in0.z) != 0 && uniform(in1.z) != 0) return;
+        } else if (uniform(info[2]) != 0) {
+            return;
+        }
+    }
+    // Not accepted at some position: from there on in the log domain, from the K vectors in front of it, through registers (both
+    // states begin where the other does).  By as many waves as the kernel above would have (more meet at more barriers: K=4 T=16 B=200 N=64,
+    // deviation 12, by all four 110 us, by one 86); the others leave.
+    if (wave == 0 && lane == 0) info[3] = stop;
+    __syncthreads();
+    stop = uniform(info[3]);
+    const double O = uniform(*Odouble);
+    const int Oi = (int)O;
+    constexpr int MOST = NBLK == 1 || MR <= 2 ? 4 : WAVES;
+    const bool one = NBLK == 1 && K <= 4;
+    double* base = reinterpret_cast<double*>(semi_smem);
+    float* ring = reinterpret_cast<float*>(base + (K + 1) / 2 * 2);
+    float* dlast = ring + (KT + 3) / 4 * 4 + 2 * (one ? 1 : MOST) * 4 * LPR;
+    const auto slot_here = [&](int q) {  // where the vector that goes to slot q lies: V_{stop - 1} to K - 1, the older ones below
+        const int x = (stop % KR) - (K - 1 - q);
+        return x < 0 ? x + KR : x;
+    };
+    float keep[2];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const int x = tid + q * W;
+        keep[q] = x < KT ? lg2(vec[slot_here(x / T) * S::VS + x % T]) : 0.f;
+    }
+    const int keepO = tid < K ? Oi - Oslot[slot_here(tid)] : 0;
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+        if (tid + q * W < KT) ring[tid + q * W] = keep[q];
+    if (tid < K) base[tid] = O - (double)keepO;
+    __syncthreads();
+    if (wave == 0) {
+        const float d = xor_max<1, 64>(lane < T ? ring[(K - 1) * T + lane] : LCCRF_NEG_INF);
+        if (lane == 0) *dlast = finite_or_zero(d);
+    }
+    __syncthreads();
+    if (wave >= (one ? 1 : MOST)) return;
+    if constexpr (NBLK == 1) {
+        if (one) {
+            if (T == 16 || T == 12 || T == 8) semi_log_steps<LPR, 1, TIN, true>(a, b, L, stop, K - 1, O, semi_smem);
+            else semi_log_steps<LPR, 1, TIN, false>(a, b, L, stop, K - 1, O, semi_smem);
+            return;
+        }
+    }
+    semi_log_steps<LPR, MOST, TIN, false>(a, b, L, stop, K - 1, O, semi_smem);
+}
+
 template <int LPR, int WAVES>
 static hipError_t launch_semi_geo(int dtype, const SemiArgs& a, hipStream_t st) {
     const size_t lds = semi_lds_bytes(a.K, a.T, LPR, WAVES);
@@ -478,6 +847,40 @@ static bool launch_semi_linear(int dtype, const SemiArgs& a, hipStream_t st, hip
     return false;
 }
 
+template <int WAVES, int NBLK, int MR, int M0>
+static bool launch_semi_chain_items(int dtype, const SemiArgs& a, hipStream_t st, hipError_t& e) {
+    constexpr int LPR = 4 * NBLK;
+    size_t bytes = SemiChainShape<WAVES, NBLK>::bytes(a.K);
+    const size_t log = semi_lds_bytes(a.K, a.T, LPR, WAVES);
+    if (log > bytes) bytes = log;
+    if (bytes > 64 * 1024 || (long long)a.K * a.T > 2 * 64 * WAVES || a.K > 64 * WAVES) return false;
+    if (dtype == 0) hipLaunchKernelGGL((semi_chain_kernel<WAVES, NBLK, MR, M0, float>), dim3(a.B), dim3(64 * WAVES), bytes, st, a);
+    else hipLaunchKernelGGL((semi_chain_kernel<WAVES, NBLK, MR, M0, uint16_t>), dim3(a.B), dim3(64 * WAVES), bytes, st, a);
+    e = hipGetLastError();
+    return true;
+}
+// Where it is taken.  Up to 16 tags always with few rows, with more while every workgroup has a compute unit to itself (us, so / every
+// wave the whole step, single precision: K=4 T=16, N=64, B=256 25.7 / 42.2, B=1024 42.6 / 45.7; K=8 T=16 B=1 N=256 107 / 137, K=8 T=12
+// bfloat16 B=300 N=64 44.4 / 41.8; K=3 T=11 B=4 N=90 bfloat16 35.9 / 61.0); with three helpers where their threads hold a row of
+// longer segments each (K=4 T=16 B=64 N=100 37.5, with seven 44), with seven above (K=6 T=16 B=4 N=100 43.7, with three 49.4).  At 17 .. 32
+// tags while every workgroup has a compute unit to itself (N=64: K=4 T=32 B=256 39.8 / 51.7; K=2 T=32 B=512 42.9 / 40.7, K=3 T=20 B=512
+// 41.8 / 39.5), with most rows half of them (K=8 T=32 B=256 90.4 / 88.0).  Above 32 tags the helpers cannot keep ahead of the chain (K=2
+// T=64 B=1 N=256 233 / 213, K=7 T=45 B=6 N=31 73.9 / 74.2).
+static bool launch_semi_chain(int dtype, const SemiArgs& a, hipStream_t st, hipError_t& e) {
+    const long long rows = (long long)(a.K - 1) * a.T;
+    if (a.T <= 16) {
+        if (rows <= 48) return launch_semi_chain_items<4, 1, 1, 1>(dtype, a, st, e);
+        if (rows <= 112 && a.B <= 256) return launch_semi_chain_items<8, 1, 1, 1>(dtype, a, st, e);
+        if (rows <= 224 && a.B <= 256) return launch_semi_chain_items<8, 1, 2, 1>(dtype, a, st, e);
+    } else if (a.T <= 32 && a.B <= (rows <= 168 ? 256 : 128)) {
+        if (rows <= 56) return launch_semi_chain_items<8, 2, 1, 1>(dtype, a, st, e);
+        if (rows <= 112) return launch_semi_chain_items<8, 2, 2, 1>(dtype, a, st, e);
+        if (rows <= 168) return launch_semi_chain_items<8, 2, 3, 1>(dtype, a, st, e);
+        if (rows <= 224) return launch_semi_chain_items<8, 2, 4, 1>(dtype, a, st, e);
+    }
+    return false;
+}
+
 // Geometry by tag count: 4 LPR >= T columns; four waves up to T = 64 (one when T <= 16 and the K
 // matrices have no more rows than one wave covers in a batch), sixteen above.
 static void semi_geometry(int K, int T, int& lpr, int& waves) {
@@ -498,6 +901,7 @@ hipError_t launch_semi_markov_forward(int dtype, const void* phi, const int32_t*
     const SemiArgs a{phi, lengths, B, N, K, T, logZ};
     if (T >= 8 && T <= 64) {
         hipError_t e = hipSuccess;
+        if (launch_semi_chain(dtype, a, st, e)) return e;
         if (T <= 16 ? launch_semi_linear<4>(dtype, a, st, e) : T <= 32 ? launch_semi_linear<8>(dtype, a, st, e) : launch_semi_linear<16>(dtype, a, st, e))
             return e;
     }
