@@ -73,7 +73,8 @@ typedef enum { LCCRF_F32 = 0, LCCRF_BF16 = 1 } lccrf_dtype;
 typedef enum {
     LCCRF_OP_LOGZ = 0,
     LCCRF_OP_MARGINALS = 1,
-    LCCRF_OP_ARGMAX = 2,
+    LCCRF_OP_ARGMAX = 2, /* above 64 tags the size may hold B*N*T doubles (rounded up to 256 bytes) at its end that a call can do
+                          * without: it then takes a slower schedule with the same results */
     LCCRF_OP_LOG_PROB = 3,
     LCCRF_OP_ENTROPY = 4,
     LCCRF_OP_SAMPLE = 5,

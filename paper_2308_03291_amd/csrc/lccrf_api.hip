@@ -153,9 +153,15 @@ struct MaxWorkspace {
     size_t bp, mid;
     size_t Mx, K, pin;  // chunked scan (T <= 32 only, else empty)
     size_t Mx2, K2, pin2;  // its group level (many chunks only, else empty)
+    size_t needed;         // bytes a call must bring; with `total` it may also take the schedule that uses `delta`
+    size_t delta;          // scores in front of every position (more than 64 tags only, else empty)
     size_t total;
 };
-inline MaxWorkspace max_workspace(size_t B, size_t N, size_t T) {
+// (the size of a workspace does not say which call it is for: dense, or structured, which is in float)
+inline bool max_scores_pay_either(int dt, int B, int N, int T) {
+    return lccrf::max_scores_pay(dt, B, N, T, false) || (dt == LCCRF_F32 && lccrf::max_scores_pay(dt, B, N, T, true));
+}
+inline MaxWorkspace max_workspace(size_t B, size_t N, size_t T, int dt) {
     MaxWorkspace w;
     size_t off = 0;
     const size_t chunk = (size_t)scan_chunk_max((long long)B, (long long)N, (long long)T);
@@ -172,8 +178,15 @@ inline MaxWorkspace max_workspace(size_t B, size_t N, size_t T) {
     w.Mx2 = off; off += round_up(BG * TPm * TPm * sizeof(double));
     w.K2 = off; off += round_up(BG * TPm);
     w.pin2 = off; off += round_up(BG * sizeof(int32_t));
+    w.needed = off;
+    w.delta = off; off += max_scores_pay_either(dt, (int)B, (int)N, (int)T) ? round_up(B * N * T * sizeof(double)) : 0;
     w.total = off;
     return w;
+}
+
+// The rows for the scores where that schedule pays and the caller has brought them.
+inline double* delta_rows(const MaxWorkspace& w, char* base, size_t bytes, int dt, int B, int N, int T, bool structured) {
+    return lccrf::max_scores_pay(dt, B, N, T, structured) && bytes >= w.total ? reinterpret_cast<double*>(base + w.delta) : nullptr;
 }
 
 inline bool shape_ok(int B, int N, int T) {
@@ -404,7 +417,7 @@ size_t lccrf_workspace_bytes(lccrf_op op, int B, int N, int T, lccrf_dtype dt) {
         case LCCRF_OP_ENTROPY:
         case LCCRF_OP_SAMPLE:
         case LCCRF_OP_CROSS_ENTROPY: return sum_workspace(B, N, T).total;
-        case LCCRF_OP_ARGMAX: return max_workspace(B, N, T).total;
+        case LCCRF_OP_ARGMAX: return max_workspace(B, N, T, dt).total;
         default: return 0;
     }
 }
@@ -462,7 +475,7 @@ int lccrf_argmax_algo(const void* phi, lccrf_dtype dt, const int32_t* lengths, i
                       float* best_score, int32_t* tags, void* workspace, size_t workspace_bytes, void* stream,
                       lccrf_algo algo) {
     const KnobSnapshot knobs;
-    const size_t need = lccrf_workspace_bytes(LCCRF_OP_ARGMAX, B, N, T, dt);
+    const size_t need = shape_ok(B, N, T) ? max_workspace(B, N, T, dt).needed : 0;
     const int rc = check_common(phi, dt, B, N, T, workspace, workspace_bytes, need, algo);
     if (rc != LCCRF_OK) return rc;
     if (!tags) return LCCRF_ENULL;
@@ -470,7 +483,7 @@ int lccrf_argmax_algo(const void* phi, lccrf_dtype dt, const int32_t* lengths, i
     if (lengths && !aligned_to(lengths, 4)) return LCCRF_EALIGN;
     if (algo == LCCRF_ALGO_SCAN && !lccrf::scan_supported_max(T)) return LCCRF_ENOTIMPL;
     if (algo == LCCRF_ALGO_SEQUENTIAL_LANES && !lccrf::lane_max_supported(T)) return LCCRF_ENOTIMPL;
-    const MaxWorkspace w = max_workspace(B, N, T);
+    const MaxWorkspace w = max_workspace(B, N, T, dt);
     char* base = static_cast<char*>(workspace);
     hipStream_t st = static_cast<hipStream_t>(stream);
     uint8_t* bp = reinterpret_cast<uint8_t*>(base + w.bp);
@@ -488,7 +501,8 @@ int lccrf_argmax_algo(const void* phi, lccrf_dtype dt, const int32_t* lengths, i
     } else {
         const bool lanes = algo == LCCRF_ALGO_SEQUENTIAL_LANES || (algo == LCCRF_ALGO_AUTO && lanes_pay_max(B, N, T));
         e = lccrf::launch_sequential_max(dt, phi, lengths, B, N, T, bp, mid, best_score, tags, st, lanes,
-                                         g_lane_poll_limit.load(std::memory_order_relaxed));
+                                         g_lane_poll_limit.load(std::memory_order_relaxed),
+                                         algo == LCCRF_ALGO_AUTO ? delta_rows(w, base, workspace_bytes, dt, B, N, T, false) : nullptr);
     }
     return e == hipSuccess ? LCCRF_OK : LCCRF_ELAUNCH;
 }
@@ -802,12 +816,12 @@ int lccrf_marginals_structured(const float* emit, const float* trans, const int3
 int lccrf_argmax_structured(const float* emit, const float* trans, const int32_t* lengths, int B, int N, int T,
                             float* best_score, int32_t* tags, void* workspace, size_t workspace_bytes, void* stream) {
     const KnobSnapshot knobs;
-    const size_t need = lccrf_workspace_bytes(LCCRF_OP_ARGMAX, B, N, T, LCCRF_F32);
+    const size_t need = shape_ok(B, N, T) ? max_workspace(B, N, T, LCCRF_F32).needed : 0;
     const int rc = check_structured(emit, trans, lengths, B, N, T, workspace, workspace_bytes, need);
     if (rc != LCCRF_OK) return rc;
     if (!tags) return LCCRF_ENULL;
     if (!aligned_to(tags, 4) || (best_score && !aligned_to(best_score, 4))) return LCCRF_EALIGN;
-    const MaxWorkspace w = max_workspace(B, N, T);
+    const MaxWorkspace w = max_workspace(B, N, T, LCCRF_F32);
     char* base = static_cast<char*>(workspace);
     if (scan_taken_max(B, N, T)) {  // the schedule lccrf_auto_algo reports for the dense call of this shape
         hipStream_t st = static_cast<hipStream_t>(stream);
@@ -829,7 +843,8 @@ int lccrf_argmax_structured(const float* emit, const float* trans, const int32_t
                                                       reinterpret_cast<uint8_t*>(base + w.bp),
                                                       reinterpret_cast<double*>(base + w.mid), best_score, tags,
                                                       static_cast<hipStream_t>(stream), T <= 32 && lanes_pay_max(B, N, T),
-                                                      g_lane_poll_limit.load(std::memory_order_relaxed));
+                                                      g_lane_poll_limit.load(std::memory_order_relaxed),
+                                                      delta_rows(w, base, workspace_bytes, LCCRF_F32, B, N, T, true));
     return e == hipSuccess ? LCCRF_OK : LCCRF_ELAUNCH;
 }
 

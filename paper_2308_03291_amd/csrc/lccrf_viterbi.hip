@@ -884,7 +884,13 @@ static hipError_t launch_T(const VitArgs& a, hipStream_t st) {
     return hipGetLastError();
 }
 
-static hipError_t launch_any(int dtype, const VitArgs& a, hipStream_t st, bool lanes = false, int lane_poll_limit = 0) {
+static hipError_t launch_any(int dtype, const VitArgs& a, hipStream_t st, bool lanes = false, int lane_poll_limit = 0, double* delta = nullptr) {
+    if (delta) {
+        const hipError_t e = launch_max_scores(dtype, a, delta, st);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(viterbi_trace_kernel, dim3(a.B), dim3(kTraceThreads), 0, st, a);
+        return hipGetLastError();
+    }
     if (lanes) {
         const hipError_t e = launch_lane_max_chains(dtype, a, lane_poll_limit, st);
         if (e != hipSuccess) return e;
@@ -900,10 +906,10 @@ size_t viterbi_mid_doubles(int B, int C, int T) { return (size_t)B * C * 2 * T; 
 
 hipError_t launch_sequential_max(int dtype, const void* phi, const int32_t* lengths, int B, int N, int T,
                                  uint8_t* bp, double* mid, float* best_score, int32_t* tags, hipStream_t st, bool lanes,
-                                 int lane_poll_limit) {
+                                 int lane_poll_limit, double* delta) {
     if (lanes && !lane_max_supported(T)) return hipErrorInvalidValue;
     return launch_any(dtype, VitArgs{phi, lengths, B, N, T, bp, mid, best_score, tags, 0, 1, nullptr, nullptr, nullptr}, st,
-                      lanes, lane_poll_limit);
+                      lanes, lane_poll_limit, delta);
 }
 
 template <typename G, bool ALIGNED>
@@ -933,10 +939,10 @@ static hipError_t launch_structured_T(const VitArgs& a, hipStream_t st) {
 // The same from structured potentials (float emit [B][N][T] + trans [T][T]; T <= 128).
 hipError_t launch_structured_max(const float* emit, const float* trans, const int32_t* lengths, int B, int N, int T,
                                  uint8_t* bp, double* mid, float* best_score, int32_t* tags, hipStream_t st, bool lanes,
-                                 int lane_poll_limit) {
+                                 int lane_poll_limit, double* delta) {
     if (T > 128 || (lanes && (T > 32 || !lane_max_supported(T)))) return hipErrorInvalidValue;
     const VitArgs a{nullptr, lengths, B, N, T, bp, mid, best_score, tags, 0, 1, nullptr, emit, trans};
-    if (lanes) return launch_any(0, a, st, true, lane_poll_limit);
+    if (lanes || delta) return launch_any(0, a, st, lanes, lane_poll_limit, delta);
     return (T % 4) == 0 ? launch_structured_T<true>(a, st) : launch_structured_T<false>(a, st);
 }
 

@@ -68,4 +68,7 @@ __device__ __forceinline__ void first_max_tree(double (&val)[n], int (&arg)[n]) 
 // leave them for the trace.
 hipError_t launch_lane_max_chains(int dtype, const VitArgs& a, int poll_limit, hipStream_t st);
 
+// The same in two kernels, the scores and then the pointers (lccrf_scores.hip; 65 .. 256 tags, whole sequences).
+hipError_t launch_max_scores(int dtype, const VitArgs& a, double* delta, hipStream_t st);
+
 }  // namespace lccrf
