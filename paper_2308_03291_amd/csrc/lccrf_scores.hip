@@ -25,22 +25,6 @@ namespace lccrf {
 
 namespace {
 
-__device__ __forceinline__ double max_plain(double a, double b) {  // (NaN operands are ignored in favour of the other)
-    double r;
-    asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
-    return r;
-}
-template <int CTRL>
-__device__ __forceinline__ double dpp_d(double x) {
-    const long long v = __double_as_longlong(x);
-    const int lo = dpp_i<CTRL>((int)v), hi = dpp_i<CTRL>((int)(v >> 32));
-    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
-}
-__device__ __forceinline__ double max_quad(double x) {  // over the four lanes of a quad
-    x = max_plain(x, dpp_d<kDppQuadXor1>(x));
-    return max_plain(x, dpp_d<kDppQuadXor2>(x));
-}
-
 template <int LPR_, int ITEMS_>
 struct ScoreGeo {
     static constexpr int LPR = LPR_, ITEMS = ITEMS_, RPP = 1024 / LPR_, TC = 4 * LPR_;

@@ -291,18 +291,127 @@ __global__ __launch_bounds__(G::W) void viterbi_half_kernel(VitArgs a) {
     if (tid < T) mid[tid] = sm.dvec[buf][tid];
 }
 
-// Structured potentials, 33 .. 64 tags, whole sequences.  The transition scores stay in registers and a position brings T emissions,
-// so nothing streams and a step is bound by its arithmetic (an fp32 and an fp64 addition, a conversion, a comparison and three
-// selections an edge) and by what the chain waits for between them.  Lane = the tag the step goes to (forward t, backward s), wave
-// w = the NS tags w NS .. it comes from: a wave takes its sources' scores from its own lanes' registers (v_readlane),
-// keeps the first maximum of each lane in order, and the four waves' candidates meet in LDS behind the step's one barrier,
-// where every wave merges them for itself, so the new scores are in every wave's registers.  The potentials of the next step, which
-// depend on nothing, are formed before the barrier.
-// Whole argmax, us, so / dense tiles formed in registers, four waves, two barriers a step: N=100 B=256 T=45 54 / 91, T=64 63 / 85, B=1024
-// T=64 193 / 215, N=16 B=1024 T=48 34 / 43; against the chain-wave kernels (a ring of matrices in LDS, which these potentials
-// do not need) B=128 T=45 40 / 59, B=1 37 / 54.
+// Structured potentials, 33 .. 56 tags, whole sequences.  The transition scores stay in registers and a position brings T emissions, so
+// nothing streams: with one workgroup a compute unit a step is bound by what its chain waits for, with more by the instructions
+// they issue.  LPT lanes a tag that the step goes to (forward t, backward s), NS tags it comes from a lane, in pieces of four that are
+// moved back to end with the row (what is then held twice is the same candidate twice): four lanes with twelve sources and three
+// waves up to 48 tags, eight with eight and seven waves up to 56, so little is padding.  A step reads the scores from LDS,
+// adds, takes plain maxima, over the lanes of a tag by rotations in the vector unit, and writes the new scores in front of its one
+// barrier; which candidate it was is found by comparing them with the maximum, one step later, while the next step's scores come
+// from LDS; the potentials, which depend on nothing, are formed behind the maximum.
+// Whole argmax, us, with the tag carried along every maximum (as at 57 .. 64 tags) / so: N=100 B=256 T=45 50 / 35, B=1024 T=45 149 / 85,
+// B=1 34 / 29; N=60 B=512 T=33 54 / 31, T=55 65 / 57; N=16 B=1024 T=48 32 / 22.
+typedef __attribute__((address_space(1))) char StructBytes;
+typedef __attribute__((address_space(1))) uint8_t StructPointers;
+template <int LPT, int NS, bool BACKWARD>
+__device__ __forceinline__ void structured_chain(const VitArgs& a, int b, int first, int n, double (*vec)[64], double* mid) {
+    constexpr int PF = 4, NP = NS / 4;  // (two positions ahead instead of four: 160 -> 325 us at B=39 N=480, 63 tags)
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), T = a.T;
+    const int q = lane % LPT, t = 64 / LPT * wave + lane / LPT, me = min(t, T - 1);
+    const bool writes = q == 0 && t < T;
+    const float* emb = a.emit + (size_t)b * a.N * T;
+    uint8_t* bpb = a.bp + (size_t)b * a.N * T;
+    const double ninf = -__builtin_huge_val();
+    int c[NP];  // first tag of a piece
+    int tag[NS];
+    float tr[NS];
+#pragma unroll
+    for (int k = 0; k < NP; ++k) {
+        c[k] = min(NS * q + 4 * k, T - 4);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            tag[4 * k + j] = c[k] + j;
+            tr[4 * k + j] = a.trans[BACKWARD ? me * T + c[k] + j : (c[k] + j) * T + me];
+        }
+    }
+    double m = BACKWARD ? 0.0 : (double)(a.trans[me] + emb[me]);
+    if (n > 0) {
+        vec[0][t] = m;
+        const auto position = [&](int s) { return BACKWARD ? first - s : first + s; };
+        vec4f em[PF][BACKWARD ? NP : 1];  // forward: the emission of this lane's tag; backward: those of its sources
+        const auto load = [&](int s, int p) __attribute__((always_inline)) {
+            const int i = __builtin_amdgcn_readfirstlane(position(s < n ? s : n - 1));
+            auto row = (const StructBytes*)(emb + (size_t)i * T);
+            asm("" : "+s"(row));  // (a scalar base and a 32-bit offset a lane)
+            if constexpr (BACKWARD) {
+#pragma unroll
+                for (int k = 0; k < NP; ++k) em[p][k] = *(const __attribute__((address_space(1))) vec4f_anywhere*)(row + 4u * (unsigned)c[k]);
+            } else {
+                em[p][0][0] = *(const __attribute__((address_space(1))) float*)(row + 4u * (unsigned)me);
+            }
+        };
+#pragma unroll
+        for (int p = 0; p < PF; ++p) load(p, p);
+        double x[NS], cand[NS];
+        const auto form = [&](int p) __attribute__((always_inline)) {  // the potentials of a step
+#pragma unroll
+            for (int k = 0; k < NS; ++k) x[k] = (double)(tr[k] + (BACKWARD ? em[p][BACKWARD ? k / 4 : 0][k & 3] : em[p][0][0]));
+        };
+        const auto point = [&](int i) __attribute__((always_inline)) {  // the pointers of position i: the first of the best
+            int from = kNoArg;
+#pragma unroll
+            for (int k = NS - 1; k >= 0; --k) from = cand[k] == m ? tag[k] : from;
+            from = min(from, dpp_i<kDppQuadXor1>(from));
+            from = min(from, dpp_i<kDppQuadXor2>(from));
+            if constexpr (LPT == 8) from = min(from, dpp_i<kDppHalfMirror>(from));
+            auto row = (StructPointers*)(bpb + (size_t)__builtin_amdgcn_readfirstlane(i) * T);
+            asm("" : "+s"(row));
+            if (writes) {
+                row[(unsigned)t] = (uint8_t)(m == ninf || from == kNoArg ? 0 : from);
+            }
+        };
+        form(0);
+        __syncthreads();
+        int done = 0;
+        bool running = true;
+        while (running) {
+#pragma unroll
+            for (int p = 0; p < PF; ++p) {
+                double d[NS];
+#pragma unroll
+                for (int k = 0; k < NS; ++k) d[k] = vec[p & 1][c[k / 4] + (k & 3)];
+                __builtin_amdgcn_sched_barrier(0);
+                if (done > 0) point(position(done - 1));
+                double best[4];
+#pragma unroll
+                for (int k = 0; k < NS; ++k) {
+                    cand[k] = d[k] + x[k];
+                    best[k & 3] = k < 4 ? cand[k] : max_plain(best[k & 3], cand[k]);
+                }
+                m = max_quad(max_plain(max_plain(best[0], best[1]), max_plain(max_plain(best[2], best[3]), ninf)));
+                if constexpr (LPT == 8) m = max_plain(m, dpp_d<kDppHalfMirror>(m));
+                vec[(p & 1) ^ 1][t] = m;
+                form((p + 1) % PF);
+                load(done + PF, p);
+                __syncthreads();
+                if (++done >= n) { running = false; break; }
+            }
+        }
+        point(position(n - 1));
+    }
+    if (writes) mid[t] = m;
+}
+template <int WAVES, int LPT, int NS>
+__global__ __launch_bounds__(64 * WAVES) void viterbi_structured_kernel(VitArgs a) {
+    __shared__ double vec[2][64];
+    const int dir = blockIdx.x & 1, b = blockIdx.x >> 1;
+    const int L = __builtin_amdgcn_readfirstlane(clamp_length(a.lengths, b, a.N));
+    if (L == 0) return;
+    const int e = L - 1, h = meeting_point(0, e);
+    double* mid = a.mid + ((size_t)b * 2 + dir) * a.T;
+    if (dir == 0) structured_chain<LPT, NS, false>(a, b, 1, h, vec, mid);
+    else structured_chain<LPT, NS, true>(a, b, e, e - h, vec, mid);
+}
+
+// Structured potentials, 57 .. 64 tags, and 49 .. 56 from 513 sequences on: the same chains with lane = the tag the step goes to (forward t, backward s), wave w = the NS
+// tags NS w .. it comes from: a wave takes its sources' scores from its own lanes' registers (v_readlane), keeps the first
+// maximum of each lane in order, and the four waves' candidates meet in LDS behind the step's one barrier, where every wave
+// merges them for itself.  At these sizes nothing is padding here (64 lanes, 64 sources), and four waves of 70 registers leave more of
+// them resident than eight of 108: whole argmax, us, so / as up to 56 tags with eight waves, B=1024 N=100 T=64 187 / 201, B=1024 N=30
+// T=58 62 / 70, B=300 N=100 T=64 82 / 86, B=1024
+// N=100 T=56 188 / 207 (B=512 N=60 T=55 65 / 57); the other way round with few chains, B=39 N=480 T=63 170 / 160, too little for a rule of its own.
 template <int NS, bool BACKWARD>
-__device__ __forceinline__ void structured_chain(const VitArgs& a, int b, int first, int n, double (*pv)[4][64], int (*pi)[4][64], double* mid) {
+__device__ __forceinline__ void structured_readlane_chain(const VitArgs& a, int b, int first, int n, double (*pv)[4][64], int (*pi)[4][64], double* mid) {
     constexpr int PF = 4;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), T = a.T;
     const bool on = lane < T;
@@ -376,7 +485,7 @@ __device__ __forceinline__ void structured_chain(const VitArgs& a, int b, int fi
     if (wave == 0 && on) mid[lane] = v;
 }
 template <int NS>
-__global__ __launch_bounds__(256) void viterbi_structured_kernel(VitArgs a) {
+__global__ __launch_bounds__(256) void viterbi_structured_readlane_kernel(VitArgs a) {
     __shared__ double pv[2][4][64];
     __shared__ int pi[2][4][64];
     const int dir = blockIdx.x & 1, b = blockIdx.x >> 1;
@@ -384,8 +493,8 @@ __global__ __launch_bounds__(256) void viterbi_structured_kernel(VitArgs a) {
     if (L == 0) return;
     const int e = L - 1, h = meeting_point(0, e);
     double* mid = a.mid + ((size_t)b * 2 + dir) * a.T;
-    if (dir == 0) structured_chain<NS, false>(a, b, 1, h, pv, pi, mid);
-    else structured_chain<NS, true>(a, b, e, e - h, pv, pi, mid);
+    if (dir == 0) structured_readlane_chain<NS, false>(a, b, 1, h, pv, pi, mid);
+    else structured_readlane_chain<NS, true>(a, b, e, e - h, pv, pi, mid);
 }
 
 // 129 .. 256 tags: the matrix of a position streams through registers in batches of 64 rows, as in the
@@ -926,8 +1035,9 @@ static hipError_t launch_structured_T(const VitArgs& a, hipStream_t st) {
     if (a.T <= 32) return launch_wave_vit<32, float, ALIGNED, true>(a, st);
     if (a.T <= 64) {
         if (a.chunk > 0) return hipErrorInvalidValue;  // (the max-plus scan ends at 32 tags)
-        if (a.T <= 48) hipLaunchKernelGGL(viterbi_structured_kernel<12>, dim3(2 * a.B), dim3(256), 0, st, a);
-        else hipLaunchKernelGGL(viterbi_structured_kernel<16>, dim3(2 * a.B), dim3(256), 0, st, a);
+        if (a.T <= 48) hipLaunchKernelGGL((viterbi_structured_kernel<3, 4, 12>), dim3(2 * a.B), dim3(192), 0, st, a);
+        else if (a.T <= 56 && a.B <= 512) hipLaunchKernelGGL((viterbi_structured_kernel<7, 8, 8>), dim3(2 * a.B), dim3(448), 0, st, a);
+        else hipLaunchKernelGGL(viterbi_structured_readlane_kernel<16>, dim3(2 * a.B), dim3(256), 0, st, a);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL(viterbi_trace_kernel, dim3(a.B), dim3(kTraceThreads), 0, st, a);

@@ -11,6 +11,22 @@ __device__ __forceinline__ void take_better(double& v, int& a, double pv, int pa
     if (pv > v || (pv == v && pa < a)) { v = pv; a = pa; }
 }
 
+__device__ __forceinline__ double max_plain(double a, double b) {  // (NaN operands are ignored in favour of the other)
+    double r;
+    asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp_d(double x) {
+    const long long v = __double_as_longlong(x);
+    const int lo = dpp_i<CTRL>((int)v), hi = dpp_i<CTRL>((int)(v >> 32));
+    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+__device__ __forceinline__ double max_quad(double x) {  // over the four lanes of a quad
+    x = max_plain(x, dpp_d<kDppQuadXor1>(x));
+    return max_plain(x, dpp_d<kDppQuadXor2>(x));
+}
+
 struct VitArgs {
     const void* phi;
     const int32_t* lengths;

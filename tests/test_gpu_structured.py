@@ -280,3 +280,22 @@ def test_structured_argmax_with_the_transitions_in_registers(crf, oracle_mod, T,
     assert torch.equal(y_a, y_b) and torch.equal(s_a, s_b)
     emit, trans = _make(7320 + T, B, N, T)
     _check(crf, oracle_mod, emit, trans, lens, f"structured argmax T={T} N={N}")
+
+
+@pytest.mark.parametrize("T", (33, 48, 49, 52, 56))
+@pytest.mark.parametrize("B", (512, 513))
+def test_structured_argmax_of_many_sequences(crf, T, B):
+    """Both kernels of 49 .. 56 tags and the one below, either side of their line: the dense call's tags and scores bit for bit
+    with exact ties, forbidden transitions and NaN."""
+    N = 6
+    g = torch.Generator().manual_seed(7340 + T)
+    lens = torch.randint(0, N + 1, (B,), generator=g).to(torch.int32)
+    emit = torch.randint(0, 3, (B, N, T), generator=g).to(torch.float32)
+    emit[3::7, 2, 1::3] = float("nan")
+    emit[5::11, 3] = float("-inf")
+    trans = torch.randint(0, 2, (T, T), generator=g).to(torch.float32)
+    trans[:, T // 2] = trans[T - 1, :] = float("-inf")
+    phi = (emit[:, :, None, :] + trans[None, None]).contiguous().cuda()
+    s_a, y_a = crf.lccrf_argmax_structured(emit.cuda(), trans.cuda(), lens.cuda())
+    s_b, y_b = crf.lccrf_argmax(phi, lens.cuda(), algo=crf.ALGO_SEQUENTIAL)
+    assert torch.equal(y_a, y_b) and torch.equal(s_a.view(torch.int32), s_b.view(torch.int32))
