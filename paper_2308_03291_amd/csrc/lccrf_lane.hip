@@ -571,6 +571,7 @@ __device__ __forceinline__ void lane_chain_wave(const ChainArgs& a, const LaneJo
                                                               __float_as_uint(kSumHi) - __float_as_uint(kSumLo), 37 /* unsigned <= */);
         unsigned ref = 0;  // the lane whose entry is the reference
         if ((inr & onmask) != onmask || (unsigned)(Onew + (1 << 28)) >= (1u << 29)) {
+            if constexpr (!kRaw) return 1;
             // (no entry of the matrix and none of the vector but exact zeros can have taken part in an underflow)
             const unsigned long long zero = __builtin_amdgcn_ballot_w64(Ssum == 0.f), some = inr & onmask;
             if (!(cur.m & 1) || ((inr | zero) & onmask) != onmask || some == 0 || (unsigned)(Onew + (1 << 28)) >= (1u << 29) ||
@@ -582,7 +583,7 @@ __device__ __forceinline__ void lane_chain_wave(const ChainArgs& a, const LaneJo
         // reference (what bounds the vector is the range test above, not where its largest entry lies), and
         // lane 0's comes without a reduction over the lanes.  Lanes without a tag hold an exact zero.
         const int kx = __builtin_amdgcn_frexp_expf(Ssum);
-        const int k = __builtin_amdgcn_readlane(kx, ref);
+        const int k = kRaw ? __builtin_amdgcn_readlane(kx, ref) : __builtin_amdgcn_readfirstlane(kx);
         V = __builtin_amdgcn_ldexpf(Ssum, kLaneHead - k);
         Oi = Onew + k - kLaneHead;
         ++q;
@@ -601,6 +602,9 @@ __device__ __forceinline__ void lane_chain_wave(const ChainArgs& a, const LaneJo
     // B=128 N=256 T=32 42.5 -> 38.4 us, sampling there 99 -> 89, log-probability B=100 N=200 T=45 bfloat16 46.0 -> 42.8, marginals B=128
     // N=200 T=30 62.3 -> 59.2.  With zeros accepted, where the quick way is left often, the ways out of every step are the cheaper
     // form: independent normal potentials of deviation 16, log-probability B=128 N=128 T=32 62.0 / 64.9 so, 67.4 without.)
+    // The second pass of 33 .. 48 tags keeps the way out of every step as well: there the chain comes to wait for its producers, and a round
+    // that a matrix is missing in costs more than the branches (marginals B=25 N=237 T=45 101.5 us so, 105.5 without).
+    constexpr bool kQuick = !(PASS2 && NBLK == 3);
     int mark = 0;
     // (Where the shared state stands, kept in a vector register: an address in it is then one instruction.)
     typedef __attribute__((address_space(3))) char LdsBytes;
@@ -658,7 +662,13 @@ __device__ __forceinline__ void lane_chain_wave(const ChainArgs& a, const LaneJo
         int why = carried ? 1 : fetch(0, tA) ? 0 : 2;
         bool zeros = false;
         for (;;) {
-            if (!kRaw || !zeros)
+            if constexpr (!kQuick) {
+                while (why == 0) {
+                    why = step(tA, tB);
+                    if (why != 0) break;
+                    why = step(tB, tA);
+                }
+            } else if (!kRaw || !zeros) {
                 while (why == 0) {
                     bool refused = false, going = true;
                     do {
@@ -667,6 +677,7 @@ __device__ __forceinline__ void lane_chain_wave(const ChainArgs& a, const LaneJo
                     } while (going);
                     why = refused ? 1 : q == count ? 3 : fetch(q, tA) ? 0 : 2;
                 }
+            }
             if constexpr (kRaw) {
                 if (why == 1 && !zeros && !carried) why = fetch(q, tA) ? 0 : 2;  // (the same matrix, which the slot still holds)
                 zeros = true;
