@@ -467,7 +467,7 @@ __global__ __launch_bounds__(64 * WAVES) void semi_chain_kernel(SemiArgs a) {
     float* vec = part + 2 * H * 64;    // [K + 1][VS]: V_q in slot (q + 1) % (K + 1)
     int* Oslot = reinterpret_cast<int*>(vec + KR * S::VS);
     int* info = Oslot + (KR + 3) / 4 * 4;  // [2][4]: for the interval of position p, at p & 1: forecast of O_{p+1}, shift of the first matrix of p + 2, whether to go on
-    double* Odouble = reinterpret_cast<double*>(info + 8);
+    double* Odouble = reinterpret_cast<double*>(info + 8);  // the offset the log-domain steps go on from, and its low word behind it
     const int tid = threadIdx.x, lane = tid & 63, b = blockIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int L = clamp_length(a.lengths, b, N);
@@ -496,19 +496,22 @@ __global__ __launch_bounds__(64 * WAVES) void semi_chain_kernel(SemiArgs a) {
         // What tag 0 grows by, on average: the last growth alone strays with the potentials (deviation 3: by ten bits and more)
         int grew4 = 4 * (m0 + 5);
         const auto average = [&]() { return max(min(grew4 >> 2, 1 << 20), -(1 << 20)); };
+        // (offsets and forecasts outside this wave are taken modulo 2^32: only differences of near ones count)
+        const auto low = [&](int more) { return (int)((unsigned)O + (unsigned)more); };
         int grew = average();
         const bool good0 = accepted(s, V);
         __syncthreads();  // (everything is cleared)
         // (the empty prefix, V_{-1}: potential 1 for row 0, nothing else)
         if (lane == 0) vec[0] = 1.f;
         if (on && copy == 0) vec[1 % KR * S::VS + u] = V;
-        int bA = (int)O + grew, bB = (int)O + 2 * grew;   // forecasts of O_p and O_{p+1}
+        int bA = low(grew), bB = low(2 * grew);   // forecasts of O_p and O_{p+1}
         int cA = grew - kSemiHead, cB = cA, cC = cA;      // shifts of the first matrices of p, p + 1, p + 2
         if (lane == 0) {
-            Oslot[1 % KR] = (int)O;
+            Oslot[1 % KR] = low(0);
             info[0] = bA; info[1] = cA; info[2] = good0 ? 1 : 0;
             info[4] = bB; info[5] = cA; info[6] = 1;
             *Odouble = 0.0;
+            info[10] = 0;
         }
         __syncthreads();
         stop = good0 ? L : 0;
@@ -552,7 +555,7 @@ __global__ __launch_bounds__(64 * WAVES) void semi_chain_kernel(SemiArgs a) {
 #pragma unroll
                     for (int w = 0; w + step < H; w += 2 * step) r[w] += r[w + step];
                 const float sum = r[0];
-                const int D = bA - kSemiSumHead - (int)O - cA;
+                const int D = (int)((unsigned)bA - (unsigned)low(cA)) - kSemiSumHead;
                 x += on ? __builtin_amdgcn_ldexpf(sum, D) : 0.f;
                 const int kx = uniform(__builtin_amdgcn_frexp_expf(x));
                 const float v = __builtin_amdgcn_ldexpf(x, -kx);
@@ -563,18 +566,19 @@ __global__ __launch_bounds__(64 * WAVES) void semi_chain_kernel(SemiArgs a) {
                     grew4 += cA + kx - (grew4 >> 2);
                     grew = average();
                     bA = bB;
-                    bB = (int)O + 2 * grew;
+                    bB = low(2 * grew);
                     cA = cB;
                     cB = cC;
                     cC = grew - kSemiHead;
                 }
                 if (on) vec[slot * S::VS + u] = V;
-                Oslot[slot] = (int)O;
+                Oslot[slot] = low(0);
                 slot = slot + 1 == KR ? 0 : slot + 1;
                 *reinterpret_cast<int4*>(info + 4 * ((p + 1) & 1)) = make_int4(bB, cC, good ? 1 : 0, 0);
                 if (!good) {
                     stop = p;
                     *Odouble = (double)O;
+                    info[10] = low(0);
                 }
                 __syncthreads();
                 return good && p + 1 < L;
@@ -676,11 +680,11 @@ __global__ __launch_bounds__(64 * WAVES) void semi_chain_kernel(SemiArgs a) {
             }
             __builtin_amdgcn_sched_barrier(0);
             going = going && uniform(in.z) != 0 && p < L;
-            const int base = uniform(in.x) - kSemiSumHead, shift = uniform(in.y);
+            const int base = (int)((unsigned)uniform(in.x) - (unsigned)kSemiSumHead), shift = uniform(in.y);
             float e[MR][4];
 #pragma unroll
             for (int m = 0; m < MR; ++m) {
-                const float c = (float)(base - Ov[m]);
+                const float c = (float)((int)((unsigned)base - (unsigned)Ov[m]));
 #pragma unroll
                 for (int j = 0; j < 4; ++j) e[m][j] = ex2(__builtin_fmaf(Raw::get(raw[at][m], j), kLog2e, -c));
             }
@@ -754,7 +758,7 @@ __global__ __launch_bounds__(64 * WAVES) void semi_chain_kernel(SemiArgs a) {
     __syncthreads();
     stop = uniform(info[3]);
     const double O = uniform(*Odouble);
-    const int Oi = (int)O;
+    const unsigned Olow = (unsigned)uniform(info[10]);  // (of the double a conversion to 32 bits would be the nearest value, not the low word)
     constexpr int MOST = NBLK == 1 || MR <= 2 ? 4 : WAVES;
     const bool one = NBLK == 1 && K <= 4;
     double* base = reinterpret_cast<double*>(semi_smem);
@@ -770,7 +774,7 @@ __global__ __launch_bounds__(64 * WAVES) void semi_chain_kernel(SemiArgs a) {
         const int x = tid + q * W;
         keep[q] = x < KT ? lg2(vec[slot_here(x / T) * S::VS + x % T]) : 0.f;
     }
-    const int keepO = tid < K ? Oi - Oslot[slot_here(tid)] : 0;
+    const int keepO = tid < K ? (int)(Olow - (unsigned)Oslot[slot_here(tid)]) : 0;
     __syncthreads();
 #pragma unroll
     for (int q = 0; q < 2; ++q)

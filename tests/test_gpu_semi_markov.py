@@ -177,3 +177,19 @@ def test_the_dependent_rows_by_one_wave(crf, oracle_mod, T, K, N, B, dtype):
         phi[:, i, i + 1:] = nan
         phi[:, i, i, 1:, :] = nan
     _check(crf, oracle_mod, phi.to(dtype), lens, f"T={T} K={K} N={N} B={B} {dtype}")
+
+
+@pytest.mark.parametrize("sign", (1, -1))
+@pytest.mark.parametrize("T,K", [(8, 1), (8, 2), (12, 5), (16, 8), (20, 2), (32, 8), (40, 2)])
+def test_offsets_past_32_bits(crf, oracle_mod, T, K, sign):
+    """Every position adds (or takes) a million bits, so that the offset of the vectors passes 2^31 near position 2127; then a
+    step that scaled probabilities do not take (a tag that is forbidden from there on), before that position, close behind
+    it and far behind it: what the log-domain steps go on from has to be the whole offset."""
+    N, at = 2400, (2000, 2140, 2300, 2395)
+    phi, _ = workloads.semi_markov_case(8900 + 131 * T + K, len(at), N, K, T, scale=1.0)
+    phi += sign * 7e5
+    if sign < 0:
+        phi[:, :, 1:] = float("-inf")  # (fewer segments would be worth more: unit segments only)
+    for b, i in enumerate(at):
+        phi[b, i:, :, :, T // 2] = float("-inf")
+    _check(crf, oracle_mod, phi, None, f"T={T} K={K} {sign}")
