@@ -180,6 +180,8 @@ __global__ __launch_bounds__(1024) void viterbi_scores_kernel(VitArgs a, double*
 
 constexpr unsigned kNoTag = 256;
 constexpr int kPointerThreads = 512;
+constexpr unsigned kPointerGroups = 4096, kPointerStep = 2531;  // (a power of two, and an odd number near five eighths of it)
+constexpr unsigned kPointersOneEach = 12288;                    // workgroups, one a position, up to which no positions are searched
 
 // The pointers of every position: up to the meeting position h the best tag in front of each tag, behind it the best tag behind each;
 // the first of equals, tag 0 where nothing is finite (as the other kernels).  The best scores are there already, so a candidate
@@ -188,17 +190,12 @@ constexpr int kPointerThreads = 512;
 // waits for its matrix, which is requested whole before anything is waited for.  Forward a thread keeps the first of its rows for each
 // of its columns and they meet in LDS; backward the first lane of a row that holds its best score names the tag.
 template <int PARTS, int ITEMS, typename TIN, bool STRUCT>
-__global__ __launch_bounds__(kPointerThreads) void viterbi_pointers_kernel(VitArgs a, const double* delta) {
+__device__ __forceinline__ void point_position(const VitArgs& a, const double* delta, int part, int b, int i, int L, double* v, double* m, unsigned* arg) {
     using Raw = RawPiece<TIN>;
     constexpr int TC = 128 * PARTS;
-    __shared__ double v[TC], m[TC];
-    __shared__ unsigned arg[TC];
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int N = a.N, T = a.T;
-    const int part = PARTS == 1 ? 0 : blockIdx.x % PARTS, q = blockIdx.x / PARTS;
-    const int b = q / N, i = q % N;
-    const int L = clamp_length(a.lengths, b, N);
-    if (i == 0 || i >= L) return;
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));  // (addresses formed again for every position: kept over a loop around this they are half the registers)
+    const int lane = tid & 63, N = a.N, T = a.T;
     const int h = meeting_point(0, L - 1);
     const bool forward = i <= h;
     const size_t vb = (size_t)b * N;
@@ -279,6 +276,42 @@ __global__ __launch_bounds__(kPointerThreads) void viterbi_pointers_kernel(VitAr
     if (t < last_tag) a.bp[(vb + i) * T + t] = (uint8_t)(m[t] == -__builtin_huge_val() ? 0u : arg[t]);
 }
 
+// SEARCH: padding is to cost next to nothing.  A workgroup looks at 64 positions at once, a lane each, and takes those that are
+// inside their sequences.  Of every kPointerGroups positions in a row it looks at one, not always at the same place (a long sequence
+// among short ones, and the first positions of all sequences, are spread over all workgroups).  Otherwise a workgroup a position.
+// An empty workgroup costs 0.6 ns, so sequences of 8 in rows of 512 were bound by them (structured, whole argmax, us, a workgroup a
+// position / searching / chains with tags: B=256 T=96 99 / 27 / 33, B=512 T=100 219 / 48 / 58; of 30 in 900, B=900 T=70 553 / 185 / 360).  Sequences
+// of full length lose up to 3 % of the call by the search, most with few positions a workgroup (structured, N=100, B=256 T=70 154 /
+// 159, bfloat16 B=32 N=256 T=201 649 / 660), or gain (B=1000 N=600 T=80 3380 / 3310); hence the line: up to it
+// padding costs 5 us at most.  With twice as many workgroups padding costs more (B=256 T=96 32), with half as many full lengths do (B=300
+// N=300 T=128 794 -> 806).
+template <int PARTS, int ITEMS, typename TIN, bool STRUCT, bool SEARCH>
+__global__ __launch_bounds__(kPointerThreads, 4) void viterbi_pointers_kernel(VitArgs a, const double* delta) {
+    constexpr int TC = 128 * PARTS;
+    __shared__ double v[TC], m[TC];
+    __shared__ unsigned arg[TC];
+    const unsigned N = (unsigned)a.N;
+    const auto take = [&](unsigned item) __attribute__((always_inline)) {
+        const int part = (int)(item % PARTS), b = (int)(item / PARTS / N), i = (int)(item / PARTS % N), L = clamp_length(a.lengths, b, a.N);
+        if (i > 0 && i < L) point_position<PARTS, ITEMS, TIN, STRUCT>(a, delta, part, b, i, L, v, m, arg);
+    };
+    if constexpr (!SEARCH) {
+        take(blockIdx.x);
+    } else {
+        const unsigned all = (unsigned)a.B * N * PARTS;
+        const auto item_of = [&](unsigned k) { return k * kPointerGroups + ((blockIdx.x + k * kPointerStep) & (kPointerGroups - 1)); };
+        for (unsigned k0 = 0; k0 * kPointerGroups < all; k0 += 64) {
+            const unsigned mine = item_of(k0 + (threadIdx.x & 63)), q = min(mine, all - 1) / PARTS;
+            const int i = (int)(q % N);
+            unsigned long long inside = __ballot(mine < all && i > 0 && i < clamp_length(a.lengths, (int)(q / N), a.N));
+            for (; inside; inside &= inside - 1) {
+                take(item_of(k0 + (unsigned)__builtin_ctzll(inside)));
+                __syncthreads();  // (its results have been read)
+            }
+        }
+    }
+}
+
 template <typename G, typename TIN, bool STRUCT>
 static hipError_t launch_scores_geo(const VitArgs& a, double* delta, hipStream_t st) {
     hipLaunchKernelGGL((viterbi_scores_kernel<G, TIN, STRUCT>), dim3(2 * a.B), dim3(1024), 0, st, a, delta);
@@ -286,7 +319,9 @@ static hipError_t launch_scores_geo(const VitArgs& a, double* delta, hipStream_t
     if (e != hipSuccess) return e;
     constexpr int PARTS = G::LPR / 32, ITEMS = (G::ITEMS * G::RPP + 15) / 16;
     static_assert(kPointerThreads / (32 * PARTS) * ITEMS * PARTS >= G::ITEMS * G::RPP, "every row");
-    hipLaunchKernelGGL((viterbi_pointers_kernel<PARTS, ITEMS, TIN, STRUCT>), dim3((unsigned)a.B * a.N * PARTS), dim3(kPointerThreads), 0, st, a, delta);
+    const unsigned all = (unsigned)a.B * a.N * PARTS;
+    if (all <= kPointersOneEach) hipLaunchKernelGGL((viterbi_pointers_kernel<PARTS, ITEMS, TIN, STRUCT, false>), dim3(all), dim3(kPointerThreads), 0, st, a, delta);
+    else hipLaunchKernelGGL((viterbi_pointers_kernel<PARTS, ITEMS, TIN, STRUCT, true>), dim3(kPointerGroups), dim3(kPointerThreads), 0, st, a, delta);
     return hipGetLastError();
 }
 template <typename TIN, bool STRUCT>

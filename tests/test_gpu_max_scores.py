@@ -64,3 +64,34 @@ def test_structured_scores_then_pointers(crf, T, N, special):
     small = torch.empty(crf.workspace_bytes(crf.OP_ARGMAX, B, N, T, crf.LCCRF_F32) - _score_bytes(B, N, T), dtype=torch.uint8, device="cuda")
     s_b, y_b = crf.lccrf_argmax_structured(emit, trans, lens, workspace=small)
     assert torch.equal(y, y_b) and torch.equal(s.view(torch.int32), s_b.view(torch.int32))
+
+
+@pytest.mark.parametrize("B,N,T", [(300, 43, 65), (128, 96, 96), (128, 97, 97), (450, 600, 65)])
+def test_positions_are_searched_in_large_padded_batches(crf, B, N, T):
+    """More positions than get a workgroup each (12288, and more than a workgroup looks at in one go, 64 of every 4096), nearly all of them
+    padding, a few sequences of full length among them: the kernels that carry the tags along give the same."""
+    g = torch.Generator().manual_seed(9300 + T)
+    emit, trans = _potentials(g, B, N, T, special=False).cuda(), _potentials(g, T, T, special=False).cuda()
+    lens = torch.randint(0, 9, (B,), generator=g).to(torch.int32)
+    lens[::37] = N
+    lens = lens.cuda()
+    room = crf.workspace_bytes(crf.OP_ARGMAX, B, N, T, crf.LCCRF_F32)
+    small = torch.empty(room - _score_bytes(B, N, T), dtype=torch.uint8, device="cuda")
+    for ln in (lens, None):
+        full = torch.empty(room, dtype=torch.uint8, device="cuda").fill_(255)
+        s, y = crf.lccrf_argmax_structured(emit, trans, ln, workspace=full)
+        s_b, y_b = crf.lccrf_argmax_structured(emit, trans, ln, workspace=small)
+        assert torch.equal(y, y_b) and torch.equal(s.view(torch.int32), s_b.view(torch.int32))
+
+
+@pytest.mark.parametrize("dtype,T,B,N", [(torch.float32, 130, 17, 400), (torch.bfloat16, 209, 24, 300), (torch.bfloat16, 73, 70, 180)])
+def test_positions_are_searched_dense(crf, dtype, T, B, N):
+    """The same over dense potentials, two workgroups a position from 129 tags on."""
+    g = torch.Generator(device="cuda").manual_seed(9400 + T)
+    phi = torch.randint(0, 4, (B, N, T, T), generator=g, device="cuda").to(dtype)
+    lens = torch.randint(0, 9, (B,), generator=g, device="cuda").to(torch.int32)
+    lens[::7] = N
+    for ln in (lens, None):
+        s, y = crf.lccrf_argmax(phi, ln)
+        s_seq, y_seq = crf.lccrf_argmax(phi, ln, algo=crf.ALGO_SEQUENTIAL)
+        assert torch.equal(y, y_seq) and torch.equal(s.view(torch.int32), s_seq.view(torch.int32))
