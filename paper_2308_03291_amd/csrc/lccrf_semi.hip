@@ -18,6 +18,8 @@
 #include "lccrf_linear.h"
 #include "lccrf_rotate.h"
 
+#include <type_traits>
+
 namespace lccrf {
 
 struct SemiArgs {
@@ -451,7 +453,7 @@ struct SemiChainShape {
 };
 
 // MR: rows of longer segments a helper thread holds; M0: rows of the first matrix.
-template <int WAVES, int NBLK, int MR, int M0, typename TIN>
+template <int WAVES, int NBLK, int MR, int M0, typename TIN, bool ALIGNED>
 __global__ __launch_bounds__(64 * WAVES) void semi_chain_kernel(SemiArgs a) {
     using Raw = RawPiece<TIN>;
     using S = SemiChainShape<WAVES, NBLK>;
@@ -753,17 +755,20 @@ __global__ __launch_bounds__(64 * WAVES) void semi_chain_kernel(SemiArgs a) {
     }
     // Not accepted at some position: from there on in the log domain, from the K vectors in front of it, through registers (both
     // states begin where the other does).  By as many waves as the kernel above would have (more meet at more barriers: K=4 T=16 B=200 N=64,
-    // deviation 12, by all four 110 us, by one 86); the others leave.
+    // deviation 12, by all four 110 us, by one 86; fewer take more rounds: 27 tags, K = 5, a forbidden tag, N=64, by eight 127, by four
+    // 160); the others leave.
     if (wave == 0 && lane == 0) info[3] = stop;
     __syncthreads();
     stop = uniform(info[3]);
     const double O = uniform(*Odouble);
     const unsigned Olow = (unsigned)uniform(info[10]);  // (of the double a conversion to 32 bits would be the nearest value, not the low word)
-    constexpr int MOST = NBLK == 1 || MR <= 2 ? 4 : WAVES;
-    const bool one = NBLK == 1 && K <= 4;
+    constexpr bool kEither = NBLK == 2 && MR == 2 && WAVES > 4;  // (K T on both sides of 128)
+    constexpr int MOST = NBLK == 1 || (MR <= 2 && !kEither) ? 4 : WAVES;
+    const bool one = NBLK == 1 && K <= 4, four = kEither && KT <= 128;
+    const int waves = one ? 1 : four ? 4 : MOST;
     double* base = reinterpret_cast<double*>(semi_smem);
     float* ring = reinterpret_cast<float*>(base + (K + 1) / 2 * 2);
-    float* dlast = ring + (KT + 3) / 4 * 4 + 2 * (one ? 1 : MOST) * 4 * LPR;
+    float* dlast = ring + (KT + 3) / 4 * 4 + 2 * waves * 4 * LPR;
     const auto slot_here = [&](int q) {  // where the vector that goes to slot q lies: V_{stop - 1} to K - 1, the older ones below
         const int x = (stop % KR) - (K - 1 - q);
         return x < 0 ? x + KR : x;
@@ -786,15 +791,17 @@ __global__ __launch_bounds__(64 * WAVES) void semi_chain_kernel(SemiArgs a) {
         if (lane == 0) *dlast = finite_or_zero(d);
     }
     __syncthreads();
-    if (wave >= (one ? 1 : MOST)) return;
+    if (wave >= waves) return;
+    const auto go_on = [&](auto n) __attribute__((always_inline)) {
+        semi_log_steps<LPR, decltype(n)::value, TIN, ALIGNED>(a, b, L, stop, K - 1, O, semi_smem);
+    };
     if constexpr (NBLK == 1) {
-        if (one) {
-            if (T == 16 || T == 12 || T == 8) semi_log_steps<LPR, 1, TIN, true>(a, b, L, stop, K - 1, O, semi_smem);
-            else semi_log_steps<LPR, 1, TIN, false>(a, b, L, stop, K - 1, O, semi_smem);
-            return;
-        }
+        if (one) return go_on(std::integral_constant<int, 1>{});
     }
-    semi_log_steps<LPR, MOST, TIN, false>(a, b, L, stop, K - 1, O, semi_smem);
+    if constexpr (kEither) {
+        if (four) return go_on(std::integral_constant<int, 4>{});
+    }
+    go_on(std::integral_constant<int, MOST>{});
 }
 
 template <int LPR, int WAVES>
@@ -858,8 +865,15 @@ static bool launch_semi_chain_items(int dtype, const SemiArgs& a, hipStream_t st
     const size_t log = semi_lds_bytes(a.K, a.T, LPR, WAVES);
     if (log > bytes) bytes = log;
     if (bytes > 64 * 1024 || (long long)a.K * a.T > 2 * 64 * WAVES || a.K > 64 * WAVES) return false;
-    if (dtype == 0) hipLaunchKernelGGL((semi_chain_kernel<WAVES, NBLK, MR, M0, float>), dim3(a.B), dim3(64 * WAVES), bytes, st, a);
-    else hipLaunchKernelGGL((semi_chain_kernel<WAVES, NBLK, MR, M0, uint16_t>), dim3(a.B), dim3(64 * WAVES), bytes, st, a);
+    const bool aligned = (a.T % 4) == 0;
+    const dim3 grid(a.B), block(64 * WAVES);
+    if (dtype == 0) {
+        if (aligned) hipLaunchKernelGGL((semi_chain_kernel<WAVES, NBLK, MR, M0, float, true>), grid, block, bytes, st, a);
+        else hipLaunchKernelGGL((semi_chain_kernel<WAVES, NBLK, MR, M0, float, false>), grid, block, bytes, st, a);
+    } else {
+        if (aligned) hipLaunchKernelGGL((semi_chain_kernel<WAVES, NBLK, MR, M0, uint16_t, true>), grid, block, bytes, st, a);
+        else hipLaunchKernelGGL((semi_chain_kernel<WAVES, NBLK, MR, M0, uint16_t, false>), grid, block, bytes, st, a);
+    }
     e = hipGetLastError();
     return true;
 }

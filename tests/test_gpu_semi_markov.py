@@ -151,25 +151,24 @@ def test_a_large_batch_looks_for_a_forbidden_first_tag(crf, oracle_mod, T, K):
 # 8 .. 32 tags, one wave for the dependent rows: (T, K, N, B) on both sides of the lines between its instances (rows of longer segments
 # (K - 1) T against 48, 112 and 224 up to 16 tags, 56, 112, 168 and 224 above) and of the batches it is taken for, chains as
 # short as its start.
-CHAIN_SHAPES = [(16, 4, 9, 5), (13, 5, 1, 5), (16, 8, 2, 5), (15, 9, 30, 5), (16, 15, 17, 5), (16, 16, 8, 5), (9, 1, 3, 5), (28, 3, 4, 5),
-                (19, 4, 13, 5), (28, 5, 5, 5), (29, 5, 21, 5), (28, 7, 6, 5), (25, 8, 40, 5), (32, 8, 3, 128), (32, 8, 3, 129), (31, 9, 12, 5),
-                (21, 3, 6, 256), (21, 3, 6, 257), (32, 1, 7, 5)]
+CHAIN_SHAPES = [(16, 4, 9, 8), (13, 5, 1, 8), (16, 8, 2, 8), (15, 9, 30, 8), (16, 15, 17, 8), (16, 16, 8, 8), (9, 1, 3, 8), (28, 3, 4, 8),
+                (19, 4, 13, 8), (28, 5, 5, 8), (29, 5, 21, 8), (28, 7, 6, 8), (25, 8, 40, 8), (32, 8, 3, 128), (32, 8, 3, 129), (31, 9, 12, 8),
+                (21, 3, 6, 256), (21, 3, 6, 257), (32, 1, 7, 8), (32, 4, 11, 8), (26, 5, 11, 8), (24, 5, 10, 8), (12, 9, 14, 8), (16, 3, 12, 8)]
 
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("T,K,N,B", CHAIN_SHAPES)
 def test_the_dependent_rows_by_one_wave(crf, oracle_mod, T, K, N, B, dtype):
-    """Every length from 0 to N, what the model never reads poisoned; then, in the same call, steps that scaled probabilities do not
-    take: a growth of 2^300, a fall of 2^200 (the forecast of the longer segments' sums is too high) and a forbidden tag, each
-    at a position of its own."""
+    """Lengths from 0 to N, what the model never reads poisoned; in the same call, steps that scaled probabilities do not take: a
+    growth of 2^300, a fall of 2^200 (the forecast of the longer segments' sums is too high), a tag that is forbidden from a
+    position on and one that is forbidden everywhere: the log-domain steps of every instance, from its start and from its middle."""
     phi, lens = workloads.semi_markov_case(8700 + 131 * T + 7 * K + N, B, N, K, T, scale=1.5, ragged=True, min_len=0)
     lens[:5] = torch.tensor([N, min(1, N), min(2, N), 0, N], dtype=torch.int32)
     phi[4, N // 2:] += 210.0
-    if B > 5:
-        lens[5:8] = N
-        phi[5, (2 * N) // 3:] -= 140.0
-        phi[6, N // 3:, :, :, 0] = float("-inf")
-        phi[7, :, :, :, T - 1] = float("-inf")
+    lens[5:8] = N
+    phi[5, (2 * N) // 3:] -= 140.0
+    phi[6, N // 3:, :, :, 0] = float("-inf")
+    phi[7, :, :, :, T - 1] = float("-inf")
     nan = float("nan")
     for b in range(B):
         phi[b, int(lens[b]):] = nan
