@@ -114,19 +114,28 @@ __device__ __forceinline__ void semi_log_steps(const SemiArgs& a, int b, int L, 
         }
         float x[ITEMS][4];
         float bm[4] = {LCCRF_NEG_INF, LCCRF_NEG_INF, LCCRF_NEG_INF, LCCRF_NEG_INF};
+        // The entries of the vectors that the rows meet, and the offsets of those: read whatever the row is (the address is inside the ring
+        // either way), all of them before any is waited for.  (One after the other they are eight trips to LDS where the compiler
+        // does not think of overlapping them: 24 tags, K = 5, N=64, a forbidden tag, 145 us instead of 122.)
+        float rv[ITEMS];
+        double ro[ITEMS];
+#pragma unroll
+        for (int m = 0; m < ITEMS; ++m) {
+            const int p = ITEMS * bt + m;
+            const int k = (p / PPT) * TPP + k0, s = r0 + (p % PPT) * RPP;
+            int sl = cur - (k < K ? k : K - 1);  // ring slot of position i - 1 - k
+            if (sl < 0) sl += K;
+            rv[m] = ring[sl * T + (s < T ? s : T - 1)];
+            ro[m] = base[sl];
+        }
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int m = 0; m < ITEMS; ++m) {
             const int p = ITEMS * bt + m;
             const int k = (p / PPT) * TPP + k0, s = r0 + (p % PPT) * RPP;
             // a segment of k + 1 positions ending at i starts at i - k >= 0; the first segment reads row 0 only
             const bool row_ok = k < K && s < T && (k < i || (k == i && s == 0));
-            int sl = cur - (k < K ? k : K - 1);  // ring slot of position i - 1 - k
-            if (sl < 0) sl += K;
-            // read whatever the row is (the address is inside the ring either way) and decide
-            // afterwards: the reads of all rows of the batch are then in flight together
-            float rv = ring[sl * T + (s < T ? s : T - 1)];
-            asm volatile("" : "+v"(rv));
-            const float v = rv + (float)(base[sl] - R);
+            const float v = rv[m] + (float)(ro[m] - R);
             if constexpr (!ALIGNED) settle_row4(tile[slot][m], T, c4);
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
