@@ -695,7 +695,9 @@ __global__ __launch_bounds__(64 * WAVES) void semi_chain_kernel(SemiArgs a) {
             float e[MR][4];
 #pragma unroll
             for (int m = 0; m < MR; ++m) {
-                const float c = (float)((int)((unsigned)base - (unsigned)Ov[m]));
+                // (no row: weight zero by the exponent.  Against the offset of a vector it does not meet a potential may be infinite: K = 1,
+                // potentials of -100, sent every chain to the log-domain steps, 30 -> 99 us)
+                const float c = srow[m] >= 0 ? (float)((int)((unsigned)base - (unsigned)Ov[m])) : __builtin_huge_valf();
 #pragma unroll
                 for (int j = 0; j < 4; ++j) e[m][j] = ex2(__builtin_fmaf(Raw::get(raw[at][m], j), kLog2e, -c));
             }
@@ -709,11 +711,9 @@ __global__ __launch_bounds__(64 * WAVES) void semi_chain_kernel(SemiArgs a) {
             }
             float acc[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int m = 0; m < MR; ++m) {
-                const float v = srow[m] >= 0 ? xv[m] : 0.f;
+            for (int m = 0; m < MR; ++m)
 #pragma unroll
-                for (int j = 0; j < 4; ++j) acc[j] = __builtin_fmaf(e[m][j], v, acc[j]);
-            }
+                for (int j = 0; j < 4; ++j) acc[j] = __builtin_fmaf(e[m][j], xv[m], acc[j]);
             float x = pair16(pair32(acc[0], acc[2]), pair32(acc[1], acc[3]));
             if (LPR <= 8) x += dpp<kDppRowRor8>(x);
             if (LPR <= 4) x += dpp<kDppRowRor4>(x);
