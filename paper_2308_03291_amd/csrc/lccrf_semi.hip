@@ -446,13 +446,14 @@ __global__ __launch_bounds__(64 * WAVES) void semi_linear_kernel(SemiArgs a) {
 // Offsets and tests are those of the kernel above.  With g_p the running average of what tag 0 grows by, up to position p, the first
 // matrix of p is held with the shift c_p = g_{p-3} less kSemiHead and the helpers' sums of p are in units of
 // 2^(O_{p-2} + 2 g_{p-2} - kSemiSumHead): their exponents reach kSemiSumHead - kSemiHead further below the sum they go into, which
-// is what the chain may stray from that forecast; if it strays further (the sums would have to be scaled up), the step is not
+// is what the chain may stray from that forecast.  If it strays further the sums are scaled up, by up to kSemiSumUp bits (what underflowed
+// in them is then at most K T 2^40 2^-126 2^7 of a sum of 2^-40, below 2^-30 for the K T <= 256 here); past that the step is not
 // accepted (independent normal potentials: none of 100 chains of 64 positions up to a deviation of 5, at 8 none that is not refused
-// for the spread of its vector as well).
+// for the spread of its vector as well).  With K = 1 there are no such sums.
 //
 // A position of 32 tags costs 0.42 us with K = 1, which is the chain, and 0.08 more for every row of longer segments a helper thread holds:
 // 0.70 with K = 8 where every wave doing the whole step costs 0.84 (B=1 N=64 56.3 -> 49.1 us); 0.40 for 11 tags, K = 3 (0.68).
-constexpr int kSemiSumHead = kSemiHead + 40;
+constexpr int kSemiSumHead = kSemiHead + 40, kSemiSumUp = 7;
 template <int WAVES, int NBLK>
 struct SemiChainShape {
     static constexpr int U = 16 * NBLK, RS = U + 4, VS = U, H = WAVES - 1;
@@ -570,7 +571,7 @@ __global__ __launch_bounds__(64 * WAVES) void semi_chain_kernel(SemiArgs a) {
                 x += on ? __builtin_amdgcn_ldexpf(sum, D) : 0.f;
                 const int kx = uniform(__builtin_amdgcn_frexp_expf(x));
                 const float v = __builtin_amdgcn_ldexpf(x, -kx);
-                const bool good = accepted(x, v) && D <= 0;
+                const bool good = accepted(x, v) && (D <= kSemiSumUp || K == 1);
                 if (good) {
                     V = v;
                     O += cA + kx;
