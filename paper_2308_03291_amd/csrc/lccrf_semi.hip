@@ -468,7 +468,8 @@ __global__ __launch_bounds__(64 * WAVES) void semi_chain_kernel(SemiArgs a) {
     using Raw = RawPiece<TIN>;
     using S = SemiChainShape<WAVES, NBLK>;
     constexpr int W = 64 * WAVES, LPR = 4 * NBLK, H = S::H, G = 64 * H / LPR, ITEMS = MR + M0;
-    constexpr int PH = Raw::WORDS * ITEMS * 3 <= (WAVES == 16 ? 64 : 96) ? 3 : 2;  // positions in flight
+    constexpr int PH = Raw::WORDS * ITEMS * 3 <= 96 ? 3 : 2;  // positions in flight
+    static_assert(WAVES <= 8, "the registers of two waves a SIMD");
     static_assert(G * M0 >= S::U, "the helpers cover a matrix");
     constexpr bool kSplit = NBLK == 2;
     constexpr int NB = kSplit ? 1 : NBLK;
@@ -764,7 +765,7 @@ __global__ __launch_bounds__(64 * WAVES) void semi_chain_kernel(SemiArgs a) {
         }
     }
     // Not accepted at some position: from there on in the log domain, from the K vectors in front of it, through registers (both
-    // states begin where the other does).  By as many waves as the kernel above would have (more meet at more barriers: K=4 T=16 B=200 N=64,
+    // states begin where the other does).  By one wave, four or eight, as their rows take (more meet at more barriers: K=4 T=16 B=200 N=64,
     // deviation 12, by all four 110 us, by one 86; fewer take more rounds: 27 tags, K = 5, a forbidden tag, N=64, by eight 127, by four
     // 160); the others leave.
     if (wave == 0 && lane == 0) info[3] = stop;
@@ -848,18 +849,15 @@ static bool launch_semi_items(int dtype, const SemiArgs& a, hipStream_t st, hipE
     return true;
 }
 // The scaled-probability kernel where it serves the shape: up to eight rows of the (K T) x T block a thread.  false: it does not.
-// Few rows a wave are worth more than few waves (us, N=256 B=1, so / log-domain steps: 32 tags K=8 214 (four waves of eight rows:
-// 289) / 513, K=2 132 / 333; 16 tags K=8 134 / 392; 64 tags K=8 553 / 2044; 8 tags K=2 166 / 321; N=64 B=1024: 32 tags K=8 355 / 383,
-// 20 tags K=3 55 / 151).  A tag that is forbidden everywhere sends a sequence to the log-domain steps at its first position; in
+// Few rows a wave are worth more than few waves (us, N=256 B=1, so / log-domain steps, the smaller of these before the chain wave took
+// them: 32 tags K=8 214 (four waves of eight rows: 289) / 513, K=2 132 / 333; 16 tags K=8 134 / 392; 64 tags K=8 553 / 2044; N=64
+// B=1024: 32 tags K=8 355 / 383, 20 tags K=3 55 / 151).  A tag that is forbidden everywhere sends a sequence to the log-domain steps at its first position; in
 // large batches before anything is fetched (32 tags K=8 N=64, so / log-domain steps alone: B=1024 384 / 391 (blocks fetched first:
 // 393), B=300 167 / 176, B=1 108 / 127; 20 tags K=3 B=1024 152 / 151).
 template <int LPR>
 static bool launch_semi_linear(int dtype, const SemiArgs& a, hipStream_t st, hipError_t& e) {
     const long long rows = (long long)a.K * a.T;
     constexpr int G = 64 / LPR;  // rows a wave holds at a time
-    if constexpr (LPR == 4) {
-        if (a.K <= 4) return launch_semi_items<1, LPR, 4>(dtype, a, st, e);
-    }
     if (rows <= 2 * 4 * G) return launch_semi_items<4, LPR, 2>(dtype, a, st, e);
     if (rows <= 4 * 4 * G) return launch_semi_items<4, LPR, 4>(dtype, a, st, e);
     if (rows <= 4 * 8 * G) return launch_semi_items<8, LPR, 4>(dtype, a, st, e);
