@@ -563,8 +563,10 @@ __device__ __forceinline__ void expect_linear_chain(EntropySmem<ExpectGeo<WAVES>
         if (!PLAIN) a.hoff[2 * b + dir] = Hoff;
     }
 }
+// (Three waves a SIMD: two potentials an edge off the 16-byte grid take 169 registers, and with one less a third workgroup has room:
+// divergence B=300 N=64 T=57 125 -> 121 us.)
 template <int WAVES, int ITEMS, typename TIN, bool ALIGNED, int MODE>
-__global__ __launch_bounds__(64 * WAVES) void expect_linear_kernel(ChainArgs a) {
+__global__ __launch_bounds__(64 * WAVES, 3) void expect_linear_kernel(ChainArgs a) {
     __shared__ EntropySmem<ExpectGeo<WAVES>> sm;
     __shared__ ExpectSmem<WAVES> lin;
     const bool plain = MODE != 0 && (int)blockIdx.x >= 2 * a.B;

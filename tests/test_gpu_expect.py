@@ -51,6 +51,20 @@ def test_steps_that_leave_the_scaled_range(crf, oracle_mod, T, dtype):
     _check_all(crf, oracle_mod, p, q, lens, f"T={T} {dtype}")
 
 
+@pytest.mark.parametrize("T", [36, 47, 50, 64])
+@pytest.mark.parametrize("N", [5, 6, 7, 8, 9, 10])
+def test_a_refused_step_at_every_place_of_a_chain(crf, oracle_mod, T, N):
+    """The steps go three a round, the last one or two behind the rounds: every remainder of both half chains, and a step that scaled
+    probabilities do not take (entries two hundred bits apart) at every position, once each."""
+    p, q, _ = _pair(9250 + 16 * T + N, 2 * N, N, T, dtype="f32", ragged=False, min_len=N)
+    lens = torch.full((2 * N,), N, dtype=torch.int32)
+    lens[N:] = torch.arange(N) + 1
+    for i in range(1, N):
+        p[i, i, :, 2] += 90.0
+        p[i, i, 1, :] -= 90.0
+    _check_all(crf, oracle_mod, p, q, lens, f"T={T} N={N}")
+
+
 @pytest.mark.parametrize("T,N", [(33, 16), (33, 256), (48, 256), (64, 128), (64, 256)])
 def test_entropy_of_nearly_deterministic_chains(crf, oracle_mod, T, N):
     """One path, a random one or one that stays in a tag for long, carries nearly all of the weight: the scaled chains form a small
