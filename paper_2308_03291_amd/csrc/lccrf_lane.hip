@@ -296,13 +296,20 @@ __device__ __forceinline__ int lane_log_dense(const ChainArgs& a, const LaneJob&
             for (int k = 0; k < 4; ++k) y[4 * p + k] = RawPiece<TIN>::get(x, k);
         }
     }
+    float from[C > 1 ? P : 1];
+    if constexpr (C > 1) {  // (all of them requested before one is waited for: left to the compiler it was a trip to LDS for every pair in the
+                            // one build and not in the other, log-probability B=128 N=128 T=32 deviation 16 64.5 and 62.0 us; so 61.0)
+#pragma unroll
+        for (int p = 0; p < P; ++p) from[p] = buf[start + p];
+        __builtin_amdgcn_sched_barrier(0);
+    }
     float mx = LCCRF_NEG_INF;
 #pragma unroll
     for (int p = 0; p < P / 4; ++p)
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             const int s = C == 1 ? min(4 * p, T - 4) : 4 * p;
-            const float x = buf[start + s + k] + y[4 * p + k] * kLog2e;
+            const float x = (C > 1 ? from[C > 1 ? 4 * p + k : 0] : buf[start + s + k]) + y[4 * p + k] * kLog2e;
             y[4 * p + k] = (C == 1 ? s + k >= 4 * p : s + k >= skip) ? x : LCCRF_NEG_INF;
             mx = fmaxf(mx, y[4 * p + k]);
         }
@@ -601,7 +608,8 @@ __device__ __forceinline__ void lane_chain_wave(const ChainArgs& a, const LaneJo
     // way out of every step four were taken a step, of 110 instructions where 90 do: 0.25 -> 0.215 us at 32 tags.  Log-probability
     // B=128 N=256 T=32 42.5 -> 38.4 us, sampling there 99 -> 89, log-probability B=100 N=200 T=45 bfloat16 46.0 -> 42.8, marginals B=128
     // N=200 T=30 62.3 -> 59.2.  With zeros accepted, where the quick way is left often, the ways out of every step are the cheaper
-    // form: independent normal potentials of deviation 16, log-probability B=128 N=128 T=32 62.0 / 64.9 so, 67.4 without.)
+    // form: independent normal potentials of deviation 16, log-probability B=128 N=128 T=32 64.9 us so, 67.4 with rounds there too; both
+    // before `lane_log_dense` requested its vector at once, 61.0 since.)
     // The second pass of 33 .. 48 tags keeps the way out of every step as well: there the chain comes to wait for its producers, and a round
     // that a matrix is missing in costs more than the branches (marginals B=25 N=237 T=45 101.5 us so, 105.5 without).
     constexpr bool kQuick = !(PASS2 && NBLK == 3);
