@@ -29,7 +29,8 @@
  *    are undefined.
  *  - workspace: device scratch of at least lccrf_workspace_bytes(op, ...) bytes,
  *    256-byte aligned, not shared by calls that may overlap in time.  Contents on
- *    entry are irrelevant; contents on exit are unspecified.
+ *    entry are irrelevant; contents on exit are unspecified.  (The best-path queries
+ *    above 64 tags take less, see LCCRF_OP_ARGMAX.)
  *  - 1 <= T <= LCCRF_MAX_T, B >= 1, N >= 1, B*N*T*T < 2^62.
  *  - Return value: LCCRF_OK (0) or a negative lccrf_status.  Argument errors (every
  *    status but LCCRF_ELAUNCH) are found before anything is enqueued.  A query is
@@ -73,8 +74,11 @@ typedef enum { LCCRF_F32 = 0, LCCRF_BF16 = 1 } lccrf_dtype;
 typedef enum {
     LCCRF_OP_LOGZ = 0,
     LCCRF_OP_MARGINALS = 1,
-    LCCRF_OP_ARGMAX = 2, /* above 64 tags the size may hold B*N*T doubles (rounded up to 256 bytes) at its end that a call can do
-                          * without: it then takes a slower schedule with the same results */
+    LCCRF_OP_ARGMAX = 2, /* Above 64 tags lccrf_argmax, its _algo form and lccrf_argmax_structured need B*N*T bytes and 2*B*T
+                          * doubles, each rounded up to 256 bytes, and are refused with less.  lccrf_workspace_bytes may add
+                          * B*N*T doubles (rounded up likewise, at most 512 MB) for shapes that are quicker with the scores of
+                          * every position kept; a call that brings less than all of it takes the other kernels, with the same
+                          * results.  Up to 64 tags all of lccrf_workspace_bytes is needed. */
     LCCRF_OP_LOG_PROB = 3,
     LCCRF_OP_ENTROPY = 4,
     LCCRF_OP_SAMPLE = 5,
@@ -113,15 +117,17 @@ typedef enum {
     LCCRF_OK = 0,
     LCCRF_EINVAL = -1,     /* bad B, N, T (1 <= T <= 256, B * N < 2e9), dtype, op or algo */
     LCCRF_ENULL = -2,      /* a required pointer is NULL */
-    LCCRF_EWORKSPACE = -3, /* workspace NULL or smaller than lccrf_workspace_bytes */
+    LCCRF_EWORKSPACE = -3, /* workspace NULL or smaller than lccrf_workspace_bytes (LCCRF_OP_ARGMAX above 64 tags: than the
+                            * minimum stated there) */
     LCCRF_EALIGN = -4,     /* phi, an output or the workspace is misaligned */
     LCCRF_ELAUNCH = -5,    /* the HIP runtime refused a launch */
     LCCRF_ENOTIMPL = -6,   /* the requested algo does not exist for this shape */
     LCCRF_ETOOBIG = -7     /* lccrf_marginals_static: the shape needs more than the built-in scratch */
 } lccrf_status;
 
-/* Bytes of device scratch the given query needs (a multiple of 256); 0 on invalid
- * arguments.  Valid for every lccrf_algo. */
+/* Bytes of device scratch the given query needs (a multiple of 256; LCCRF_OP_ARGMAX
+ * above 64 tags: can make use of, see there); 0 on invalid arguments.  Valid for every
+ * lccrf_algo. */
 size_t lccrf_workspace_bytes(lccrf_op op, int B, int N, int T, lccrf_dtype dt);
 
 /*
@@ -345,7 +351,9 @@ int lccrf_set_lane_poll_limit(int polls);
 /* The schedule LCCRF_ALGO_AUTO takes for `op` at this shape under the current chunk size:
  * LCCRF_ALGO_SEQUENTIAL, LCCRF_ALGO_SEQUENTIAL_LANES or LCCRF_ALGO_SCAN.  Host-side arithmetic, nothing is launched;
  * LCCRF_EINVAL for a shape or op the library does not serve.  For callers that size or time a run
- * by the schedule it will take (the benchmark names its dominant kernel from it). */
+ * by the schedule it will take (the benchmark names its dominant kernel from it).  Best paths
+ * above 64 tags are LCCRF_ALGO_SEQUENTIAL, whether their pointers are found along the chains or,
+ * with the whole workspace, from the scores afterwards. */
 int lccrf_auto_algo(lccrf_op op, int B, int N, int T);
 
 /* Static, human-readable text for a status code. */

@@ -115,6 +115,24 @@ def test_bad_arguments_are_rejected_without_a_gpu(lib):
     assert lib.lccrf_argmax_algo(fake, 0, None, 1, 4, 4, None, fake, fake, ws, None, 17) == EINVAL
 
 
+@pytest.mark.parametrize("dt", (0, 1))
+@pytest.mark.parametrize("B,N,T", [(1, 6, 65), (7, 33, 128), (4, 50, 145), (600, 30, 100), (2000, 600, 256)])
+def test_best_paths_above_64_tags_state_the_least_workspace(lib, B, N, T, dt):
+    """What the header says such a call cannot do without is accepted (the next check, the workspace's alignment, is then the one
+    that fails), 256 bytes less are not; what it may bring besides is B*N*T doubles or nothing."""
+    def up(n):
+        return (n + 255) // 256 * 256
+    fake, EWS, EALIGN = 4096, -3, -4
+    least, size = up(B * N * T) + up(16 * B * T), binding.workspace_bytes(binding.OP_ARGMAX, B, N, T, dt)
+    assert size in (least, least + up(8 * B * N * T))
+    assert size - least <= 1 << 29
+    assert lib.lccrf_argmax(fake, dt, None, B, N, T, None, fake, fake + 16, least, None) == EALIGN
+    assert lib.lccrf_argmax(fake, dt, None, B, N, T, None, fake, fake, least - 256, None) == EWS
+    if T <= 128 and dt == 0:
+        assert lib.lccrf_argmax_structured(fake, fake, None, B, N, T, None, fake, fake + 16, least, None) == EALIGN
+        assert lib.lccrf_argmax_structured(fake, fake, None, B, N, T, None, fake, fake, least - 256, None) == EWS
+
+
 def test_tuning_knobs_check_their_range(lib):
     assert lib.lccrf_set_scan_chunk(3) == -1 and lib.lccrf_set_scan_chunk(5000) == -1
     assert lib.lccrf_set_scan_chunk(0) == 0
