@@ -7,10 +7,11 @@
 //                            of the other kernels: every score is the same number) and stores the vector in front of every position;
 //   viterbi_pointers_kernel  finds the pointers of all positions from them, the whole chip at once;
 // the trace follows as behind the other kernels.  A chain is bound by its double-precision additions, conversions and maxima
-// (T^2 a step on one compute unit), the pointers by the second reading of the potentials (6.5 TB/s at B=64 N=40 T=128).
-// Measured, whole argmax, us, chains with tags / these: B=8 N=64 T=78 65 / 41 (the chains 31, the pointers 4), bf16 B=32 N=100
-// T=96 125 / 71, B=4 N=50 T=145 134 / 60, bf16 B=2 N=60 T=201 235 / 94, B=8 N=30 T=256 107 / 71; structured B=5 N=41 T=70 66 / 28,
-// B=64 N=100 T=96 150 / 76, B=600 N=30 T=100 224 / 146.  Where it is not taken: B=64 N=40 T=128 46 / 57, B=128 N=40 T=145 130 / 167.
+// (T^2 a step on one compute unit), the pointers of large calls by the second reading of the potentials (6.1 TB/s at B=4 N=512 T=128, 6.2
+// at B=8 N=512 T=256, 3.6 for bfloat16 rows off the 8-byte grid, B=32 N=256 T=201), structured ones by their comparisons.
+// Measured, whole argmax, us, chains with tags / these: B=8 N=64 T=78 65 / 39 (the chains 29, the pointers 5), bf16 B=32 N=100
+// T=96 125 / 72, B=4 N=50 T=145 134 / 60, bf16 B=2 N=60 T=201 234 / 94, B=8 N=30 T=256 107 / 71; structured B=5 N=41 T=70 66 / 28,
+// B=64 N=100 T=96 150 / 75, B=600 N=30 T=100 223 / 147.  Where it is not taken: B=64 N=40 T=128 46 / 57, B=128 N=40 T=145 130 / 167.
 //
 // Layout of a chain: sixteen waves, LPR lanes a row with four columns each, ITEMS rows a thread.  Loads never leave a matrix: rows
 // past it are its last row again, and the last piece of a row is moved back to end with it; what is then held twice is the

@@ -245,7 +245,7 @@ __global__ __launch_bounds__(64 * WAVES) void semi_forward_kernel(SemiArgs a) {
 //
 // Layout: row r = k T + s of the block, LPR lanes a row, G = W / LPR row groups; thread (g, cl) holds rows g, g + G, ...; the
 // last piece of a row is moved back to end with it, rows past the block are its last one again, as in lccrf_linear.h.
-// A step of 32 tags, K = 8 costs 0.84 us (log-domain steps 2.0): two LDS round trips and the barrier on the dependent path, then
+// A step of 32 tags, K = 8 costs 0.81 us (log-domain steps 2.0): two LDS round trips and the barrier on the dependent path, then
 // the next block's exponentials, which wait for the newest offset.
 constexpr int kSemiHead = 24;
 constexpr int kSemiLookFirst = 256;  // batches above the number of compute units
@@ -451,8 +451,9 @@ __global__ __launch_bounds__(64 * WAVES) void semi_linear_kernel(SemiArgs a) {
 // accepted (independent normal potentials: none of 100 chains of 64 positions up to a deviation of 5, at 8 none that is not refused
 // for the spread of its vector as well).  With K = 1 there are no such sums.
 //
-// A position of 32 tags costs 0.42 us with K = 1, which is the chain, and 0.08 more for every row of longer segments a helper thread holds:
-// 0.70 with K = 8 where every wave doing the whole step costs 0.84 (B=1 N=64 56.3 -> 49.1 us); 0.40 for 11 tags, K = 3 (0.68).
+// A position of 32 tags costs 0.42 us with K = 1, which is the chain, and 0.04 .. 0.08 more for every row of longer segments a helper thread
+// holds: 0.50 with K = 4, 0.67 with K = 8 where every wave doing the whole step costs 0.81 (from N=64 to N=256 at B=1; whole calls of
+// N=64 56.7 -> 48.7 us); 0.33 for 11 tags, K = 3 (0.62).
 constexpr int kSemiSumHead = kSemiHead + 40, kSemiSumUp = 7;
 template <int WAVES, int NBLK>
 struct SemiChainShape {
