@@ -294,7 +294,7 @@ __device__ __forceinline__ int expect_run(ExpectSmem<WAVES>& sm, const TIN* phib
         prepare(next, at + PH, c_next, more);
     };
     const int rest = n % 3;
-    for (int r = n / 3; going && r > 0; --r) {
+    while (going && at + 3 <= n) {
         step(1, std::true_type{});
         step(2, std::true_type{});
         step(0, std::true_type{});
