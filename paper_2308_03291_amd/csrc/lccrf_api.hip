@@ -397,7 +397,7 @@ int sum_query(int op, const void* phi, int dt, const int32_t* lengths, int B, in
         algo == LCCRF_ALGO_AUTO ? reinterpret_cast<unsigned long long*>(base + w.mail) : nullptr,
         reinterpret_cast<int*>(base + w.failed), nullptr, nullptr, nullptr,
         g_pair_poll_limit.load(std::memory_order_relaxed), algo == LCCRF_ALGO_AUTO ? current_device_cus() : 0, lanes,
-        g_lane_poll_limit.load(std::memory_order_relaxed));
+        g_lane_poll_limit.load(std::memory_order_relaxed), base + w.maps);
     if (e != hipSuccess) return LCCRF_ELAUNCH;
     if (ev_end && hipEventRecord(static_cast<hipEvent_t>(ev_end), st) != hipSuccess) return LCCRF_ELAUNCH;
     return LCCRF_OK;
@@ -555,8 +555,8 @@ static hipError_t launch_log_partition64(const void* phi, int dt, const int32_t*
     return lccrf::launch_sequential_sum(0, dt, phi, lengths, B, N, T, reinterpret_cast<float*>(base + w.ua),
                                         reinterpret_cast<float*>(base + w.ub), reinterpret_cast<double*>(base + w.Oa),
                                         reinterpret_cast<double*>(base + w.Ob), nullptr, nullptr, st, nullptr, false,
-                                        nullptr, nullptr, lz64, nullptr, nullptr, 0, 0, lanes,
-                                        g_lane_poll_limit.load(std::memory_order_relaxed));
+                                        nullptr, nullptr, lz64, nullptr, nullptr, 0, current_device_cus(), lanes,
+                                        g_lane_poll_limit.load(std::memory_order_relaxed), base + w.maps);
 }
 
 int lccrf_log_prob(const void* phi, lccrf_dtype dt, const int32_t* lengths, const int32_t* tags, int B, int N, int T,
@@ -578,7 +578,8 @@ int lccrf_log_prob(const void* phi, lccrf_dtype dt, const int32_t* lengths, cons
     const double* lz64 = nullptr;
     hipError_t e;
     if (lanes || (T > 32 && !scan_pays_sum(B, N, T))) {
-        e = lccrf::launch_meeting_vectors(dt, phi, lengths, B, N, T, ua, ub, Oa, Ob, lanes, g_lane_poll_limit.load(std::memory_order_relaxed), st);
+        e = lccrf::launch_meeting_vectors(dt, phi, lengths, B, N, T, ua, ub, Oa, Ob, lanes, g_lane_poll_limit.load(std::memory_order_relaxed),
+                                           current_device_cus(), base + w.maps, st);
     } else {
         e = launch_log_partition64(phi, dt, lengths, B, N, T, w, base, st);
         lz64 = reinterpret_cast<const double*>(base + w.lz64);
@@ -730,7 +731,7 @@ static int sample_query(const void* phi, lccrf_dtype dt, const int32_t* lengths,
             e = lccrf::launch_chunked_full_forward(dt, phi, lengths, B, N, T, ua, ub, Oa, Ob, scan_chunk(B, N, T), Fv, OF, st);
     } else {
         e = lccrf::launch_full_forward(dt, phi, lengths, B, N, T, ua, ub, Oa, Ob, lanes,
-                                       g_lane_poll_limit.load(std::memory_order_relaxed), st);
+                                       g_lane_poll_limit.load(std::memory_order_relaxed), current_device_cus(), base + w.maps, st);
     }
     if (e == hipSuccess)
         e = lccrf::launch_backward_sample(dt, phi, lengths, ua, Oa, seeded ? nullptr : uniforms, seed, B, N, T,

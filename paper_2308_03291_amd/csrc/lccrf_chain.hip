@@ -39,6 +39,7 @@
 #include "lccrf_device.h"
 #include "lccrf_launch.h"
 #include "lccrf_linear.h"
+#include "lccrf_pieces.h"
 
 namespace lccrf {
 
@@ -803,54 +804,18 @@ __device__ __attribute__((noinline)) LogStepsResult chain_log_steps(const void* 
     return r;
 }
 
-// ITEMS: rows a thread holds of a matrix, linear_instance(G::W, T).
-template <typename G, typename TIN, bool ALIGNED, int ITEMS>
+// ITEMS: rows a thread holds of a matrix, linear_instance(G::W, T).  COMPARE: the second launch of a chain in pieces (lccrf_pieces.h).
+template <typename G, typename TIN, bool ALIGNED, int ITEMS, bool COMPARE>
 __global__ __launch_bounds__(G::W, 4) void linear_half_kernel(ChainArgs a) {  // (four waves a SIMD: large batches of 33 .. 64 tags)
     using LG = LinGeo<G::WAVES, G::TCAP, ITEMS>;
-    LinSmem<LG>& lin = *reinterpret_cast<LinSmem<LG>*>(half_smem);
-    const int tid = threadIdx.x;
-    const int dir = blockIdx.x & 1, b = blockIdx.x >> 1;
-    const int N = a.N, T = a.T;
-    const int L = clamp_length(a.lengths, b, N);
-    if (L == 0 || (a.full_forward && dir == 1)) return;
-    const int e = L - 1;
-    const int mid = meeting_point(0, e);
-    const size_t vb = (size_t)b * N;
-    const TIN* phib = static_cast<const TIN*>(a.phi) + vb * T * T;
-    float* uout = (dir == 0 ? a.ua : a.ub) + vb * T;
-    double* Oout = (dir == 0 ? a.Oa : a.Ob) + vb;
-    // the vector the chain starts from, and the positions it walks
-    const int start = a.extend ? mid : dir == 0 ? 0 : e;
-    const int end = a.extend ? (dir == 0 ? e : 0) : dir == 0 ? forward_end(a, 0, e) : mid;
-    const int first = dir == 0 ? start + 1 : start, n = dir == 0 ? end - start : start - end;
-    float v = LCCRF_NEG_INF;
-    double O = 0.0;
-    if (a.extend) {
-        if (tid < T) v = uout[(size_t)start * T + tid];
-        O = Oout[start];
-    } else if (tid < T) {
-        v = dir == 0 ? Elem<TIN>::get(phib + tid) * kLog2e : 0.f;
+    if (!COMPARE && a.pair_mail && a.piece_pass == 0 && (blockIdx.x & 1) == 0 && (int)blockIdx.x < 2 * a.B) {  // (as chain_half_kernel does)
+        const int b = blockIdx.x >> 1;
+        for (int k = threadIdx.x; k < a.pair_words; k += G::W) a.pair_mail[(size_t)b * a.pair_words + k] = 0ull;
+        if (threadIdx.x == 0) a.pair_failed[b] = 0;
     }
-    int steps = 0;
-    LogBlocks blocks;
-    const float x = tid < T ? (dir == 1 && !a.extend ? Elem<TIN>::get(phib + tid) : v) : 0.f;
-    blocks.hopeless = a.exact_only || (n > 0 && linear_hopeless(phib + (size_t)first * T * T, T, dir == 1, x == LCCRF_NEG_INF, v));
-    for (;;) {
-        const int before = steps;
-        if (!blocks.hopeless) {
-            if (dir == 0) steps = linear_run<LG, TIN, ALIGNED, false>(lin, {phib, T, first, n, uout, Oout}, v, steps, O);
-            else steps = linear_run<LG, TIN, ALIGNED, true>(lin, {phib, T, first, n, uout, Oout}, v, steps, O);
-        }
-        if (steps >= n) break;
-        const int m = blocks.next(steps - before, n - steps);
-        const LogStepsResult r = chain_log_steps<G, TIN, ALIGNED>(a.phi, a.ua, a.ub, a.Oa, a.Ob, a.B, N, T, a.exact_only, b, dir,
-                                                                  dir == 0 ? first + steps : first - steps, m, v, O);
-        v = r.v;
-        O = r.O;
-        steps += m;
-    }
-    if (tid < T) uout[(size_t)end * T + tid] = v;
-    if (tid == 0) Oout[end] = O;
+    piece_walk<LG, TIN, ALIGNED, COMPARE>(*reinterpret_cast<LinSmem<LG>*>(half_smem), a, [&](int b, int dir, int first, int m, float v, double O) {
+        return chain_log_steps<G, TIN, ALIGNED>(a.phi, a.ua, a.ub, a.Oa, a.Ob, a.B, a.N, a.T, a.exact_only, b, dir, first, m, v, O);
+    });
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1041,7 +1006,6 @@ struct PairPlan {
     int* failed;
     int dtype;
     int poll_limit;
-    int cus;
 };
 
 // The first pass in the log domain (whole sequences, the chunks of the scan) ...
@@ -1058,24 +1022,69 @@ static hipError_t launch_chain_half(const ChainArgs& a, hipStream_t st) {
     return hipGetLastError();
 }
 // ... and in scaled probabilities (whole sequences).
-template <typename G, typename TIN, bool ALIGNED, int ITEMS>
-static hipError_t launch_linear_items(const ChainArgs& a, hipStream_t st) {
+template <typename G, typename TIN, bool ALIGNED, int ITEMS, bool COMPARE>
+static hipError_t launch_linear_items(const ChainArgs& a, int workgroups, hipStream_t st) {
     const size_t lin = sizeof(LinSmem<LinGeo<G::WAVES, G::TCAP, ITEMS>>), turn = turn_floats<G>() * sizeof(float);
     const size_t bytes = lin > turn ? lin : turn;
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&linear_half_kernel<G, TIN, ALIGNED, ITEMS>),
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&linear_half_kernel<G, TIN, ALIGNED, ITEMS, COMPARE>),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((linear_half_kernel<G, TIN, ALIGNED, ITEMS>), dim3(2 * a.B), dim3(G::W), bytes, st, a);
+    hipLaunchKernelGGL((linear_half_kernel<G, TIN, ALIGNED, ITEMS, COMPARE>), dim3(workgroups), dim3(G::W), bytes, st, a);
     return hipGetLastError();
 }
 template <typename G, typename TIN, bool ALIGNED>
 static hipError_t launch_linear_half(const ChainArgs& a, hipStream_t st) {
+    ChainArgs as = a;
+    as.pieces = a.pieces > 1 ? a.pieces : 1;
+    const bool compare = as.pieces > 1 && a.piece_pass == 1;
+    const int workgroups = 2 * a.B * (as.pieces == 1 || a.piece_pass == 2 ? 1 : compare ? as.pieces - 1 : as.pieces);
     switch (linear_instance(G::W, a.T)) {  // 2 (33 or 65 tags) .. 4
-        case 2: return launch_linear_items<G, TIN, ALIGNED, 2>(a, st);
-        case 3: return launch_linear_items<G, TIN, ALIGNED, 3>(a, st);
-        case 4: return launch_linear_items<G, TIN, ALIGNED, 4>(a, st);
+#define LCCRF_LINEAR_HALF(I) case I: return compare ? launch_linear_items<G, TIN, ALIGNED, I, true>(as, workgroups, st) : launch_linear_items<G, TIN, ALIGNED, I, false>(as, workgroups, st)
+        LCCRF_LINEAR_HALF(2);
+        LCCRF_LINEAR_HALF(3);
+        LCCRF_LINEAR_HALF(4);
+#undef LCCRF_LINEAR_HALF
     }
     return hipErrorInvalidValue;
+}
+
+// The buffers of chains in pieces (ChainArgs), in a scratch of B N T bytes: 4 (2 T + 8) B C of them and C <= N / kPieceSteps.
+static void set_pieces(ChainArgs& a, int pieces, void* scratch) {
+    const size_t slots = (size_t)2 * a.B * pieces;
+    char* p = static_cast<char*>(scratch);
+    a.pieces = pieces;
+    a.end_offsets = reinterpret_cast<double*>(p);
+    a.end_offsets2 = a.end_offsets + slots;
+    a.deltas = a.end_offsets2 + slots;
+    a.ends = reinterpret_cast<float*>(a.deltas + slots);
+    a.ends2 = a.ends + slots * a.T;
+    a.matched_from = reinterpret_cast<int*>(a.ends2 + slots * a.T);
+}
+static_assert(kPieceSteps >= 18, "the buffers of a piece take 8 (2 T + 7) bytes of a sequence's N T at 65 tags and more, two chains a sequence");
+
+// The chains of a first pass in pieces, where that pays if the potentials forget quickly.  whole: to the far ends; forward: one chain a
+// sequence, over all of it.  One workgroup a chain takes about 0.7 + 5.5e-5 T^2 us a step (96 tags 1.2, 201 tags 2.6 .. 3.5) and all of them
+// together draw 6.5 TB/s at most; the launches, the guess and the two more beginnings take about 18 us; eight steps to a match.  us, as a
+// whole / in pieces: log-partition B=10 N=135 T=96 91 / 66, B=4 N=256 T=256 482 / 155; marginals B=2 N=447 T=85 bfloat16 420 / 88, B=32 N=256
+// T=201 bfloat16 1293 / 743.  Where the potentials forget slowly the guess and two launches that have nothing to do are lost: 8 us (independent
+// scores of deviation three, log-partition B=1 N=126 T=156 110 / 118, B=15 N=274 T=130 189 / 197); a gain below 28 % is left alone for that.
+static void cut_chains(ChainArgs& a, int dtype, bool whole, bool forward, int cus, void* scratch) {
+    a.pieces = 1;
+    if (cus <= 0 || a.T <= 64 || a.T > 256 || !scratch) return;
+    const int chains = forward ? a.B : 2 * a.B, n = whole || forward ? a.N - 1 : a.N / 2;
+    const double alone = 0.7 + 5.5e-5 * a.T * a.T, bytes = (double)chains * a.T * a.T * (dtype == 0 ? 4 : 2);
+    double best = (a.T <= 128 && dtype == 0 ? 0.65 : 0.72) * n * alone;  // (single precision up to 128 tags: the turned steps are quicker than these)
+    int pieces = 1;
+    for (int C = 2; C * chains <= cus && C * kPieceSteps <= n; ++C) {
+        const double step = C * bytes / 6.5e6, us = (step > alone ? step : alone) * ((double)n / C + 8) + 18.0;
+        if (us < best) {
+            best = us;
+            pieces = C;
+        }
+    }
+    if (pieces == 1) return;
+    set_pieces(a, pieces, scratch);
+    a.piece_overhead = (int)(18.0 / alone);
 }
 
 // Whether the second halves of few chains take their steps without writing, and one more kernel writes the marginals with the
@@ -1095,13 +1104,17 @@ bool marginals_by_edges(int dtype, int B, int T, int cus) {
 
 template <typename G, typename TIN, bool ALIGNED, int PF1, int PF2>
 static hipError_t launch_geo(int op, ChainArgs a, hipStream_t st, hipEvent_t between, const PairPlan& pair) {
-    const bool spread = op == 1 && a.chunk <= 0 && a.T > 64 && marginals_by_edges(pair.dtype, a.B, a.T, pair.cus);
-    // Otherwise the first pass runs in scaled probabilities for bfloat16 rows off the 8-byte grid, which linear_run widens
+    // Otherwise the first pass runs in scaled probabilities in pieces, and for bfloat16 rows off the 8-byte grid, which linear_run widens
     // where they are used and not where they are loaded (B=64 N=256 T=99 log-partition 292 -> 169 us, B=1024 N=64 T=45 160 -> 92);
     // elsewhere the turned steps are as quick or quicker at these sizes (single precision B=64 N=256 T=100 185 / 178,
     // B=64 N=512 T=128 422 / 469, B=64 N=256 T=64 104 / 108).
-    const bool linear = a.chunk <= 0 && !a.exact_only && (spread || (!ALIGNED && sizeof(TIN) == 2));
-    hipError_t e = linear ? launch_linear_half<G, TIN, ALIGNED>(a, st) : launch_chain_half<G, TIN, ALIGNED, PF1>(a, st);
+    const bool linear = a.chunk <= 0 && !a.exact_only && (a.whole || a.pieces > 1 || (!ALIGNED && sizeof(TIN) == 2));
+    hipError_t e = hipSuccess;
+    if (linear) {
+        for (a.piece_pass = 0; e == hipSuccess && a.piece_pass < (a.pieces > 1 ? 3 : 1); ++a.piece_pass) e = launch_linear_half<G, TIN, ALIGNED>(a, st);
+    } else {
+        e = launch_chain_half<G, TIN, ALIGNED, PF1>(a, st);
+    }
     if (e != hipSuccess) return e;
     if (between) {
         e = hipEventRecord(between, st);
@@ -1112,12 +1125,7 @@ static hipError_t launch_geo(int op, ChainArgs a, hipStream_t st, hipEvent_t bet
         hipLaunchKernelGGL(logz_combine_kernel, dim3(a.B), dim3(64), 0, st, a);
         return hipGetLastError();
     }
-    if (spread) {
-        ChainArgs rest = a;
-        rest.extend = 1;
-        e = launch_linear_half<G, TIN, ALIGNED>(rest, st);
-        return e != hipSuccess ? e : launch_edge_marginals(pair.dtype, a, st);
-    }
+    if (a.whole) return launch_edge_marginals(pair.dtype, a, st);
     if (pair.mail) {
         // two workgroups per chain, speculative steps only; whatever they flag as failed is redone below
         // (the first pass above has cleared the mailboxes and the flags: a.pair_mail)
@@ -1184,10 +1192,11 @@ static hipError_t launch_wave(int op, int dtype, const ChainArgs& a, hipStream_t
     return launch_wave_pass(true, dtype, a, st);
 }
 
-// Both passes in row batches (128 < T <= 256).  cus: compute units of the device (0: unknown).
-static hipError_t launch_stream(int op, int dtype, ChainArgs a, hipStream_t st, hipEvent_t between, int cus = 0) {
-    a.spread = op == 1 && marginals_by_edges(dtype, a.B, a.T, cus) ? 1 : 0;
-    hipError_t e = launch_stream_pass(false, dtype, a, st);
+// Both passes in row batches (128 < T <= 256).
+static hipError_t launch_stream(int op, int dtype, ChainArgs a, hipStream_t st, hipEvent_t between) {
+    a.scaled = a.whole || a.pieces > 1;
+    hipError_t e = hipSuccess;
+    for (a.piece_pass = 0; e == hipSuccess && a.piece_pass < (a.pieces > 1 ? 3 : 1); ++a.piece_pass) e = launch_stream_pass(false, dtype, a, st);
     if (e != hipSuccess) return e;
     if (between) {
         e = hipEventRecord(between, st);
@@ -1198,13 +1207,7 @@ static hipError_t launch_stream(int op, int dtype, ChainArgs a, hipStream_t st, 
         hipLaunchKernelGGL(logz_combine_kernel, dim3(a.B), dim3(64), 0, st, a);
         return hipGetLastError();
     }
-    if (a.spread) {
-        ChainArgs rest = a;
-        rest.extend = 1;
-        e = launch_stream_pass(false, dtype, rest, st);
-        return e != hipSuccess ? e : launch_edge_marginals(dtype, a, st);
-    }
-    return launch_stream_pass(true, dtype, a, st);
+    return a.whole ? launch_edge_marginals(dtype, a, st) : launch_stream_pass(true, dtype, a, st);
 }
 
 bool structured_supported(int T) { return T >= 1 && T <= 128; }
@@ -1212,13 +1215,14 @@ bool lane_chains_supported(int T) { return lane_supported(T); }
 
 // Forward chains over whole sequences, every alpha stored (ua, Oa): the first pass of sampling.
 hipError_t launch_full_forward(int dtype, const void* phi, const int32_t* lengths, int B, int N, int T, float* ua,
-                               float* ub, double* Oa, double* Ob, bool lanes, int lane_poll_limit, hipStream_t st) {
+                               float* ub, double* Oa, double* Ob, bool lanes, int lane_poll_limit, int cus, void* scratch, hipStream_t st) {
     ChainArgs a{phi, lengths, B, N, T, ua, ub, Oa, Ob, nullptr, nullptr, 0, nullptr, 0, 1, nullptr, nullptr, nullptr, nullptr};
     a.full_forward = 1;
+    cut_chains(a, dtype, false, true, cus, scratch);
     if (lanes) return launch_lane_pass(false, dtype, a, false, lane_poll_limit, st);
     if (wave_supported(T)) return launch_wave(2, dtype, a, st, nullptr);
     if (stream_supported(T)) return launch_stream(2, dtype, a, st, nullptr);
-    const PairPlan pair{nullptr, nullptr, dtype, 0, 0};
+    const PairPlan pair{nullptr, nullptr, dtype, 0};
     const bool aligned = (T % 4) == 0;
     if (dtype == 0)
         return aligned ? launch_T<float, true>(2, a, st, nullptr, pair) : launch_T<float, false>(2, a, st, nullptr, pair);
@@ -1226,12 +1230,13 @@ hipError_t launch_full_forward(int dtype, const void* phi, const int32_t* length
 }
 
 hipError_t launch_meeting_vectors(int dtype, const void* phi, const int32_t* lengths, int B, int N, int T, float* ua, float* ub,
-                                  double* Oa, double* Ob, bool lanes, int lane_poll_limit, hipStream_t st) {
+                                  double* Oa, double* Ob, bool lanes, int lane_poll_limit, int cus, void* scratch, hipStream_t st) {
     ChainArgs a{phi, lengths, B, N, T, ua, ub, Oa, Ob, nullptr, nullptr, 0, nullptr, 0, 1, nullptr, nullptr, nullptr, nullptr};
+    cut_chains(a, dtype, false, false, cus, scratch);
     if (lanes) return launch_lane_pass(false, dtype, a, true, lane_poll_limit, st);
     if (stream_supported(T)) return launch_stream(2, dtype, a, st, nullptr);
     if (wave_supported(T)) return hipErrorInvalidValue;  // (their log-partition is one launch already)
-    const PairPlan pair{nullptr, nullptr, dtype, 0, 0};
+    const PairPlan pair{nullptr, nullptr, dtype, 0};
     const bool aligned = (T % 4) == 0;
     if (dtype == 0)
         return aligned ? launch_T<float, true>(2, a, st, nullptr, pair) : launch_T<float, false>(2, a, st, nullptr, pair);
@@ -1253,7 +1258,7 @@ hipError_t launch_sequential_sum(int op, int dtype, const void* phi, const int32
                                  float* ua, float* ub, double* Oa, double* Ob, float* logZ, float* mu,
                                  hipStream_t st, hipEvent_t between, bool exact_only, unsigned long long* mail,
                                  int* failed, double* logZ64, const float* emit, const float* trans, int pair_poll_limit,
-                                 int cus, bool lanes, int lane_poll_limit) {
+                                 int cus, bool lanes, int lane_poll_limit, void* scratch) {
     ChainArgs a{phi, lengths, B, N, T, ua, ub, Oa, Ob, logZ, mu, exact_only ? 1 : 0, nullptr, 0, 1, nullptr, nullptr, nullptr, nullptr};
     a.logZ64 = logZ64;
     a.emit = emit;
@@ -1290,10 +1295,13 @@ hipError_t launch_sequential_sum(int op, int dtype, const void* phi, const int32
     }
     if (wave_supported(T)) return launch_wave(op, dtype, a, st, between);
     if (emit) return (T % 4) == 0 ? launch_structured_sum<true>(op, a, st, between) : launch_structured_sum<false>(op, a, st, between);
-    if (stream_supported(T)) return launch_stream(op, dtype, a, st, between, exact_only ? 0 : cus);
+    if (exact_only) cus = 0;
+    a.whole = op == 1 && marginals_by_edges(dtype, B, T, cus) ? 1 : 0;
+    cut_chains(a, dtype, a.whole != 0, false, cus, scratch);
+    if (stream_supported(T)) return launch_stream(op, dtype, a, st, between);
     // Pairs pay off when one workgroup per chain would leave at least half of the chip idle.
     const bool use_pairs = op == 1 && !exact_only && mail && failed && pair_supported(T) && 4 * B <= cus;
-    const PairPlan pair{use_pairs ? mail : nullptr, failed, dtype, pair_poll_limit, exact_only ? 0 : cus};
+    const PairPlan pair{use_pairs ? mail : nullptr, failed, dtype, pair_poll_limit};
     if (use_pairs) {
         a.pair_mail = mail;
         a.pair_failed = failed;
@@ -1334,7 +1342,7 @@ hipError_t launch_chunked_marginals(int dtype, const void* phi, const int32_t* l
         return launch_wave_chunks(dtype, a, st);
     }
     if (wave_supported(T)) return launch_wave(1, dtype, a, st, between);
-    const PairPlan pair{nullptr, nullptr, dtype, 0, 0};
+    const PairPlan pair{nullptr, nullptr, dtype, 0};
     const bool aligned = (T % 4) == 0;
     if (dtype == 0)
         return aligned ? launch_T<float, true>(1, a, st, between, pair) : launch_T<float, false>(1, a, st, between, pair);

@@ -54,10 +54,16 @@ struct ChainArgs {
     // 1: the forward chain runs over the whole span and stores every alpha; no backward chain
     // (first pass of sampling, whose backward sweep needs alpha everywhere).
     int full_forward;
-    // 1: a first pass over the other halves (scaled steps, whole sequences): the chains start from the vectors that
-    // an ordinary first pass has stored for the meeting position and run on to the far ends, vectors stored.
-    int extend;
-    int spread;  // 1: both of these first passes, with the edge kernel behind them (row-batch kernels: scaled steps whatever the batch)
+    // First passes in scaled probabilities over whole sequences at 65 .. 256 tags (lccrf_pieces.h):
+    int whole;   // 1: either chain runs to the far end of the sequence, every vector stored
+    int scaled;  // row-batch kernels: scaled steps whatever the batch
+    int pieces;  // workgroups a chain (1: the chain as a whole) ...
+    int piece_pass;  // ... and which of their three launches this is
+    int piece_overhead;  // what three launches take more than one, in steps
+    float *ends, *ends2;               // [2 B][pieces][T] last vectors of the pieces (chain 2 b + direction) ...
+    double *end_offsets, *end_offsets2;  // [2 B][pieces] ... and their offsets
+    double* deltas;                    // [2 B][pieces]
+    int* matched_from;                 // [2 B][pieces] the first step whose row is launch 0's; of piece 0: the plan, see piece_walk
 };
 
 // The stretch of positions one pair of workgroups handles: all of a sequence, or one chunk.
@@ -89,6 +95,9 @@ __device__ __forceinline__ Span make_span(const ChainArgs& a, int v) {
     }
     return s;
 }
+
+// Steps a piece of a chain has at least.
+constexpr int kPieceSteps = 18;
 
 // Where the forward and the backward chain of positions p0 .. e meet: the forward chain covers
 // p0 .. h, the backward chain h .. e.  Every kernel of both passes derives it from here.

@@ -21,14 +21,16 @@ hipError_t launch_sequential_sum(int op, int dtype, const void* phi, const int32
                                  hipStream_t st, hipEvent_t between = nullptr, bool exact_only = false,
                                  unsigned long long* mail = nullptr, int* failed = nullptr, double* logZ64 = nullptr,
                                  const float* emit = nullptr, const float* trans = nullptr, int pair_poll_limit = 0,
-                                 int cus = 0, bool lanes = false, int lane_poll_limit = 1 << 16);
+                                 int cus = 0, bool lanes = false, int lane_poll_limit = 1 << 16, void* scratch = nullptr);
+// scratch: B N T bytes for chains in pieces at 65 .. 256 tags (lccrf_pieces.h), here and below; null: every chain as a whole.
 // lanes: the chain-wave / producer-wave kernels of lccrf_lane.hip (lane_chains_supported(T); dense or structured potentials);
 // lane_poll_limit: polls their chain wave spends on a late matrix before it continues in the log domain.
 bool lane_chains_supported(int T);
 // Sampling (lccrf_chain.hip, lccrf_extras.hip): forward chains over whole sequences with every alpha
 // stored, then the backward sweep that draws the tags from the given uniforms [B][N].
 hipError_t launch_full_forward(int dtype, const void* phi, const int32_t* lengths, int B, int N, int T, float* ua,
-                               float* ub, double* Oa, double* Ob, bool lanes, int lane_poll_limit, hipStream_t st);
+                               float* ub, double* Oa, double* Ob, bool lanes, int lane_poll_limit, int cus, void* scratch,
+                               hipStream_t st);
 size_t sample_winmap_bytes(int B, int N, int T);
 // uniforms null: drawn by the counter-based generator under `seed` instead (lccrf_extras.hip, Uniforms).
 hipError_t launch_backward_sample(int dtype, const void* phi, const int32_t* lengths, const float* ua, const double* Oa,
@@ -86,7 +88,7 @@ hipError_t launch_path_log_prob(int dtype, const void* phi, const int32_t* lengt
                                 int T, const double* logZ64, const MeetingVectors& mv, float* out, hipStream_t st);
 // A first pass alone, for what is made of the vectors of the meeting position (lanes or more than 32 tags).
 hipError_t launch_meeting_vectors(int dtype, const void* phi, const int32_t* lengths, int B, int N, int T, float* ua, float* ub,
-                                  double* Oa, double* Ob, bool lanes, int lane_poll_limit, hipStream_t st);
+                                  double* Oa, double* Ob, bool lanes, int lane_poll_limit, int cus, void* scratch, hipStream_t st);
 // Two-pass forward-backward inside every chunk from those boundary vectors (lccrf_chain.hip); chunk >= 4.
 hipError_t launch_chunked_marginals(int dtype, const void* phi, const int32_t* lengths, int B, int N, int T,
                                     float* ua, float* ub, double* Oa, double* Ob, float* mu, int chunk,

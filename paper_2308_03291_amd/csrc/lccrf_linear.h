@@ -93,6 +93,7 @@ struct LinSmem {
     // from TCAP on, and from TCAP + 8 on the entries of a row's last piece, zero where its neighbour holds them already.
     alignas(16) float vec[2][LG::VEC];
     alignas(16) float wmax[2][16];        // per-wave largest entries of S_n; +inf: the step was not accepted
+    alignas(16) float over[2][16], under[2][16];  // comparing runs: per-wave largest D - tol and -(D + tol) of a row (LinMatch)
 };
 
 // Four consecutive potentials as they lie in memory (bfloat16 is widened where the piece is used: widening at the load
@@ -186,6 +187,23 @@ __device__ __forceinline__ bool linear_hopeless(const TIN* mat, int T, bool back
     return !__syncthreads_or(way);
 }
 
+// What a run that compares has found.  Another workgroup has walked the same positions before, from another vector, and left its
+// vectors in the rows this run is about to write.  D(t) = this run's logarithm less the one that is there, of one row: where the two
+// vectors are multiples of each other D is the same for every tag, and so it is in every row behind, since the steps are
+// linear.  A row matches if one number lies within tol(t) of every D(t), and a tag is an exact zero in both or in neither.  tol is 2^-20,
+// four roundings of a logarithm of one or two bits, and grows with the logarithm as its rounding does.  (Non-negative matrices never
+// widen such a gap, and all of it but a common factor shrinks from step to step as fast as it came down to tol.)
+struct LinMatch {
+    bool hit = false;
+    double delta = 0.0;  // what has to be added to the offsets of the rows behind
+};
+__device__ __forceinline__ void linear_gap(float x, float old, float& over, float& under) {
+    const float d = x - old, tol = 0x1p-20f * fmaxf(1.f, -0.25f * fmaxf(x, -0x1p20f));
+    const bool finite = fabsf(d) < __builtin_huge_valf(), zeros = x == LCCRF_NEG_INF && old == LCCRF_NEG_INF;
+    over = zeros ? LCCRF_NEG_INF : finite ? d - tol : __builtin_huge_valf();
+    under = zeros ? LCCRF_NEG_INF : finite ? -(d + tol) : __builtin_huge_valf();
+}
+
 // What a run works on (uniform over the workgroup).  Step s (0 .. n - 1) of the chain takes the matrix of position
 // first + s (forward) or first - s (backward).
 template <typename TIN, bool BACKWARD>
@@ -201,9 +219,10 @@ struct LinJob {
 // Takes steps from `from` on while they are accepted; returns the steps done in all.  v: thread tid's entry of the
 // vector in front of step `from` (base-2 logarithms; -inf from tid = T on), O its offset; on return those of the
 // vector behind the last step taken.  The vectors in front of every step taken are stored to uout / Oout; that of the
-// last one is not (the caller stores it or goes on from it).  Called by the whole workgroup.
-template <typename LG, typename TIN, bool ALIGNED, bool BACKWARD>
-__device__ __forceinline__ int linear_run(LinSmem<LG>& ls, const LinJob<TIN, BACKWARD>& job, float& v0, int from, double& O) {
+// last one is not (the caller stores it or goes on from it).  COMPARE: the rows are looked at before they are written, and the
+// run ends behind one that matches (v0 and O are then of no use).  Called by the whole workgroup.
+template <typename LG, typename TIN, bool ALIGNED, bool BACKWARD, bool COMPARE = false>
+__device__ __forceinline__ int linear_run(LinSmem<LG>& ls, const LinJob<TIN, BACKWARD>& job, float& v0, int from, double& O, LinMatch& match) {
     constexpr int ITEMS = LG::ITEMS, Q = LG::Q, TCAP = LG::TCAP;
     using Raw = RawPiece<TIN>;
     // Pieces in flight: as many whole tiles as fit the registers beside E (PH of them, three at most), half or a quarter
@@ -218,6 +237,37 @@ __device__ __forceinline__ int linear_run(LinSmem<LG>& ls, const LinJob<TIN, BAC
     const int T = job.T;
     const int n = job.n;
     if (from >= n) return from;
+    const size_t TT = (size_t)T * T;
+    const int Q4 = (T + 3) >> 2, G = linear_groups(LG::W, T);  // threads a row, row groups
+    const int g = tid / Q4, cl = tid - g * Q4;    // (g = G: left over, holds zeros of the vector)
+    const int c4 = min(4 * cl, T - 4);
+    const unsigned voff = (unsigned)(g * T + c4) * (unsigned)sizeof(TIN);
+    constexpr int TAIL = linear_tail(ITEMS), BODY = ITEMS - TAIL;  // (the rows of the first BODY items: linear_row(.., k) = g + G k)
+    unsigned voff_tail[TAIL];
+#pragma unroll
+    for (int k = 0; k < TAIL; ++k) voff_tail[k] = (unsigned)(linear_row(ITEMS, T, G, g, BODY + k) * T + c4) * (unsigned)sizeof(TIN);
+    const unsigned row_bytes = (unsigned)(uniform(G) * T) * (unsigned)sizeof(TIN);
+
+    typename Raw::type raw[R];
+    float e[ITEMS][4];
+    // The matrices are requested in the order of the steps: `ahead` is the one that is taken next (past the end the last one again, never
+    // used), so that an address is an addition.
+    const GlobalBytes* ahead = (const GlobalBytes*)(job.phib + (size_t)job.matrix(from) * TT);
+    int ahead_left = n - 1 - from;  // matrices behind it
+    const ptrdiff_t stride = (BACKWARD ? -1 : 1) * (ptrdiff_t)(TT * sizeof(TIN));
+    const auto advance = [&]() __attribute__((always_inline)) {
+        ahead += ahead_left > 0 ? stride : 0;
+        --ahead_left;
+    };
+    // row k of this thread's part of that matrix
+    auto fetch = [&](int k) __attribute__((always_inline)) {
+        auto row = ahead + (k < BODY ? row_bytes * (unsigned)k : 0u);
+        unsigned offset = k < BODY ? voff : voff_tail[k < BODY ? 0 : k - BODY];
+        // The base is uniform, in scalar registers (not an address of its own per row, hoisted out of the loop), and the offset is 32 bits
+        // wide where it is used: the load adds the two up.
+        asm("" : "+s"(row), "+v"(offset));
+        return Raw::template load<ALIGNED>(row + offset);
+    };
     // The largest entry, and whether every entry is an exact zero or within 2^-120 of it: held without loss, whatever its
     // products lose is below 2^-126.
     const float top = xor_max<1, 64>(v0);
@@ -231,44 +281,37 @@ __device__ __forceinline__ int linear_run(LinSmem<LG>& ls, const LinJob<TIN, BAC
     __syncthreads();
     if (uniform_f(max16(ls.wmax[1])) != 0.f) return from;
 
-    const size_t TT = (size_t)T * T;
-    const int Q4 = (T + 3) >> 2, G = linear_groups(LG::W, T);  // threads a row, row groups
-    const int g = tid / Q4, cl = tid - g * Q4;    // (g = G: left over, holds zeros of the vector)
-    const int c4 = min(4 * cl, T - 4);
-    const unsigned voff = (unsigned)(g * T + c4) * (unsigned)sizeof(TIN);
-    constexpr int TAIL = linear_tail(ITEMS), BODY = ITEMS - TAIL;  // (the rows of the first BODY items: linear_row(.., k) = g + G k)
-    unsigned voff_tail[TAIL];
-#pragma unroll
-    for (int k = 0; k < TAIL; ++k) voff_tail[k] = (unsigned)(linear_row(ITEMS, T, G, g, BODY + k) * T + c4) * (unsigned)sizeof(TIN);
-    const size_t row_step = (size_t)(uniform(G) * T);
-
-    typename Raw::type raw[R];
-    float e[ITEMS][4];
-    // row k of this thread's part of the matrix of step s (past the end: the last one again, never used)
-    auto fetch = [&](int s, int k) {
-        auto row = (const GlobalBytes*)(job.phib + (size_t)job.matrix(s < n ? s : n - 1) * TT + (k < BODY ? row_step * k : 0));
-        asm("" : "+s"(row));  // uniform, in scalar registers (not an address of its own per row, hoisted out of the loop)
-        return Raw::template load<ALIGNED>(row + (k < BODY ? voff : voff_tail[k < BODY ? 0 : k - BODY]));
-    };
-    // E of step s from the ring, shift c; every piece that is used up is requested again for what follows
-    auto prepare = [&](int s, int slot, int shift) __attribute__((always_inline)) {
+    // E of the next step from the ring, shift c; every piece that is used up is requested again for what follows
+    auto prepare = [&](int slot, int shift) __attribute__((always_inline)) {
         const float c = (float)shift;
+        if constexpr (!HALF) advance();
 #pragma unroll
         for (int k = 0; k < ITEMS; ++k) {
             const int r = HALF ? k % R : slot * ITEMS + k;
 #pragma unroll
             for (int j = 0; j < 4; ++j) e[k][j] = ex2(__builtin_fmaf(Raw::get(raw[r], j), kLog2e, -c));
-            if constexpr (HALF) raw[r] = k + R < ITEMS ? fetch(s, k + R) : fetch(s + 1, k + R - ITEMS);
-            else raw[r] = fetch(s + PH, k);
+            asm volatile("" : "+v"(e[k][0]), "+v"(e[k][1]), "+v"(e[k][2]), "+v"(e[k][3]));  // (here: not sunk behind the barrier to where they are used)
+            if constexpr (HALF) {
+                if (k + R == ITEMS) advance();
+                raw[r] = fetch(k + R < ITEMS ? k + R : k + R - ITEMS);
+            } else {
+                raw[r] = fetch(k);
+            }
             if (k % 2 == 1) __builtin_amdgcn_sched_barrier(0);  // (keeps the new loads from being hoisted over the old values' use)
         }
     };
+
 #pragma unroll
-    for (int r = 0; r < R; ++r) raw[r] = HALF ? fetch(from, r) : fetch(from + r / ITEMS, r % ITEMS);
+    for (int r = 0; r < R; ++r) {
+        if (!HALF && r > 0 && r % ITEMS == 0) advance();
+        raw[r] = fetch(r % ITEMS);
+    }
 
     // where the entries of the vector lie, for the thread that publishes (`mine`) or stores (tid) one
     const auto slot_of = [&](int v) { return BACKWARD ? v : v % G * LG::IPAD + v / G; };
-    const int mine = min(tid / Q, T - 1), vmine = slot_of(mine);
+    const int mine = min(tid / Q, T - 1), vmine = slot_of(mine), vstore = slot_of(min(tid, T - 1));
+    const bool stores = 64 * wave < T;
+    const unsigned store_offset = 4u * (unsigned)min(tid, T - 1);
     const int vcopy = BACKWARD && mine >= 4 * (Q4 - 1) ? TCAP + 8 + mine - (T - 4) : vmine;  // (or the same place again)
     for (int k = tid; k < 2 * LG::VEC; k += LG::W) (&ls.vec[0][0])[k] = 0.f;
     for (int k = tid; k < LG::SCRATCH; k += LG::W) ls.part[k] = 0.f;
@@ -303,20 +346,37 @@ __device__ __forceinline__ int linear_run(LinSmem<LG>& ls, const LinJob<TIN, BAC
     int c_cur = uniform((int)fminf(fmaxf(ceilf(finite_or_zero(big)), -0x1p20f), 0x1p20f)), c_last = c_cur + kLinearHead - 1;
     __syncthreads();
     if (tid < 32) ls.wmax[tid >> 4][tid & 15] = tid == 0 ? 1.f : 0.f;
-    prepare(from, 0, c_cur);
+    if (COMPARE && tid < 32) ls.over[tid >> 4][tid & 15] = ls.under[tid >> 4][tid & 15] = tid == 0 ? __builtin_huge_valf() : LCCRF_NEG_INF;  // (waves that store nothing leave theirs)
+    // Comparing: what is in the row of the step to come, requested a step ahead of its use and ahead of that step's matrix.
+    float old = 0.f;
+    double oldO = 0.0, gap = 0.0;
+    const auto look = [&](int s) __attribute__((always_inline)) {
+        auto row = (const GlobalBytes*)(job.uout + (size_t)job.position(s < n ? s : n - 1) * T);
+        unsigned offset = store_offset;
+        asm("" : "+s"(row), "+v"(offset));
+        old = *(LCCRF_GLOBAL(float))(row + offset);
+        oldO = job.Oout[job.position(s < n ? s : n - 1)];
+    };
+    if constexpr (COMPARE) look(from);
+    prepare(0, c_cur);
     __syncthreads();
 
     int done = from, buf = 0;
     const double O0 = uniform(O + (double)d);
     long long Oi = 0, Oi_last = 0;  // offset of the vector in vec[buf] and of the one before it, less O0
-    bool rejected = false;
-    const auto step = [&](int slot_next) __attribute__((always_inline)) -> bool {  // false: the run is over
-        const float M = uniform_f(max16(ls.wmax[buf]));
-        if (!(M <= 0x1p60f)) {
-            rejected = true;
-            return false;
+    float M = 1.f;  // the largest entry of the vector in vec[buf]
+    // Whether there is a step to take.  (One condition and one way out of the loop below: where a path without loads joins one with them
+    // the compiler waits for all of them, and a step took what memory takes.)
+    const auto more = [&]() __attribute__((always_inline)) -> bool {
+        if constexpr (COMPARE) {
+            const float over = uniform_f(max16(ls.over[buf])), under = uniform_f(max16(ls.under[buf]));
+            match.hit = over + under <= 0.f;
+            match.delta = gap + 0.5 * (double)(over - under);
         }
-        if (done == n || !(M >= 0x1p-30f)) return false;
+        M = uniform_f(max16(ls.wmax[buf]));
+        return (M <= 0x1p60f) & (M >= 0x1p-30f) & (done != n) & !(COMPARE && match.hit);
+    };
+    const auto step = [&](int slot_next) __attribute__((always_inline)) {
         const int k = uniform(__builtin_amdgcn_frexp_expf(M));
         // (c_last + k - kLinearHead: what the last step grew by.  In front of the first step c_last is such that this is what the
         // first one will grow by, the exponent of its vector being 1.)
@@ -341,11 +401,25 @@ __device__ __forceinline__ int linear_run(LinSmem<LG>& ls, const LinJob<TIN, BAC
                 ls.part[pslot + r * LG::GMAX * LG::RSTRIDE] = __builtin_fmaf(e[r][0], v.x, e[r][1] * v.y) + __builtin_fmaf(e[r][2], v.z, e[r][3] * v.w);
         }
         // the vector in front of this step is final: store it (off the dependent path), its largest entry brought below 1:
-        // the closer the logarithms are to zero, the less their rounding takes
-        {
+        // the closer the logarithms are to zero, the less their rounding takes.  (By the first waves, a tag a thread.)
+        if (stores) {
             auto out = (__attribute__((address_space(1))) char*)(job.uout + (size_t)job.position(done) * T);
-            asm("" : "+s"(out));  // (as above)
-            *(__attribute__((address_space(1))) float*)(out + 4u * (unsigned)min(tid / Q, T - 1)) = lg2(__builtin_amdgcn_ldexpf(ls.vec[buf][vmine], -k));  // (Q threads, the same value)
+            unsigned offset = store_offset;
+            asm("" : "+s"(out), "+v"(offset));  // (as above)
+            const float x = lg2(__builtin_amdgcn_ldexpf(ls.vec[buf][vstore], -k));
+            if constexpr (COMPARE) {
+                float over, under;
+                linear_gap(x, old, over, under);
+                over = xor_max<1, 64>(over);
+                under = xor_max<1, 64>(under);
+                if (lane == 0) {
+                    ls.over[buf ^ 1][wave] = over;
+                    ls.under[buf ^ 1][wave] = under;
+                }
+                gap = O0 + (double)(Oi + k) - oldO;
+                look(done + 1);
+            }
+            *(__attribute__((address_space(1))) float*)(out + offset) = x;
         }
         if (tid == 0) job.Oout[job.position(done)] = O0 + (double)(Oi + k);
         __syncthreads();
@@ -373,20 +447,25 @@ __device__ __forceinline__ int linear_run(LinSmem<LG>& ls, const LinJob<TIN, BAC
         Oi += k - kLinearHead + c_cur;
         c_last = c_cur;
         c_cur = c_next;
-        prepare(done + 1, slot_next, c_next);
+        prepare(slot_next, c_next);
         buf ^= 1;
         ++done;
         __syncthreads();
-        return true;
     };
-    if constexpr (PH == 1) {
-        while (step(0)) {}
-    } else if constexpr (PH == 2) {
-        while (step(1) && step(0)) {}
-    } else {
-        while (step(1) && step(2) && step(0)) {}
+    for (;;) {
+        if (!more()) break;
+        step(PH > 1 ? 1 : 0);
+        if constexpr (PH > 1) {
+            if (!more()) break;
+            step(PH > 2 ? 2 : 0);
+        }
+        if constexpr (PH > 2) {
+            if (!more()) break;
+            step(0);
+        }
     }
-    if (rejected) {  // the vector in front of the rejected step is still in the other buffer
+    if (COMPARE && match.hit) return done;
+    if (!(M <= 0x1p60f)) {  // the vector in front of the rejected step is still in the other buffer
         buf ^= 1;
         --done;
         Oi = Oi_last;

@@ -8,8 +8,8 @@
 //
 // First pass (stream_half_kernel): the scaled probabilities of lccrf_linear.h, whose exponentials replace the potentials they come
 // from in the registers; steps those do not accept are taken by stream_log_steps.
-// Second pass, few chains: the first pass's kernel runs on to the far ends (extend), then edge_marginal_kernel writes the
-// marginals of every edge, the whole chip at once.
+// Few chains: the first pass's kernel walks either chain to the far end of its sequence, in pieces (lccrf_pieces.h), then
+// edge_marginal_kernel writes the marginals of every edge, the whole chip at once.
 // Second pass, many chains (stream_marginal_kernel), and the log-domain steps: a matrix is taken as four batches of 64 rows,
 // four rows a thread, through a ring of batch slots that is refilled across position boundaries.  Nothing in a speculative step
 // (one shift for the whole matrix, see lccrf_chain.hip) needs the matrix whole: it only adds up exponentials.
@@ -26,6 +26,7 @@
 #include "lccrf_device.h"
 #include "lccrf_launch.h"
 #include "lccrf_linear.h"
+#include "lccrf_pieces.h"
 
 namespace lccrf {
 
@@ -463,74 +464,43 @@ __device__ __attribute__((noinline)) LogStepsResult stream_log_steps(const void*
     return r;
 }
 
-// Pass 1: both half chains, vectors stored.  The steps are taken in scaled probabilities (linear_run) as long as they are
-// accepted, and from one that is not, a block of positions in the log domain (LogBlocks).
+// Pass 1: both half chains, vectors stored, in pieces where a.pieces says so (lccrf_pieces.h).  The steps are taken in scaled probabilities
+// (linear_run) as long as they are accepted, and from one that is not, a block of positions in the log domain (LogBlocks).
 // ITEMS: rows a thread holds of a matrix there, linear_instance(1024, T); 0: every step in the log domain.
-template <typename TIN, bool ALIGNED, int ITEMS>
+// COMPARE: the second launch of a chain in pieces.
+template <typename TIN, bool ALIGNED, int ITEMS, bool COMPARE>
 __global__ __launch_bounds__(1024) void stream_half_kernel(ChainArgs a) {
-    const int tid = threadIdx.x;
-    const int dir = blockIdx.x & 1, b = blockIdx.x >> 1;
-    const int N = a.N, T = a.T;
-    const int L = clamp_length(a.lengths, b, N);
-    if (L == 0 || (a.full_forward && dir == 1)) return;
-    const int e = L - 1;
-    const int mid = meeting_point(0, e);
-    const size_t vb = (size_t)b * N;
-    const TIN* phib = static_cast<const TIN*>(a.phi) + vb * T * T;
-    float* uout = (dir == 0 ? a.ua : a.ub) + vb * T;
-    double* Oout = (dir == 0 ? a.Oa : a.Ob) + vb;
-    // the vector the chain starts from, and the positions it walks
-    const int start = a.extend ? mid : dir == 0 ? 0 : e;
-    const int end = a.extend ? (dir == 0 ? e : 0) : dir == 0 ? forward_end(a, 0, e) : mid;
-    const int first = dir == 0 ? start + 1 : start, n = dir == 0 ? end - start : start - end;
-    float v = LCCRF_NEG_INF;
-    double O = 0.0;
-    if (a.extend) {
-        if (tid < T) v = uout[(size_t)start * T + tid];
-        O = Oout[start];
-    } else if (tid < T) {
-        v = dir == 0 ? Elem<TIN>::get(phib + tid) * kLog2e : 0.f;
-    }
     if constexpr (ITEMS > 0) {
         using LG = LinGeo<16, 256, ITEMS>;
         __shared__ LinSmem<LG> lin;
-        int steps = 0;
-        LogBlocks blocks;
-        const float x = tid < T ? (dir == 1 && !a.extend ? Elem<TIN>::get(phib + tid) : v) : 0.f;
-        blocks.hopeless = n > 0 && linear_hopeless(phib + (size_t)first * T * T, T, dir == 1, x == LCCRF_NEG_INF, v);
-        for (;;) {
-            const int before = steps;
-            if (!blocks.hopeless) {
-                if (dir == 0) steps = linear_run<LG, TIN, ALIGNED, false>(lin, {phib, T, first, n, uout, Oout}, v, steps, O);
-                else steps = linear_run<LG, TIN, ALIGNED, true>(lin, {phib, T, first, n, uout, Oout}, v, steps, O);
-            }
-            if (steps >= n) break;
-            const int m = blocks.next(steps - before, n - steps);
-            const LogStepsResult r = stream_log_steps<TIN, ALIGNED>(a.phi, a.ua, a.ub, a.Oa, a.Ob, a.B, N, T, a.exact_only, b, dir,
-                                                                    dir == 0 ? first + steps : first - steps, m, v, O);
-            v = r.v;
-            O = r.O;
-            steps += m;
-        }
+        piece_walk<LG, TIN, ALIGNED, COMPARE>(lin, a, [&](int b, int dir, int first, int m, float v, double O) {
+            return stream_log_steps<TIN, ALIGNED>(a.phi, a.ua, a.ub, a.Oa, a.Ob, a.B, a.N, a.T, a.exact_only, b, dir, first, m, v, O);
+        });
     } else {
+        const int tid = threadIdx.x;
+        const int dir = blockIdx.x & 1, b = blockIdx.x >> 1;
+        const int N = a.N, T = a.T;
+        const int L = clamp_length(a.lengths, b, N);
+        if (L == 0 || (a.full_forward && dir == 1)) return;
+        const int e = L - 1, end = dir == 0 ? forward_end(a, 0, e) : meeting_point(0, e);
+        const size_t vb = (size_t)b * N;
+        const TIN* phib = static_cast<const TIN*>(a.phi) + vb * T * T;
         __shared__ ChainSmem<SG> sm;
         smem_init<SG>(sm, tid);
         __syncthreads();
-        publish_columns<SG>(sm, 0, tid, v);
+        publish_columns<SG>(sm, 0, tid, tid < T ? (dir == 0 ? Elem<TIN>::get(phib + tid) * kLog2e : 0.f) : LCCRF_NEG_INF);
         __syncthreads();
         int buf = 0;
-        stream_walk<TIN, ALIGNED, false>(sm, a, b, dir, first, n, 0.0, true, buf, O);
+        double O = 0.0;
+        stream_walk<TIN, ALIGNED, false>(sm, a, b, dir, dir == 0 ? 1 : e, dir == 0 ? end : e - end, 0.0, true, buf, O);
         const float d = read_shift<SG>(sm, buf);
-        O += (double)d;
-        v = tid < T ? sm.rvec[buf][tid] - d : LCCRF_NEG_INF;
+        if (tid < T) ((dir == 0 ? a.ua : a.ub) + (vb + end) * T)[tid] = sm.rvec[buf][tid] - d;
+        if (tid == 0) (dir == 0 ? a.Oa : a.Ob)[vb + end] = O + (double)d;
     }
-    if (tid < T) uout[(size_t)end * T + tid] = v;
-    if (tid == 0) Oout[end] = O;
 }
 
 // ---------------------------------------------------------------------------------------
-// Marginals of every position at once from the vectors of all positions (alpha and beta everywhere: two first passes, the
-// second with `extend`):
+// Marginals of every position at once from the vectors of all positions (alpha and beta everywhere: a first pass over whole chains):
 //     mu_i(s, t) = 2^(ua_{i-1}(s) + phi2_i(s, t) + ub_i(t) + K_i),   K_i = Oa_{i-1} - Oa_i - log2 sum_t 2^(ua_i(t) + ub_i(t)),
 // one workgroup a position.  K_i comes from the position's own vectors (the sum over its edges is sum_t alpha_i(t) beta_i(t)),
 // so rounding drift between the chains' offsets does not reach the result.  Nothing here depends on another position:
@@ -992,16 +962,27 @@ static bool scaled_pays(bool single, int B, int T) {
 }
 template <typename TIN, bool ALIGNED>
 static hipError_t launch_stream_half(const ChainArgs& a, hipStream_t st) {
-    const dim3 grid(2 * a.B), block(1024);
-    const int items = linear_instance(1024, a.T);
+    const dim3 block(1024);
+    const int items = linear_instance(1024, a.T), pieces = a.pieces > 1 ? a.pieces : 1;
+    const bool compare = pieces > 1 && a.piece_pass == 1;
+    const dim3 grid(2 * a.B * (pieces == 1 || a.piece_pass == 2 ? 1 : compare ? pieces - 1 : pieces));
     if (items < 5) return hipErrorInvalidValue;
-    switch (!a.exact_only && (a.spread || scaled_pays(sizeof(TIN) == 4, a.B, a.T)) ? items : 0) {  // 5 (129 tags) .. 16 (256 tags)
-#define LCCRF_STREAM_HALF(I) case I: hipLaunchKernelGGL((stream_half_kernel<TIN, ALIGNED, I>), grid, block, 0, st, a); break
+    ChainArgs as = a;
+    as.pieces = pieces;
+    switch (!a.exact_only && (a.scaled || scaled_pays(sizeof(TIN) == 4, a.B, a.T)) ? items : 0) {  // 5 (129 tags) .. 16 (256 tags)
+#define LCCRF_STREAM_HALF(I) case I: \
+            if (compare) hipLaunchKernelGGL((stream_half_kernel<TIN, ALIGNED, I, true>), grid, block, 0, st, as); \
+            else hipLaunchKernelGGL((stream_half_kernel<TIN, ALIGNED, I, false>), grid, block, 0, st, as); \
+            break
         LCCRF_STREAM_HALF(5); LCCRF_STREAM_HALF(6); LCCRF_STREAM_HALF(7); LCCRF_STREAM_HALF(8); LCCRF_STREAM_HALF(9); LCCRF_STREAM_HALF(10);
-        LCCRF_STREAM_HALF(11); LCCRF_STREAM_HALF(12); LCCRF_STREAM_HALF(14); LCCRF_STREAM_HALF(16); LCCRF_STREAM_HALF(0);
+        LCCRF_STREAM_HALF(11); LCCRF_STREAM_HALF(12); LCCRF_STREAM_HALF(14); LCCRF_STREAM_HALF(16);
+#undef LCCRF_STREAM_HALF
+        case 0:
+            if (pieces > 1 || a.whole) return hipErrorInvalidValue;
+            hipLaunchKernelGGL((stream_half_kernel<TIN, ALIGNED, 0, false>), grid, block, 0, st, as);
+            break;
         default: return hipErrorInvalidValue;
     }
-#undef LCCRF_STREAM_HALF
     return hipGetLastError();
 }
 template <typename TIN, bool ALIGNED>

@@ -1,0 +1,73 @@
+"""Chains of 65 .. 256 tags walked in pieces by several workgroups (the schedule AUTO takes for long chains in small batches), against the
+oracle: potentials that forget quickly (every piece matches), one sequence among them that forgets nothing (its pieces do not, and
+the rest of its chains is walked again), batches whose potentials are seen to forget slowly (one piece), steps in the log
+domain inside a piece, sequences of every short length.  Tolerances as everywhere for these queries (fp32 sums: 1e-5)."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2308_03291_amd import workloads
+from test_gpu_parity import check_case, crf  # noqa: F401  (crf: the module-scoped binding fixture)
+from test_gpu_sample import _check, _check_every_draw
+
+pytestmark = pytest.mark.gpu
+
+
+def _slow(phi, b):
+    """Sequence b stays where it is: what a chain started with is still there at its end."""
+    phi[b] += (25.0 * torch.eye(phi.shape[-1])).to(phi.dtype)
+
+
+@pytest.mark.parametrize("T,dtype", [(65, "f32"), (66, "bf16"), (96, "f32"), (101, "bf16"), (128, "f32"), (129, "f32"), (156, "f32"), (201, "bf16"), (256, "f32")])
+def test_marginals_and_log_partition(crf, oracle_mod, T, dtype):
+    N = 150
+    phi, _ = workloads.random_case(9300 + T, 5, N, T, scale=1.0, dtype=dtype)
+    _slow(phi, 4)
+    phi[1, 31, :, 5] = float("-inf")   # steps that are not accepted, in either chain's pieces
+    phi[1, 97, 7, :] = float("-inf")
+    phi[2, 50] += 250.0
+    phi[2, 103] -= 250.0
+    lens = torch.tensor([N, N, N - 1, 83, N], dtype=torch.int32)
+    check_case(crf, oracle_mod, phi, lens, what=f"pieces T={T} {dtype}", queries=("logz", "mu"))
+
+
+@pytest.mark.parametrize("T", [72, 144])
+def test_every_sequence_forgets_nothing_or_slowly(crf, oracle_mod, T):
+    N = 130
+    for scale in (3.0, 12.0):
+        phi, _ = workloads.random_case(9400 + T, 3, N, T, scale=scale)
+        check_case(crf, oracle_mod, phi, None, what=f"slow T={T} scale={scale}", queries=("logz", "mu"))
+    phi, _ = workloads.random_case(9500 + T, 6, N, T)
+    for b in (3, 5):  # (not among the sequences whose matrices are looked at)
+        _slow(phi, b)
+    phi[5, :, :, T - 1] = float("-inf")
+    check_case(crf, oracle_mod, phi, None, what=f"some slow T={T}", queries=("logz", "mu"))
+
+
+@pytest.mark.parametrize("T", [68, 200])
+def test_every_short_length(crf, oracle_mod, T):
+    N = 120
+    lengths = [N, 0, 1, 2, 3, 17, 18, 19, 35, 36, 37, 38, 39, 55, 73, 74]
+    phi, _ = workloads.random_case(9600 + T, len(lengths), N, T)
+    check_case(crf, oracle_mod, phi, torch.tensor(lengths, dtype=torch.int32), what=f"lengths T={T}", queries=("logz", "mu"))
+
+
+@pytest.mark.parametrize("T,dtype", [(65, "f32"), (100, "bf16"), (128, "f32"), (200, "f32")])
+def test_log_prob(crf, oracle_mod, T, dtype):
+    N = 200
+    phi, _ = workloads.random_case(9700 + T, 5, N, T, dtype=dtype)
+    _slow(phi, 4)
+    lens = torch.tensor([N, N, 0, 90, N], dtype=torch.int32)
+    tags = torch.randint(0, T, (5, N), generator=torch.Generator().manual_seed(T)).to(torch.int32)
+    got = crf.lccrf_log_prob(phi.cuda(), tags.cuda(), lens.cuda()).cpu().numpy()
+    want = oracle_mod.log_prob(phi, tags.numpy(), lens.numpy())
+    assert np.allclose(got, want, rtol=1e-5, atol=1e-5)
+
+
+@pytest.mark.parametrize("T", [66, 128, 150])
+def test_sampling(crf, oracle_mod, T):
+    phi, _ = workloads.random_case(9800 + T, 5, 120, T)
+    _slow(phi, 4)
+    lens = torch.tensor([120, 119, 40, 2, 120], dtype=torch.int32)
+    _check(crf, oracle_mod, phi, lens, 300 + T, f"sample in pieces T={T}", min_exact=0.0)
+    _check_every_draw(crf, oracle_mod, phi, lens, 300 + T, f"sample in pieces T={T}")
