@@ -6,6 +6,7 @@
 #include "lccrf_device.h"
 #include "lccrf_expect.h"
 #include "lccrf_launch.h"
+#include "lccrf_linear.h"
 
 namespace lccrf {
 
@@ -802,15 +803,15 @@ struct Uniforms {
     }
 };
 
-// LPP lanes serve one position (16, 32 or 64: the tag count rounded up), CPT columns a lane (more
-// than one only above 64 tags); a wave serves 64 / LPP positions, a workgroup four waves.
-template <typename TIN, int LPP, int CPT>
+// LPP lanes serve one position (16, 32 or 64: the tag count rounded up, one column a lane); a wave serves 64 / LPP positions, a
+// workgroup four waves.
+template <typename TIN, int LPP>
 __global__ __launch_bounds__(256) void sample_map_kernel(const TIN* __restrict__ phi, const int32_t* __restrict__ lengths,
                                                          const float* __restrict__ ua, const double* __restrict__ Oa,
                                                          const Uniforms uniforms, int B, int N, int T,
                                                          uint8_t* __restrict__ F) {
-    constexpr int PPW = 64 / LPP, TCAP = LPP * CPT;
-    __shared__ float alds[4][PPW][TCAP];
+    constexpr int PPW = 64 / LPP;
+    __shared__ float alds[4][PPW][LPP];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int pl = lane / LPP, tl = lane % LPP;
     const long long unit = ((long long)blockIdx.x * 4 + wave) * PPW + pl;  // (b, i), i = 0 .. N-2
@@ -819,41 +820,115 @@ __global__ __launch_bounds__(256) void sample_map_kernel(const TIN* __restrict__
     const int L = clamp_length(lengths, b, N);
     if (i >= L - 1) return;
     const size_t TT = (size_t)T * T, vb = (size_t)b * N;
-    const TIN* mat = phi + (vb + i + 1) * TT;  // phi_{i+1}
+    const int col = tl < T ? tl : T - 1;
+    const TIN* mat = phi + (vb + i + 1) * TT + col;  // phi_{i+1}
     const float dO = (float)(Oa[vb + i] - Oa[vb + i + 1]);
     const float u = uniforms.at(vb + i);
-    float base[CPT], cum[CPT];
-    int first[CPT], last[CPT], col[CPT];
-#pragma unroll
-    for (int c = 0; c < CPT; ++c) {
-        const int t = tl + c * LPP;
-        col[c] = t < T ? t : T - 1;
-        base[c] = t < T ? dO - ua[(vb + i + 1) * T + t] : LCCRF_NEG_INF;  // an unreachable tag above: +inf, no weight
-        if (!(base[c] < __builtin_huge_valf())) base[c] = LCCRF_NEG_INF;
-        alds[wave][pl][t] = t < T ? ua[(vb + i) * T + t] : LCCRF_NEG_INF;
-        cum[c] = 0.f;
-        first[c] = -1;
-        last[c] = -1;
-    }
+    float base = tl < T ? dO - ua[(vb + i + 1) * T + tl] : LCCRF_NEG_INF;  // an unreachable tag above: +inf, no weight
+    if (!(base < __builtin_huge_valf())) base = LCCRF_NEG_INF;
+    alds[wave][pl][tl] = tl < T ? ua[(vb + i) * T + tl] : LCCRF_NEG_INF;
+    float cum = 0.f;
+    int first = -1, last = -1;
     const float* arow = alds[wave][pl];
 #pragma unroll 4
     for (int s = 0; s < T; ++s) {
-        const float as = arow[s];
-        const TIN* row = mat + (size_t)s * T;
+        const float w = ex2(__builtin_fmaf(Elem<TIN>::get(mat + (size_t)s * T), kLog2e, base) + arow[s]);
+        cum += w;
+        last = w > 0.f ? s : last;
+        first = (first < 0 && cum > u) ? s : first;
+    }
+    const int pick = first >= 0 ? first : (last >= 0 ? last : 0);
+    if (tl < T) F[(vb + i) * T + tl] = (uint8_t)pick;
+}
+
+// The same maps at 65 .. 256 tags, a workgroup a position.  One wave a position read the rows of its matrix one after the other, two or
+// four bytes a lane: what a row takes from memory T / 4 times over, and at most 2.1 TB/s (B=40 N=256 T=200 785 us, a lone sequence of 19 positions
+// at 144 tags 60).  Here the whole matrix is requested at once: the rows are cut into G = W / ceil(T / 4) groups of consecutive ones, a thread
+// holds four columns of at most R rows and their weights stay in its registers.  The groups' sums of a column meet in LDS, a thread a column finds the
+// group in which the running sum passes u, and the thread that holds it finds the row.  (A row's last piece is moved back to end with
+// it, T >= 4; what is then held twice has the same sums and the same row.)
+template <typename TIN, bool ALIGNED, int W, int R>
+__global__ __launch_bounds__(W, 4) void sample_map_wide_kernel(const TIN* __restrict__ phi, const int32_t* __restrict__ lengths,
+                                                               const float* __restrict__ ua, const double* __restrict__ Oa,
+                                                               const Uniforms uniforms, int N, int T, uint8_t* __restrict__ F) {
+    using Raw = RawPiece<TIN>;
+    __shared__ __attribute__((aligned(16))) float part[4 * W];  // [group][T]: G T <= 4 W
+    __shared__ float av[256], bv[256], before[256];
+    __shared__ int where[256];  // the group that holds the row; negative: of none that passes u the last of positive weight (-1 - group)
+    __shared__ unsigned char pick[256];
+    __shared__ float us;
+    const int tid = threadIdx.x;
+    const int b = blockIdx.x / (N - 1), i = blockIdx.x % (N - 1);
+    const int L = clamp_length(lengths, b, N);
+    if (i >= L - 1) return;
+    const size_t TT = (size_t)T * T, vb = (size_t)b * N;
+    const int Q4 = (T + 3) >> 2, G = W / Q4, rows = (T + G - 1) / G;  // (rows <= R)
+    const int g = tid / Q4, cl = tid - g * Q4, c4 = min(4 * cl, T - 4), row0 = g * rows;
+    const GlobalBytes* mat = (const GlobalBytes*)(phi + (vb + i + 1) * TT);  // phi_{i+1}
+    typename Raw::type raw[R];
 #pragma unroll
-        for (int c = 0; c < CPT; ++c) {
-            const float w = ex2(__builtin_fmaf(Elem<TIN>::get(row + col[c]), kLog2e, base[c]) + as);
-            cum[c] += w;
-            last[c] = w > 0.f ? s : last[c];
-            first[c] = (first[c] < 0 && cum[c] > u) ? s : first[c];
+    for (int k = 0; k < R; ++k) raw[k] = Raw::template load<ALIGNED>(mat + ((size_t)min(row0 + min(k, rows - 1), T - 1) * T + c4) * sizeof(TIN));
+    for (int t = tid; t < T; t += W) {
+        const float base = (float)(Oa[vb + i] - Oa[vb + i + 1]) - ua[(vb + i + 1) * T + t];
+        bv[t] = base < __builtin_huge_valf() ? base : LCCRF_NEG_INF;  // an unreachable tag above: +inf, no weight
+        av[t] = ua[(vb + i) * T + t];
+        pick[t] = 0;
+    }
+    if (tid == 0) us = uniforms.at(vb + i);
+    __syncthreads();
+    const float u = us;
+    float w[R][4], base[4], sum[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int j = 0; j < 4; ++j) base[j] = bv[c4 + j];
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+        const bool mine = k < rows && row0 + k < T;
+        const float as = mine ? av[min(row0 + k, T - 1)] : LCCRF_NEG_INF;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            w[k][j] = ex2(__builtin_fmaf(Raw::get(raw[k], j), kLog2e, base[j]) + as);
+            w[k][j] = mine ? w[k][j] : 0.f;
+            sum[j] += w[k][j];
         }
     }
+    if (g < G) {
 #pragma unroll
-    for (int c = 0; c < CPT; ++c) {
-        const int t = tl + c * LPP;
-        const int pick = first[c] >= 0 ? first[c] : (last[c] >= 0 ? last[c] : 0);
-        if (t < T) F[(vb + i) * T + t] = (uint8_t)pick;
+        for (int j = 0; j < 4; ++j) part[g * T + c4 + j] = sum[j];
     }
+    __syncthreads();
+    for (int t = tid; t < T; t += W) {
+        float cum = 0.f, at = 0.f;
+        int found = -1, last = -1;
+        for (int q = 0; q < G; ++q) {
+            const float p = part[q * T + t], next = cum + p;
+            const bool over = found < 0 && next > u;
+            if (over || (found < 0 && p > 0.f)) at = cum;
+            last = p > 0.f ? q : last;
+            found = over ? q : found;
+            cum = next;
+        }
+        before[t] = at;
+        where[t] = found >= 0 ? found : -1 - last;  // (no weight at all: 0, nobody's, and tag 0)
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int at = where[c4 + j], group = at >= 0 ? at : -1 - at;
+        if (group == g && g < G) {
+            float cum = before[c4 + j];
+            int first = -1, last = 0;
+#pragma unroll
+            for (int k = 0; k < R; ++k) {
+                cum += w[k][j];
+                last = w[k][j] > 0.f ? k : last;
+                first = first < 0 && cum > u ? k : first;
+            }
+            // (a group whose sum passes u may stop short of it row by row, by rounding: its last row of positive weight)
+            pick[c4 + j] = (unsigned char)(row0 + (at >= 0 && first >= 0 ? first : last));
+        }
+    }
+    __syncthreads();
+    for (int t = tid; t < T; t += W) F[(vb + i) * T + t] = pick[t];
 }
 
 constexpr int kWalkWindow = 16384;  // bytes of the table of maps held in LDS at a time
@@ -1072,6 +1147,36 @@ __global__ __launch_bounds__(64) void sample_window_walk_kernel(const int32_t* _
     walk_window(win, segmap, entry, lo, hi - lo, T, lane, cur, y);
 }
 
+// Four waves a position up to 128 tags (sixteen rows a thread at most), eight up to 176, sixteen above.
+template <typename TIN, bool ALIGNED>
+static void launch_sample_map_wide(const TIN* phi, const int32_t* lengths, const float* ua, const double* Oa, const Uniforms uniforms, int B,
+                                   int N, int T, uint8_t* F, hipStream_t st) {
+    const dim3 grid((unsigned)((long long)B * (N - 1)));
+    const int W = T <= 128 ? 256 : T <= 176 ? 512 : 1024, G = W / ((T + 3) / 4), rows = (T + G - 1) / G;
+#define LCCRF_SAMPLE_MAP(W_, R_) hipLaunchKernelGGL((sample_map_wide_kernel<TIN, ALIGNED, W_, R_>), grid, dim3(W_), 0, st, phi, lengths, ua, Oa, uniforms, N, T, F)
+    if (W == 256) {
+        if (rows <= 5) LCCRF_SAMPLE_MAP(256, 5);
+        else if (rows <= 6) LCCRF_SAMPLE_MAP(256, 6);
+        else if (rows <= 8) LCCRF_SAMPLE_MAP(256, 8);
+        else if (rows <= 10) LCCRF_SAMPLE_MAP(256, 10);
+        else if (rows <= 13) LCCRF_SAMPLE_MAP(256, 13);
+        else LCCRF_SAMPLE_MAP(256, 16);
+    } else if (W == 512) {
+        if (rows <= 10) LCCRF_SAMPLE_MAP(512, 10);
+        else if (rows <= 12) LCCRF_SAMPLE_MAP(512, 12);
+        else if (rows <= 14) LCCRF_SAMPLE_MAP(512, 14);
+        else LCCRF_SAMPLE_MAP(512, 16);
+    } else {
+        if (rows <= 9) LCCRF_SAMPLE_MAP(1024, 9);
+        else if (rows <= 10) LCCRF_SAMPLE_MAP(1024, 10);
+        else if (rows <= 11) LCCRF_SAMPLE_MAP(1024, 11);
+        else if (rows <= 12) LCCRF_SAMPLE_MAP(1024, 12);
+        else if (rows <= 14) LCCRF_SAMPLE_MAP(1024, 14);
+        else LCCRF_SAMPLE_MAP(1024, 16);
+    }
+#undef LCCRF_SAMPLE_MAP
+}
+
 template <typename TIN>
 static hipError_t launch_sample_T(const TIN* phi, const int32_t* lengths, const float* ua, const double* Oa,
                                   const Uniforms uniforms, int B, int N, int T, uint8_t* F, uint8_t* winmap, int32_t* tags,
@@ -1080,15 +1185,13 @@ static hipError_t launch_sample_T(const TIN* phi, const int32_t* lengths, const 
         const long long units = (long long)B * (N - 1);
         auto blocks = [&](int ppw) { return dim3((unsigned)((units + 4 * ppw - 1) / (4 * ppw))); };
         if (T <= 16)
-            hipLaunchKernelGGL((sample_map_kernel<TIN, 16, 1>), blocks(4), dim3(256), 0, st, phi, lengths, ua, Oa, uniforms, B, N, T, F);
+            hipLaunchKernelGGL((sample_map_kernel<TIN, 16>), blocks(4), dim3(256), 0, st, phi, lengths, ua, Oa, uniforms, B, N, T, F);
         else if (T <= 32)
-            hipLaunchKernelGGL((sample_map_kernel<TIN, 32, 1>), blocks(2), dim3(256), 0, st, phi, lengths, ua, Oa, uniforms, B, N, T, F);
+            hipLaunchKernelGGL((sample_map_kernel<TIN, 32>), blocks(2), dim3(256), 0, st, phi, lengths, ua, Oa, uniforms, B, N, T, F);
         else if (T <= 64)
-            hipLaunchKernelGGL((sample_map_kernel<TIN, 64, 1>), blocks(1), dim3(256), 0, st, phi, lengths, ua, Oa, uniforms, B, N, T, F);
-        else if (T <= 128)
-            hipLaunchKernelGGL((sample_map_kernel<TIN, 64, 2>), blocks(1), dim3(256), 0, st, phi, lengths, ua, Oa, uniforms, B, N, T, F);
-        else
-            hipLaunchKernelGGL((sample_map_kernel<TIN, 64, 4>), blocks(1), dim3(256), 0, st, phi, lengths, ua, Oa, uniforms, B, N, T, F);
+            hipLaunchKernelGGL((sample_map_kernel<TIN, 64>), blocks(1), dim3(256), 0, st, phi, lengths, ua, Oa, uniforms, B, N, T, F);
+        else if ((T & 3) == 0) launch_sample_map_wide<TIN, true>(phi, lengths, ua, Oa, uniforms, B, N, T, F, st);
+        else launch_sample_map_wide<TIN, false>(phi, lengths, ua, Oa, uniforms, B, N, T, F, st);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }

@@ -205,3 +205,24 @@ def test_sample_forward_chain_by_the_chain_waves(crf, oracle_mod, T, N):
     phi[0, N // 2] *= 60.0
     phi[4, N // 3, :, 0] = float("-inf")
     _check_every_draw(crf, oracle_mod, phi, lens, 7700 + T + N, f"lanes T={T} N={N}")
+
+
+@pytest.mark.parametrize("T,dtype", [(65, "f32"), (66, "bf16"), (72, "f32"), (92, "f32"), (101, "bf16"), (112, "f32"), (127, "f32"), (128, "bf16"), (129, "f32"),
+                                     (141, "f32"), (160, "bf16"), (175, "f32"), (176, "f32"), (177, "bf16"), (200, "f32"), (205, "f32"), (216, "bf16"),
+                                     (224, "f32"), (255, "f32"), (256, "f32")])
+def test_sample_maps_by_a_workgroup(crf, oracle_mod, T, dtype):
+    """65 .. 256 tags: every number of rows a thread holds, rows off the 16-byte grid; tags that cannot be reached, forbidden predecessors,
+    one predecessor that carries all the weight, uniforms of zero and just below one."""
+    N, ninf = 9, float("-inf")
+    phi, _ = workloads.random_case(8600 + T, 6, N, T, scale=2.0, dtype=dtype)
+    phi[1, 4, :, 7] = ninf
+    phi[1, 5, T - 3:, :] = ninf
+    phi[2, 3, T - 1, :] += 40.0
+    phi[2, 6, 0, :] += 40.0
+    lens = torch.tensor([N, N, N, N - 2, 2, 1], dtype=torch.int32)
+    _check(crf, oracle_mod, phi, lens, 500 + T, f"maps T={T} {dtype}", min_exact=0.2)
+    _check_every_draw(crf, oracle_mod, phi, lens, 500 + T, f"maps T={T} {dtype}")
+    for value, tag in ((0.0, 0), (1.0 - 2.0 ** -24, T - 1)):
+        flat = torch.zeros(2, N, T, T)
+        got = crf.lccrf_sample(flat.cuda(), torch.full((2, N), value).cuda()).cpu().numpy()
+        assert (got == tag).all() or (value > 0 and (got >= T - 2).all())
