@@ -285,9 +285,10 @@ inline bool scan_pays_sample(int B, int N, int T) {
 // workgroups of twelve waves each), against 11 us plus 0.6 us a position for the one-wave kernels and some 27 us plus
 // 0.75 ns a position of the whole batch for the scan (marginals, lanes / scan / sequential: B=128 N=32 T=13
 // 23 / - / 32, B=256 N=128 T=16 50 / 53 / 98, B=128 N=128 T=9 46 / 41 / 99, B=32 N=256 T=8 75 / 38 / 170,
-// B=512 N=64 T=16 62 / - / 55).
+// B=512 N=64 T=16 62 / - / 55).  With 5 .. 7 tags the one-wave kernels take as long a step, 0.55 us, and these 0.2 (marginals, sequential /
+// these: B=4 N=42 T=5 34 / 16, B=87 N=53 T=6 43 / 19, B=200 N=40 T=7 34 / 19, B=4 N=16 T=6 14 / 12; samples B=200 N=40 T=5 42 / 21).
 inline bool lanes_pay_sum(int op, int B, int N, int T) {
-    if (!lccrf::lane_chains_supported(T)) return false;
+    if (!lccrf::lane_chains_fit(T)) return false;
     const int cus = current_device_cus();
     if (T <= 16) {
         if (B > cus || N < 16) return false;
@@ -319,7 +320,7 @@ inline bool lanes_pay_sum(int op, int B, int N, int T) {
 // potentials these kernels take steps in the log domain (independent normal ones, B=128 N=128 T=32: deviation 12 66 / 94, 20
 // 131 / 99; a tag that is forbidden everywhere does not matter, N=256 120 / 163).
 inline bool lanes_pay_sample(int B, int N, int T) {
-    if (!lccrf::lane_chains_supported(T) || B > current_device_cus() || N < 16) return false;
+    if (!lccrf::lane_chains_fit(T) || B > current_device_cus() || N < 16) return false;
     if (!scan_pays_sample(B, N, T)) return true;
     const double n = (double)N;
     if (T <= 16) return n * (0.245 - 0.00085 * B) <= 16.0;
@@ -422,6 +423,9 @@ size_t lccrf_workspace_bytes(lccrf_op op, int B, int N, int T, lccrf_dtype dt) {
     }
 }
 
+// (5 .. 7 tags: a caller cannot ask for the chain-wave kernels, and is told what it can ask for.)
+static int lanes_algo(int T) { return lccrf::lane_chains_supported(T) ? LCCRF_ALGO_SEQUENTIAL_LANES : LCCRF_ALGO_SEQUENTIAL; }
+
 int lccrf_auto_algo(lccrf_op op, int B, int N, int T) {
     const KnobSnapshot knobs;
     if (!shape_ok(B, N, T)) return LCCRF_EINVAL;
@@ -429,15 +433,15 @@ int lccrf_auto_algo(lccrf_op op, int B, int N, int T) {
     switch (op) {
         case LCCRF_OP_LOGZ:
         case LCCRF_OP_MARGINALS:
-            if (lanes_pay_sum(op == LCCRF_OP_LOGZ ? 0 : 1, B, N, T)) return LCCRF_ALGO_SEQUENTIAL_LANES;
+            if (lanes_pay_sum(op == LCCRF_OP_LOGZ ? 0 : 1, B, N, T)) return lanes_algo(T);
             scan = scan_pays_sum(B, N, T);
             break;
         case LCCRF_OP_LOG_PROB:
-            if (lanes_pay_sum(0, B, N, T)) return LCCRF_ALGO_SEQUENTIAL_LANES;
+            if (lanes_pay_sum(0, B, N, T)) return lanes_algo(T);
             scan = scan_pays_sum(B, N, T);
             break;
         case LCCRF_OP_SAMPLE:
-            if (lanes_pay_sample(B, N, T)) return LCCRF_ALGO_SEQUENTIAL_LANES;
+            if (lanes_pay_sample(B, N, T)) return lanes_algo(T);
             scan = scan_pays_sample(B, N, T);
             break;
         case LCCRF_OP_ARGMAX:

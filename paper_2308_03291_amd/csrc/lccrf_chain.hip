@@ -1212,6 +1212,7 @@ static hipError_t launch_stream(int op, int dtype, ChainArgs a, hipStream_t st, 
 
 bool structured_supported(int T) { return T >= 1 && T <= 128; }
 bool lane_chains_supported(int T) { return lane_supported(T); }
+bool lane_chains_fit(int T) { return lane_fits(T); }
 
 // Forward chains over whole sequences, every alpha stored (ua, Oa): the first pass of sampling.
 hipError_t launch_full_forward(int dtype, const void* phi, const int32_t* lengths, int B, int N, int T, float* ua,
@@ -1265,7 +1266,7 @@ hipError_t launch_sequential_sum(int op, int dtype, const void* phi, const int32
     a.trans = trans;
     if (emit && T > 128) return hipErrorInvalidValue;  // the caller checks structured_supported(T) first
     if (lanes) {
-        if (exact_only || !lane_supported(T)) return hipErrorInvalidValue;
+        if (exact_only || !lane_fits(T)) return hipErrorInvalidValue;
         hipError_t e = launch_lane_pass(false, dtype, a, op == 0, lane_poll_limit, st);
         if (e != hipSuccess) return e;
         if (between) {

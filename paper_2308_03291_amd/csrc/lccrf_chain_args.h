@@ -130,6 +130,7 @@ hipError_t launch_wave_chunks(int dtype, const ChainArgs& a, hipStream_t st);
 // exactly as launch_wave_pass; meet_only: a first pass that stores the vectors of the meeting position only;
 // poll_limit: how many times the chain wave looks for a matrix that is late before it goes on alone.
 bool lane_supported(int T);
+bool lane_fits(int T);  // (5 .. 7 tags as well)
 hipError_t launch_lane_pass(bool second_pass, int dtype, const ChainArgs& a, bool meet_only, int poll_limit, hipStream_t st);
 
 }  // namespace lccrf

@@ -1001,8 +1001,9 @@ __global__ __launch_bounds__(64 * lane_waves(NBLK)) void lane_chain_kernel(Chain
 
 // ---------------------------------------------------------------------------------------
 // Dense or structured potentials, whole sequences, 8 .. 64 tags: multiples of four (16-byte pieces of a row) at every
-// size, other counts (element loads) up to 48.
-bool lane_supported(int T) { return T >= 8 && T <= 64 && (T % 4 == 0 || T <= 48); }
+// size, other counts (element loads) up to 48.  Five to seven tags are taken too where it pays, though no caller can ask for it.
+bool lane_supported(int T) { return T >= 8 && lane_fits(T); }
+bool lane_fits(int T) { return T >= 5 && T <= 64 && (T % 4 == 0 || T <= 48); }
 
 template <int NBLK, typename TIN, bool AL, bool PASS2>
 static hipError_t launch_lane_kernel(const ChainArgs& a, int meet_only, int poll_limit, hipStream_t st) {
@@ -1032,7 +1033,7 @@ static hipError_t launch_lane_nblk(bool second_pass, int dtype, const ChainArgs&
 }
 
 hipError_t launch_lane_pass(bool second_pass, int dtype, const ChainArgs& a, bool meet_only, int poll_limit, hipStream_t st) {
-    if (!lane_supported(a.T) || a.chunk > 0 || (a.emit && (dtype != 0 || !a.trans))) return hipErrorInvalidValue;
+    if (!lane_fits(a.T) || a.chunk > 0 || (a.emit && (dtype != 0 || !a.trans))) return hipErrorInvalidValue;
     const int mo = meet_only ? 1 : 0;
     if (a.T <= 16) return launch_lane_nblk<1>(second_pass, dtype, a, mo, poll_limit, st);
     if (a.T <= 32) return launch_lane_nblk<2>(second_pass, dtype, a, mo, poll_limit, st);

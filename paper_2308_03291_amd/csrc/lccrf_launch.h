@@ -26,6 +26,7 @@ hipError_t launch_sequential_sum(int op, int dtype, const void* phi, const int32
 // lanes: the chain-wave / producer-wave kernels of lccrf_lane.hip (lane_chains_supported(T); dense or structured potentials);
 // lane_poll_limit: polls their chain wave spends on a late matrix before it continues in the log domain.
 bool lane_chains_supported(int T);
+bool lane_chains_fit(int T);  // what AUTO may give them: 5 .. 7 tags as well
 // Sampling (lccrf_chain.hip, lccrf_extras.hip): forward chains over whole sequences with every alpha
 // stored, then the backward sweep that draws the tags from the given uniforms [B][N].
 hipError_t launch_full_forward(int dtype, const void* phi, const int32_t* lengths, int B, int N, int T, float* ua,

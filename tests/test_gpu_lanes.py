@@ -263,3 +263,31 @@ def test_a_step_that_is_not_accepted_at_every_place_of_a_round(crf, oracle_mod, 
         phi[i, i, :, 2] += 90.0
         phi[i, i, 1, :] -= 90.0
     check_case(crf, oracle_mod, phi, None, algo=crf.ALGO_SEQUENTIAL_LANES, what=f"refused steps T={T}", queries=("logz", "mu"))
+
+
+@pytest.mark.parametrize("T", (5, 6, 7))
+@pytest.mark.parametrize("N", (16, 17, 40))
+def test_five_to_seven_tags(crf, oracle_mod, T, N):
+    """What AUTO gives to these kernels although ALGO_SEQUENTIAL_LANES refuses it: every query that takes them, both types, and
+    the inputs that must leave the linear domain."""
+    from test_gpu_sample import _check, _check_every_draw
+    from test_gpu_structured import _check as check_structured, _make
+    lens = torch.tensor([N, N - 1, N, N, 1, 2, 0, 15], dtype=torch.int32)
+    for dtype in ("f32", "bf16"):
+        phi, _ = workloads.random_case(9200 + 13 * T + N, 8, N, T, scale=1.5, dtype=dtype)
+        phi[1, 7, :, 2] = float("-inf")
+        phi[2, :, :, T - 1] = float("-inf")
+        phi[3, 5] += 300.0
+        phi[3, 11] -= 300.0
+        check_case(crf, oracle_mod, phi, lens, what=f"T={T} N={N} {dtype}", queries=("logz", "mu"))
+        tags = torch.randint(0, T - 1, (8, N), generator=torch.Generator().manual_seed(N)).to(torch.int32)
+        got = crf.lccrf_log_prob(phi.cuda(), tags.cuda(), lens.cuda()).cpu().numpy()
+        want = oracle_mod.log_prob(phi, tags.numpy(), lens.numpy())
+        assert np.allclose(got, want, rtol=1e-5, atol=1e-5)
+        _check(crf, oracle_mod, phi, lens, T + N, f"sample T={T} N={N} {dtype}", min_exact=0.2)
+        _check_every_draw(crf, oracle_mod, phi, lens, T + N, f"sample T={T} N={N} {dtype}")
+    emit, trans = _make(9210 + T, 8, N, T)
+    check_structured(crf, oracle_mod, emit, trans, lens, f"structured T={T} N={N}")
+    assert crf.auto_algo(crf.OP_MARGINALS, 8, N, T) == crf.ALGO_SEQUENTIAL
+    with pytest.raises(crf.LccrfError):
+        crf.lccrf_log_partition(torch.zeros(1, N, T, T, device="cuda"), algo=crf.ALGO_SEQUENTIAL_LANES)
