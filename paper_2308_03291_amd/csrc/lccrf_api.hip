@@ -334,10 +334,10 @@ inline bool lanes_pay_sample(int B, int N, int T) {
 // B=128 N=256 T=32 106 / 59, B=256 N=128 T=32 64 / 57, B=384 N=128 T=32 68 / 75; B=128 N=128 T=48 99 / 74,
 // B=64 N=256 T=40 181 / 117, B=256 N=128 T=48 127 / 130; above 48 tags the ring holds too few matrices
 // (B=32 N=256 T=64 182 / 208).  Tag counts that are no multiple of four gain the same (B=128 N=128 T=45 106 / 76,
-// T=48 96 / 72; B=32 N=64 T=30 43 / 27); chains of fewer than 16 positions do not pay the kernel's start
-// (B=4 N=8 T=5 17.8 / 18.6).
+// T=48 96 / 72; B=32 N=64 T=30 43 / 27).  Short chains of up to 32 tags go to the one-wave kernels, whose workgroup traces the path as well
+// (these / one launch: T=16 N=16 11.1 / 9.6, N=24 11.3 / 9.8, N=32 11.4 / 11.4, N=40 11.3 / 12.9; T=32 N=16 11.3 / 10.5, N=20 11.9 / 11.7, N=24 11.6 / 12.7).
 inline bool lanes_pay_max(int B, int N, int T) {
-    if (!lccrf::lane_max_supported(T) || T > 48 || N < 16) return false;
+    if (!lccrf::lane_max_supported(T) || T > 48 || N < (T <= 16 ? 32 : T <= 32 ? 20 : 16)) return false;
     const int cus = current_device_cus();
     return T <= 16 ? B <= 2 * cus : T <= 32 ? B <= cus : 2 * B <= cus;
 }

@@ -931,7 +931,7 @@ __global__ __launch_bounds__(kTraceThreads) void viterbi_trace_kernel(VitArgs a)
     trace_span<kTraceThreads, kTraceBytes>(a, vit_span(a, blockIdx.x), sm);
 }
 
-// A chunk of the scan (up to 32 tags) by one workgroup of two waves: its forward and its backward chain side by
+// A chunk of the scan, or a whole sequence (up to 32 tags), by one workgroup of two waves: its forward and its backward chain side by
 // side, then, behind one barrier, its trace: the pointers and the two vectors of the meeting point come back
 // from memory the same workgroup has just written (one launch and one trip through the launch queue less).
 constexpr int kFusedTraceBytes = 2048;
@@ -968,7 +968,10 @@ static hipError_t launch_geo(const VitArgs& a, hipStream_t st) {
 
 template <int TP, typename TIN, bool ALIGNED, bool STRUCT>
 static hipError_t launch_wave_vit(const VitArgs& a, hipStream_t st) {
-    if (a.chunk > 0) {
+    // Whole sequences: short ones, whose second launch would take a third of the time (B=52 N=14 T=16 12.3 -> 9.6 us, structured
+    // 14.7 -> 9.9, B=1024 N=64 T=8 24.9 -> 21.0), and the largest batches (B=2048 N=512 T=8 196 -> 171); in between a trace by 128 threads takes longer
+    // than it saves (B=300 N=100 T=32 45 / 50, B=1024 N=300 T=9 90 / 97).
+    if (a.chunk > 0 || a.N <= (TP == 16 ? 64 : 32) || a.B >= 2048) {
         hipLaunchKernelGGL((viterbi_chunk_kernel<TP, TIN, ALIGNED, STRUCT>), dim3(a.B * a.C), dim3(128), 0, st, a);
         return hipGetLastError();
     }

@@ -151,3 +151,26 @@ def test_auto_takes_the_chain_wave_kernels_where_they_pay(crf):
     assert A(32, 64, 30) == crf.ALGO_SEQUENTIAL_LANES       # any tag count up to 48
     assert A(128, 128, 45) == crf.ALGO_SEQUENTIAL_LANES
     assert A(4, 8, 5) == crf.ALGO_SEQUENTIAL                # config 1: too short to pay
+
+
+@pytest.mark.parametrize("T", (1, 3, 4, 5, 9, 16, 17, 23, 32))
+@pytest.mark.parametrize("N", (1, 2, 15, 19, 20, 31, 32, 33, 64, 65))
+def test_short_sequences_by_one_launch(crf, oracle_mod, T, N):
+    """Either side of the lengths up to which one workgroup of two waves serves both chains and the trace."""
+    lens = torch.tensor([N, N - 1, 1, 0, max(1, N // 2), N], dtype=torch.int32)
+    for dtype in ("f32", "bf16"):
+        phi, _ = workloads.random_case(9900 + 13 * T + N, 6, N, T, scale=1.5, dtype=dtype)
+        if T > 2:
+            phi[5, N // 2, :, 1] = float("-inf")
+        check_case(crf, oracle_mod, phi, lens, what=f"one launch T={T} N={N} {dtype}", queries=("vit",))
+
+
+def test_large_batches_by_one_launch(crf):
+    """2048 sequences whose halves are longer than the window of pointers a trace holds (2048 bytes): the same as the chain-wave kernels."""
+    phi = torch.randn(2048, 500, 9, 9, generator=torch.Generator(device="cuda").manual_seed(77), device="cuda")
+    lens = torch.randint(0, 501, (2048,), generator=torch.Generator(device="cuda").manual_seed(78), device="cuda").to(torch.int32)
+    score, tags = crf.lccrf_argmax(phi, lens)
+    for b in range(0, 2048, 512):
+        part = slice(b, b + 512)
+        want = crf.lccrf_argmax(phi[part].contiguous(), lens[part].contiguous(), algo=crf.ALGO_SEQUENTIAL_LANES)
+        assert torch.equal(score[part], want[0]) and torch.equal(tags[part], want[1])
