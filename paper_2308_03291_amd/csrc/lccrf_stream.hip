@@ -506,11 +506,13 @@ __global__ __launch_bounds__(1024) void stream_half_kernel(ChainArgs a) {
 // so rounding drift between the chains' offsets does not reach the result.  Nothing here depends on another position:
 // where two workgroups a sequence leave most of the chip idle, the chains take their steps without writing and this kernel
 // moves the bytes with the whole chip.
-constexpr int kEdgeThreads = 256;
+constexpr int kEdgeThreads = 256, kEdgeUnroll = 8;
 template <typename TIN, bool ALIGNED>
 __global__ __launch_bounds__(kEdgeThreads) void edge_marginal_kernel(ChainArgs a) {
     using Raw = RawPiece<TIN>;
-    __shared__ float av[256], bv[256], red[2][4];
+    __shared__ __attribute__((aligned(16))) float av[256], bv[256], red[2][4];
+    // (tag counts off the grid: beta from entry c on, and on from its beginning, so that any four in a row are one read)
+    __shared__ __attribute__((aligned(16))) float shifted[ALIGNED ? 1 : 4][ALIGNED ? 4 : 260];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int N = a.N, T = a.T, TT = T * T;
     const int b = blockIdx.x / N, i = blockIdx.x % N;
@@ -538,6 +540,13 @@ __global__ __launch_bounds__(kEdgeThreads) void edge_marginal_kernel(ChainArgs a
     if (lane == 0) red[0][wave] = wm;
     av[tid] = i > 0 && tid < T ? a.ua[(vb + i - 1) * T + tid] : 0.f;
     bv[tid] = beta;
+    if (!ALIGNED) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            if (tid < T && tid >= c) shifted[c][tid - c] = beta;
+            if (tid < 4 + c) shifted[c][T + tid - c] = beta;
+        }
+    }
     __syncthreads();
     const float M = fmaxf(fmaxf(red[0][0], red[0][1]), fmaxf(red[0][2], red[0][3]));
     const float ws = xor_sum<1, 64>(ex2(z - finite_or_zero(M)));
@@ -563,22 +572,47 @@ __global__ __launch_bounds__(kEdgeThreads) void edge_marginal_kernel(ChainArgs a
     const double K = a.Oa[vb + i - 1] - a.Oa[vb + i] - lzd;
     const int Ki = uniform((int)rintf(fminf(fmaxf((float)K, -40.f), 0.f)));
     const float Kf = (float)(K - (double)Ki);
-    // A wave takes whole rows; the last piece of a row is moved back to end with it (what it holds twice is written
-    // twice, the same values).
+    // Four entries a thread, as they lie in memory: groups that begin on a 16-byte boundary of the tensors whatever the tag count, every lane
+    // at work, and what is over at either end one by one.  With a wave a row, its last piece moved back to end with it, 25 of 64 lanes worked at
+    // 100 tags and rows of odd tag counts lay off the grid: so / now, us, B=24 N=287 T=115 132 / 118, B=9 N=256 T=66 bfloat16 19.5 / 13.7, B=16 N=200
+    // T=201 bfloat16 156 / 138, B=16 N=200 T=100 42 / 41; B=32 N=256 T=201 bfloat16 385 either way, 5.2 TB/s.  (Streaming stores only where rows lie on
+    // the grid: of odd tag counts every wave's 1 KB has lines in common with the next, B=32 N=256 T=201 437.)
+    const unsigned from = (unsigned)((vb + i) * TT & 3), head = (4 - from) & 3, groups = (TT - head) >> 2;
     const TIN* mat = static_cast<const TIN*>(a.phi) + (vb + i) * TT;
-    if (4 * lane < T) {
-        const int c4 = min(4 * lane, T - 4);
-        const float b0 = bv[c4] + Kf, b1 = bv[c4 + 1] + Kf, b2 = bv[c4 + 2] + Kf, b3 = bv[c4 + 3] + Kf;
-#pragma unroll 8
-        for (int s = wave; s < T; s += kEdgeThreads / 64) {
-            const typename Raw::type r = Raw::template load<ALIGNED>((const GlobalBytes*)(mat + (size_t)s * T + c4));
-            const float as = av[s];
-            const auto edge = [&](int j, float b) { return __builtin_amdgcn_ldexpf(ex2(__builtin_fmaf(Raw::get(r, j), kLog2e, as) + b), Ki); };
-            const float m0 = edge(0, b0), m1 = edge(1, b1), m2 = edge(2, b2), m3 = edge(3, b3);
-            float* out = mu + (size_t)s * T + c4;
-            if (ALIGNED) stream_store4(out, m0, m1, m2, m3);
-            else store4_anywhere(out, m0, m1, m2, m3);
+    const unsigned recip = (unsigned)((0x100000000ull + T - 1) / T);  // k / T = umulhi(k, recip): k < 2^16, T <= 256
+    const auto edge = [&](float x, float as, float bs) { return __builtin_amdgcn_ldexpf(ex2(__builtin_fmaf(x, kLog2e, as) + (bs + Kf)), Ki); };
+    for (unsigned q = tid; q < groups; q += kEdgeThreads * kEdgeUnroll) {
+        typename Raw::type raw[kEdgeUnroll];
+#pragma unroll
+        for (int r = 0; r < kEdgeUnroll; ++r)
+            raw[r] = Raw::template load<true>((const GlobalBytes*)(mat + head + 4 * min(q + kEdgeThreads * r, groups - 1)));
+#pragma unroll
+        for (int r = 0; r < kEdgeUnroll; ++r) {
+            const unsigned k = head + 4 * min(q + kEdgeThreads * r, groups - 1);  // (past the end: the last group again, the same values)
+            const unsigned s = __umulhi(k, recip), t = k - s * (unsigned)T;
+            float m[4];
+            if (ALIGNED) {
+                const float as = av[s];
+                const float4 b4 = *reinterpret_cast<const float4*>(&bv[t]);
+                m[0] = edge(Raw::get(raw[r], 0), as, b4.x);
+                m[1] = edge(Raw::get(raw[r], 1), as, b4.y);
+                m[2] = edge(Raw::get(raw[r], 2), as, b4.z);
+                m[3] = edge(Raw::get(raw[r], 3), as, b4.w);
+            } else {
+                const float a0 = av[s], a1 = av[min(s + 1, (unsigned)T - 1)];
+                const float4 b4 = *reinterpret_cast<const float4*>(&shifted[t & 3][t & ~3u]);
+                m[0] = edge(Raw::get(raw[r], 0), a0, b4.x);
+                m[1] = edge(Raw::get(raw[r], 1), t + 1 < (unsigned)T ? a0 : a1, b4.y);
+                m[2] = edge(Raw::get(raw[r], 2), t + 2 < (unsigned)T ? a0 : a1, b4.z);
+                m[3] = edge(Raw::get(raw[r], 3), t + 3 < (unsigned)T ? a0 : a1, b4.w);
+            }
+            if (ALIGNED) stream_store4(mu + k, m[0], m[1], m[2], m[3]);
+            else *reinterpret_cast<float4*>(mu + k) = make_float4(m[0], m[1], m[2], m[3]);
         }
+    }
+    if (!ALIGNED && (unsigned)tid < (unsigned)TT - 4 * groups) {
+        const unsigned k = (unsigned)tid < head ? tid : 4 * groups + tid, s = __umulhi(k, recip), t = k - s * (unsigned)T;
+        mu[k] = edge(Elem<TIN>::get(mat + k), av[s], bv[t]);
     }
 }
 
@@ -996,7 +1030,7 @@ bool stream_supported(int T) { return T > 128 && T <= 256; }
 int first_pass_largest_row(int T) { return T > 32 && T <= 256 ? linear_largest_row(T > 64 ? 1024 : 256, T) : -1; }
 
 hipError_t launch_edge_marginals(int dtype, const ChainArgs& a, hipStream_t st) {
-    if (a.T < 4 || a.T > 256 || a.chunk > 0 || a.emit) return hipErrorInvalidValue;
+    if (a.T < 8 || a.T > 256 || a.chunk > 0 || a.emit) return hipErrorInvalidValue;
     const bool aligned = (a.T % 4) == 0;
     const dim3 grid((unsigned)a.B * a.N), block(kEdgeThreads);
     if (dtype == 0) {
