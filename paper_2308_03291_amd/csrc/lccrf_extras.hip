@@ -976,175 +976,246 @@ __device__ __forceinline__ int draw_last_tag(const float* __restrict__ alpha_las
     return first_over != 0x7fffffff ? first_over : last_pos;
 }
 
+constexpr int kWalkShort = 128;
+
+// The walk through a window of the table, by a workgroup.  Walked tag by tag it is one look-up in LDS behind the other, 60 ns each; so
+// the window is cut into stretches, a thread takes a tag that a stretch may be entered on and follows it to the end of the stretch, and
+// what is left one behind the other is a look-up a stretch.
+template <int THREADS>
+struct WalkShared {
+    __attribute__((aligned(16))) uint8_t win[kWalkWindow];  // the maps, [position][tag]
+    static constexpr int ITEMS = THREADS == 64 ? 4 : 1;  // stretches and tags a thread follows side by side
+    static constexpr int ALL = ITEMS * THREADS;          // (T <= 256: at least one stretch)
+    __attribute__((aligned(16))) uint8_t passed[kWalkWindow + ALL];  // [step][stretch][tag entered on]: the tag reached by that step
+    uint8_t left_on[ALL];      // [stretch][tag entered on]
+    uint8_t entered[ALL + 1];  // the tag every stretch is entered on
+    int last;
+};
+
 // The maps of positions lo .. lo + np - 1 of a sequence (Fb: its rows of the table) into LDS.
-__device__ __forceinline__ void load_window(uint8_t* win, const uint8_t* __restrict__ Fb, int lo, int np, int T, int lane) {
+template <int THREADS>
+__device__ __forceinline__ void load_window(uint8_t* win, const uint8_t* __restrict__ Fb, int lo, int np, int T) {
     const uint8_t* src = Fb + (size_t)lo * T;
-    const int nbytes = np * T;
+    const int nbytes = np * T, tid = threadIdx.x;
     if (((reinterpret_cast<uintptr_t>(src) | (uintptr_t)nbytes) & 15) == 0) {
-        for (int k = lane; k < nbytes / 16; k += 64)
+        for (int k = tid; k < nbytes / 16; k += THREADS)
             reinterpret_cast<uint4*>(win)[k] = reinterpret_cast<const uint4*>(src)[k];
+    } else if (((reinterpret_cast<uintptr_t>(src) | (uintptr_t)nbytes) & 3) == 0) {
+        for (int k = tid; k < nbytes / 4; k += THREADS)
+            reinterpret_cast<unsigned*>(win)[k] = reinterpret_cast<const unsigned*>(src)[k];
     } else {
-        for (int k = lane; k < nbytes; k += 64) win[k] = src[k];
+        for (int k = tid; k < nbytes; k += THREADS) win[k] = src[k];
     }
 }
 
-// A long window is cut into 64 segments: lane l composes the maps of segment l for all T possible
-// tags above it (independent look-ups, so they overlap) into segmap[l][.].
-__device__ __forceinline__ void compose_segments(const uint8_t* win, uint8_t* segmap, int np, int T, int lane, int& bot, int& top) {
-    const int seg = (np + 63) / 64;
-    bot = lane * seg < np ? lane * seg : np;  // window-relative
-    top = bot + seg < np ? bot + seg : np;
-    for (int c0 = 0; c0 < T; c0 += 4) {
-        int t0 = c0, t1 = c0 + 1 < T ? c0 + 1 : c0, t2 = c0 + 2 < T ? c0 + 2 : c0, t3 = c0 + 3 < T ? c0 + 3 : c0;
-        for (int r = top - 1; r >= bot; --r) {
-            const uint8_t* row = win + r * T;
-            t0 = row[t0]; t1 = row[t1]; t2 = row[t2]; t3 = row[t3];
+// Stretches of a window of np positions: as many steps in a stretch as there are stretches, if there are the threads for it.
+struct Stretches {
+    int steps, count;
+};
+template <int THREADS>
+__device__ __forceinline__ Stretches stretches_of(int np, int T) {
+    const int most = WalkShared<THREADS>::ALL / T;
+    const int steps = max((np + most - 1) / most, (int)sqrtf((float)np) + 1);
+    return {steps, (np + steps - 1) / steps};
+}
+
+// Every stretch from every tag (downwards from position np - 1).  Called by the whole workgroup, behind a barrier; one has to follow.
+template <int THREADS>
+__device__ __forceinline__ void walk_stretches(WalkShared<THREADS>& sm, const Stretches& st, int np, int T) {
+    constexpr int ITEMS = WalkShared<THREADS>::ITEMS;
+    int g[ITEMS], t[ITEMS], cur[ITEMS], top[ITEMS], n[ITEMS];
+#pragma unroll
+    for (int q = 0; q < ITEMS; ++q) {
+        const int k = threadIdx.x + q * THREADS;
+        g[q] = k / T;
+        t[q] = cur[q] = k - g[q] * T;
+        top[q] = np - 1 - g[q] * st.steps;
+        n[q] = g[q] < st.count ? min(st.steps, top[q] + 1) : 0;
+    }
+    for (int j = 0; j < st.steps; ++j) {
+        int next[ITEMS];
+#pragma unroll
+        for (int q = 0; q < ITEMS; ++q) next[q] = sm.win[max(top[q] - j, 0) * T + cur[q]];
+#pragma unroll
+        for (int q = 0; q < ITEMS; ++q) {
+            cur[q] = next[q];  // (past the end of the stretch: never used)
+            if (THREADS > 64 && j < n[q]) sm.passed[(j * st.count + g[q]) * T + t[q]] = (uint8_t)next[q];
+            if (j == n[q] - 1) sm.left_on[g[q] * T + t[q]] = (uint8_t)next[q];
         }
-        segmap[lane * T + c0] = (uint8_t)t0;
-        if (c0 + 1 < T) segmap[lane * T + c0 + 1] = (uint8_t)t1;
-        if (c0 + 2 < T) segmap[lane * T + c0 + 2] = (uint8_t)t2;
-        if (c0 + 3 < T) segmap[lane * T + c0 + 3] = (uint8_t)t3;
     }
 }
 
-// Positions lo .. lo + np - 1 (their maps in win) from the tag `cur` above them, tags written to y;
-// returns the tag of position lo.  A short window is walked by one lane; a long one (small tag sets)
-// segment by segment: every lane composes its segment, one lane passes the actual tag down through
-// the 64 segment maps, and every lane walks its segment from the tag it was handed.
-__device__ __forceinline__ int walk_window(const uint8_t* win, uint8_t* segmap, uint8_t* entry, int lo, int np, int T,
-                                           int lane, int cur, int32_t* __restrict__ y) {
-    if (np <= 128) {
-        if (lane == 0) {
-            for (int r = np - 1; r >= 0; --r) {
-                cur = win[r * T + cur];
-                y[lo + r] = cur;
-            }
-            entry[64] = (uint8_t)cur;
+// Positions lo .. lo + np - 1 (their maps in sm.win, behind a barrier) from the tag `cur` above them, tags written to y; returns the tag of
+// position lo.
+template <int THREADS>
+__device__ __forceinline__ int walk_window(WalkShared<THREADS>& sm, int lo, int np, int T, int cur, int32_t* __restrict__ y) {
+    const Stretches st = stretches_of<THREADS>(np, T);
+    walk_stretches(sm, st, np, T);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int q = 0; q < st.count; ++q) {
+            sm.entered[q] = (uint8_t)cur;
+            cur = sm.left_on[q * T + cur];
         }
-    } else {
-        int bot, top;
-        compose_segments(win, segmap, np, T, lane, bot, top);
-        __syncthreads();
-        if (lane == 0) {
-            for (int l = 63; l >= 0; --l) {
-                entry[l] = (uint8_t)cur;
-                cur = segmap[l * T + cur];
-            }
-            entry[64] = (uint8_t)cur;
-        }
-        __syncthreads();
-        int t = entry[lane];
-        for (int r = top - 1; r >= bot; --r) {
-            t = win[r * T + t];
-            y[lo + r] = t;
-        }
+        sm.entered[st.count] = (uint8_t)cur;
     }
     __syncthreads();
-    return entry[64];
+    if constexpr (THREADS > 64) {
+        for (int k = threadIdx.x; k < np; k += THREADS) {
+            const int q = k / st.steps, j = k - q * st.steps;
+            y[lo + np - 1 - k] = sm.passed[(j * st.count + q) * T + sm.entered[q]];
+        }
+    } else {  // (one wave: writing down every tag passed costs more than a second walk, a lane a stretch: B=512 N=512 T=16 20.0 / 16.2 us, with eight stretches and tags a thread)
+        for (int q = threadIdx.x; q < st.count; q += THREADS) {
+            const int top = np - 1 - q * st.steps, n = min(st.steps, top + 1);
+            int t = sm.entered[q];
+            for (int j = 0; j < n; ++j) {
+                t = sm.win[(top - j) * T + t];
+                y[lo + top - j] = t;
+            }
+        }
+    }
+    return sm.entered[st.count];
 }
 
-// One wave per sequence: draws y_{L-1} from alpha_{L-1}, then follows the maps down through LDS
+// The tag of the last position, in every thread (-1: no finite path).
+template <int K, int THREADS>
+__device__ __forceinline__ void share_last_tag(WalkShared<THREADS>& sm, const float* __restrict__ alpha_last, float u, int T) {
+    if (threadIdx.x < 64) {
+        const int last = draw_last_tag<K>(alpha_last, u, T, threadIdx.x);
+        if (threadIdx.x == 0) sm.last = last;
+    }
+}
+
+// One workgroup a sequence (a grid of bounded size): draws y_{L-1} from alpha_{L-1}, then follows the maps down through LDS
 // windows of the table, one after the other.
+// us a draw, by a wave, one lane of it where a window has up to 128 positions / so: B=64 N=128 T=20 48 / 42, B=128 N=256 T=32 90.9 / 87.6, B=32 N=100
+// T=100 135 / 122, B=4 N=4096 T=16 (several windows) 87 / 77, the walk alone at B=1000 N=120 T=8 11.3 / 5.7.
+template <int K, int THREADS>
+__global__ __launch_bounds__(THREADS) void sample_walk_kernel(const int32_t* __restrict__ lengths, const float* __restrict__ ua,
+                                                                   const Uniforms uniforms, const uint8_t* __restrict__ F,
+                                                                   int B, int N, int T, int32_t* __restrict__ tags) {
+    __shared__ WalkShared<THREADS> sm;
+    const int tid = threadIdx.x;
+    const int wp = kWalkWindow / T;  // positions a window (T <= 256: at least 64)
+    for (int b = blockIdx.x; b < B; b += gridDim.x) {
+        const int L = clamp_length(lengths, b, N);
+        int32_t* y = tags + (size_t)b * N;
+        for (int i = L + tid; i < N; i += THREADS) y[i] = -1;
+        if (L == 0) continue;
+        const size_t vb = (size_t)b * N;
+        int hi = L - 1;  // positions [0, hi) still to walk
+        int lo = hi - wp > 0 ? hi - wp : 0;
+        load_window<THREADS>(sm.win, F + vb * T, lo, hi - lo, T);
+        share_last_tag<K>(sm, ua + (vb + L - 1) * T, uniforms.at(vb + L - 1), T);
+        __syncthreads();
+        int cur = sm.last;
+        if (cur < 0) {  // no finite path: all tags 0
+            for (int i = tid; i < L; i += THREADS) y[i] = 0;
+            hi = 0;
+        } else if (tid == 0) {
+            y[L - 1] = cur;
+        }
+        while (hi > 0) {
+            cur = walk_window(sm, lo, hi - lo, T, cur, y);
+            hi = lo;
+            lo = hi - wp > 0 ? hi - wp : 0;
+            __syncthreads();
+            if (hi > 0) load_window<THREADS>(sm.win, F + vb * T, lo, hi - lo, T);
+            __syncthreads();
+        }
+        __syncthreads();
+    }
+}
+
+// Short sequences, one window each: a wave a sequence, one of its lanes walks.
 template <int K>
-__global__ __launch_bounds__(64) void sample_walk_kernel(const int32_t* __restrict__ lengths, const float* __restrict__ ua,
-                                                         const Uniforms uniforms, const uint8_t* __restrict__ F,
-                                                         int N, int T, int32_t* __restrict__ tags) {
+__global__ __launch_bounds__(64) void sample_short_walk_kernel(const int32_t* __restrict__ lengths, const float* __restrict__ ua,
+                                                               const Uniforms uniforms, const uint8_t* __restrict__ F,
+                                                               int N, int T, int32_t* __restrict__ tags) {
     __shared__ __attribute__((aligned(16))) uint8_t win[kWalkWindow];
-    __shared__ uint8_t segmap[64 * 256];
-    __shared__ uint8_t entry[65];
+    __shared__ uint8_t path[kWalkShort];
     const int b = blockIdx.x, lane = threadIdx.x;
     const int L = clamp_length(lengths, b, N);
     int32_t* y = tags + (size_t)b * N;
     for (int i = L + lane; i < N; i += 64) y[i] = -1;
     if (L == 0) return;
     const size_t vb = (size_t)b * N;
-    int cur = draw_last_tag<K>(ua + (vb + L - 1) * T, uniforms.at(vb + L - 1), T, lane);
-    if (cur < 0) {  // no finite path: all tags 0
-        for (int i = lane; i < L; i += 64) y[i] = 0;
-        return;
+    load_window<64>(win, F + vb * T, 0, L - 1, T);
+    const int last = draw_last_tag<K>(ua + (vb + L - 1) * T, uniforms.at(vb + L - 1), T, lane);
+    __syncthreads();
+    if (last >= 0 && lane == 0) {
+        int cur = last;
+        for (int r = L - 2; r >= 0; --r) {
+            cur = win[r * T + cur];
+            path[r] = (uint8_t)cur;
+        }
     }
-    if (lane == 0) y[L - 1] = cur;
-    const int wp = kWalkWindow / T;  // positions a window (T <= 256: at least 64)
-    int hi = L - 1;                  // positions [0, hi) still to walk
-    while (hi > 0) {
-        const int lo = hi - wp > 0 ? hi - wp : 0;
-        load_window(win, F + vb * T, lo, hi - lo, T, lane);
-        __syncthreads();
-        cur = walk_window(win, segmap, entry, lo, hi - lo, T, lane, cur, y);
-        hi = lo;
-    }
+    __syncthreads();
+    for (int i = lane; i < L; i += 64) y[i] = last < 0 ? 0 : i == L - 1 ? last : path[i];  // (no finite path: all tags 0)
 }
 
 // Long sequences, all windows at once (W windows a sequence, counted from the top: window w holds the
 // positions below L - 1 - w wp).  First every window's maps are composed into one map of the tag above
 // the window to the tag of its lowest position (winmap [B][W][T] bytes) ...
-__global__ __launch_bounds__(64) void sample_window_map_kernel(const int32_t* __restrict__ lengths,
-                                                               const uint8_t* __restrict__ F, int N, int T, int W,
-                                                               uint8_t* __restrict__ winmap) {
-    __shared__ __attribute__((aligned(16))) uint8_t win[kWalkWindow];
-    __shared__ uint8_t segmap[64 * 256];
-    const int b = blockIdx.x / W, w = blockIdx.x % W, lane = threadIdx.x;
+template <int THREADS>
+__global__ __launch_bounds__(THREADS) void sample_window_map_kernel(const int32_t* __restrict__ lengths,
+                                                                         const uint8_t* __restrict__ F, int N, int T, int W,
+                                                                         uint8_t* __restrict__ winmap) {
+    __shared__ WalkShared<THREADS> sm;
+    const int b = blockIdx.x / W, w = blockIdx.x % W;
     const int L = clamp_length(lengths, b, N);
     const int wp = kWalkWindow / T;
     const int hi = L - 1 - w * wp;
     if (hi <= 0) return;
     const int lo = hi - wp > 0 ? hi - wp : 0, np = hi - lo;
-    load_window(win, F + (size_t)b * N * T, lo, np, T, lane);
+    load_window<THREADS>(sm.win, F + (size_t)b * N * T, lo, np, T);
     __syncthreads();
-    uint8_t* out = winmap + ((size_t)b * W + w) * T;
-    if (np <= 128) {
-        for (int t = lane; t < T; t += 64) {
-            int cur = t;
-            for (int r = np - 1; r >= 0; --r) cur = win[r * T + cur];
-            out[t] = (uint8_t)cur;
-        }
-    } else {
-        int bot, top;
-        compose_segments(win, segmap, np, T, lane, bot, top);
-        __syncthreads();
-        for (int t = lane; t < T; t += 64) {
-            int cur = t;
-            for (int l = 63; l >= 0; --l) cur = segmap[l * T + cur];
-            out[t] = (uint8_t)cur;
-        }
+    const Stretches st = stretches_of<THREADS>(np, T);
+    walk_stretches(sm, st, np, T);
+    __syncthreads();
+    for (int t = threadIdx.x; t < T; t += THREADS) {
+        int cur = t;
+        for (int q = 0; q < st.count; ++q) cur = sm.left_on[q * T + cur];
+        winmap[((size_t)b * W + w) * T + t] = (uint8_t)cur;
     }
 }
 
 // ... then every window finds the tag above it by passing the tag of the last position through the
 // maps of the windows above (at most W look-ups in LDS) and walks its own positions.
-template <int K>
-__global__ __launch_bounds__(64) void sample_window_walk_kernel(const int32_t* __restrict__ lengths, const float* __restrict__ ua,
-                                                                const Uniforms uniforms, const uint8_t* __restrict__ F,
-                                                                int N, int T, int W, const uint8_t* __restrict__ winmap,
-                                                                int32_t* __restrict__ tags) {
-    __shared__ __attribute__((aligned(16))) uint8_t win[kWalkWindow];
-    __shared__ uint8_t segmap[64 * 256];  // first the maps of the windows above (W T <= 16384 bytes)
-    __shared__ uint8_t entry[65];
-    const int b = blockIdx.x / W, w = blockIdx.x % W, lane = threadIdx.x;
+template <int K, int THREADS>
+__global__ __launch_bounds__(THREADS) void sample_window_walk_kernel(const int32_t* __restrict__ lengths, const float* __restrict__ ua,
+                                                                          const Uniforms uniforms, const uint8_t* __restrict__ F,
+                                                                          int N, int T, int W, const uint8_t* __restrict__ winmap,
+                                                                          int32_t* __restrict__ tags) {
+    __shared__ WalkShared<THREADS> sm;
+    const int b = blockIdx.x / W, w = blockIdx.x % W, tid = threadIdx.x;
     const int L = clamp_length(lengths, b, N);
     int32_t* y = tags + (size_t)b * N;
     if (w == 0)
-        for (int i = L + lane; i < N; i += 64) y[i] = -1;
+        for (int i = L + tid; i < N; i += THREADS) y[i] = -1;
     if (L == 0) return;
     const size_t vb = (size_t)b * N;
     const int wp = kWalkWindow / T;
     const int hi = L - 1 - w * wp;
     const int lo = hi - wp > 0 ? hi - wp : 0;
-    int cur = draw_last_tag<K>(ua + (vb + L - 1) * T, uniforms.at(vb + L - 1), T, lane);
+    if (hi <= 0 && w > 0) return;
+    if (hi > 0) load_window<THREADS>(sm.win, F + vb * T, lo, hi - lo, T);
+    const uint8_t* above = winmap + (size_t)b * W * T;  // (W T <= kWalkWindow bytes)
+    for (int k = tid; k < w * T; k += THREADS) sm.passed[k] = above[k];
+    share_last_tag<K>(sm, ua + (vb + L - 1) * T, uniforms.at(vb + L - 1), T);
+    __syncthreads();
+    int cur = sm.last;
     if (cur < 0) {  // no finite path: all tags 0
-        if (w == 0 && lane == 0) y[L - 1] = 0;
-        for (int i = lo + lane; i < hi; i += 64) y[i] = 0;
+        if (w == 0 && tid == 0) y[L - 1] = 0;
+        for (int i = lo + tid; i < hi; i += THREADS) y[i] = 0;
         return;
     }
-    if (w == 0 && lane == 0) y[L - 1] = cur;
+    if (w == 0 && tid == 0) y[L - 1] = cur;
     if (hi <= 0) return;
-    load_window(win, F + vb * T, lo, hi - lo, T, lane);
-    const uint8_t* above = winmap + (size_t)b * W * T;
-    for (int k = lane; k < w * T; k += 64) segmap[k] = above[k];
+    for (int v = 0; v < w; ++v) cur = sm.passed[v * T + cur];
     __syncthreads();
-    for (int v = 0; v < w; ++v) cur = segmap[v * T + cur];
-    __syncthreads();
-    walk_window(win, segmap, entry, lo, hi - lo, T, lane, cur, y);
+    walk_window(sm, lo, hi - lo, T, cur, y);
 }
 
 // Four waves a position up to 128 tags (sixteen rows a thread at most), eight up to 176, sixteen above.
@@ -1177,6 +1248,20 @@ static void launch_sample_map_wide(const TIN* phi, const int32_t* lengths, const
 #undef LCCRF_SAMPLE_MAP
 }
 
+// A lane walks short sequences (us a draw, so / in stretches: B=4 N=16 T=12 13.3 / 12.9, B=2048 N=16 T=16 32.8 / 39.5, B=1000 N=120 T=8 105 / 102).
+// Eight waves a workgroup while each has a compute unit to itself; beyond, one.  (Two or eight waves there walk as fast, but the next call's
+// forward chains, workgroups of one wave, then come to lie two to a SIMD: B=512 N=512 T=16 312 us, behind them 348.)
+#define LCCRF_WALK_BY_SIZE(LAUNCH_, workgroups_)                  \
+    do {                                                          \
+        const bool few = (workgroups_) <= 256;                    \
+        if (T <= 64 && few) LAUNCH_(1, 512);                      \
+        else if (T <= 64) LAUNCH_(1, 64);                         \
+        else if (T <= 128 && few) LAUNCH_(2, 512);                \
+        else if (T <= 128) LAUNCH_(2, 64);                        \
+        else if (few) LAUNCH_(4, 512);                            \
+        else LAUNCH_(4, 64);                                      \
+    } while (0)
+
 template <typename TIN>
 static hipError_t launch_sample_T(const TIN* phi, const int32_t* lengths, const float* ua, const double* Oa,
                                   const Uniforms uniforms, int B, int N, int T, uint8_t* F, uint8_t* winmap, int32_t* tags,
@@ -1197,19 +1282,29 @@ static hipError_t launch_sample_T(const TIN* phi, const int32_t* lengths, const 
     }
     // Several windows a sequence: all of them at once, two launches, if their maps fit the LDS staging.
     const int wp = kWalkWindow / T, W = N > 1 ? (N - 1 + wp - 1) / wp : 1;
-    if (W >= 2 && (size_t)W * T <= 64 * 256 && winmap) {
-        hipLaunchKernelGGL(sample_window_map_kernel, dim3(B * W), dim3(64), 0, st, lengths, F, N, T, W, winmap);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
+    if (W >= 2 && (size_t)W * T <= kWalkWindow && winmap) {
         const dim3 grid(B * W);
-        if (T <= 64) hipLaunchKernelGGL(sample_window_walk_kernel<1>, grid, dim3(64), 0, st, lengths, ua, uniforms, F, N, T, W, winmap, tags);
-        else if (T <= 128) hipLaunchKernelGGL(sample_window_walk_kernel<2>, grid, dim3(64), 0, st, lengths, ua, uniforms, F, N, T, W, winmap, tags);
-        else hipLaunchKernelGGL(sample_window_walk_kernel<4>, grid, dim3(64), 0, st, lengths, ua, uniforms, F, N, T, W, winmap, tags);
+#define LCCRF_WINDOWS(K_, THREADS_)                                                                                                          \
+    do {                                                                                                                                     \
+        hipLaunchKernelGGL(sample_window_map_kernel<THREADS_>, grid, dim3(THREADS_), 0, st, lengths, F, N, T, W, winmap);                    \
+        const hipError_t e = hipGetLastError();                                                                                              \
+        if (e != hipSuccess) return e;                                                                                                       \
+        hipLaunchKernelGGL((sample_window_walk_kernel<K_, THREADS_>), grid, dim3(THREADS_), 0, st, lengths, ua, uniforms, F, N, T, W, winmap, tags); \
+    } while (0)
+        LCCRF_WALK_BY_SIZE(LCCRF_WINDOWS, B * (long long)W);
+#undef LCCRF_WINDOWS
         return hipGetLastError();
     }
-    if (T <= 64) hipLaunchKernelGGL(sample_walk_kernel<1>, dim3(B), dim3(64), 0, st, lengths, ua, uniforms, F, N, T, tags);
-    else if (T <= 128) hipLaunchKernelGGL(sample_walk_kernel<2>, dim3(B), dim3(64), 0, st, lengths, ua, uniforms, F, N, T, tags);
-    else hipLaunchKernelGGL(sample_walk_kernel<4>, dim3(B), dim3(64), 0, st, lengths, ua, uniforms, F, N, T, tags);
+    if (N - 1 <= wp && N <= (B > 2048 ? kWalkShort : B > 256 ? 64 : 12)) {  // (of many sequences the look-ups of the ones hide behind those of the others)
+        if (T <= 64) hipLaunchKernelGGL(sample_short_walk_kernel<1>, dim3(B), dim3(64), 0, st, lengths, ua, uniforms, F, N, T, tags);
+        else if (T <= 128) hipLaunchKernelGGL(sample_short_walk_kernel<2>, dim3(B), dim3(64), 0, st, lengths, ua, uniforms, F, N, T, tags);
+        else hipLaunchKernelGGL(sample_short_walk_kernel<4>, dim3(B), dim3(64), 0, st, lengths, ua, uniforms, F, N, T, tags);
+        return hipGetLastError();
+    }
+    const dim3 grid(B < (1 << 20) ? B : 1 << 20);
+#define LCCRF_WALK(K_, THREADS_) hipLaunchKernelGGL((sample_walk_kernel<K_, THREADS_>), grid, dim3(THREADS_), 0, st, lengths, ua, uniforms, F, B, N, T, tags)
+    LCCRF_WALK_BY_SIZE(LCCRF_WALK, (long long)B);
+#undef LCCRF_WALK
     return hipGetLastError();
 }
 

@@ -226,3 +226,20 @@ def test_sample_maps_by_a_workgroup(crf, oracle_mod, T, dtype):
         flat = torch.zeros(2, N, T, T)
         got = crf.lccrf_sample(flat.cuda(), torch.full((2, N), value).cuda()).cpu().numpy()
         assert (got == tag).all() or (value > 0 and (got >= T - 2).all())
+
+
+# the walk: a wave a sequence and a workgroup, on both sides of the line between them; stretches that do and do not divide the window
+# (one tag a row included), several windows whose maps are composed; windows one after the other (more of them than the composed maps have room for)
+@pytest.mark.parametrize("B,N,T", [(5, 32, 6), (5, 33, 6), (5, 34, 200), (5, 82, 200), (2049, 128, 3), (2049, 129, 3), (4, 1025, 16), (3, 40000, 1), (2, 17000, 9)])
+def test_sample_walks(crf, oracle_mod, B, N, T):
+    phi, lens = workloads.random_case(8800 + N + T, B, N, T, scale=1.0, ragged=True, min_len=N // 2)
+    lens[0] = N
+    lens[1] = 1
+    if B > 100:
+        few = slice(0, 8)
+        u = torch.rand(B, N, generator=torch.Generator().manual_seed(N))
+        got = crf.lccrf_sample(phi.cuda(), u.cuda(), lens.cuda())
+        assert torch.equal(got[few], crf.lccrf_sample(phi[few].cuda(), u[few].cuda(), lens[few].cuda()))
+        mask = torch.arange(N)[None] < lens[:, None]
+        assert torch.equal(got.cpu() >= 0, mask) and int(got.max()) < T
+    _check_every_draw(crf, oracle_mod, phi[:8], lens[:8], 800 + N, f"walk N={N} T={T}")
