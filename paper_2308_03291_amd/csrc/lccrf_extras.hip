@@ -850,7 +850,7 @@ __global__ __launch_bounds__(256) void sample_map_kernel(const TIN* __restrict__
 template <typename TIN, bool ALIGNED, int W, int R>
 __global__ __launch_bounds__(W, 4) void sample_map_wide_kernel(const TIN* __restrict__ phi, const int32_t* __restrict__ lengths,
                                                                const float* __restrict__ ua, const double* __restrict__ Oa,
-                                                               const Uniforms uniforms, int N, int T, uint8_t* __restrict__ F) {
+                                                               const Uniforms uniforms, unsigned from, int N, int T, uint8_t* __restrict__ F) {
     using Raw = RawPiece<TIN>;
     __shared__ __attribute__((aligned(16))) float part[4 * W];  // [group][T]: G T <= 4 W
     __shared__ float av[256], bv[256], before[256];
@@ -858,7 +858,8 @@ __global__ __launch_bounds__(W, 4) void sample_map_wide_kernel(const TIN* __rest
     __shared__ unsigned char pick[256];
     __shared__ float us;
     const int tid = threadIdx.x;
-    const int b = blockIdx.x / (N - 1), i = blockIdx.x % (N - 1);
+    const unsigned at = from + blockIdx.x;
+    const int b = at / (unsigned)(N - 1), i = at % (unsigned)(N - 1);
     const int L = clamp_length(lengths, b, N);
     if (i >= L - 1) return;
     const size_t TT = (size_t)T * T, vb = (size_t)b * N;
@@ -1219,31 +1220,36 @@ __global__ __launch_bounds__(THREADS) void sample_window_walk_kernel(const int32
 }
 
 // Four waves a position up to 128 tags (sixteen rows a thread at most), eight up to 176, sixteen above.
+// (A launch holds fewer than 2^32 threads: 2^22 positions of sixteen waves.  Launches of 2^18 positions take half a millisecond and more each.)
+constexpr unsigned kWidePart = 1u << 18;
 template <typename TIN, bool ALIGNED>
 static void launch_sample_map_wide(const TIN* phi, const int32_t* lengths, const float* ua, const double* Oa, const Uniforms uniforms, int B,
                                    int N, int T, uint8_t* F, hipStream_t st) {
-    const dim3 grid((unsigned)((long long)B * (N - 1)));
+    const unsigned positions = (unsigned)B * (unsigned)(N - 1);  // (below 2^31: the potentials of as many would be 18 TB)
     const int W = T <= 128 ? 256 : T <= 176 ? 512 : 1024, G = W / ((T + 3) / 4), rows = (T + G - 1) / G;
-#define LCCRF_SAMPLE_MAP(W_, R_) hipLaunchKernelGGL((sample_map_wide_kernel<TIN, ALIGNED, W_, R_>), grid, dim3(W_), 0, st, phi, lengths, ua, Oa, uniforms, N, T, F)
-    if (W == 256) {
-        if (rows <= 5) LCCRF_SAMPLE_MAP(256, 5);
-        else if (rows <= 6) LCCRF_SAMPLE_MAP(256, 6);
-        else if (rows <= 8) LCCRF_SAMPLE_MAP(256, 8);
-        else if (rows <= 10) LCCRF_SAMPLE_MAP(256, 10);
-        else if (rows <= 13) LCCRF_SAMPLE_MAP(256, 13);
-        else LCCRF_SAMPLE_MAP(256, 16);
-    } else if (W == 512) {
-        if (rows <= 10) LCCRF_SAMPLE_MAP(512, 10);
-        else if (rows <= 12) LCCRF_SAMPLE_MAP(512, 12);
-        else if (rows <= 14) LCCRF_SAMPLE_MAP(512, 14);
-        else LCCRF_SAMPLE_MAP(512, 16);
-    } else {
-        if (rows <= 9) LCCRF_SAMPLE_MAP(1024, 9);
-        else if (rows <= 10) LCCRF_SAMPLE_MAP(1024, 10);
-        else if (rows <= 11) LCCRF_SAMPLE_MAP(1024, 11);
-        else if (rows <= 12) LCCRF_SAMPLE_MAP(1024, 12);
-        else if (rows <= 14) LCCRF_SAMPLE_MAP(1024, 14);
-        else LCCRF_SAMPLE_MAP(1024, 16);
+#define LCCRF_SAMPLE_MAP(W_, R_) hipLaunchKernelGGL((sample_map_wide_kernel<TIN, ALIGNED, W_, R_>), grid, dim3(W_), 0, st, phi, lengths, ua, Oa, uniforms, from, N, T, F)
+    for (unsigned from = 0; from < positions; from += kWidePart) {
+        const dim3 grid(positions - from < kWidePart ? positions - from : kWidePart);
+        if (W == 256) {
+            if (rows <= 5) LCCRF_SAMPLE_MAP(256, 5);
+            else if (rows <= 6) LCCRF_SAMPLE_MAP(256, 6);
+            else if (rows <= 8) LCCRF_SAMPLE_MAP(256, 8);
+            else if (rows <= 10) LCCRF_SAMPLE_MAP(256, 10);
+            else if (rows <= 13) LCCRF_SAMPLE_MAP(256, 13);
+            else LCCRF_SAMPLE_MAP(256, 16);
+        } else if (W == 512) {
+            if (rows <= 10) LCCRF_SAMPLE_MAP(512, 10);
+            else if (rows <= 12) LCCRF_SAMPLE_MAP(512, 12);
+            else if (rows <= 14) LCCRF_SAMPLE_MAP(512, 14);
+            else LCCRF_SAMPLE_MAP(512, 16);
+        } else {
+            if (rows <= 9) LCCRF_SAMPLE_MAP(1024, 9);
+            else if (rows <= 10) LCCRF_SAMPLE_MAP(1024, 10);
+            else if (rows <= 11) LCCRF_SAMPLE_MAP(1024, 11);
+            else if (rows <= 12) LCCRF_SAMPLE_MAP(1024, 12);
+            else if (rows <= 14) LCCRF_SAMPLE_MAP(1024, 14);
+            else LCCRF_SAMPLE_MAP(1024, 16);
+        }
     }
 #undef LCCRF_SAMPLE_MAP
 }

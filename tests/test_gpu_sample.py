@@ -243,3 +243,13 @@ def test_sample_walks(crf, oracle_mod, B, N, T):
         mask = torch.arange(N)[None] < lens[:, None]
         assert torch.equal(got.cpu() >= 0, mask) and int(got.max()) < T
     _check_every_draw(crf, oracle_mod, phi[:8], lens[:8], 800 + N, f"walk N={N} T={T}")
+
+
+def test_sample_maps_in_several_launches(crf, oracle_mod):
+    """65 tags, more positions than one launch of the maps takes: the same sequence 1100 times over."""
+    B, N, T = 1100, 240, 65
+    phi, _ = workloads.random_case(8900, 1, N, T, scale=1.0, dtype="bf16")
+    u = torch.rand(1, N, generator=torch.Generator().manual_seed(89))
+    got = crf.lccrf_sample(phi.cuda().expand(B, N, T, T).contiguous(), u.cuda().expand(B, N).contiguous())
+    assert bool((got == got[:1]).all())
+    assert _draws_miss(oracle_mod, phi[0], N, got[0].cpu().numpy(), u[0].numpy().astype(np.float64), "maps in parts") <= 1e-4
