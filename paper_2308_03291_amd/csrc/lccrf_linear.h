@@ -190,7 +190,8 @@ __device__ __forceinline__ bool linear_hopeless(const TIN* mat, int T, bool back
 // What a run that compares has found.  Another workgroup has walked the same positions before, from another vector, and left its
 // vectors in the rows this run is about to write.  D(t) = this run's logarithm less the one that is there, of one row: where the two
 // vectors are multiples of each other D is the same for every tag, and so it is in every row behind, since the steps are
-// linear.  A row matches if one number lies within tol(t) of every D(t), and a tag is an exact zero in both or in neither.  tol is 2^-20,
+// linear.  A row matches if one number lies within tol(t) of every D(t), and a tag is an exact zero in both or in neither (a row of
+// zeros alone says nothing: what follows it may have any factor, and no path has a finite score).  tol is 2^-20,
 // four roundings of a logarithm of one or two bits, and grows with the logarithm as its rounding does.  (Non-negative matrices never
 // widen such a gap, and all of it but a common factor shrinks from step to step as fast as it came down to tol.)
 struct LinMatch {
@@ -370,7 +371,7 @@ __device__ __forceinline__ int linear_run(LinSmem<LG>& ls, const LinJob<TIN, BAC
     const auto more = [&]() __attribute__((always_inline)) -> bool {
         if constexpr (COMPARE) {
             const float over = uniform_f(max16(ls.over[buf])), under = uniform_f(max16(ls.under[buf]));
-            match.hit = over + under <= 0.f;
+            match.hit = over > LCCRF_NEG_INF && over + under <= 0.f;
             match.delta = gap + 0.5 * (double)(over - under);
         }
         M = uniform_f(max16(ls.wmax[buf]));

@@ -71,3 +71,27 @@ def test_sampling(crf, oracle_mod, T):
     lens = torch.tensor([120, 119, 40, 2, 120], dtype=torch.int32)
     _check(crf, oracle_mod, phi, lens, 300 + T, f"sample in pieces T={T}", min_exact=0.0)
     _check_every_draw(crf, oracle_mod, phi, lens, 300 + T, f"sample in pieces T={T}")
+
+
+@pytest.mark.parametrize("T,dtype", [(66, "f32"), (128, "f32"), (136, "f32"), (201, "bf16")])
+def test_one_position_forbids_every_edge(crf, oracle_mod, T, dtype):
+    """A position whose whole matrix is -inf, at every place of every piece, and two of them in neighbouring pieces: no finite path, so
+    logZ = -inf and marginals 0.  (Behind it both the chain and the row it is compared with are zero everywhere, which says nothing.)"""
+    N, batch = 240, 16
+    base, _ = workloads.random_case(9900 + T, 1, N, T, dtype=dtype)
+    want_lz, want_mu = oracle_mod.marginals(base, None)
+    want_mu = torch.from_numpy(np.ascontiguousarray(want_mu)).cuda()
+    base = base.cuda()
+    dead = [(p,) for p in range(1, N)] + [(p, p + d) for d in (17, 23, 41) for p in range(1, N - d, 5)]
+    for k in range(0, len(dead), batch - 1):
+        places = dead[k:k + batch - 1]
+        phi = base.repeat(len(places) + 1, 1, 1, 1)  # (the last one as it is)
+        for b, positions in enumerate(places):
+            phi[b, list(positions)] = float("-inf")
+        lz, mu = crf.lccrf_marginals(phi)
+        for got in (crf.lccrf_log_partition(phi), lz):
+            got = got.cpu().numpy()
+            assert np.all(got[:-1] == -np.inf), (T, [p for p, x in zip(places, got) if x != -np.inf])
+            assert np.allclose(got[-1:], want_lz, rtol=1e-5, atol=0)
+        assert not mu[:-1].any()
+        assert float((mu[-1] - want_mu[0]).abs().max()) <= 1e-5
