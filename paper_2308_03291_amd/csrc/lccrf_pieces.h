@@ -95,7 +95,7 @@ __device__ __forceinline__ int piece_steps(const ChainArgs& a) {
 // Whether a row of log-domain steps matches (see LinMatch): v, O this thread's entry and the offset, against those of the row.
 // Called by the whole workgroup.
 __device__ __forceinline__ void row_matches(const float* urow, double Orow, int T, float v, double O, LinMatch& match) {
-    __shared__ float worst[2][16];
+    __shared__ __attribute__((aligned(16))) float worst[2][16];  // (max16 reads four at a time)
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     float over = LCCRF_NEG_INF, under = LCCRF_NEG_INF;
     if (tid < T) linear_gap(v, urow[tid], over, under);
