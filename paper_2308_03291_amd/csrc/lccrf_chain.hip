@@ -1048,7 +1048,8 @@ static hipError_t launch_linear_half(const ChainArgs& a, hipStream_t st) {
     return hipErrorInvalidValue;
 }
 
-// The buffers of chains in pieces (ChainArgs), in a scratch of B N T bytes: 4 (2 T + 8) B C of them and C <= N / kPieceSteps.
+// The buffers of chains in pieces (ChainArgs) in a scratch: of every piece of either direction two last vectors, three offsets and a step.
+static size_t piece_bytes(int B, int T, int pieces) { return (size_t)2 * B * pieces * (2 * T * sizeof(float) + 3 * sizeof(double) + sizeof(int)); }
 static void set_pieces(ChainArgs& a, int pieces, void* scratch) {
     const size_t slots = (size_t)2 * a.B * pieces;
     char* p = static_cast<char*>(scratch);
@@ -1060,7 +1061,6 @@ static void set_pieces(ChainArgs& a, int pieces, void* scratch) {
     a.ends2 = a.ends + slots * a.T;
     a.matched_from = reinterpret_cast<int*>(a.ends2 + slots * a.T);
 }
-static_assert(kPieceSteps >= 18, "the buffers of a piece take 8 (2 T + 7) bytes of a sequence's N T at 65 tags and more, two chains a sequence");
 
 // The chains of a first pass in pieces, where that pays if the potentials forget quickly.  whole: to the far ends; forward: one chain a
 // sequence, over all of it.  One workgroup a chain takes about 0.7 + 5.5e-5 T^2 us a step (96 tags 1.2, 201 tags 2.6 .. 3.5) and all of them
@@ -1075,7 +1075,8 @@ static void cut_chains(ChainArgs& a, int dtype, bool whole, bool forward, int cu
     const double alone = 0.7 + 5.5e-5 * a.T * a.T, bytes = (double)chains * a.T * a.T * (dtype == 0 ? 4 : 2);
     double best = (a.T <= 128 && dtype == 0 ? 0.65 : 0.72) * n * alone;  // (single precision up to 128 tags: the turned steps are quicker than these)
     int pieces = 1;
-    for (int C = 2; C * chains <= cus && C * kPieceSteps <= n; ++C) {
+    // (the scratch is the maps of the samples, B N T bytes: at 65 tags eighteen steps of a sequence bring 1170 bytes, a piece of its two chains takes 1096)
+    for (int C = 2; C * chains <= cus && C * kPieceSteps <= n && piece_bytes(a.B, a.T, C) <= (size_t)a.B * a.N * a.T; ++C) {
         const double step = C * bytes / 6.5e6, us = (step > alone ? step : alone) * ((double)n / C + 8) + 18.0;
         if (us < best) {
             best = us;
