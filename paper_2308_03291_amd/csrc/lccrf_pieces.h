@@ -7,7 +7,7 @@
 // one) it is a multiple of the true one.  So the chain is cut into pieces, one workgroup each, in three launches:
 //   0  piece 0 is walked from the true start, all others from a vector of ones; vectors and offsets are stored, the last vector of a piece
 //      beside them (ends, end_offsets);
-//   1  pieces 1 .. are walked again, each from the last vector of the piece before it, until a row agrees with the one that is there (LinMatch):
+//   1  pieces 1 .. are walked again, each from the last vector of the piece before it, until its rows agree with those that are there (LinMatch):
 //      from there on launch 0's rows are right but for a constant in the offset.  Where no row does, the last vector goes to ends2;
 //   2  a workgroup a chain adds up the constants and puts them into the offsets.  From the first piece on of which no row agreed, the
 //      rest of the chain is walked as a whole, from that piece's last vector, which is the true one: what started behind it was not.
@@ -40,7 +40,8 @@ __host__ __device__ __forceinline__ Piece piece_of(int n, int C, int least, int 
 // differences that its tags came with.  (Columns, whichever way the chain runs: a factor of a column's own, an emission, slows nothing
 // down.)  Steps until 20 bits agree, times -log2 r (mean over 64 columns), the largest of twelve or more chains of 66 .. 256 tags: independent
 // scores of deviation one 37 .. 40, two 57 .. 68, three 79 .. 102, ten 37 .. 63; emissions of deviation two with transitions of deviation
-// one 62 .. 81, two 71 .. 90.  The guess, 85 (1 + 2 r) / -log2 r, lies a third and more above what these take.  Where the longest of these four chains gains too little by it (a.piece_overhead: what the launches take, in
+// one 62 .. 81, two 71 .. 90; a match takes a quarter of them more (LinMatch).  The guess, 106 (1 + 2 r) / -log2 r, lies a third and more above
+// what these take.  Where the longest of these four chains gains too little by it (a.piece_overhead: what the launches take, in
 // steps), one piece.  The same for all workgroups; it decides nothing but how fast a call is.  Called by the whole workgroup of 16 waves.
 template <typename TIN>
 __device__ __forceinline__ int piece_steps(const ChainArgs& a) {
@@ -85,16 +86,16 @@ __device__ __forceinline__ int piece_steps(const ChainArgs& a) {
         fine = fine && mean >= 0.f;  // (not NaN)
         r = fmaxf(r, mean);
     }
-    const float guess = 85.f * (1.f + 2.f * r) / -lg2(r);
+    const float guess = 106.f * (1.f + 2.f * r) / -lg2(r);
     if (!(fine && guess > 0.f && guess < 1e6f)) return 1 << 20;
     const int least = uniform((int)fmaxf(guess, (float)kPieceSteps));
     const int n = a.whole || a.full_forward ? uniform(longest) - 1 : uniform(longest) / 2, cut = min(a.pieces, n / least);
     return cut > 1 && (float)n / (float)cut + 0.8f * guess + (float)a.piece_overhead <= 0.85f * (float)n ? least : 1 << 20;
 }
 
-// Whether a row of log-domain steps matches (see LinMatch): v, O this thread's entry and the offset, against those of the row.
+// The row that log-domain steps have come to (see LinMatch): v, O this thread's entry and the offset, against those of the row.
 // Called by the whole workgroup.
-__device__ __forceinline__ void row_matches(const float* urow, double Orow, int T, float v, double O, LinMatch& match) {
+__device__ __forceinline__ void look_at_row(const float* urow, double Orow, int T, int step, float v, double O, LinMatch& match) {
     __shared__ __attribute__((aligned(16))) float worst[2][16];  // (max16 reads four at a time)
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     float over = LCCRF_NEG_INF, under = LCCRF_NEG_INF;
@@ -110,8 +111,7 @@ __device__ __forceinline__ void row_matches(const float* urow, double Orow, int 
     __syncthreads();
     over = uniform_f(max16(worst[0]));
     under = uniform_f(max16(worst[1]));
-    match.hit = over > LCCRF_NEG_INF && over + under <= 0.f;
-    match.delta = O - Orow + 0.5 * (double)(over - under);
+    match.look(step, over, under, O - Orow);
     __syncthreads();
 }
 
@@ -183,6 +183,7 @@ __device__ __forceinline__ void piece_walk(LinSmem<LG>& lin, const ChainArgs& a,
     }
     int steps = p.s0;
     LinMatch match;
+    match.start = p.s0;
     LogBlocks blocks;
     if (!COMPARE && a.piece_pass == 0) {
         hopeless = hopeless || (n > 0 && linear_hopeless(phib + (size_t)(dir == 0 ? first + steps : first - steps) * T * T, T, dir == 1, x == LCCRF_NEG_INF, v));
@@ -204,7 +205,7 @@ __device__ __forceinline__ void piece_walk(LinSmem<LG>& lin, const ChainArgs& a,
         steps += m;
         if constexpr (COMPARE) {
             if (steps < p.s1) {
-                row_matches(uout + (size_t)position(steps) * T, Oout[position(steps)], T, v, O, match);
+                look_at_row(uout + (size_t)position(steps) * T, Oout[position(steps)], T, steps, v, O, match);
                 if (match.hit) break;
             }
         }

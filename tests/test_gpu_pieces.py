@@ -95,3 +95,29 @@ def test_one_position_forbids_every_edge(crf, oracle_mod, T, dtype):
             assert np.allclose(got[-1:], want_lz, rtol=1e-5, atol=0)
         assert not mu[:-1].any()
         assert float((mu[-1] - want_mu[0]).abs().max()) <= 1e-5
+
+
+@pytest.mark.parametrize("T,dtype", [(67, "bf16"), (144, "f32")])
+def test_rows_behind_a_match_are_as_exact_as_a_whole_chains(crf, T, dtype):
+    """Potentials that forget slowly enough that what is left of a piece's beginning can be followed behind its match: the stored forward vectors
+    (the workspace's first [B][N][T] floats, base-2 logarithms) against 64 bits, in pieces (AUTO) and as a whole (SEQUENTIAL; the same
+    steps in scaled probabilities at these tag counts).  Either error is the steps' own rounding, the largest of some 2000 rows: within a quarter."""
+    B, N = 3, 1500
+    g = torch.Generator(device="cuda").manual_seed(T)
+    phi = torch.randn(B, N, T, T, generator=g, device="cuda") + 4.0 * torch.eye(T, device="cuda")
+    phi = phi.to(torch.bfloat16) if dtype == "bf16" else phi
+    half = N // 2 - 2
+    a, exact = phi[:, 0, 0].double(), []
+    for i in range(1, half):
+        a = torch.logsumexp(a[:, :, None] + phi[:, i].double(), 1)
+        exact.append(a)
+    exact = torch.stack(exact, 1) / np.log(2.0)
+    heavy = exact > exact.amax(2, keepdim=True) - 4.0  # (logarithms whose rounding is at most 2^-23)
+    error = {}
+    for algo in (crf.ALGO_AUTO, crf.ALGO_SEQUENTIAL):
+        ws = torch.zeros(crf.workspace_bytes(crf.OP_LOGZ, B, N, T, crf.LCCRF_BF16 if dtype == "bf16" else crf.LCCRF_F32), dtype=torch.uint8, device="cuda")
+        crf.lccrf_log_partition(phi, workspace=ws, algo=algo)
+        d = ws[:4 * B * N * T].view(torch.float32).view(B, N, T)[:, 1:half].double() - exact
+        span = torch.where(heavy, d, -np.inf).amax(2) - torch.where(heavy, d, np.inf).amin(2)  # (a row's common factor is its offset's)
+        error[algo] = 0.5 * float(span.max())
+    assert error[crf.ALGO_AUTO] <= 1.25 * error[crf.ALGO_SEQUENTIAL], error
