@@ -1064,7 +1064,7 @@ static void set_pieces(ChainArgs& a, int pieces, void* scratch) {
 
 // The chains of a first pass in pieces, where that pays if the potentials forget quickly.  whole: to the far ends; forward: one chain a
 // sequence, over all of it.  One workgroup a chain takes about 0.7 + 5.5e-5 T^2 us a step (96 tags 1.2, 201 tags 2.6 .. 3.5) and all of them
-// together draw 6.5 TB/s at most; the launches, the guess and the two more beginnings take about 18 us; ten steps to a match.  us, as a
+// together draw 6.5 TB/s at most; the launches, the guess and the two more beginnings take about 18 us; nine steps to a match.  us, as a
 // whole / in pieces: log-partition B=10 N=135 T=96 91 / 66, B=4 N=256 T=256 482 / 155; marginals B=2 N=447 T=85 bfloat16 420 / 88, B=32 N=256
 // T=201 bfloat16 1293 / 743.  Where the potentials forget slowly the guess and two launches that have nothing to do are lost: 8 us (independent
 // scores of deviation three, log-partition B=1 N=126 T=156 110 / 118, B=15 N=274 T=130 189 / 197); a gain below 28 % is left alone for that.
@@ -1077,7 +1077,7 @@ static void cut_chains(ChainArgs& a, int dtype, bool whole, bool forward, int cu
     int pieces = 1;
     // (the scratch is the maps of the samples, B N T bytes: at 65 tags eighteen steps of a sequence bring 1170 bytes, a piece of its two chains takes 1096)
     for (int C = 2; C * chains <= cus && C * kPieceSteps <= n && piece_bytes(a.B, a.T, C) <= (size_t)a.B * a.N * a.T; ++C) {
-        const double step = C * bytes / 6.5e6, us = (step > alone ? step : alone) * ((double)n / C + 10) + 18.0;
+        const double step = C * bytes / 6.5e6, us = (step > alone ? step : alone) * ((double)n / C + 9) + 18.0;
         if (us < best) {
             best = us;
             pieces = C;

@@ -194,7 +194,7 @@ __device__ __forceinline__ bool linear_hopeless(const TIN* mat, int T, bool back
 // zeros alone says nothing: what follows it may have any factor, and no path has a finite score).  tol is 2^-20,
 // four roundings of a logarithm of one or two bits, and grows with the logarithm as its rounding does.  Non-negative matrices never
 // widen such a gap, and all of it but a common factor shrinks from step to step as fast as it came down to tol: a run has found its match
-// when rows have been alike for a quarter of the steps that the first of them took and one more, behind which less than 2^-25 is left of the gap.
+// when rows have been alike for an eighth of the steps that the first of them took and one more, behind which less is left of the gap than storing a row takes.
 // (With a match at the first row that is alike, rows behind it were off by up to 9.1e-7 bits where those of a whole chain are by 5.0e-7:
 // 66 tags, the diagonal raised by four.)
 struct LinMatch {
@@ -204,7 +204,7 @@ struct LinMatch {
     double delta = 0.0;  // what has to be added to the offsets of the rows behind
     __device__ __forceinline__ void look(int row, float over, float under, double gap) {
         alike = over > LCCRF_NEG_INF && over + under <= 0.f ? (alike < 0 ? row : alike) : -1;
-        hit = alike >= 0 && row > alike + ((alike - start) >> 2);
+        hit = alike >= 0 && row > alike + ((alike - start) >> 3);
         delta = gap + 0.5 * (double)(over - under);
     }
 };

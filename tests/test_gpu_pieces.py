@@ -101,7 +101,8 @@ def test_one_position_forbids_every_edge(crf, oracle_mod, T, dtype):
 def test_rows_behind_a_match_are_as_exact_as_a_whole_chains(crf, T, dtype):
     """Potentials that forget slowly enough that what is left of a piece's beginning can be followed behind its match: the stored forward vectors
     (the workspace's first [B][N][T] floats, base-2 logarithms) against 64 bits, in pieces (AUTO) and as a whole (SEQUENTIAL; the same
-    steps in scaled probabilities at these tag counts).  Either error is the steps' own rounding, the largest of some 2000 rows: within a quarter."""
+    steps in scaled probabilities at these tag counts).  In pieces a row may be off by as much more as the vector that its piece began with: a
+    stored row, rounded by 2^-23 at four bits, turned into a logarithm and back by instructions good to one unit in the last place, 2^-23."""
     B, N = 3, 1500
     g = torch.Generator(device="cuda").manual_seed(T)
     phi = torch.randn(B, N, T, T, generator=g, device="cuda") + 4.0 * torch.eye(T, device="cuda")
@@ -120,4 +121,4 @@ def test_rows_behind_a_match_are_as_exact_as_a_whole_chains(crf, T, dtype):
         d = ws[:4 * B * N * T].view(torch.float32).view(B, N, T)[:, 1:half].double() - exact
         span = torch.where(heavy, d, -np.inf).amax(2) - torch.where(heavy, d, np.inf).amin(2)  # (a row's common factor is its offset's)
         error[algo] = 0.5 * float(span.max())
-    assert error[crf.ALGO_AUTO] <= 1.25 * error[crf.ALGO_SEQUENTIAL], error
+    assert error[crf.ALGO_AUTO] <= error[crf.ALGO_SEQUENTIAL] + 2.0 ** -22, error
