@@ -804,16 +804,16 @@ __device__ __attribute__((noinline)) LogStepsResult chain_log_steps(const void* 
     return r;
 }
 
-// ITEMS: rows a thread holds of a matrix, linear_instance(G::W, T).  COMPARE: the second launch of a chain in pieces (lccrf_pieces.h).
-template <typename G, typename TIN, bool ALIGNED, int ITEMS, bool COMPARE>
+// ITEMS: rows a thread holds of a matrix, linear_instance(G::W, T).  MODE: PieceMode (lccrf_pieces.h).
+template <typename G, typename TIN, bool ALIGNED, int ITEMS, int MODE>
 __global__ __launch_bounds__(G::W, 4) void linear_half_kernel(ChainArgs a) {  // (four waves a SIMD: large batches of 33 .. 64 tags)
     using LG = LinGeo<G::WAVES, G::TCAP, ITEMS>;
-    if (!COMPARE && a.pair_mail && a.piece_pass == 0 && (blockIdx.x & 1) == 0 && (int)blockIdx.x < 2 * a.B) {  // (as chain_half_kernel does)
+    if (MODE != kComparePieces && a.pair_mail && a.piece_pass == 0 && (blockIdx.x & 1) == 0 && (int)blockIdx.x < 2 * a.B) {  // (as chain_half_kernel does)
         const int b = blockIdx.x >> 1;
         for (int k = threadIdx.x; k < a.pair_words; k += G::W) a.pair_mail[(size_t)b * a.pair_words + k] = 0ull;
         if (threadIdx.x == 0) a.pair_failed[b] = 0;
     }
-    piece_walk<LG, TIN, ALIGNED, COMPARE>(*reinterpret_cast<LinSmem<LG>*>(half_smem), a, [&](int b, int dir, int first, int m, float v, double O) {
+    piece_walk<LG, TIN, ALIGNED, MODE>(*reinterpret_cast<LinSmem<LG>*>(half_smem), a, [&](int b, int dir, int first, int m, float v, double O) {
         return chain_log_steps<G, TIN, ALIGNED>(a.phi, a.ua, a.ub, a.Oa, a.Ob, a.B, a.N, a.T, a.exact_only, b, dir, first, m, v, O);
     });
 }
@@ -1022,28 +1022,30 @@ static hipError_t launch_chain_half(const ChainArgs& a, hipStream_t st) {
     return hipGetLastError();
 }
 // ... and in scaled probabilities (whole sequences).
-template <typename G, typename TIN, bool ALIGNED, int ITEMS, bool COMPARE>
-static hipError_t launch_linear_items(const ChainArgs& a, int workgroups, hipStream_t st) {
+template <typename G, typename TIN, bool ALIGNED, int ITEMS, int MODE>
+static hipError_t launch_linear_mode(const ChainArgs& a, int workgroups, hipStream_t st) {
     const size_t lin = sizeof(LinSmem<LinGeo<G::WAVES, G::TCAP, ITEMS>>), turn = turn_floats<G>() * sizeof(float);
     const size_t bytes = lin > turn ? lin : turn;
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&linear_half_kernel<G, TIN, ALIGNED, ITEMS, COMPARE>),
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&linear_half_kernel<G, TIN, ALIGNED, ITEMS, MODE>),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((linear_half_kernel<G, TIN, ALIGNED, ITEMS, COMPARE>), dim3(workgroups), dim3(G::W), bytes, st, a);
+    hipLaunchKernelGGL((linear_half_kernel<G, TIN, ALIGNED, ITEMS, MODE>), dim3(workgroups), dim3(G::W), bytes, st, a);
     return hipGetLastError();
+}
+template <typename G, typename TIN, bool ALIGNED, int ITEMS>
+static hipError_t launch_linear_items(const ChainArgs& a, hipStream_t st) {
+    if constexpr (G::TCAP > 64) {
+        if (a.pieces > 1 && a.piece_pass == 1) return launch_linear_mode<G, TIN, ALIGNED, ITEMS, kComparePieces>(a, 2 * a.B * (a.pieces - 1), st);
+        if (a.pieces > 1) return launch_linear_mode<G, TIN, ALIGNED, ITEMS, kChainsInPieces>(a, 2 * a.B * (a.piece_pass == 2 ? 1 : a.pieces), st);
+    }
+    return launch_linear_mode<G, TIN, ALIGNED, ITEMS, kChainsWhole>(a, 2 * a.B, st);
 }
 template <typename G, typename TIN, bool ALIGNED>
 static hipError_t launch_linear_half(const ChainArgs& a, hipStream_t st) {
-    ChainArgs as = a;
-    as.pieces = a.pieces > 1 ? a.pieces : 1;
-    const bool compare = as.pieces > 1 && a.piece_pass == 1;
-    const int workgroups = 2 * a.B * (as.pieces == 1 || a.piece_pass == 2 ? 1 : compare ? as.pieces - 1 : as.pieces);
     switch (linear_instance(G::W, a.T)) {  // 2 (33 or 65 tags) .. 4
-#define LCCRF_LINEAR_HALF(I) case I: return compare ? launch_linear_items<G, TIN, ALIGNED, I, true>(as, workgroups, st) : launch_linear_items<G, TIN, ALIGNED, I, false>(as, workgroups, st)
-        LCCRF_LINEAR_HALF(2);
-        LCCRF_LINEAR_HALF(3);
-        LCCRF_LINEAR_HALF(4);
-#undef LCCRF_LINEAR_HALF
+        case 2: return launch_linear_items<G, TIN, ALIGNED, 2>(a, st);
+        case 3: return launch_linear_items<G, TIN, ALIGNED, 3>(a, st);
+        case 4: return launch_linear_items<G, TIN, ALIGNED, 4>(a, st);
     }
     return hipErrorInvalidValue;
 }

@@ -115,16 +115,22 @@ __device__ __forceinline__ void look_at_row(const float* urow, double Orow, int 
     __syncthreads();
 }
 
+// What a kernel of a first pass is for: chains as a whole (without anything of the pieces: one kernel for these and launch 0 took 1.3 us a call more, B=54 N=8
+// log-partition T=97 bfloat16 16.8 / 15.4, T=131 single precision 19.4 / 18.4), launches 0 and 2 of chains in pieces, or launch 1.
+enum PieceMode { kChainsWhole, kChainsInPieces, kComparePieces };
+
 // One workgroup of a first pass.  log_steps(first position, number, v, O): that many positions in the log domain.
-template <typename LG, typename TIN, bool ALIGNED, bool COMPARE, typename LogSteps>
+template <typename LG, typename TIN, bool ALIGNED, int MODE, typename LogSteps>
 __device__ __forceinline__ void piece_walk(LinSmem<LG>& lin, const ChainArgs& a, LogSteps log_steps) {
+    constexpr bool COMPARE = MODE == kComparePieces;
     const int tid = threadIdx.x;
-    const int chain = blockIdx.x % (2 * a.B), c = blockIdx.x / (2 * a.B) + (COMPARE ? 1 : 0);
+    const int chain = MODE == kChainsWhole ? blockIdx.x : blockIdx.x % (2 * a.B), c = MODE == kChainsWhole ? 0 : blockIdx.x / (2 * a.B) + (COMPARE ? 1 : 0);
     const int dir = chain & 1, b = chain >> 1;
     const int N = a.N, T = a.T;
-    const size_t slot = (size_t)chain * a.pieces;
+    const int pass = MODE == kChainsWhole ? 0 : COMPARE ? 1 : a.piece_pass;
+    const size_t slot = MODE == kChainsWhole ? 0 : (size_t)chain * a.pieces;
     // matched_from of piece 0, written by launch 0 for those behind it: twice the least steps, and one more if the chain takes no scaled steps.
-    const int plan = COMPARE || a.piece_pass == 2 ? a.matched_from[slot] : 0;
+    const int plan = pass > 0 ? a.matched_from[slot] : 0;
     const int L = clamp_length(a.lengths, b, N);
     if (L == 0 || (a.full_forward && dir == 1)) return;
     const int e = L - 1, mid = meeting_point(0, e);
@@ -138,21 +144,21 @@ __device__ __forceinline__ void piece_walk(LinSmem<LG>& lin, const ChainArgs& a,
     const auto position = [&](int s) { return dir == 0 ? s : e - s; };  // of the vector behind s steps
     int least = kPieceSteps;
     bool hopeless = a.exact_only != 0;
-    if (COMPARE || a.piece_pass == 2) {
+    if (pass > 0) {
         least = uniform(plan) >> 1;
         hopeless = uniform(plan) & 1;
-    } else if (a.pieces > 1) {
-        if constexpr (LG::WAVES == 16) least = piece_steps<TIN>(a);  // (more than 64 tags)
+    } else if (MODE == kChainsInPieces) {
+        least = piece_steps<TIN>(a);
     }
-    Piece p = piece_of(n, a.pieces, least, c);
-    if (c >= p.count || (a.piece_pass == 2 && p.count == 1)) return;
+    Piece p = MODE == kChainsWhole ? Piece{1, 0, n} : piece_of(n, a.pieces, least, c);
+    if (c >= p.count || (pass == 2 && p.count == 1)) return;
     float v = LCCRF_NEG_INF, x = 0.f;  // x: -inf where a tag cannot be in front of the sequence's first edge
     double O = 0.0;
     bool last = c == p.count - 1;
     if constexpr (COMPARE) {
         if (tid < T) v = a.ends[(slot + c - 1) * T + tid];
         O = a.end_offsets[slot + c - 1];
-    } else if (a.piece_pass == 0) {
+    } else if (pass == 0) {
         if (tid < T) {
             x = Elem<TIN>::get(phib + tid);
             v = dir == 0 && c == 0 ? x * kLog2e : 0.f;
@@ -185,9 +191,9 @@ __device__ __forceinline__ void piece_walk(LinSmem<LG>& lin, const ChainArgs& a,
     LinMatch match;
     match.start = p.s0;
     LogBlocks blocks;
-    if (!COMPARE && a.piece_pass == 0) {
+    if (pass == 0) {
         hopeless = hopeless || (n > 0 && linear_hopeless(phib + (size_t)(dir == 0 ? first + steps : first - steps) * T * T, T, dir == 1, x == LCCRF_NEG_INF, v));
-        if (a.pieces > 1 && c == 0 && tid == 0) a.matched_from[slot] = 2 * least + (hopeless ? 1 : 0);
+        if (MODE == kChainsInPieces && c == 0 && tid == 0) a.matched_from[slot] = 2 * least + (hopeless ? 1 : 0);
     }
     blocks.hopeless = hopeless;
     for (;;) {

@@ -467,13 +467,13 @@ __device__ __attribute__((noinline)) LogStepsResult stream_log_steps(const void*
 // Pass 1: both half chains, vectors stored, in pieces where a.pieces says so (lccrf_pieces.h).  The steps are taken in scaled probabilities
 // (linear_run) as long as they are accepted, and from one that is not, a block of positions in the log domain (LogBlocks).
 // ITEMS: rows a thread holds of a matrix there, linear_instance(1024, T); 0: every step in the log domain.
-// COMPARE: the second launch of a chain in pieces.
-template <typename TIN, bool ALIGNED, int ITEMS, bool COMPARE>
+// MODE: PieceMode.
+template <typename TIN, bool ALIGNED, int ITEMS, int MODE>
 __global__ __launch_bounds__(1024) void stream_half_kernel(ChainArgs a) {
     if constexpr (ITEMS > 0) {
         using LG = LinGeo<16, 256, ITEMS>;
         __shared__ LinSmem<LG> lin;
-        piece_walk<LG, TIN, ALIGNED, COMPARE>(lin, a, [&](int b, int dir, int first, int m, float v, double O) {
+        piece_walk<LG, TIN, ALIGNED, MODE>(lin, a, [&](int b, int dir, int first, int m, float v, double O) {
             return stream_log_steps<TIN, ALIGNED>(a.phi, a.ua, a.ub, a.Oa, a.Ob, a.B, a.N, a.T, a.exact_only, b, dir, first, m, v, O);
         });
     } else {
@@ -997,23 +997,22 @@ static bool scaled_pays(bool single, int B, int T) {
 template <typename TIN, bool ALIGNED>
 static hipError_t launch_stream_half(const ChainArgs& a, hipStream_t st) {
     const dim3 block(1024);
-    const int items = linear_instance(1024, a.T), pieces = a.pieces > 1 ? a.pieces : 1;
-    const bool compare = pieces > 1 && a.piece_pass == 1;
-    const dim3 grid(2 * a.B * (pieces == 1 || a.piece_pass == 2 ? 1 : compare ? pieces - 1 : pieces));
+    const int items = linear_instance(1024, a.T);
+    const bool in_pieces = a.pieces > 1, compare = in_pieces && a.piece_pass == 1;
+    const dim3 grid(2 * a.B * (!in_pieces || a.piece_pass == 2 ? 1 : compare ? a.pieces - 1 : a.pieces));
     if (items < 5) return hipErrorInvalidValue;
-    ChainArgs as = a;
-    as.pieces = pieces;
     switch (!a.exact_only && (a.scaled || scaled_pays(sizeof(TIN) == 4, a.B, a.T)) ? items : 0) {  // 5 (129 tags) .. 16 (256 tags)
 #define LCCRF_STREAM_HALF(I) case I: \
-            if (compare) hipLaunchKernelGGL((stream_half_kernel<TIN, ALIGNED, I, true>), grid, block, 0, st, as); \
-            else hipLaunchKernelGGL((stream_half_kernel<TIN, ALIGNED, I, false>), grid, block, 0, st, as); \
+            if (compare) hipLaunchKernelGGL((stream_half_kernel<TIN, ALIGNED, I, kComparePieces>), grid, block, 0, st, a); \
+            else if (in_pieces) hipLaunchKernelGGL((stream_half_kernel<TIN, ALIGNED, I, kChainsInPieces>), grid, block, 0, st, a); \
+            else hipLaunchKernelGGL((stream_half_kernel<TIN, ALIGNED, I, kChainsWhole>), grid, block, 0, st, a); \
             break
         LCCRF_STREAM_HALF(5); LCCRF_STREAM_HALF(6); LCCRF_STREAM_HALF(7); LCCRF_STREAM_HALF(8); LCCRF_STREAM_HALF(9); LCCRF_STREAM_HALF(10);
         LCCRF_STREAM_HALF(11); LCCRF_STREAM_HALF(12); LCCRF_STREAM_HALF(14); LCCRF_STREAM_HALF(16);
 #undef LCCRF_STREAM_HALF
         case 0:
-            if (pieces > 1 || a.whole) return hipErrorInvalidValue;
-            hipLaunchKernelGGL((stream_half_kernel<TIN, ALIGNED, 0, false>), grid, block, 0, st, as);
+            if (in_pieces || a.whole) return hipErrorInvalidValue;
+            hipLaunchKernelGGL((stream_half_kernel<TIN, ALIGNED, 0, kChainsWhole>), grid, block, 0, st, a);
             break;
         default: return hipErrorInvalidValue;
     }
