@@ -1023,22 +1023,22 @@ static hipError_t launch_chain_half(const ChainArgs& a, hipStream_t st) {
 }
 // ... and in scaled probabilities (whole sequences).
 template <typename G, typename TIN, bool ALIGNED, int ITEMS, int MODE>
-static hipError_t launch_linear_mode(const ChainArgs& a, int workgroups, hipStream_t st) {
+static hipError_t launch_linear_mode(const ChainArgs& a, hipStream_t st) {
     const size_t lin = sizeof(LinSmem<LinGeo<G::WAVES, G::TCAP, ITEMS>>), turn = turn_floats<G>() * sizeof(float);
     const size_t bytes = lin > turn ? lin : turn;
     const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&linear_half_kernel<G, TIN, ALIGNED, ITEMS, MODE>),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((linear_half_kernel<G, TIN, ALIGNED, ITEMS, MODE>), dim3(workgroups), dim3(G::W), bytes, st, a);
+    hipLaunchKernelGGL((linear_half_kernel<G, TIN, ALIGNED, ITEMS, MODE>), dim3(piece_workgroups(a)), dim3(G::W), bytes, st, a);
     return hipGetLastError();
 }
 template <typename G, typename TIN, bool ALIGNED, int ITEMS>
 static hipError_t launch_linear_items(const ChainArgs& a, hipStream_t st) {
     if constexpr (G::TCAP > 64) {
-        if (a.pieces > 1 && a.piece_pass == 1) return launch_linear_mode<G, TIN, ALIGNED, ITEMS, kComparePieces>(a, 2 * a.B * (a.pieces - 1), st);
-        if (a.pieces > 1) return launch_linear_mode<G, TIN, ALIGNED, ITEMS, kChainsInPieces>(a, 2 * a.B * (a.piece_pass == 2 ? 1 : a.pieces), st);
+        if (a.pieces > 1 && a.piece_pass == 1) return launch_linear_mode<G, TIN, ALIGNED, ITEMS, kComparePieces>(a, st);
+        if (a.pieces > 1) return launch_linear_mode<G, TIN, ALIGNED, ITEMS, kChainsInPieces>(a, st);
     }
-    return launch_linear_mode<G, TIN, ALIGNED, ITEMS, kChainsWhole>(a, 2 * a.B, st);
+    return launch_linear_mode<G, TIN, ALIGNED, ITEMS, kChainsWhole>(a, st);
 }
 template <typename G, typename TIN, bool ALIGNED>
 static hipError_t launch_linear_half(const ChainArgs& a, hipStream_t st) {

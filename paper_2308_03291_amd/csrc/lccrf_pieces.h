@@ -119,12 +119,20 @@ __device__ __forceinline__ void look_at_row(const float* urow, double Orow, int 
 // log-partition T=97 bfloat16 16.8 / 15.4, T=131 single precision 19.4 / 18.4), launches 0 and 2 of chains in pieces, or launch 1.
 enum PieceMode { kChainsWhole, kChainsInPieces, kComparePieces };
 
+// Workgroups of a launch.
+__host__ __forceinline__ int piece_workgroups(const ChainArgs& a) {
+    const int chains = a.full_forward ? a.B : 2 * a.B;
+    return chains * (a.pieces <= 1 || a.piece_pass == 2 ? 1 : a.piece_pass == 1 ? a.pieces - 1 : a.pieces);
+}
+
 // One workgroup of a first pass.  log_steps(first position, number, v, O): that many positions in the log domain.
 template <typename LG, typename TIN, bool ALIGNED, int MODE, typename LogSteps>
 __device__ __forceinline__ void piece_walk(LinSmem<LG>& lin, const ChainArgs& a, LogSteps log_steps) {
     constexpr bool COMPARE = MODE == kComparePieces;
     const int tid = threadIdx.x;
-    const int chain = MODE == kChainsWhole ? blockIdx.x : blockIdx.x % (2 * a.B), c = MODE == kChainsWhole ? 0 : blockIdx.x / (2 * a.B) + (COMPARE ? 1 : 0);
+    // (Neighbouring workgroups go to different XCDs: without backward chains every second one would leave half of the chip idle.)
+    const int chains = a.full_forward ? a.B : 2 * a.B, unit = MODE == kChainsWhole ? blockIdx.x : blockIdx.x % chains;
+    const int chain = a.full_forward ? 2 * unit : unit, c = MODE == kChainsWhole ? 0 : blockIdx.x / chains + (COMPARE ? 1 : 0);
     const int dir = chain & 1, b = chain >> 1;
     const int N = a.N, T = a.T;
     const int pass = MODE == kChainsWhole ? 0 : COMPARE ? 1 : a.piece_pass;
@@ -132,7 +140,7 @@ __device__ __forceinline__ void piece_walk(LinSmem<LG>& lin, const ChainArgs& a,
     // matched_from of piece 0, written by launch 0 for those behind it: twice the least steps, and one more if the chain takes no scaled steps.
     const int plan = pass > 0 ? a.matched_from[slot] : 0;
     const int L = clamp_length(a.lengths, b, N);
-    if (L == 0 || (a.full_forward && dir == 1)) return;
+    if (L == 0) return;
     const int e = L - 1, mid = meeting_point(0, e);
     const size_t vb = (size_t)b * N;
     const TIN* phib = static_cast<const TIN*>(a.phi) + vb * T * T;

@@ -999,7 +999,7 @@ static hipError_t launch_stream_half(const ChainArgs& a, hipStream_t st) {
     const dim3 block(1024);
     const int items = linear_instance(1024, a.T);
     const bool in_pieces = a.pieces > 1, compare = in_pieces && a.piece_pass == 1;
-    const dim3 grid(2 * a.B * (!in_pieces || a.piece_pass == 2 ? 1 : compare ? a.pieces - 1 : a.pieces));
+    const dim3 grid(piece_workgroups(a));
     if (items < 5) return hipErrorInvalidValue;
     switch (!a.exact_only && (a.scaled || scaled_pays(sizeof(TIN) == 4, a.B, a.T)) ? items : 0) {  // 5 (129 tags) .. 16 (256 tags)
 #define LCCRF_STREAM_HALF(I) case I: \
@@ -1012,7 +1012,7 @@ static hipError_t launch_stream_half(const ChainArgs& a, hipStream_t st) {
 #undef LCCRF_STREAM_HALF
         case 0:
             if (in_pieces || a.whole) return hipErrorInvalidValue;
-            hipLaunchKernelGGL((stream_half_kernel<TIN, ALIGNED, 0, kChainsWhole>), grid, block, 0, st, a);
+            hipLaunchKernelGGL((stream_half_kernel<TIN, ALIGNED, 0, kChainsWhole>), dim3(2 * a.B), block, 0, st, a);
             break;
         default: return hipErrorInvalidValue;
     }
