@@ -47,7 +47,7 @@
  *    LCCRF_EWORKSPACE if it is too small.
  *  - Repeat runs: results are bit-identical from run to run, with one exception:
  *    marginals at T = 128 in batches that fill at most a quarter of the chip's
- *    compute units are computed by pairs of workgroups (see
+ *    compute units may be computed by pairs of workgroups (see
  *    lccrf_set_pair_poll_limit); a pair that gives its sequence up hands it to the
  *    one-workgroup kernel, which rounds differently, so where that hand-over depends
  *    on timing two runs may differ in the low-order bits (far inside the tolerance).
@@ -90,7 +90,7 @@ typedef enum {
 typedef enum {
     LCCRF_ALGO_AUTO = 0,
     LCCRF_ALGO_SEQUENTIAL = 1, /* position by position (the forward algorithm as the paper uses it), one
-                                  workgroup per chain; AUTO may instead split a chain over two workgroups */
+                                  workgroup per chain; AUTO may instead split a chain over several workgroups */
     LCCRF_ALGO_SCAN = 2,       /* chunked associative scan over positions (the parallel variant the
                                   paper cites in "Sequence Tagging"): products of the T x T matrices
                                   of each chunk, a short serial pass over chunks, then every chunk

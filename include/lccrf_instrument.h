@@ -44,7 +44,7 @@ size_t lccrf_stream_probe_bytes(size_t bytes, int workgroups);
 /*
  * 1 where the sequential schedule of lccrf_marginals, in place of a second pass that writes the marginals as the chains go, runs
  * the chains on to the far ends without writing (a second read of phi) and writes every edge in a kernel of its own (a third).
- * 0 elsewhere, or without a device.
+ * 0 elsewhere, or without a device.  (At 128 tags 0, though AUTO does the same with chains that it walks in pieces.)
  */
 int lccrf_marginals_by_edges(lccrf_dtype dt, int B, int T);
 

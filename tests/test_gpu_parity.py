@@ -484,8 +484,8 @@ def test_config4_full_size_all_sequences(crf, oracle_mod):
 
 
 def test_paired_second_pass_bf16_full_length(crf, oracle_mod):
-    """T = 128, N = 512 (config 4's chain length) with bfloat16-stored potentials: two workgroups per
-    chain exchange half vectors 256 times in each direction; every marginal against the oracle."""
+    """T = 128, N = 512 (config 4's chain length) with bfloat16-stored potentials; every marginal against the oracle.  (So few
+    chains are walked in pieces; two workgroups per chain at this length: test_gpu_pieces.py.)"""
     phi, _ = workloads.random_case(4500, 3, 512, 128, scale=3.0, dtype="bf16")
     lens = torch.tensor([512, 511, 300], dtype=torch.int32)
     check_case(crf, oracle_mod, phi, lens, poison=False, what="paired bf16 N=512", queries=("logz", "mu"))

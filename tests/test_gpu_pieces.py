@@ -122,3 +122,39 @@ def test_rows_behind_a_match_are_as_exact_as_a_whole_chains(crf, T, dtype):
         span = torch.where(heavy, d, -np.inf).amax(2) - torch.where(heavy, d, np.inf).amin(2)  # (a row's common factor is its offset's)
         error[algo] = 0.5 * float(span.max())
     assert error[crf.ALGO_AUTO] <= error[crf.ALGO_SEQUENTIAL] + 2.0 ** -22, error
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_marginals_of_128_tags_do_not_drift(crf, dtype):
+    """The marginals of a few long chains against 64 bits.  The exponent of a marginal is a sum of four logarithms below sixteen bits, each rounded by
+    2^-21, and of two vectors that are themselves off by up to 1.1e-6 bits: 3e-6 in all.  (Half chains in pieces with the paired second pass: 2e-5.)"""
+    B, N, T = 3, 400, 128
+    phi = 2.0 * torch.randn(B, N, T, T, generator=torch.Generator(device="cuda").manual_seed(128), device="cuda")
+    phi = phi.to(torch.bfloat16) if dtype == "bf16" else phi
+    a, alpha = phi[:, 0, 0].double(), []
+    for i in range(N):
+        a = a if i == 0 else torch.logsumexp(a[:, :, None] + phi[:, i].double(), 1)
+        alpha.append(a)
+    logZ = torch.logsumexp(a, 1)[:, None, None]
+    _, mu = crf.lccrf_marginals(phi)
+    b, wrong, all_of_it = torch.zeros_like(a), 0.0, 0.0
+    for i in range(N - 1, 0, -1):
+        want = torch.exp(alpha[i - 1][:, :, None] + phi[:, i].double() + b[:, None, :] - logZ)
+        wrong += float(((mu[:, i].double() - want) ** 2).sum())
+        all_of_it += float((want ** 2).sum())
+        b = torch.logsumexp(phi[:, i].double() + b[:, None, :], 2)
+    assert (wrong / all_of_it) ** 0.5 <= 3e-6
+
+
+def test_paired_second_pass_over_long_chains(crf, oracle_mod):
+    """128 tags, N = 512, more sequences than are walked in pieces and few enough for two workgroups a chain, which exchange half vectors 256
+    times in each direction: every marginal of three sequences against the oracle, and their copies in the batch the same."""
+    phi, _ = workloads.random_case(4501, 3, 512, 128, scale=1.0, dtype="bf16")
+    lens = torch.tensor([512, 511, 300], dtype=torch.int32)
+    want_lz, want_mu = oracle_mod.marginals(phi, lens.numpy())
+    assert crf.load_library().lccrf_marginals_by_edges(crf.LCCRF_BF16, 54, 127) == 0
+    lz, mu = crf.lccrf_marginals(phi.cuda().repeat(18, 1, 1, 1), lens.cuda().repeat(18))
+    assert np.allclose(lz[:3].cpu().numpy(), want_lz, rtol=1e-5, atol=0)
+    assert np.abs(mu[:3].cpu().numpy() - want_mu).max() <= 1e-5
+    for k in range(3, 54, 3):
+        assert torch.equal(mu[k:k + 3], mu[:3])
