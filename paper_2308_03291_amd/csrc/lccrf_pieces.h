@@ -40,7 +40,7 @@ __host__ __device__ __forceinline__ Piece piece_of(int n, int C, int least, int 
 // differences that its tags came with.  (Columns, whichever way the chain runs: a factor of a column's own, an emission, slows nothing
 // down.)  Steps until 20 bits agree, times -log2 r (mean over 64 columns), the largest of twelve or more chains of 66 .. 256 tags: independent
 // scores of deviation one 37 .. 40, two 57 .. 68, three 79 .. 102, ten 37 .. 63; emissions of deviation two with transitions of deviation
-// one 62 .. 81, two 71 .. 90; a match takes an eighth of them more (LinMatch).  The guess, 92 (1 + 2 r) / -log2 r, lies a fifth and more above
+// one 62 .. 81, two 71 .. 90; a match takes an eighth of them more (LinMatch).  The guess, 85 (1 + 2 r) / -log2 r, lies a sixth and more above
 // what these take.  Where the longest of these four chains gains too little by it (a.piece_overhead: what the launches take, in
 // steps), one piece.  The same for all workgroups; it decides nothing but how fast a call is.  Called by the whole workgroup of 16 waves.
 template <typename TIN>
@@ -86,7 +86,7 @@ __device__ __forceinline__ int piece_steps(const ChainArgs& a) {
         fine = fine && mean >= 0.f;  // (not NaN)
         r = fmaxf(r, mean);
     }
-    const float guess = 92.f * (1.f + 2.f * r) / -lg2(r);
+    const float guess = 85.f * (1.f + 2.f * r) / -lg2(r);
     if (!(fine && guess > 0.f && guess < 1e6f)) return 1 << 20;
     const int least = uniform((int)fmaxf(guess, (float)kPieceSteps));
     const int n = a.whole || a.full_forward ? uniform(longest) - 1 : uniform(longest) / 2, cut = min(a.pieces, n / least);
