@@ -239,9 +239,10 @@ __device__ __forceinline__ int linear_run(LinSmem<LG>& ls, const LinJob<TIN, BAC
     // Pieces in flight: as many whole tiles as fit the registers beside E (PH of them, three at most), half or a quarter
     // of a tile of single precision where not even one does.  (bfloat16 with more than six rows: two, with ten or more one; the next one up spills registers
     // inside the loop.  Log-partition, us, one tile more / so: ten rows B=48 N=64 T=195 102.8 / 92.5, B=32 N=256 T=192 373 / 334, B=8 N=9 T=199 27.0 / 24.6;
-    // seven and eight B=96 N=48 T=165 63.4 / 62.1, T=172 67.3 / 62.6.)
+    // seven and eight B=96 N=48 T=165 63.4 / 62.1, T=172 67.3 / 62.6.  Comparing takes registers of its own: a tile less, B=26 N=329 T=129 single
+    // precision 214.7 / 181.8, B=17 N=358 T=172 bfloat16 159.5 / 152.5.)
     constexpr int kRawRegs = Raw::WORDS * ITEMS, kFree = (sizeof(TIN) == 2 ? 86 : 88) - 4 * ITEMS;
-    constexpr int kMost = sizeof(TIN) == 4 || ITEMS <= 6 ? 3 : ITEMS < 10 ? 2 : 1;
+    constexpr int kTiles = sizeof(TIN) == 4 || ITEMS <= 6 ? 3 : ITEMS < 10 ? 2 : 1, kMost = COMPARE && kTiles > 1 ? kTiles - 1 : kTiles;
     constexpr bool HALF = kRawRegs > kFree;
     constexpr int PH = HALF ? 1 : kFree / kRawRegs > kMost ? kMost : kFree / kRawRegs;
     constexpr int R = HALF ? (kRawRegs / 2 + 4 * ITEMS > 92 ? ITEMS / 4 : ITEMS / 2) : PH * ITEMS;
