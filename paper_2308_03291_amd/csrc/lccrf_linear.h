@@ -195,6 +195,8 @@ __device__ __forceinline__ bool linear_hopeless(const TIN* mat, int T, bool back
 // four roundings of a logarithm of one or two bits, and grows with the logarithm as its rounding does.  Non-negative matrices never
 // widen such a gap, and all of it but a common factor shrinks from step to step as fast as it came down to tol: a run has found its match
 // when rows have been alike for an eighth of the steps that the first of them took and one more, behind which less is left of the gap than storing a row takes.
+// At the end of a piece half of that is enough: what is left is then no more than the rounding of the vector that the next piece begins with, and the
+// rest of the chain need not be walked again (B=4 N=551 T=145 bfloat16, log-partition, emissions and transitions of deviation two, 418 / 157 us).
 // (With a match at the first row that is alike, rows behind it were off by up to 9.1e-7 bits where those of a whole chain are by 5.0e-7:
 // 66 tags, the diagonal raised by four.)
 struct LinMatch {
@@ -202,9 +204,10 @@ struct LinMatch {
     int alike = -1;  // step of the first of the rows that are alike (-1: the last one was not)
     bool hit = false;
     double delta = 0.0;  // what has to be added to the offsets of the rows behind
+    __device__ __forceinline__ bool alike_for(int row, int shift) const { return alike >= 0 && row > alike + ((alike - start) >> shift); }
     __device__ __forceinline__ void look(int row, float over, float under, double gap) {
         alike = over > LCCRF_NEG_INF && over + under <= 0.f ? (alike < 0 ? row : alike) : -1;
-        hit = alike >= 0 && row > alike + ((alike - start) >> 3);
+        hit = alike_for(row, 3);
         delta = gap + 0.5 * (double)(over - under);
     }
 };
@@ -478,6 +481,7 @@ __device__ __forceinline__ int linear_run(LinSmem<LG>& ls, const LinJob<TIN, BAC
             step(0);
         }
     }
+    if (COMPARE && done == n && M <= 0x1p60f) match.hit = match.hit || match.alike_for(done - 1, 4);
     if (COMPARE && match.hit) return done;
     if (!(M <= 0x1p60f)) {  // the vector in front of the rejected step is still in the other buffer
         buf ^= 1;
