@@ -1257,15 +1257,14 @@ static void launch_sample_map_wide(const TIN* phi, const int32_t* lengths, const
 // A lane walks short sequences (us a draw, so / in stretches: B=4 N=16 T=12 13.3 / 12.9, B=2048 N=16 T=16 32.8 / 39.5, B=1000 N=120 T=8 105 / 102).
 // Eight waves a workgroup while each has a compute unit to itself; beyond, one.  (Two or eight waves there walk as fast, but the next call's
 // forward chains, workgroups of one wave, then come to lie two to a SIMD: B=512 N=512 T=16 312 us, behind them 348.)
-#define LCCRF_WALK_BY_SIZE(LAUNCH_, workgroups_)                  \
-    do {                                                          \
-        const bool few = (workgroups_) <= 256;                    \
-        if (T <= 64 && few) LAUNCH_(1, 512);                      \
-        else if (T <= 64) LAUNCH_(1, 64);                         \
-        else if (T <= 128 && few) LAUNCH_(2, 512);                \
-        else if (T <= 128) LAUNCH_(2, 64);                        \
-        else if (few) LAUNCH_(4, 512);                            \
-        else LAUNCH_(4, 64);                                      \
+// The windows of long sequences: eight waves where the forward chains are workgroups of many waves (up to 256 sequences), four elsewhere; one wave takes
+// twice as long over a window of twenty tags as four.  us a draw, one wave / four / eight: B=118 N=2213 T=20 638 / 601 / 593, B=44 N=3177 T=31 589 / 557 / 550,
+// B=300 N=1370 T=12 448 / 415 / 410, but B=441 N=767 T=24 748 / 761 / 798.
+#define LCCRF_WALK_BY_TAGS(LAUNCH_, threads_) \
+    do {                                      \
+        if (T <= 64) LAUNCH_(1, threads_);    \
+        else if (T <= 128) LAUNCH_(2, threads_); \
+        else LAUNCH_(4, threads_);            \
     } while (0)
 
 template <typename TIN>
@@ -1297,7 +1296,8 @@ static hipError_t launch_sample_T(const TIN* phi, const int32_t* lengths, const 
         if (e != hipSuccess) return e;                                                                                                       \
         hipLaunchKernelGGL((sample_window_walk_kernel<K_, THREADS_>), grid, dim3(THREADS_), 0, st, lengths, ua, uniforms, F, N, T, W, winmap, tags); \
     } while (0)
-        LCCRF_WALK_BY_SIZE(LCCRF_WINDOWS, B * (long long)W);
+        if (B <= 256) LCCRF_WALK_BY_TAGS(LCCRF_WINDOWS, 512);
+        else LCCRF_WALK_BY_TAGS(LCCRF_WINDOWS, 256);
 #undef LCCRF_WINDOWS
         return hipGetLastError();
     }
@@ -1309,7 +1309,8 @@ static hipError_t launch_sample_T(const TIN* phi, const int32_t* lengths, const 
     }
     const dim3 grid(B < (1 << 20) ? B : 1 << 20);
 #define LCCRF_WALK(K_, THREADS_) hipLaunchKernelGGL((sample_walk_kernel<K_, THREADS_>), grid, dim3(THREADS_), 0, st, lengths, ua, uniforms, F, B, N, T, tags)
-    LCCRF_WALK_BY_SIZE(LCCRF_WALK, (long long)B);
+    if (B <= 256) LCCRF_WALK_BY_TAGS(LCCRF_WALK, 512);
+    else LCCRF_WALK_BY_TAGS(LCCRF_WALK, 64);
 #undef LCCRF_WALK
     return hipGetLastError();
 }
