@@ -969,9 +969,12 @@ static hipError_t launch_geo(const VitArgs& a, hipStream_t st) {
 template <int TP, typename TIN, bool ALIGNED, bool STRUCT>
 static hipError_t launch_wave_vit(const VitArgs& a, hipStream_t st) {
     // Whole sequences: short ones, whose second launch would take a third of the time (B=52 N=14 T=16 12.3 -> 9.6 us, structured
-    // 14.7 -> 9.9, B=1024 N=64 T=8 24.9 -> 21.0), and the largest batches (B=2048 N=512 T=8 196 -> 171); in between a trace by 128 threads takes longer
-    // than it saves (B=300 N=100 T=32 45 / 50, B=1024 N=300 T=9 90 / 97).
-    if (a.chunk > 0 || a.N <= (TP == 16 ? 64 : 32) || a.B >= 2048) {
+    // 14.7 -> 9.9, B=1024 N=64 T=8 24.9 -> 21.0), and of the largest batches all up to 16 tags (B=2048 N=300 T=8 118 -> 100, T=16 156 -> 148, N=1000 T=12
+    // 391 -> 379, B=4096 N=300 T=4 structured 166 -> 145) and above them the shorter ones (B=2048 N=40 T=32 78 -> 73, N=64 bfloat16 67 -> 71, N=100
+    // T=20 103 -> 110, N=300 T=24 bfloat16 261 -> 316, structured N=100 T=32 80 -> 72, B=4096 N=70 T=32 237 -> 215, N=300 T=20 structured 366 -> 389); in between a trace by 128 threads takes longer than it saves (B=300 N=100 T=32 45 / 50, B=1024
+    // N=300 T=9 90 / 97).
+    const bool large = a.B >= 2048 && (TP == 16 || a.N <= (STRUCT ? 100 : sizeof(TIN) == 4 ? 70 : 48));
+    if (a.chunk > 0 || a.N <= (TP == 16 ? 64 : 32) || large) {
         hipLaunchKernelGGL((viterbi_chunk_kernel<TP, TIN, ALIGNED, STRUCT>), dim3(a.B * a.C), dim3(128), 0, st, a);
         return hipGetLastError();
     }
