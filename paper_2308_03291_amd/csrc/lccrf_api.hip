@@ -334,10 +334,13 @@ inline bool lanes_pay_sample(int B, int N, int T) {
 // B=128 N=256 T=32 106 / 59, B=256 N=128 T=32 64 / 57, B=384 N=128 T=32 68 / 75; B=128 N=128 T=48 99 / 74,
 // B=64 N=256 T=40 181 / 117, B=256 N=128 T=48 127 / 130; above 48 tags the ring holds too few matrices
 // (B=32 N=256 T=64 182 / 208).  Tag counts that are no multiple of four gain the same (B=128 N=128 T=45 106 / 76,
-// T=48 96 / 72; B=32 N=64 T=30 43 / 27).  Short chains of up to 32 tags go to the one-wave kernels, whose workgroup traces the path as well
-// (these / one launch: T=16 N=16 11.1 / 9.6, N=24 11.3 / 9.8, N=32 11.4 / 11.4, N=40 11.3 / 12.9; T=32 N=16 11.3 / 10.5, N=20 11.9 / 11.7, N=24 11.6 / 12.7).
+// T=48 96 / 72; B=32 N=64 T=30 43 / 27).  Short chains of up to 32 tags go to the one-wave kernels, whose workgroup traces the path as well.
+// How short is set by the batch, which the chain waves take longer to begin with, and by the tag count, whose unaligned rows the one-wave
+// kernels load slowly (one launch / these, us, single precision or bfloat16: T=16 B=2 N=20 8.5 / 8.4, B=200 N=26 10.2 / 10.2, B=500 N=32 12.6 / 14.5; T=5 B=2 N=24 9.6 / 9.9, T=4 B=8 N=22 8.8 / 10.7; T=13 B=32
+// N=16 9.0 / 9.0, N=20 10.2 / 9.2, B=200 N=22 10.8 / 10.5, B=500 N=32 13.4 / 16.2; T=32 B=2 N=16 9.8 / 9.0, B=200 N=20 11.6 / 12.4; T=27 B=32 N=16 11.9 / 10.6).
 inline bool lanes_pay_max(int B, int N, int T) {
-    if (!lccrf::lane_max_supported(T) || T > 48 || N < (T <= 16 ? 32 : T <= 32 ? 20 : 16)) return false;
+    const int least = T > 32 ? 16 : T > 16 ? 16 + B / 64 : T <= 4 || B > 256 ? 32 : (T % 4 == 0 ? 20 + B / 32 : 17 + B / 40) + (T <= 8 ? 3 : 0);
+    if (!lccrf::lane_max_supported(T) || T > 48 || N < least) return false;
     const int cus = current_device_cus();
     return T <= 16 ? B <= 2 * cus : T <= 32 ? B <= cus : 2 * B <= cus;
 }
