@@ -52,7 +52,7 @@
  *    one-workgroup kernel, which rounds differently, so where that hand-over depends
  *    on timing two runs may differ in the low-order bits (far inside the tolerance).
  *    LCCRF_ALGO_SEQUENTIAL never uses pairs.  Likewise a sum-product chain of LCCRF_ALGO_SEQUENTIAL_LANES
- *    (which AUTO takes for mid-sized batches of 17 .. 64 tags) whose producers fall behind its poll limit
+ *    (which AUTO takes for mid-sized batches of 5 .. 64 tags) whose producers fall behind its poll limit
  *    (lccrf_set_lane_poll_limit; milliseconds, not seen in practice) finishes in the log domain and
  *    rounds differently from a run in which they kept up.  (lccrf_argmax is bit-identical from run to run
  *    under every schedule: a max-plus chain that stops waiting computes the same sums and maxima alone.)
@@ -90,7 +90,9 @@ typedef enum {
 typedef enum {
     LCCRF_ALGO_AUTO = 0,
     LCCRF_ALGO_SEQUENTIAL = 1, /* position by position (the forward algorithm as the paper uses it), one
-                                  workgroup per chain; AUTO may instead split a chain over several workgroups */
+                                  workgroup per chain; AUTO may instead split a chain over several workgroups.
+                                  Sum queries at 5 .. 7 tags: by the kernels of
+                                  LCCRF_ALGO_SEQUENTIAL_LANES where AUTO takes those */
     LCCRF_ALGO_SCAN = 2,       /* chunked associative scan over positions (the parallel variant the
                                   paper cites in "Sequence Tagging"): products of the T x T matrices
                                   of each chunk, a short serial pass over chunks, then every chunk
@@ -349,7 +351,8 @@ int lccrf_set_pair_poll_limit(int polls);
 int lccrf_set_lane_poll_limit(int polls);
 
 /* The schedule LCCRF_ALGO_AUTO takes for `op` at this shape under the current chunk size:
- * LCCRF_ALGO_SEQUENTIAL, LCCRF_ALGO_SEQUENTIAL_LANES or LCCRF_ALGO_SCAN.  Host-side arithmetic, nothing is launched;
+ * LCCRF_ALGO_SEQUENTIAL, LCCRF_ALGO_SEQUENTIAL_LANES or LCCRF_ALGO_SCAN (5 .. 7 tags: SEQUENTIAL also where that takes
+ * the chain-wave kernels, which cannot be asked for by name there).  Host-side arithmetic, nothing is launched;
  * LCCRF_EINVAL for a shape or op the library does not serve.  For callers that size or time a run
  * by the schedule it will take (the benchmark names its dominant kernel from it).  Best paths
  * above 64 tags are LCCRF_ALGO_SEQUENTIAL, whether their pointers are found along the chains or,

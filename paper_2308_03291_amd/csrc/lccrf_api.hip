@@ -369,7 +369,9 @@ int sum_query(int op, const void* phi, int dt, const int32_t* lengths, int B, in
     if (lengths && !aligned_to(lengths, 4)) return LCCRF_EALIGN;
     if (algo == LCCRF_ALGO_SCAN && !lccrf::scan_supported(T)) return LCCRF_ENOTIMPL;
     if (algo == LCCRF_ALGO_SEQUENTIAL_LANES && !lccrf::lane_chains_supported(T)) return LCCRF_ENOTIMPL;
-    const bool lanes = algo == LCCRF_ALGO_SEQUENTIAL_LANES || (algo == LCCRF_ALGO_AUTO && lanes_pay_sum(op, B, N, T));
+    // (5 .. 7 tags: SEQUENTIAL is what lccrf_auto_algo reports, so it takes what AUTO takes)
+    const bool quickest = algo == LCCRF_ALGO_AUTO || (algo == LCCRF_ALGO_SEQUENTIAL && !lccrf::lane_chains_supported(T));
+    const bool lanes = algo == LCCRF_ALGO_SEQUENTIAL_LANES || (quickest && lanes_pay_sum(op, B, N, T));
     const SumWorkspace w = sum_workspace(B, N, T);
     char* base = static_cast<char*>(workspace);
     hipStream_t st = static_cast<hipStream_t>(stream);
@@ -426,7 +428,7 @@ size_t lccrf_workspace_bytes(lccrf_op op, int B, int N, int T, lccrf_dtype dt) {
     }
 }
 
-// (5 .. 7 tags: a caller cannot ask for the chain-wave kernels, and is told what it can ask for.)
+// (5 .. 7 tags: a caller cannot ask for the chain-wave kernels by name; asked for SEQUENTIAL it gets them wherever AUTO does.)
 static int lanes_algo(int T) { return lccrf::lane_chains_supported(T) ? LCCRF_ALGO_SEQUENTIAL_LANES : LCCRF_ALGO_SEQUENTIAL; }
 
 int lccrf_auto_algo(lccrf_op op, int B, int N, int T) {

@@ -291,3 +291,16 @@ def test_five_to_seven_tags(crf, oracle_mod, T, N):
     assert crf.auto_algo(crf.OP_MARGINALS, 8, N, T) == crf.ALGO_SEQUENTIAL
     with pytest.raises(crf.LccrfError):
         crf.lccrf_log_partition(torch.zeros(1, N, T, T, device="cuda"), algo=crf.ALGO_SEQUENTIAL_LANES)
+
+
+@pytest.mark.parametrize("T", (5, 6, 7, 8))
+def test_the_reported_schedule_is_the_one_auto_takes(crf, T):
+    """A call that asks for what lccrf_auto_algo reports runs the kernels of AUTO: the same bits.  Shapes on either side of where
+    the chain waves pay, and the scan's."""
+    for B, N in ((4, 15), (4, 16), (87, 53), (200, 40), (256, 20), (257, 20), (3, 200), (2, 1200)):
+        phi, _ = workloads.random_case(9300 + 17 * T + N, B, N, T)
+        phi = phi.cuda()
+        took = crf.auto_algo(crf.OP_LOGZ, B, N, T), crf.auto_algo(crf.OP_MARGINALS, B, N, T)
+        assert torch.equal(crf.lccrf_log_partition(phi), crf.lccrf_log_partition(phi, algo=took[0])), (B, N, took)
+        for a, b in zip(crf.lccrf_marginals(phi), crf.lccrf_marginals(phi, algo=took[1])):
+            assert torch.equal(a, b), (B, N, took)
