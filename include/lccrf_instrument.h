@@ -49,6 +49,16 @@ size_t lccrf_stream_probe_bytes(size_t bytes, int workgroups);
 int lccrf_marginals_by_edges(lccrf_dtype dt, int B, int T);
 
 /*
+ * How many pieces, walked by a workgroup each, the default schedule of lccrf_log_partition, lccrf_marginals, lccrf_log_prob or lccrf_sample
+ * cuts a chain into at most (1: none; 65 .. 256 tags only).  *plan (may be NULL): where in the workspace a call leaves what became of
+ * that, int32 [2 B][pieces], chain 2 b forward and 2 b + 1 backward.  Entry 0: twice the least steps of a piece, one more if the chain takes
+ * no steps in scaled probabilities; 2^21 and more: the batch was not cut.  Entry c > 0: the step from which piece c stands as it was
+ * walked without its predecessor, 2^31 - 1 if the chain was walked again from its end on.  (Sampling overwrites it.)  0 without pieces.
+ * LCCRF_EINVAL for other queries and shapes that are not served.
+ */
+int lccrf_first_pass_pieces(lccrf_op op, lccrf_dtype dt, int B, int N, int T, size_t* plan);
+
+/*
  * The largest row of a T x T matrix that any thread of a first pass in scaled probabilities (33 .. 256 tags) takes, by the
  * kernels' own arithmetic over every thread and item of the instance the dispatch chooses: at most T - 1, or the pass
  * reads past the matrix.  Host only; -1 for other tag counts.

@@ -35,7 +35,7 @@ EXPORTS = (
     "lccrf_marginals_structured", "lccrf_argmax_structured", "lccrf_set_scan_chunk", "lccrf_auto_algo",
     "lccrf_strerror", "lccrf_version", "lccrf_marginals_static", "lccrf_static_scratch_bytes",
     "lccrf_set_pair_poll_limit", "lccrf_set_lane_poll_limit", "lccrf_stream_probe", "lccrf_stream_probe_bytes", "lccrf_sample_seeded",
-    "lccrf_first_pass_largest_row", "lccrf_marginals_by_edges",
+    "lccrf_first_pass_largest_row", "lccrf_marginals_by_edges", "lccrf_first_pass_pieces",
 )
 
 _lib = None
@@ -103,6 +103,8 @@ def load_library() -> ctypes.CDLL:
     lib.lccrf_stream_probe_bytes.restype = sz
     lib.lccrf_marginals_by_edges.argtypes = [i, i, i]
     lib.lccrf_marginals_by_edges.restype = i
+    lib.lccrf_first_pass_pieces.argtypes = [i, i, i, i, i, ctypes.POINTER(sz)]
+    lib.lccrf_first_pass_pieces.restype = i
     lib.lccrf_first_pass_largest_row.argtypes = [i]
     lib.lccrf_first_pass_largest_row.restype = i
     lib.lccrf_set_pair_poll_limit.argtypes = [i]

@@ -861,6 +861,14 @@ int lccrf_argmax_structured(const float* emit, const float* trans, const int32_t
 int lccrf_marginals_by_edges(lccrf_dtype dt, int B, int T) {
     return B >= 1 && dtype_ok(dt) && lccrf::marginals_by_edges(dt, B, T, current_device_cus()) ? 1 : 0;
 }
+int lccrf_first_pass_pieces(lccrf_op op, lccrf_dtype dt, int B, int N, int T, size_t* plan) {
+    if (!shape_ok(B, N, T) || !dtype_ok(dt)) return LCCRF_EINVAL;
+    if (op != LCCRF_OP_LOGZ && op != LCCRF_OP_MARGINALS && op != LCCRF_OP_LOG_PROB && op != LCCRF_OP_SAMPLE) return LCCRF_EINVAL;
+    size_t at = 0;
+    const int pieces = lccrf::first_pass_pieces(op == LCCRF_OP_SAMPLE ? 2 : op == LCCRF_OP_MARGINALS ? 1 : 0, dt, B, N, T, current_device_cus(), &at);
+    if (plan) *plan = pieces > 1 ? sum_workspace(B, N, T).maps + at : 0;
+    return pieces;
+}
 int lccrf_first_pass_largest_row(int T) { return lccrf::first_pass_largest_row(T); }
 
 const char* lccrf_strerror(int code) {

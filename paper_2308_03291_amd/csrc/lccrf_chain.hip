@@ -1257,6 +1257,30 @@ hipError_t launch_chunked_full_forward(int dtype, const void* phi, const int32_t
     return launch_wave(2, dtype, a, st, nullptr);
 }
 
+// What a first pass over whole sequences of dense potentials at 65 .. 256 tags does (op: 0 log-partition, 1 marginals).
+static void plan_first_pass(ChainArgs& a, int op, int dtype, int cus, void* scratch) {
+    // Marginals: chains are cut only if they run to the far ends, behind which every marginal is made of its position's own two vectors.  (A second pass
+    // that goes on from the first one's vectors in the log domain sets its steps off against those of the first pass, whose sum is log Z: what either
+    // rounds off a step has to be alike.  First pass in the log domain / in pieces, relative error of the marginals at 128 tags, scores of deviation one
+    // N=400 1.5e-6 / 3.1e-6, of deviation two 8.0e-6 / 1.5e-5; with whole chains in pieces 1.0e-7 and 2.5e-7.)  128 tags have the paired second pass where
+    // they are not cut (us, pairs behind halves in pieces / whole chains in pieces: B=8 N=300 388 / 146, deviation three 975 / 290).
+    const bool edges = op == 1 && marginals_by_edges(dtype, a.B, a.T, cus), edges_if_cut = op == 1 && a.T == 128 && marginals_by_edges(dtype, a.B, a.T - 1, cus);
+    if (op != 1 || edges || edges_if_cut) cut_chains(a, dtype, edges || edges_if_cut, false, cus, scratch);
+    a.whole = edges || (edges_if_cut && a.pieces > 1) ? 1 : 0;
+}
+
+int first_pass_pieces(int op, int dtype, int B, int N, int T, int cus, size_t* plan) {
+    ChainArgs a{};
+    a.B = B;
+    a.N = N;
+    a.T = T;
+    char* const scratch = reinterpret_cast<char*>(256);  // (never looked into)
+    if (op == 2) cut_chains(a, dtype, false, true, cus, scratch);
+    else plan_first_pass(a, op, dtype, cus, scratch);
+    if (plan) *plan = a.pieces > 1 ? (size_t)(reinterpret_cast<char*>(a.matched_from) - scratch) : 0;
+    return a.pieces > 1 ? a.pieces : 1;
+}
+
 // op: 0 = logZ only, 1 = marginals (+ logZ).  Workspace pointers already carved by the caller.
 hipError_t launch_sequential_sum(int op, int dtype, const void* phi, const int32_t* lengths, int B, int N, int T,
                                  float* ua, float* ub, double* Oa, double* Ob, float* logZ, float* mu,
@@ -1300,14 +1324,7 @@ hipError_t launch_sequential_sum(int op, int dtype, const void* phi, const int32
     if (wave_supported(T)) return launch_wave(op, dtype, a, st, between);
     if (emit) return (T % 4) == 0 ? launch_structured_sum<true>(op, a, st, between) : launch_structured_sum<false>(op, a, st, between);
     if (exact_only) cus = 0;
-    // Marginals: chains are cut only if they run to the far ends, behind which every marginal is made of its position's own two vectors.  (A second pass
-    // that goes on from the first one's vectors in the log domain sets its steps off against those of the first pass, whose sum is log Z: what either
-    // rounds off a step has to be alike.  First pass in the log domain / in pieces, relative error of the marginals at 128 tags, scores of deviation one
-    // N=400 1.5e-6 / 3.1e-6, of deviation two 8.0e-6 / 1.5e-5; with whole chains in pieces 1.0e-7 and 2.5e-7.)  128 tags have the paired second pass where
-    // they are not cut (us, pairs behind halves in pieces / whole chains in pieces: B=8 N=300 388 / 146, deviation three 975 / 290).
-    const bool edges = op == 1 && marginals_by_edges(dtype, B, T, cus), edges_if_cut = op == 1 && T == 128 && marginals_by_edges(dtype, B, T - 1, cus);
-    if (op != 1 || edges || edges_if_cut) cut_chains(a, dtype, edges || edges_if_cut, false, cus, scratch);
-    a.whole = edges || (edges_if_cut && a.pieces > 1) ? 1 : 0;
+    plan_first_pass(a, op, dtype, cus, scratch);
     if (stream_supported(T)) return launch_stream(op, dtype, a, st, between);
     // Pairs pay off when one workgroup per chain would leave at least half of the chip idle.
     const bool use_pairs = op == 1 && !exact_only && mail && failed && pair_supported(T) && 4 * B <= cus;

@@ -23,6 +23,8 @@ hipError_t launch_sequential_sum(int op, int dtype, const void* phi, const int32
                                  const float* emit = nullptr, const float* trans = nullptr, int pair_poll_limit = 0,
                                  int cus = 0, bool lanes = false, int lane_poll_limit = 1 << 16, void* scratch = nullptr);
 // scratch: B N T bytes for chains in pieces at 65 .. 256 tags (lccrf_pieces.h), here and below; null: every chain as a whole.
+// Workgroups a chain of a first pass is cut into at most (op 2: sampling), and where in that scratch matched_from begins.
+int first_pass_pieces(int op, int dtype, int B, int N, int T, int cus, size_t* plan);
 // lanes: the chain-wave / producer-wave kernels of lccrf_lane.hip (lane_chains_supported(T); dense or structured potentials);
 // lane_poll_limit: polls their chain wave spends on a late matrix before it continues in the log domain.
 bool lane_chains_supported(int T);
