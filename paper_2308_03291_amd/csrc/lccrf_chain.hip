@@ -644,7 +644,7 @@ __global__ __launch_bounds__(G::W) void chain_half_kernel(ChainArgs a) {
     if (sp.empty) return;
     const int p0 = sp.p0, e = sp.e;
     const int h = forward_end(a, p0, e);
-    if (a.full_forward && dir == 1) return;
+    if ((a.full_forward && dir == 1) || walked_in_pieces(a)) return;
     const int c4 = 4 * (tid % G::LPR), r0 = tid / G::LPR;
     const TIN* phib = static_cast<const TIN*>(a.phi) + (size_t)b * N * T * T;
     const size_t TT = (size_t)T * T;
@@ -1088,6 +1088,7 @@ static void cut_chains(ChainArgs& a, int dtype, bool whole, bool forward, int cu
     if (pieces == 1) return;
     set_pieces(a, pieces, scratch);
     a.piece_overhead = (int)(18.0 / alone);
+    a.chain_us = (int)(n * alone < 1e9 ? n * alone : 1e9);
 }
 
 // Whether the second halves of few chains take their steps without writing, and one more kernel writes the marginals with the
@@ -1112,9 +1113,16 @@ static hipError_t launch_geo(int op, ChainArgs a, hipStream_t st, hipEvent_t bet
     // elsewhere the turned steps are as quick or quicker at these sizes (single precision B=64 N=256 T=100 185 / 178,
     // B=64 N=512 T=128 422 / 469, B=64 N=256 T=64 104 / 108).
     const bool linear = a.chunk <= 0 && !a.exact_only && (a.whole || a.pieces > 1 || (!ALIGNED && sizeof(TIN) == 2));
+    // A batch whose chains turn out not to be cut: the turned steps are the quicker ones for single precision from 112 tags on where the potentials do not stay
+    // in the memory-side cache.  They take a fourth launch, 5 us of the calls that are cut, so only long chains get it.  us, in scaled probabilities / so, scores
+    // that stay where they are: log-partition B=8 N=2400 T=128 1681 / 1596, B=32 N=600 T=128 452 / 438,
+    // samples B=8 N=2400 T=120 3533 / 3397; in the cache B=8 N=600 T=116 395 / 414, samples B=1 N=300 T=128 385 / 411.
+    a.whole_elsewhere = linear && a.pieces > 1 && !a.whole && sizeof(TIN) == 4 && ALIGNED && a.T >= 112 && a.chain_us >= 400 &&
+                        (double)a.B * a.N * a.T * a.T * sizeof(TIN) > 268435456.0;
     hipError_t e = hipSuccess;
     if (linear) {
         for (a.piece_pass = 0; e == hipSuccess && a.piece_pass < (a.pieces > 1 ? 3 : 1); ++a.piece_pass) e = launch_linear_half<G, TIN, ALIGNED>(a, st);
+        if (e == hipSuccess && a.whole_elsewhere) e = launch_chain_half<G, TIN, ALIGNED, PF1>(a, st);
     } else {
         e = launch_chain_half<G, TIN, ALIGNED, PF1>(a, st);
     }

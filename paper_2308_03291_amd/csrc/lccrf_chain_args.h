@@ -59,7 +59,10 @@ struct ChainArgs {
     int scaled;  // row-batch kernels: scaled steps whatever the batch
     int pieces;  // workgroups a chain (1: the chain as a whole) ...
     int piece_pass;  // ... and which of their three launches this is
+    // 1: a batch that forgets too slowly to be cut is left to a fourth launch, of chain_half_kernel
+    int whole_elsewhere;
     int piece_overhead;  // what three launches take more than one, in steps
+    int chain_us;        // (host) about what the longest chain would take as a whole
     float *ends, *ends2;               // [2 B][pieces][T] last vectors of the pieces (chain 2 b + direction) ...
     double *end_offsets, *end_offsets2;  // [2 B][pieces] ... and their offsets
     double* deltas;                    // [2 B][pieces]
@@ -96,8 +99,13 @@ __device__ __forceinline__ Span make_span(const ChainArgs& a, int v) {
     return s;
 }
 
-// Steps a piece of a chain has at least.
-constexpr int kPieceSteps = 18;
+// Steps a piece of a chain has at least, and what stands for that where a batch is not cut.
+constexpr int kPieceSteps = 18, kNoPieces = 1 << 20;
+
+// Workgroups of that fourth launch (2 b + direction): whether the chain has been walked in pieces.
+__device__ __forceinline__ bool walked_in_pieces(const ChainArgs& a) {
+    return a.whole_elsewhere && a.matched_from[(size_t)blockIdx.x * a.pieces] >> 1 != kNoPieces;
+}
 
 // Where the forward and the backward chain of positions p0 .. e meet: the forward chain covers
 // p0 .. h, the backward chain h .. e.  Every kernel of both passes derives it from here.

@@ -12,7 +12,8 @@
 //   2  a workgroup a chain adds up the constants and puts them into the offsets.  From the first piece on of which no row agreed, the
 //      rest of the chain is walked as a whole, from that piece's last vector, which is the true one: what started behind it was not.
 // Potentials that forget slowly (deviation three and up: forty steps and more) cost no more steps one after the other than without
-// pieces: n/C + n/C + (C - 2) n/C.
+// pieces: n/C + n/C + (C - 2) n/C.  Batches that are seen to are not cut (piece_steps): launch 0 walks their chains as a whole, or leaves them to a
+// fourth launch where that is quicker at it (launch_geo in lccrf_chain.hip).
 #pragma once
 
 #include "lccrf_chain_args.h"
@@ -87,10 +88,10 @@ __device__ __forceinline__ int piece_steps(const ChainArgs& a) {
         r = fmaxf(r, mean);
     }
     const float guess = 85.f * (1.f + 2.f * r) / -lg2(r);
-    if (!(fine && guess > 0.f && guess < 1e6f)) return 1 << 20;
+    if (!(fine && guess > 0.f && guess < 1e6f)) return kNoPieces;
     const int least = uniform((int)fmaxf(guess, (float)kPieceSteps));
     const int n = a.whole || a.full_forward ? uniform(longest) - 1 : uniform(longest) / 2, cut = min(a.pieces, n / least);
-    return cut > 1 && (float)n / (float)cut + 0.8f * guess + (float)a.piece_overhead <= 0.85f * (float)n ? least : 1 << 20;
+    return cut > 1 && (float)n / (float)cut + 0.8f * guess + (float)a.piece_overhead <= 0.85f * (float)n ? least : kNoPieces;
 }
 
 // The row that log-domain steps have come to (see LinMatch): v, O this thread's entry and the offset, against those of the row.
@@ -157,6 +158,10 @@ __device__ __forceinline__ void piece_walk(LinSmem<LG>& lin, const ChainArgs& a,
         hopeless = uniform(plan) & 1;
     } else if (MODE == kChainsInPieces) {
         least = piece_steps<TIN>(a);
+        if (a.whole_elsewhere && least == kNoPieces) {
+            if (c == 0 && tid == 0) a.matched_from[slot] = 2 * kNoPieces;
+            return;
+        }
     }
     Piece p = MODE == kChainsWhole ? Piece{1, 0, n} : piece_of(n, a.pieces, least, c);
     if (c >= p.count || (pass == 2 && p.count == 1)) return;

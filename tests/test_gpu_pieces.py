@@ -215,3 +215,28 @@ def test_paired_second_pass_over_long_chains(crf, oracle_mod):
     assert np.abs(mu[:3].cpu().numpy() - want_mu).max() <= 1e-5
     for k in range(3, 54, 3):
         assert torch.equal(mu[k:k + 3], mu[:3])
+
+
+@pytest.mark.parametrize("T,B,N", [(116, 8, 660), (128, 8, 600), (112, 6, 1000)])
+def test_long_chains_left_to_a_fourth_launch(crf, oracle_mod, T, B, N):
+    """Single precision where steps in the log domain are quicker for chains as a whole: a batch that is not cut is walked by a kernel of its own behind
+    the launches of the pieces, one that is cut is not walked again; log-partition and samples, ragged, with a chain that forgets nothing among quick ones."""
+    phi, _ = workloads.random_case(10100 + T, 2, N, T)
+    lens = torch.tensor([N, N - 77], dtype=torch.int32)
+    uniforms = torch.rand(2, N, generator=torch.Generator().manual_seed(T))
+    for slow in (False, True):
+        if slow:
+            phi += 25.0 * torch.eye(T)
+        want = oracle_mod.log_partition(phi, lens.numpy())
+        many, many_lens = phi.cuda().repeat(B // 2, 1, 1, 1), lens.cuda().repeat(B // 2)
+        if not slow:
+            many[B - 1] += 25.0 * torch.eye(T, device="cuda")  # (not among the sequences whose matrices are looked at, the last of which is 3 B / 4)
+        got = crf.lccrf_log_partition(many, many_lens).cpu().numpy()
+        ok = slice(0, B if slow else B - 1)
+        assert np.allclose(got[ok], np.tile(want, B // 2)[ok], rtol=1e-5, atol=0), slow
+        _, found = _pieces(crf, crf.OP_LOGZ, many, many_lens)
+        assert all((in_log_domain is None) == slow for in_log_domain, _ in found.values())
+        alone = crf.lccrf_sample(phi.cuda(), uniforms.cuda(), lens.cuda())  # (another batch: other pieces or none, the same draws but for rounding)
+        drawn = crf.lccrf_sample(many, uniforms.cuda().repeat(B // 2, 1), many_lens)
+        for k in range(0, (B if slow else B - 2), 2):
+            assert float((drawn[k:k + 2] != alone).float().mean()) <= 0.02
