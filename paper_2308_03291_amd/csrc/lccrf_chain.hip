@@ -1067,9 +1067,11 @@ static void set_pieces(ChainArgs& a, int pieces, void* scratch) {
 // The chains of a first pass in pieces, where that pays if the potentials forget quickly.  whole: to the far ends; forward: one chain a
 // sequence, over all of it.  One workgroup a chain takes about 0.7 + 5.5e-5 T^2 us a step (96 tags 1.2, 201 tags 2.6 .. 3.5) and all of them
 // together draw 6.5 TB/s at most; the launches, the guess and the two more beginnings take about 18 us; nine steps to a match.  us, as a
-// whole / in pieces: log-partition B=10 N=135 T=96 91 / 66, B=4 N=256 T=256 482 / 155; marginals B=2 N=447 T=85 bfloat16 420 / 88, B=32 N=256
-// T=201 bfloat16 1293 / 743.  Where the potentials forget slowly the guess and two launches that have nothing to do are lost: 8 us (independent
-// scores of deviation three, log-partition B=1 N=126 T=156 110 / 118, B=15 N=274 T=130 189 / 197); a gain below 28 % is left alone for that.
+// whole / in pieces: log-partition B=26 N=300 T=130 267 / 166, B=4 N=256 T=256 518 / 165; marginals B=2 N=447 T=85 bfloat16 502 / 84, B=32 N=256
+// T=201 bfloat16 1319 / 758.  Where the potentials forget slowly the guess and two launches that have nothing to do are lost: 8 us (independent
+// scores of deviation three, log-partition B=1 N=126 T=156 108 / 114, B=15 N=274 T=130 232 / 243); a gain below 28 % is left alone for that.  The chains are then
+// walked in scaled probabilities or, launch_geo, by the turned steps; what that loses is 10 % of the log-partition of about 26 sequences of 240 .. 256 tags in single
+// precision (N=300 T=256 812 / 906), which would take their steps in the log domain if they could not be cut.
 static void cut_chains(ChainArgs& a, int dtype, bool whole, bool forward, int cus, void* scratch) {
     a.pieces = 1;
     if (cus <= 0 || a.T <= 64 || a.T > 256 || !scratch) return;
@@ -1099,7 +1101,8 @@ static void cut_chains(ChainArgs& a, int dtype, bool whole, bool forward, int cu
 // 315 / 313, bfloat16 B=128 240 / 301; 100 tags, single precision B=64 294 / 331, B=128 501 / 421, bfloat16 B=64 251 / 311, B=128
 // 403 / 354 (128 tags have the paired second pass).  Up to 127 tags the line lies below where they cross: where hard constraints
 // send the chains to the log-domain steps, two launches of them must not cost more than what is saved (N=128 B=64, two tags
-// forbidden everywhere: 80 tags 462 / 466, 100 tags 539 / 541; 136 tags B=32 1218 / 1419).
+// forbidden everywhere: 80 tags 462 / 466, 100 tags 539 / 541; 136 tags B=32 1218 / 1419).  All of this is measured with chains walked as a whole; where
+// they are cut the first pass has become up to five times as fast, and the limits may lie too low.
 bool marginals_by_edges(int dtype, int B, int T, int cus) {
     if (cus <= 0 || T <= 64 || T == 128 || T > 256) return false;
     const int limit = T < 128 ? (dtype == 0 ? 16 : 24) : (dtype == 0 ? 40 : 48);
@@ -1271,7 +1274,7 @@ static void plan_first_pass(ChainArgs& a, int op, int dtype, int cus, void* scra
     // that goes on from the first one's vectors in the log domain sets its steps off against those of the first pass, whose sum is log Z: what either
     // rounds off a step has to be alike.  First pass in the log domain / in pieces, relative error of the marginals at 128 tags, scores of deviation one
     // N=400 1.5e-6 / 3.1e-6, of deviation two 8.0e-6 / 1.5e-5; with whole chains in pieces 1.0e-7 and 2.5e-7.)  128 tags have the paired second pass where
-    // they are not cut (us, pairs behind halves in pieces / whole chains in pieces: B=8 N=300 388 / 146, deviation three 975 / 290).
+    // they are not cut (us, pairs behind halves in pieces / whole chains in pieces: B=8 N=300 399 / 143, deviation three 982 / 270).
     const bool edges = op == 1 && marginals_by_edges(dtype, a.B, a.T, cus), edges_if_cut = op == 1 && a.T == 128 && marginals_by_edges(dtype, a.B, a.T - 1, cus);
     if (op != 1 || edges || edges_if_cut) cut_chains(a, dtype, edges || edges_if_cut, false, cus, scratch);
     a.whole = edges || (edges_if_cut && a.pieces > 1) ? 1 : 0;
