@@ -352,6 +352,7 @@ def main():
     auto_taken = crf.auto_algo(crf.OP_MARGINALS, w.B, w.N, w.T)
     scan_taken = algo == crf.ALGO_SCAN or (algo == crf.ALGO_AUTO and auto_taken == crf.ALGO_SCAN)
     lanes_taken = algo == crf.ALGO_SEQUENTIAL_LANES or (algo == crf.ALGO_AUTO and auto_taken == crf.ALGO_SEQUENTIAL_LANES)
+    first_kernel, first_reads = "lane_chain_kernel (first pass)" if lanes_taken else "stream_half_kernel" if w.T > 128 else "chain_half_kernel", 1
     if lanes_taken:
         # second pass of the chain-wave / producer-wave kernels: one read of phi + one write of mu
         kernel, alg_bytes = "lane_chain_kernel (second pass)", eff_pots * (esz + 4)
@@ -367,16 +368,17 @@ def main():
         # dominant kernel: second pass = one read of phi + one write of mu over the positions in the chains.
         # With few sequences and T = 128 that pass is the two-workgroups-per-chain kernel (plus two
         # few-microsecond helpers the event interval also covers: mailbox reset, exact fix-up launch); with few sequences of
-        # 65 .. 256 tags otherwise the chains run on to the far ends first (one read of phi) and a kernel of its own reads it
-        # again and writes every edge: both in this interval.
+        # 65 .. 256 tags otherwise the first pass runs to the far ends (two reads of phi) and a kernel of its own reads it once more
+        # and writes every edge: that kernel alone is this interval.
         alg_bytes = eff_pots * (esz + 4)
         paired = w.T == 128 and 4 * w.B <= torch.cuda.get_device_properties(dev).multi_processor_count
-        by_edges = bool(crf.load_library().lccrf_marginals_by_edges(crf.LCCRF_F32 if esz == 4 else crf.LCCRF_BF16, w.B, w.T))
+        dt, lib = crf.LCCRF_F32 if esz == 4 else crf.LCCRF_BF16, crf.load_library()
+        by_edges = algo == crf.ALGO_AUTO and (bool(lib.lccrf_marginals_by_edges(dt, w.B, w.T)) or
+                                              lib.lccrf_first_pass_pieces(crf.OP_MARGINALS, dt, w.B, w.N, w.T, None) > 1)
         kernel = "pair_marginal_kernel" if paired else ("wave_marginal_kernel" if w.T <= 32 else
                                                         "stream_marginal_kernel" if w.T > 128 else "chain_marginal_kernel")
-        if by_edges and algo in (crf.ALGO_AUTO, crf.ALGO_SEQUENTIAL):
-            kernel = f"{'stream' if w.T > 128 else 'linear'}_half_kernel (second halves) + edge_marginal_kernel"
-            alg_bytes = eff_pots * (2 * esz + 4)
+        if by_edges:
+            kernel, first_kernel, first_reads = "edge_marginal_kernel", f"{'stream' if w.T > 128 else 'linear'}_half_kernel (whole chains)", 2
     achieved = alg_bytes / (pass2_avg * 1e-3) / 1e9
     roofline = {"bound": "hbm", "kernel": kernel,
                 "achieved": achieved, "peak": HBM_PEAK_GBPS,
@@ -384,11 +386,9 @@ def main():
                 # counters cannot be read inside the run: this figure comes from the committed rocprofv3 --pmc summary
                 "traffic": committed_traffic(w.key), "traffic_source": f"profiles/marginals_{w.key}_traffic.txt (committed)",
                 "algorithmic_bytes_per_launch": alg_bytes, "avg_launch_ms": pass2_avg,
-                "first_pass": {"kernel": "lane_chain_kernel (first pass)" if lanes_taken else
-                               "stream_half_kernel" if w.T > 128 else "chain_half_kernel",
-                               "algorithmic_bytes": eff_pots * esz,
+                "first_pass": {"kernel": first_kernel, "algorithmic_bytes": first_reads * eff_pots * esz,
                                "avg_ms": sum(pass1) / len(pass1),
-                               "frac": eff_pots * esz / (sum(pass1) / len(pass1) * 1e-3) / 1e9 / HBM_PEAK_GBPS},
+                               "frac": first_reads * eff_pots * esz / (sum(pass1) / len(pass1) * 1e-3) / 1e9 / HBM_PEAK_GBPS},
                 "whole_call": {"algorithmic_bytes": call_bytes, "avg_ms": sum(whole) / len(whole),
                                "achieved": call_bytes / (sum(whole) / len(whole) * 1e-3) / 1e9,
                                "frac": call_bytes / (sum(whole) / len(whole) * 1e-3) / 1e9 / HBM_PEAK_GBPS}}

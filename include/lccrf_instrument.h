@@ -17,7 +17,8 @@ extern "C" {
  * lccrf_marginals_algo (section "Computing Marginals" of the paper, Eq. 3-4) with three
  * caller-created hipEvent_t handles (passed as void*, any may be NULL) recorded on `stream`
  * before the first kernel, between the two passes of the sequential schedule (after every
- * matrix has been read once and the half-way vectors are stored; before the pass that
+ * matrix has been read once and the half-way vectors are stored, or, where lccrf_marginals_by_edges says so, twice and the
+ * vectors of every position; before the pass that
  * re-reads phi and writes the marginals), and after the last kernel.  Lets a caller time the
  * passes separately with hipEventElapsedTime.  Same results and errors as lccrf_marginals_algo.
  */
@@ -42,8 +43,8 @@ int lccrf_stream_probe(const void* in, void* out, size_t bytes, int workgroups, 
 size_t lccrf_stream_probe_bytes(size_t bytes, int workgroups);
 
 /*
- * 1 where the sequential schedule of lccrf_marginals, in place of a second pass that writes the marginals as the chains go, runs
- * the chains on to the far ends without writing (a second read of phi) and writes every edge in a kernel of its own (a third).
+ * 1 where the default schedule of lccrf_marginals, in place of a second pass that writes the marginals as the chains go, runs
+ * the chains of the first one to the far ends (two reads of phi) and writes every edge in a kernel of its own (a third).
  * 0 elsewhere, or without a device.  (At 128 tags 0, though AUTO does the same with chains that it walks in pieces.)
  */
 int lccrf_marginals_by_edges(lccrf_dtype dt, int B, int T);
